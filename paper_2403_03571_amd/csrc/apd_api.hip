@@ -996,6 +996,8 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     bytes = align_up(bytes + (size_t)nsuper * sizeof(int), 256);
     const size_t o_s0 = bytes;
     bytes = align_up(bytes + (size_t)(B + 1) * sizeof(int64_t), 256);
+    const size_t o_at = bytes;
+    bytes = align_up(bytes + 2 * (size_t)(B + 1) * sizeof(int64_t), 256);
     if (bytes > c->batch_bytes) {
         (void)hipFree(c->batch_buf);
         c->batch_buf = nullptr;
@@ -1027,6 +1029,8 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     int *d_sl = (int *)(base + o_sl);
     int *d_sc = (int *)(base + o_sc);
     int64_t *d_super0 = (int64_t *)(base + o_s0);
+    int64_t *d_act = (int64_t *)(base + o_at);
+    const apd::BWork work{d_tile0, d_super0, d_act, d_act + B + 1};
 
     std::vector<apd::BState> hst(B);
     std::vector<double *> hdst(B);
@@ -1097,15 +1101,15 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) dev_cu = prop.multiProcessorCount;
     }
-    const int grid_assign = dev_cu * 4;
+    const int grid_assign = (int)std::min<int64_t>(ntiles, (int64_t)dev_cu * apd::kBatchBlocksPerCu);
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     // the re-check: one block per queue segment (a tile's queued pixels);
     // blocks past the segments leave at once
     const int recheck_blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(512, ntiles / 8));
-    hipError_t le = apd::launch_batch_step(dim, d_inst, d_st, d_tile0, B, d_ctl, d_queue, d_segs,
-                                           grid_assign, bvariant, recheck_blocks, d_super0, nsuper, s);
+    hipError_t le = apd::launch_batch_step(dim, d_inst, d_st, work, B, d_ctl, d_queue, d_segs,
+                                           grid_assign, bvariant, recheck_blocks, nsuper, s);
     hipError_t ce = hipStreamEndCapture(s, &graph);
     if (le != hipSuccess || ce != hipSuccess)
         return fail(c, APD_ERR_DEVICE, "graph capture failed: %s / %s", hipGetErrorString(le), hipGetErrorString(ce));

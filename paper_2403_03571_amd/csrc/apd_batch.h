@@ -57,7 +57,6 @@ struct BCtl {
     // pixels): an 8-byte pair advanced by one atomic
     unsigned qcount;
     unsigned segcount;
-    unsigned next;    // work-item counter of kb_assign
     int active;       // instances still running
     int max_iter, max_evals;
     double eps;
@@ -67,12 +66,23 @@ struct BCtl {
 static_assert(offsetof(BCtl, qcount) % 8 == 0 && offsetof(BCtl, segcount) == offsetof(BCtl, qcount) + 4,
               "the queue counters form one aligned 8-byte pair");
 
+// The batch's work items: prefix sums over the instances of their tiles and
+// super-tiles ([B + 1], fixed), and the same over the active instances only
+// (written by kb_prep for each evaluation).
+struct BWork {
+    const int64_t *tile0;
+    const int64_t *super0;
+    int64_t *act_tile;
+    int64_t *act_super;
+};
+
+constexpr int kBatchBlocksPerCu = 64;  // blocks of kb_assign per compute unit
+
 hipError_t launch_batch_setup(int dim, BInst *inst, BState *st, int B, hipStream_t s);
-// super0: prefix sums of the instances' super-tile counts (used with lists)
 // segs: room for one queue segment per tile of the batch
-hipError_t launch_batch_step(int dim, BInst *inst, BState *st, const int64_t *tile0, int B,
+hipError_t launch_batch_step(int dim, BInst *inst, BState *st, BWork wk, int B,
                              BCtl *ctl, uint64_t *queue, QSeg *segs, int grid_assign, int variant,
-                             int recheck_blocks, const int64_t *super0, int64_t nsuper, hipStream_t s);
+                             int recheck_blocks, int64_t nsuper, hipStream_t s);
 hipError_t launch_batch_init(BInst *inst, double *const *src, int B, bool warm, hipStream_t s);
 hipError_t launch_batch_scatter(BInst *inst, double *const *dst, int B, hipStream_t s);
 

@@ -4,11 +4,11 @@
 // Every evaluation of every active instance is one replay of a captured
 // HIP graph of five kernels:
 //   kb_prep      block per instance: gauge max of the trial weights, zeroed
-//                moments; block 0 resets the work counters.
-//   kb_assign    persistent: blocks pull (instance, tile) work items from an
-//                atomic counter over the concatenated tile lists (largest
-//                instances first) and run the matrix-core tile of the
-//                single-instance path on it; converged instances are skipped.
+//                moments; one block more lists the work of the active
+//                instances (prefix sums of their tiles and super-tiles).
+//   kb_assign    the blocks stride over the (instance, tile) work items of the
+//                active instances (largest instances first) and run the
+//                tile of the single-instance path on them.
 //   kb_recheck   persistent over one queue of (instance, pixel) entries:
 //                the double re-check of near-tie pixels.
 //   kb_finalize  block per instance: objective, gradient, max rel. error.
@@ -125,15 +125,46 @@ __global__ __launch_bounds__(kThreads) void kb_setup(BInst *inst, BState *st) {
 
 // ---------------------------------------------------------------- kb_prep
 
+// act[b] = sum over the active instances k < b of count[k + 1] - count[k]
+// (b = 0 .. B), by one block: each thread sums a run of instances, the runs'
+// sums are scanned in LDS.
+__device__ inline void active_prefix(const int64_t *count, const BState *st, int B, int64_t *act, int64_t *s) {
+    const int per = (B + kThreads - 1) / kThreads;
+    const int lo = min(B, (int)threadIdx.x * per), hi = min(B, lo + per);
+    int64_t sum = 0;
+    for (int k = lo; k < hi; ++k)
+        if (st[k].active) sum += count[k + 1] - count[k];
+    __syncthreads();
+    s[threadIdx.x] = sum;
+    __syncthreads();
+    for (int o = 1; o < kThreads; o <<= 1) {
+        const int64_t v = (int)threadIdx.x >= o ? s[threadIdx.x - o] : 0;
+        __syncthreads();
+        s[threadIdx.x] += v;
+        __syncthreads();
+    }
+    int64_t run = s[threadIdx.x] - sum;
+    for (int k = lo; k < hi; ++k) {
+        act[k] = run;
+        if (st[k].active) run += count[k + 1] - count[k];
+    }
+    if (threadIdx.x == 0) act[B] = s[kThreads - 1];
+}
+
 template <int D>
-__global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCtl *ctl) {
+__global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCtl *ctl, BWork wk, int B) {
     __shared__ double red[kWaves];
+    __shared__ int64_t s_run[kThreads];
     constexpr int K = moments_per_cell(D);
     const int b = blockIdx.x;
-    if (b == 0 && threadIdx.x == 0) {
-        ctl->next = 0u;
-        ctl->qcount = 0u;
-        ctl->segcount = 0u;
+    if (b == B) {
+        if (threadIdx.x == 0) {
+            ctl->qcount = 0u;
+            ctl->segcount = 0u;
+        }
+        active_prefix(wk.tile0, st, B, wk.act_tile, s_run);
+        active_prefix(wk.super0, st, B, wk.act_super, s_run);
+        return;
     }
     if (!st[b].active) return;
     const BInst &I = inst[b];
@@ -147,28 +178,28 @@ __global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCt
 
 // -------------------------------------------------------------- kb_assign
 
-__device__ inline int find_instance(const int64_t *tile0, int B, int64_t item) {
-    int lo = 0, hi = B;  // tile0[lo] <= item < tile0[hi]
+// The instance of work item `item`: prefix[b] <= item < prefix[b + 1].
+__device__ inline int find_instance(const int64_t *prefix, int B, int64_t item) {
+    int lo = 0, hi = B;  // prefix[lo] <= item < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (tile0[mid] <= item) lo = mid;
+        if (prefix[mid] <= item) lo = mid;
         else hi = mid;
     }
     return lo;
 }
 
-// One block per (instance, super-tile): the super-tile candidate lists of
-// the active instances (dev::super_tile_list).
+// One block per super-tile of an active instance: its candidate list
+// (dev::super_tile_list); blocks past the active ones leave at once.
 template <int D>
-__global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BState *st,
-                                                    const int64_t *super0, int B) {
+__global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BState *st, BWork wk, int B) {
     __shared__ int s_cnt;
     __shared__ double s_red[kWaves];
     const int64_t item = blockIdx.x;
-    const int b = find_instance(super0, B, item);
-    if (!st[b].active) return;
+    if (item >= wk.act_super[B]) return;
+    const int b = find_instance(wk.act_super, B, item);
     const BInst &I = inst[b];
-    const int local = (int)(item - super0[b]);
+    const int local = (int)(item - wk.act_super[b]);
     Seeds sd{I.x, I.A, I.wt, I.v};
     PassOut out{nullptr, nullptr, nullptr};
     out.tp = I.tp;
@@ -180,6 +211,17 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
                        I.super_count + local, kBatchSuperCap, s_cnt, s_red);
 }
 
+// The work is split without a counter: block k takes the tiles k, k + grid,
+// ... of the active instances.  An atomic counter over every tile of the
+// batch (converged instances skipped tile by tile) set a floor of 12 ns per
+// tile, the rate of same-address atomics across the XCDs: 1.27 ms per
+// evaluation of 512 maps (107 k tiles) with hardly one still active, where
+// this form takes 0.04; the whole solve 870 -> 722 ms.  The stride keeps the
+// blocks that run together on neighbouring tiles (one run of consecutive tiles per
+// block put every instance's seeds in the L2s at once: 0.6 ms more per
+// evaluation), and 64 blocks per compute unit leave the balance to the
+// dispatcher (solve at 4 / 16 / 64 / 256: 806 / 756 / 722 / 740 ms).
+//
 // V: 0 fp32 matrix cores, 1 fp32 vector, 2 fp32 vector with candidate
 // lists (8 pixels per lane), 3 bf16 matrix cores, 4 fp32 vector with
 // candidate lists (4 pixels per lane), 5 bf16 matrix cores with candidate
@@ -188,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
 // batched C4-type solve 1.5 times faster than at one wave -- measured)
 template <int D, int V>
 __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) void kb_assign(const BInst *inst, const BState *st,
-                                                     const int64_t *tile0, int B, BCtl *ctl,
+                                                     BWork wk, int B, BCtl *ctl,
                                                      uint64_t *queue, QSeg *segs) {
     __shared__ union {
         float mf[kMfmaLds];
@@ -196,18 +238,12 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
         Bf16Smem<D, 256, V == 5> bf;
     } sm;
     float *sC = sm.mf;
-    __shared__ int64_t s_item;
-    const int64_t total = tile0[B];
-    for (;;) {
-        __syncthreads();
-        if (threadIdx.x == 0) s_item = (int64_t)atomicAdd(&ctl->next, 1u);
-        __syncthreads();
-        const int64_t item = s_item;
-        if (item >= total) break;
-        const int b = find_instance(tile0, B, item);
-        if (!st[b].active) continue;
+    const int64_t total = wk.act_tile[B];
+    for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
+        const int b = find_instance(wk.act_tile, B, item);
+        __syncthreads();  // the previous tile is done with the shared memory
         const BInst &I = inst[b];
-        const int64_t local = item - tile0[b];
+        const int64_t local = item - wk.act_tile[b];
         Seeds sd{I.x, I.A, I.wt, I.v};
         PassOut out{nullptr, I.mom, nullptr};
         out.queue64 = queue;
@@ -518,32 +554,32 @@ hipError_t launch_batch_setup(int dim, BInst *inst, BState *st, int B, hipStream
 }
 
 template <int D>
-void batch_assign(int variant, dim3 grid, BInst *inst, BState *st, const int64_t *tile0, int B,
+void batch_assign(int variant, dim3 grid, BInst *inst, BState *st, BWork wk, int B,
                   BCtl *ctl, uint64_t *queue, QSeg *segs, hipStream_t s) {
     switch (variant) {
-    case 0: kb_assign<D, 0><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
-    case 1: kb_assign<D, 1><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
-    case 2: kb_assign<D, 2><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
-    case 4: kb_assign<D, 4><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
-    case 5: kb_assign<D, 5><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
-    default: kb_assign<D, 3><<<grid, kThreads, 0, s>>>(inst, st, tile0, B, ctl, queue, segs); break;
+    case 0: kb_assign<D, 0><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    case 1: kb_assign<D, 1><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    case 2: kb_assign<D, 2><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    case 4: kb_assign<D, 4><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    case 5: kb_assign<D, 5><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    default: kb_assign<D, 3><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
     }
 }
 
-hipError_t launch_batch_step(int dim, BInst *inst, BState *st, const int64_t *tile0, int B,
+hipError_t launch_batch_step(int dim, BInst *inst, BState *st, BWork wk, int B,
                              BCtl *ctl, uint64_t *queue, QSeg *segs, int grid_assign, int variant,
-                             int recheck_blocks, const int64_t *super0, int64_t nsuper, hipStream_t s) {
+                             int recheck_blocks, int64_t nsuper, hipStream_t s) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
     if (dim == 2) {
-        kb_prep<2><<<B, kThreads, 0, s>>>(inst, st, ctl);
-        if (nsuper > 0) kb_super<2><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, super0, B);
-        batch_assign<2>(variant, grid_assign, inst, st, tile0, B, ctl, queue, segs, s);
+        kb_prep<2><<<B + 1, kThreads, 0, s>>>(inst, st, ctl, wk, B);
+        if (nsuper > 0) kb_super<2><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, wk, B);
+        batch_assign<2>(variant, grid_assign, inst, st, wk, B, ctl, queue, segs, s);
         kb_recheck<2><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
         kb_finalize<2><<<B, kThreads, 0, s>>>(inst, st);
     } else {
-        kb_prep<3><<<B, kThreads, 0, s>>>(inst, st, ctl);
-        if (nsuper > 0) kb_super<3><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, super0, B);
-        batch_assign<3>(variant, grid_assign, inst, st, tile0, B, ctl, queue, segs, s);
+        kb_prep<3><<<B + 1, kThreads, 0, s>>>(inst, st, ctl, wk, B);
+        if (nsuper > 0) kb_super<3><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, wk, B);
+        batch_assign<3>(variant, grid_assign, inst, st, wk, B, ctl, queue, segs, s);
         kb_recheck<3><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
         kb_finalize<3><<<B, kThreads, 0, s>>>(inst, st);
     }
