@@ -34,13 +34,8 @@ struct apd_ctx {
     double *eig = nullptr;            // [cap_n][2] eigenvalue range of every A_i (culling)
     int *ord = nullptr;               // [cap_n] the hybrid kernel's seed order
     int *ws_nb = nullptr;             // [cap_n][16] nearest seeds (warm-start features)
-    int *tile_lists = nullptr;        // [cap_tiles][kCullCap] candidate seeds per tile
-    int *tile_count = nullptr;        // [cap_tiles]
-    double *tile_U = nullptr;         // [cap_tiles] cost bound of the seeds left out of each list
     double *cost_part = nullptr;      // [cap_parts] per-block cost sums (costs other than |.|^2_A)
     int64_t cap_parts = 0;
-    apd::QSeg *segs = nullptr;        // [cap_tiles] segments of the re-check queue
-    int64_t cap_tiles = 0;
     int *super_lists = nullptr;       // [cap_super][kSuperCap] candidate seeds per super-tile
     int *super_count = nullptr;       // [cap_super]
     int64_t cap_super = 0;
@@ -162,7 +157,7 @@ apd::Geo make_geo(const apd_problem *p) {
     return g;
 }
 
-apd_status ensure_scratch(apd_ctx *c, int64_t n, int64_t J) {
+apd_status ensure_scratch(apd_ctx *c, int64_t n) {
     if (n > c->cap_n) {
         (void)hipFree(c->mom); c->mom = nullptr;
         (void)hipFree(c->wbuf); c->wbuf = nullptr;
@@ -187,6 +182,11 @@ apd_status ensure_scratch(apd_ctx *c, int64_t n, int64_t J) {
             return fail(c, APD_ERR_OOM, "cannot allocate seed scratch for n = %lld", (long long)n);
         c->cap_n = nn;
     }
+    return APD_OK;
+}
+
+// The re-check queue of the single-precision passes over every seed.
+apd_status ensure_queue(apd_ctx *c, int64_t J) {
     if (J > c->cap_J) {
         (void)hipFree(c->queue); c->queue = nullptr;
         c->cap_J = 0;
@@ -213,12 +213,6 @@ struct PassBufs {
     unsigned *queue = nullptr;     // [J]
     double *eig = nullptr;         // [n][2]
     int *ord = nullptr;            // [n] seed order of the hybrid kernel
-    int *tile_lists = nullptr;     // [tiles][list_cap]
-    int *tile_count = nullptr;     // [tiles]
-    double *tile_U = nullptr;      // [tiles]
-    apd::QSeg *segs = nullptr;     // [tiles]
-    int64_t cap_tiles = 0;
-    int list_cap = apd::kCullCap;
     int *super_lists = nullptr;    // [super-tiles][super_cap]
     int *super_count = nullptr;    // [super-tiles]
     int64_t cap_super = 0;
@@ -272,10 +266,9 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     if (fixed) {
         b = *fixed;
     } else {
-        apd_status st = ensure_scratch(c, p->n, J);
+        apd_status st = ensure_scratch(c, p->n);
         if (st != APD_OK) return st;
         b.mom = c->mom;
-        b.queue = c->queue;
         b.eig = c->eig;
         b.ord = c->ord;
         b.sc = c->sc;
@@ -316,7 +309,14 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
         c->stats.kernel = APD_KERNEL_FP64;
         c->stats.pixels_per_lane = 0;
     } else {
-        out.queue = b.queue;
+        if (!cull) {
+            if (!fixed) {
+                const apd_status qs = ensure_queue(c, J);
+                if (qs != APD_OK) return qs;
+                b.queue = c->queue;
+            }
+            out.queue = b.queue;
+        }
         if (prec == APD_BF16 && !cull) {
             HIP_TRY(c, apd::launch_assign_bf16(g, sd, b.sc, nullptr, out, c->stream));
             c->stats.kernel = APD_KERNEL_BF16_MATRIX;
@@ -324,33 +324,10 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
         } else if (cull) {
             const ListGeometry L = list_geometry(p, g, prec);
             out.tp = L.tp;
-            for (int d = 0; d < 3; ++d) out.ntile[d] = L.ntile[d];
             if (fixed) {
-                if (L.tiles > b.cap_tiles || L.nsuper > b.cap_super)
+                if (L.nsuper > b.cap_super)
                     return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
             } else {
-                if (L.tiles > c->cap_tiles) {
-                    (void)hipFree(c->tile_lists);
-                    (void)hipFree(c->tile_count);
-                    (void)hipFree(c->tile_U);
-                    (void)hipFree(c->segs);
-                    c->tile_lists = nullptr;
-                    c->tile_count = nullptr;
-                    c->tile_U = nullptr;
-                    c->segs = nullptr;
-                    c->cap_tiles = 0;
-                    if (hipMalloc(&c->tile_lists, (size_t)L.tiles * apd::kCullCap * sizeof(int)) != hipSuccess ||
-                        hipMalloc(&c->tile_count, (size_t)L.tiles * sizeof(int)) != hipSuccess ||
-                        hipMalloc(&c->tile_U, (size_t)L.tiles * sizeof(double)) != hipSuccess ||
-                        hipMalloc(&c->segs, (size_t)L.tiles * sizeof(apd::QSeg)) != hipSuccess)
-                        return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld tiles",
-                                    (long long)L.tiles);
-                    c->cap_tiles = L.tiles;
-                }
-                b.tile_lists = c->tile_lists;
-                b.tile_count = c->tile_count;
-                b.tile_U = c->tile_U;
-                b.segs = c->segs;
                 if (L.nsuper > c->cap_super) {
                     (void)hipFree(c->super_lists);
                     (void)hipFree(c->super_count);
@@ -366,13 +343,8 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
                 b.super_lists = c->super_lists;
                 b.super_count = c->super_count;
             }
-            out.tile_lists = b.tile_lists;
-            out.tile_count = b.tile_count;
-            out.list_cap = b.list_cap;
             out.adaptive = c->adaptive;
             out.credited = &b.sc->credited;
-            if (rel_gap) out.tile_U = b.tile_U;
-            out.segs = b.segs;
             for (int d = 0; d < 3; ++d) {
                 out.sf[d] = L.sf[d];
                 out.nst[d] = L.nst[d];
@@ -404,7 +376,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
             c->stats.pixels_per_lane = 0;
         }
         if (timing) HIP_TRY(c, hipEventRecord(c->ev[2], c->stream));
-        HIP_TRY(c, apd::launch_recheck(g, sd, b.sc, out, c->stream));
+        if (!cull) HIP_TRY(c, apd::launch_recheck(g, sd, b.sc, out, c->stream));
     }
     if (finalize) HIP_TRY(c, apd::launch_finalize(g, sd, b.mom, b.sc, fo, b.parts, c->stream));
     c->stats.pixels = J;
@@ -689,7 +661,7 @@ apd_status fit_impl(apd_ctx *c, const apd_problem *p, const double *x, double *w
                     const apd_fit_opts *o, apd_fit_report *rep) {
     const auto t_start = std::chrono::steady_clock::now();
     const int64_t n = p->n;
-    apd_status st = ensure_scratch(c, n, num_pixels(p));
+    apd_status st = ensure_scratch(c, n);
     if (st != APD_OK) return st;
     if (!(o->eps > 0.0) || o->max_iter < 0 || o->max_evals < 1 || o->history < 0)
         return fail(c, APD_ERR_INVALID_ARG, "bad fit options");
@@ -948,7 +920,6 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         hinst[q].tiles0 = t0;
         tile0[q + 1] = tile0[q] + (int64_t)t0 * t1 * t2;
     }
-    // candidate lists of the tiles, kept for the re-check (lists only)
     const int64_t ntiles = tile0[B];
     const bool lists = bvariant == 2 || bvariant == 4 || bvariant == 5;
     // super-tiles about six cell diameters across ((J/N)^(1/D) pixels),
@@ -984,12 +955,11 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     const size_t o_tile = bytes; bytes = align_up(bytes + (B + 1) * sizeof(int64_t), 256);
     const size_t o_ctl = bytes; bytes = align_up(bytes + sizeof(apd::BCtl), 256);
     const size_t o_dst = bytes; bytes = align_up(bytes + B * sizeof(double *), 256);
-    const size_t o_q = bytes; bytes = align_up(bytes + (size_t)qcap * sizeof(uint64_t), 256);
-    const size_t o_seg = bytes; bytes = align_up(bytes + (size_t)ntiles * sizeof(apd::QSeg), 256);
-    const size_t o_tl = bytes;
-    if (lists) bytes = align_up(bytes + (size_t)ntiles * apd::kBatchListCap * sizeof(int), 256);
-    const size_t o_tc = bytes;
-    if (lists) bytes = align_up(bytes + (size_t)ntiles * sizeof(int), 256);
+    // the re-check queue (with lists the tiles re-check their own pixels)
+    const size_t o_q = bytes;
+    if (!lists) bytes = align_up(bytes + (size_t)qcap * sizeof(uint64_t), 256);
+    const size_t o_seg = bytes;
+    if (!lists) bytes = align_up(bytes + (size_t)ntiles * sizeof(apd::QSeg), 256);
     const size_t o_sl = bytes;
     bytes = align_up(bytes + (size_t)nsuper * apd::kBatchSuperCap * sizeof(int), 256);
     const size_t o_sc = bytes;
@@ -1024,8 +994,6 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     double **d_dst = (double **)(base + o_dst);
     uint64_t *d_queue = (uint64_t *)(base + o_q);
     apd::QSeg *d_segs = (apd::QSeg *)(base + o_seg);
-    int *d_tl = lists ? (int *)(base + o_tl) : nullptr;
-    int *d_tc = lists ? (int *)(base + o_tc) : nullptr;
     int *d_sl = (int *)(base + o_sl);
     int *d_sc = (int *)(base + o_sc);
     int64_t *d_super0 = (int64_t *)(base + o_s0);
@@ -1053,8 +1021,6 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         I.rho = v0 + (5 + 2 * kBatchHist) * n;
         I.eig = I.rho + kBatchHist;
         I.mom = mom + off_m[q];
-        I.tile_lists = lists ? d_tl + tile0[q] * apd::kBatchListCap : nullptr;
-        I.tile_count = lists ? d_tc + tile0[q] : nullptr;
         const bool has_super = super0[q + 1] > super0[q];
         I.super_lists = has_super ? d_sl + super0[q] * apd::kBatchSuperCap : nullptr;
         I.super_count = has_super ? d_sc + super0[q] : nullptr;
@@ -1107,7 +1073,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     HIP_TRY(c, hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     // the re-check: one block per queue segment (a tile's queued pixels);
     // blocks past the segments leave at once
-    const int recheck_blocks = (int)std::min<int64_t>(4096, std::max<int64_t>(512, ntiles / 8));
+    const int recheck_blocks = lists ? 0 : (int)std::min<int64_t>(4096, std::max<int64_t>(512, ntiles / 8));
     hipError_t le = apd::launch_batch_step(dim, d_inst, d_st, work, B, d_ctl, d_queue, d_segs,
                                            grid_assign, bvariant, recheck_blocks, nsuper, s);
     hipError_t ce = hipStreamEndCapture(s, &graph);
@@ -1217,9 +1183,7 @@ WsBufs ws_bufs(apd_ws_model *m) {
 // Warm-start features: one pass at W = 0 gives the deficits (gradient in
 // c->gbuf), then the per-seed features and their neighbour means.
 apd_status ws_features_impl(apd_ctx *c, const apd_problem *p, float *F) {
-    int64_t J = 1;
-    for (int d = 0; d < p->dim; ++d) J *= p->grid[d];
-    apd_status st = ensure_scratch(c, p->n, J);
+    apd_status st = ensure_scratch(c, p->n);
     if (st != APD_OK) return st;
     HIP_TRY(c, hipMemsetAsync(c->wbuf, 0, (size_t)p->n * sizeof(double), c->stream));
     double g0 = 0.0, mr0 = 0.0;
@@ -1254,7 +1218,7 @@ apd_status ws_infer_impl(apd_ctx *c, apd_ws_model *m, const float *F, int64_t S,
 // on the host that name is only a stand-in for the symbol).
 namespace {
 constexpr size_t kStaticScratch = (size_t)96 << 20;  // bytes per device
-constexpr int kStaticListCap = 256;                  // candidates kept per tile
+constexpr int kStaticListCap = 256;                  // seeds counted per tile (the limit)
 constexpr int kStaticSuperCap = 512;                 // candidates kept per super-tile
 constexpr int kMaxDevices = 64;
 }  // namespace
@@ -1336,11 +1300,7 @@ void apd_destroy(apd_ctx *c) {
     (void)hipFree(c->eig);
     (void)hipFree(c->ord);
     (void)hipFree(c->ws_nb);
-    (void)hipFree(c->tile_lists);
-    (void)hipFree(c->tile_count);
-    (void)hipFree(c->tile_U);
     (void)hipFree(c->cost_part);
-    (void)hipFree(c->segs);
     (void)hipFree(c->super_lists);
     (void)hipFree(c->super_count);
     (void)hipFree(c->batch_buf);
@@ -1427,12 +1387,13 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
     }
     if (cull) {
         const ListGeometry L = list_geometry(p, geo, prec);
-        b.tile_lists = k.take<int>((size_t)L.tiles * kStaticListCap);
-        b.tile_count = k.take<int>((size_t)L.tiles);
-        b.tile_U = k.take<double>((size_t)L.tiles);
-        b.segs = k.take<apd::QSeg>((size_t)L.tiles);
-        b.cap_tiles = L.tiles;
-        b.list_cap = kStaticListCap;
+        // the call's documented limit counts a list of kStaticListCap seeds,
+        // its length and bound and a queue segment for every tile, whether or
+        // not the pass uses them
+        k.take<int>((size_t)L.tiles * kStaticListCap);
+        k.take<int>((size_t)L.tiles);
+        k.take<double>((size_t)L.tiles);
+        k.take<apd::QSeg>((size_t)L.tiles);
         b.super_lists = k.take<int>((size_t)L.nsuper * kStaticSuperCap);
         b.super_count = k.take<int>((size_t)L.nsuper);
         b.cap_super = L.nsuper;

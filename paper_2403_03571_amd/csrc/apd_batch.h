@@ -26,8 +26,6 @@ struct BInst {
     int tiles1;       // tiles along axis 1
     int tiles2;       // tiles along axis 2 (3D)
     int tiles0;       // tiles along axis 0
-    int *tile_lists;  // [tiles][kBatchListCap] candidate lists (vector kernel with lists) or null
-    int *tile_count;  // [tiles]
     int *super_lists; // [super-tiles][kBatchSuperCap] (vector kernel with lists) or null
     int *super_count; // [super-tiles]
     int sf[3];        // tiles per super-tile along each axis
@@ -35,7 +33,6 @@ struct BInst {
     int tp;           // pixels per lane of the vector kernel's tiles
 };
 
-constexpr int kBatchListCap = 256;   // candidate seeds kept per tile for the batched re-check
 constexpr int kBatchSuperCap = 512;  // candidate seeds kept per super-tile
 
 // Scalar solver state of one instance.
@@ -79,7 +76,8 @@ struct BWork {
 constexpr int kBatchBlocksPerCu = 64;  // blocks of kb_assign per compute unit
 
 hipError_t launch_batch_setup(int dim, BInst *inst, BState *st, int B, hipStream_t s);
-// segs: room for one queue segment per tile of the batch
+// segs: room for one queue segment per tile of the batch; without lists the
+// step ends in the re-check of the queue, with them the tiles re-check
 hipError_t launch_batch_step(int dim, BInst *inst, BState *st, BWork wk, int B,
                              BCtl *ctl, uint64_t *queue, QSeg *segs, int grid_assign, int variant,
                              int recheck_blocks, int64_t nsuper, hipStream_t s);

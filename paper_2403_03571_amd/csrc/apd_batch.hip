@@ -2,15 +2,16 @@
 // arXiv 2403.03571 for a batch of problems of uneven N and grid size).
 //
 // Every evaluation of every active instance is one replay of a captured
-// HIP graph of five kernels:
+// HIP graph of these kernels:
 //   kb_prep      block per instance: gauge max of the trial weights, zeroed
 //                moments; one block more lists the work of the active
 //                instances (prefix sums of their tiles and super-tiles).
 //   kb_assign    the blocks stride over the (instance, tile) work items of the
 //                active instances (largest instances first) and run the
 //                tile of the single-instance path on them.
-//   kb_recheck   persistent over one queue of (instance, pixel) entries:
-//                the double re-check of near-tie pixels.
+//   kb_recheck   passes without candidate lists: over one queue of (instance,
+//                pixel) entries, the double re-check of near-tie pixels (with
+//                lists the tiles re-check their own).
 //   kb_finalize  block per instance: objective, gradient, max rel. error.
 //   kb_lbfgs     block per instance: one step of the L-BFGS state machine
 //                (the same specification as the host solver), which writes
@@ -238,6 +239,7 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
         Bf16Smem<D, 256, V == 5> bf;
     } sm;
     float *sC = sm.mf;
+    constexpr bool kLists = V == 2 || V == 4 || V == 5;
     const int64_t total = wk.act_tile[B];
     for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
         const int b = find_instance(wk.act_tile, B, item);
@@ -246,10 +248,12 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
         const int64_t local = item - wk.act_tile[b];
         Seeds sd{I.x, I.A, I.wt, I.v};
         PassOut out{nullptr, I.mom, nullptr};
-        out.queue64 = queue;
-        out.tag = (uint32_t)b;
-        out.segs = segs;
-        out.tile_id = (int)local;
+        if (!kLists) {
+            out.queue64 = queue;
+            out.tag = (uint32_t)b;
+            out.segs = segs;
+            out.tile_id = (int)local;
+        }
         int b0, b1, b2 = 0;
         if (D == 2) {
             b0 = (int)(local / I.tiles1);
@@ -264,15 +268,8 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
         if (V == 0) {
             mfma_tile<D>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, b0, b1, b2, sC, out, &ctl->qcount);
         } else {
-            constexpr bool kLists = V == 2 || V == 4 || V == 5;
-            if (kLists && I.tile_lists) {
-                out.tile_lists = I.tile_lists;
-                out.tile_count = I.tile_count;
-                out.list_cap = kBatchListCap;
+            if (kLists) {
                 out.tp = I.tp;
-                out.ntile[0] = I.tiles0;
-                out.ntile[1] = I.tiles1;
-                out.ntile[2] = I.tiles2;
                 out.adaptive = true;  // single-candidate tiles credited whole
             }
             if (kLists && I.super_lists) {
@@ -286,10 +283,10 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
             }
             if constexpr (V == 3 || V == 5)
                 bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, b0, b1, b2,
-                                                              sm.bf, out, &ctl->qcount);
+                                                              sm.bf, out, kLists ? nullptr : &ctl->qcount);
             else
                 vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, b0, b1, b2,
-                                                       sm.vec, out, &ctl->qcount);
+                                                       sm.vec, out, kLists ? nullptr : &ctl->qcount);
         }
     }
 }
@@ -304,19 +301,12 @@ __global__ __launch_bounds__(kThreads) void kb_recheck(const BInst *inst, const 
     const unsigned nseg = ctl->segcount;
     const int wave = threadIdx.x >> 6;
     for (unsigned s = blockIdx.x * kWaves + wave; s < nseg; s += gridDim.x * kWaves) {
-        // one tile's queued pixels against its candidate list (or every
-        // seed of the instance: no lists, or an overflowed one), one wave
+        // one tile's queued pixels against every seed of its instance
         const QSeg seg = segs[s];
         const BInst &I = inst[seg.tag];
         Seeds sd{I.x, I.A, I.wt, I.v};
-        const int *list = nullptr;
-        int cnt = 0;
-        if (I.tile_lists) {
-            cnt = I.tile_count[seg.tile];
-            if (cnt <= kBatchListCap) list = I.tile_lists + (size_t)seg.tile * kBatchListCap;
-        }
-        recheck_segment<D, S>(I.g, sd, seg.start, seg.count, list, cnt,
-                              [&](unsigned q) { return (uint32_t)queue[q]; }, nullptr, I.mom, sm[wave]);
+        recheck_segment<D, S>(I.g, sd, seg.start, seg.count, [&](unsigned q) { return (uint32_t)queue[q]; }, I.mom,
+                              sm[wave]);
     }
 }
 
@@ -574,13 +564,13 @@ hipError_t launch_batch_step(int dim, BInst *inst, BState *st, BWork wk, int B,
         kb_prep<2><<<B + 1, kThreads, 0, s>>>(inst, st, ctl, wk, B);
         if (nsuper > 0) kb_super<2><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, wk, B);
         batch_assign<2>(variant, grid_assign, inst, st, wk, B, ctl, queue, segs, s);
-        kb_recheck<2><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
+        if (recheck_blocks > 0) kb_recheck<2><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
         kb_finalize<2><<<B, kThreads, 0, s>>>(inst, st);
     } else {
         kb_prep<3><<<B + 1, kThreads, 0, s>>>(inst, st, ctl, wk, B);
         if (nsuper > 0) kb_super<3><<<(unsigned)nsuper, kThreads, 0, s>>>(inst, st, wk, B);
         batch_assign<3>(variant, grid_assign, inst, st, wk, B, ctl, queue, segs, s);
-        kb_recheck<3><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
+        if (recheck_blocks > 0) kb_recheck<3><<<recheck_blocks, kThreads, 0, s>>>(inst, ctl, queue, segs);
         kb_finalize<3><<<B, kThreads, 0, s>>>(inst, st);
     }
     kb_lbfgs<<<B, kThreads, 0, s>>>(inst, st, ctl);

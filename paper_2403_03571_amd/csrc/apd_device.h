@@ -243,8 +243,8 @@ __device__ inline double wave_min(double v) {
 
 // ------------------------------------------------------ tile epilogue
 
-// Labels, the re-check queue, and the exact per-cell moments of every
-// settled pixel.  For a cell the moments are the pixel count and the sums
+// Labels, the re-check queue (where the pass has one), and the exact
+// per-cell moments of every settled pixel.  For a cell the moments are the pixel count and the sums
 // of o_d = 2 k_d + 1 and o_d o_e over its pixels (unsigned 64-bit atomics,
 // so the result does not depend on the order of the additions).  Within a
 // wave the pixels of one cell are first summed in 32 bits relative to the
@@ -255,11 +255,11 @@ __device__ inline void tile_epilogue(const Geo &g, const Tile<D> &t, const bool 
                                      const PassOut &out, unsigned *qcount) {
     constexpr int K = moments_per_cell(D);
     const int lane = t.lane;
-    // labels (queued pixels are overwritten by the re-check)
+    // labels (a flagged pixel's is written by the re-check)
     if (out.labels) {
 #pragma unroll
         for (int p = 0; p < P; ++p)
-            if (act[p]) out.labels[pixel_index<D>(g, t.k0w + p, t)] = lab[p];
+            if (act[p] && !flag[p]) out.labels[pixel_index<D>(g, t.k0w + p, t)] = lab[p];
     }
     // re-check queue: one atomic per block (the counter is a single address
     // shared by every block of the pass).  Every thread of the block comes
@@ -508,6 +508,132 @@ __device__ inline float gap_exact(double b, double s, double wmax) {
     if (!(den > 0.0)) return 0.0f;
     const double g = (s - b) / den;
     return g > 0.0 ? __double2float_rd(g) : 0.0f;
+}
+
+// ------------------------------------------- double re-check in the tile
+
+// (value, seed) minimum over the G lanes of a group (G a power of two up to
+// 64, groups aligned within the wave): the lowest seed among equal values.
+__device__ inline void group_min(double &b, int &bi, int G) {
+    for (int o = G / 2; o >= 1; o >>= 1) {
+        const double ob = __shfl_xor(b, o);
+        const int oi = __shfl_xor(bi, o);
+        if (ob < b || (ob == b && oi < bi)) {
+            b = ob;
+            bi = oi;
+        }
+    }
+}
+
+// The same with the runner-up value s (the smallest value other than the
+// winner's, ties included) carried along.
+__device__ inline void group_min2(double &b, int &bi, double &s, int G) {
+    for (int o = G / 2; o >= 1; o >>= 1) {
+        const double ob = __shfl_xor(b, o);
+        const int oi = __shfl_xor(bi, o);
+        const double os = __shfl_xor(s, o);
+        if (ob < b || (ob == b && oi < bi)) {
+            s = fmin(os, b);
+            b = ob;
+            bi = oi;
+        } else {
+            s = fmin(s, ob);
+        }
+    }
+}
+
+// Orders this wave's LDS writes before its lanes' later reads (and earlier
+// reads before later writes): the wave's own barrier.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Double re-check of a wave's flagged pixels inside the tile's kernel (passes
+// with candidate lists): all against the tile's list (list[0, nlist), seed
+// numbers) or, without one, every seed 0 .. nlist - 1.  The list holds every
+// seed that can attain the minimum anywhere in the tile, exact ties included,
+// so the (value, lowest seed) minimum equals that of a scan over every seed
+// in the definition's order.  A group of G lanes takes one pixel (G the
+// largest power of two, up to 64, that leaves a group for every flagged pixel
+// of the wave) and lane r of the group reads the seeds r, r + G, ... from
+// global memory: a few pixels cost one round of loads and a reduction, and
+// with many flagged every lane has its own.  About 2 in 10^4 pixels come
+// here; a queue in global memory and a kernel of its own for them took 4.5 us
+// per pass in 2D, 8.7 in 3D, and one list per tile to be written for it.
+//
+// scr: room of the wave for 64 P entries.  Writes the pixels' labels and
+// moments, and with rel_gap their relative top-two gaps (gap_exact): the
+// runner-up over the list, or, below it, the list's bound U (in the gauge
+// w - w_max) under which no seed outside the list costs.  Every lane of the
+// wave must call it.
+template <int D, int P>
+__device__ inline void recheck_flagged(const Geo &g, const Seeds &sd, const Tile<D> &t, const bool (&act)[P],
+                                       const bool (&flag)[P], const int *list, int nlist, uint16_t *scr,
+                                       const PassOut &out, unsigned *qcount, double wmax, double U) {
+    static_assert(P <= 8, "a flagged pixel's code holds the lane and p");
+    unsigned count = 0;
+    unsigned long long mk[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        mk[p] = __ballot(act[p] && flag[p]);
+        count += (unsigned)__popcll(mk[p]);
+    }
+    if (!count) return;
+    const int lane = t.lane;
+    wave_lds_sync();  // earlier reads of the room are done
+    unsigned base = 0;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const unsigned below = __builtin_amdgcn_mbcnt_hi((unsigned)(mk[p] >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo((unsigned)mk[p], 0u));
+        if (act[p] && flag[p]) scr[base + below] = (uint16_t)(lane | (p << 6));
+        base += (unsigned)__popcll(mk[p]);
+    }
+    if (lane == 0 && qcount) atomicAdd(qcount, count);
+    wave_lds_sync();
+    int G = 64;
+    while (G > 1 && (unsigned)(64 / G) < count) G >>= 1;
+    const unsigned ngroups = (unsigned)(64 / G);
+    const int grp = lane / G, r = lane % G;
+    for (unsigned p0 = 0; p0 < count; p0 += ngroups) {
+        const unsigned q = p0 + (unsigned)grp;
+        const bool valid = q < count;
+        const int code = valid ? scr[q] : 0;
+        int k[3];
+        lane_pixel<D, P>(t.org, code & 63, k[0], k[1], k[2]);
+        k[0] += code >> 6;
+        double y[D];
+        for (int d = 0; d < D; ++d) y[d] = centre(g, d, k[d]);
+        double b = INFINITY, s2 = INFINITY;
+        int bi = 0x7fffffff;
+        for (int z = r; z < nlist; z += G) {
+            const int i = list ? list[z] : z;
+            const double c = exact_cost<D>(sd.x, sd.A, sd.w, i, y);
+            if (c < b || (c == b && i < bi)) {
+                s2 = b;
+                b = c;
+                bi = i;
+            } else {
+                s2 = fmin(s2, c);
+            }
+        }
+        if (out.rel_gap) group_min2(b, bi, s2, G);
+        else group_min(b, bi, G);
+        if (bi >= g.n) bi = 0;  // no finite cost (non-finite input, reported by the prep step)
+        if (valid && r == 0) {
+            uint32_t j = (uint32_t)k[0];
+            for (int d = 1; d < D; ++d) j = j * (uint32_t)g.grid[d] + (uint32_t)k[d];
+            if (out.labels) out.labels[j] = bi;
+            if (out.mom) pixel_moments_add<D>(out.mom, bi, k, pixel_weight(g, j));
+            if (out.rel_gap) {
+                // a seed outside the list costs more than U - w_max (unshifted)
+                const double su = U - wmax;
+                out.rel_gap[j] = su < s2 ? gap_exact(b, su - 1e-9 * fabs(U), wmax) : gap_exact(b, s2, wmax);
+            }
+        }
+    }
 }
 
 // ------------------------------------------------------ k_assign_mfma
@@ -1110,11 +1236,6 @@ __device__ inline void credit_tile(const Geo &g, const Tile<D> &t, int b0, int b
             b[d] = min(base[d] + ext[d], g.grid[d]) - 1;
         }
         if (out.mom) box_moments_add<D>(out.mom, L, a, b);
-        if (out.tile_lists) {
-            const int tid = ((b0 * out.ntile[1]) + b1) * out.ntile[2] + b2;
-            out.tile_lists[(size_t)tid * out.list_cap] = L;
-            out.tile_count[tid] = 1;
-        }
         if (out.credited) atomicAdd(out.credited, 1u);
     }
 }
@@ -1136,7 +1257,7 @@ struct VecSmem {
     float4 sC[VecCfg<D, CULL>::kRows][VecCfg<D, CULL>::kChunk + 1];
     float4 sB[CULL ? VecCfg<D, CULL>::kChunk : 1];  // (x - anchor, w - wmax) in FP32
     int list[CULL ? kCullCap : 1];        // candidate seeds of the tile
-    int wl[kWaves][CULL ? kWaveCap : 1];  // staged positions of each wave's candidates
+    int wl[kWaves][CULL ? kWaveCap : 1];  // staged positions of each wave's candidates; then its flagged pixels
     double red[kWaves];
     int redi[kWaves];
     int cnt;
@@ -1157,7 +1278,6 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     const bool lane_ok = lane_in_grid<D>(g, t);
     int nscan = g.n;
     bool full = true;
-    int ncand_kept = 0;
     double Utile = INFINITY;  // no seed left out of the tile's list costs less
     float Uwave = INFINITY;   // nor out of this wave's list
     if (CULL) {
@@ -1180,7 +1300,6 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                                               s_cnt, s_red, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
-        ncand_kept = ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
         if (out.adaptive && !full && !g.mass && !out.rel_gap) {
             const int own = box_owner<D>(sd, wmax, blo, bhi, s_list, ncand, s_red, sm.redi);
@@ -1514,21 +1633,10 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = fs[p] > 0.0f ? gap_lower(c1u, c2l) : 0.0f;
         }
     }
-    PassOut o = out;
-    if (CULL && out.tile_lists) {
-        // keep the candidates for the re-check of this tile's queued pixels
-        const int tid = ((b0 * out.ntile[1]) + b1) * out.ntile[2] + b2;
-        o.tile_id = tid;
-        const bool keep = !full && ncand_kept <= out.list_cap;
-        if (keep)
-            for (int q = threadIdx.x; q < ncand_kept; q += kThreads)
-                out.tile_lists[(size_t)tid * out.list_cap + q] = s_list[q];
-        if (threadIdx.x == 0) {
-            out.tile_count[tid] = keep ? ncand_kept : out.list_cap + 1;
-            if (out.tile_U) out.tile_U[tid] = keep ? Utile : INFINITY;
-        }
-    }
-    tile_epilogue<D, P>(g, t, act, lab, flag, o, qcount);
+    tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+    if constexpr (CULL)
+        recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : s_list, full ? g.n : nscan,
+                              reinterpret_cast<uint16_t *>(wl), out, qcount, wmax, Utile);
 }
 
 
@@ -2104,6 +2212,7 @@ struct Bf16Smem {
     float4 sF4[D - 1][C];
     float2 sF2[C];
     int list[CULL ? kCullCap : 1];
+    uint16_t flagged[kWaves][CULL ? 64 * 4 : 1];  // recheck_flagged's pixels (at most 4 per lane)
     double red[kWaves];
     int redi[kWaves];
     int cnt;
@@ -2228,7 +2337,6 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     // ---- the candidate list, from the super-tile's list when it has one
     int nscan = g.n;
     bool full = true;
-    int ncand_kept = 0;
     double Utile = INFINITY;  // no seed left out of the tile's list costs less
     if (CULL) {
         double blo[3], bhi[3];
@@ -2249,7 +2357,6 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
                                               sm.red, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
-        ncand_kept = ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
         if (out.adaptive && !full && !g.mass && !out.rel_gap) {
             const int own = box_owner<D>(sd, wmax, blo, bhi, sm.list, ncand, sm.red, sm.redi);
@@ -2454,32 +2561,20 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             }
         }
     }
-    PassOut o = out;
-    if (CULL && out.tile_lists) {
-        // keep the candidates for the re-check of this tile's queued pixels
-        const int tid = ((b0 * out.ntile[1]) + b1) * out.ntile[2] + b2;
-        o.tile_id = tid;
-        const bool keep = !full && ncand_kept <= out.list_cap;
-        if (keep)
-            for (int q = threadIdx.x; q < ncand_kept; q += kThreads)
-                out.tile_lists[(size_t)tid * out.list_cap + q] = sm.list[q];
-        if (threadIdx.x == 0) {
-            out.tile_count[tid] = keep ? ncand_kept : out.list_cap + 1;
-            if (out.tile_U) out.tile_U[tid] = keep ? Utile : INFINITY;
-        }
-    }
-    tile_epilogue<D, P>(g, t, act, labe, flag, o, qcount);
+    tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
+    if constexpr (CULL)
+        recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : sm.list, full ? g.n : nscan,
+                              sm.flagged[threadIdx.x >> 6], out, qcount, wmax, Utile);
 }
 
 // ------------------------------------------------------- double re-check
 
 // Seeds staged in LDS for the double re-check: x, the upper triangle of A
-// (row by row) and w of up to S seeds, and their seed numbers.
+// (row by row) and w of up to S seeds.
 template <int D, int S>
 struct StagedSeeds {
     static constexpr int kSeeds = S;
     static constexpr int kTri = D * (D + 1) / 2;
-    int idx[S];
     double x[D][S];
     double a[kTri][S];
     double w[S];
@@ -2497,7 +2592,6 @@ __device__ inline void stage_seed(StagedSeeds<D, S> &sm, const Seeds &sd, int q,
         for (int c = r; c < D; ++c, ++t) sm.a[t][q] = ai[r * D + c];
     }
     sm.w[q] = sd.w[i];
-    sm.idx[q] = i;
 }
 
 // The double cost of the staged seed at position q at y, in the expression
@@ -2535,66 +2629,17 @@ __device__ inline void pixel_of(const Geo &g, uint32_t j, int *k, double *y) {
     for (int d = 0; d < D; ++d) y[d] = centre(g, d, k[d]);
 }
 
-// (value, seed) minimum over the G lanes of a group (G a power of two up to
-// 64, groups aligned within the wave): the lowest seed among equal values.
-__device__ inline void group_min(double &b, int &bi, int G) {
-    for (int o = G / 2; o >= 1; o >>= 1) {
-        const double ob = __shfl_xor(b, o);
-        const int oi = __shfl_xor(bi, o);
-        if (ob < b || (ob == b && oi < bi)) {
-            b = ob;
-            bi = oi;
-        }
-    }
-}
-
-// The same with the runner-up value s (the smallest value other than the
-// winner's, ties included) carried along.
-__device__ inline void group_min2(double &b, int &bi, double &s, int G) {
-    for (int o = G / 2; o >= 1; o >>= 1) {
-        const double ob = __shfl_xor(b, o);
-        const int oi = __shfl_xor(bi, o);
-        const double os = __shfl_xor(s, o);
-        if (ob < b || (ob == b && oi < bi)) {
-            s = fmin(os, b);
-            b = ob;
-            bi = oi;
-        } else {
-            s = fmin(s, ob);
-        }
-    }
-}
-
-// Orders this wave's LDS writes before its lanes' later reads (and earlier
-// reads before later writes): the wave's own barrier.
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Double re-check, by one wave, of the `count` queued pixels from queue
-// position `start`, all of one tile, against the tile's candidate list
-// (list[0, nlist), seed numbers) or, without one, every seed.  The
-// candidates are staged in the wave's own LDS (sm) chunk by chunk; a group
-// of G lanes takes one pixel (G the largest power of two, up to 64, that
-// leaves a group for every pixel of the segment), lane r of the group scans
-// the staged positions r, r + G, ...  The list holds every seed that can
-// attain the minimum anywhere in the tile, exact ties included, so the
-// (value, lowest seed) minimum equals that of a scan over every seed in the
-// definition's order.  pixel_at(q) gives the pixel index at queue position
-// q.  Every lane of the wave must call it.
-//
-// With rel_gap it also writes each pixel's relative top-two gap
-// (gap_exact): the runner-up over the list, or, below it, the list's bound
-// U (in the gauge w - w_max) under which no seed outside the list costs.
+// position `start` against every seed (the batched passes without candidate
+// lists).  The seeds are staged in the wave's own LDS (sm) chunk by chunk; a
+// group of G lanes takes one pixel (G the largest power of two, up to 64,
+// that leaves a group for every pixel of the segment), lane r of the group
+// scans the staged positions r, r + G, ...  pixel_at(q) gives the pixel index
+// at queue position q.  Every lane of the wave must call it.
 template <int D, int S, class PixelAt>
 __device__ inline void recheck_segment(const Geo &g, const Seeds &sd, unsigned start, unsigned count,
-                                       const int *list, int nlist, PixelAt pixel_at, int32_t *labels,
-                                       uint64_t *mom, StagedSeeds<D, S> &sm, float *rel_gap = nullptr,
-                                       double wmax = 0.0, double U = INFINITY) {
+                                       PixelAt pixel_at, uint64_t *mom, StagedSeeds<D, S> &sm) {
     const int lane = __lane_id();
-    const int nseed = list ? nlist : g.n;
     int G = 64;
     while (G > 1 && (unsigned)(64 / G) < count) G >>= 1;
     const unsigned ngroups = (unsigned)(64 / G);
@@ -2606,37 +2651,24 @@ __device__ inline void recheck_segment(const Geo &g, const Seeds &sd, unsigned s
         int k[3];
         double y[D];
         pixel_of<D>(g, j, k, y);
-        double b = INFINITY, s2 = INFINITY;
+        double b = INFINITY;
         int bi = 0x7fffffff;
-        for (int c0 = 0; c0 < nseed; c0 += S) {
-            const int cnt = min(S, nseed - c0);
+        for (int c0 = 0; c0 < g.n; c0 += S) {
+            const int cnt = min(S, g.n - c0);
             wave_lds_sync();
-            for (int q = lane; q < cnt; q += 64) stage_seed<D, S>(sm, sd, q, list ? list[c0 + q] : c0 + q);
+            for (int q = lane; q < cnt; q += 64) stage_seed<D, S>(sm, sd, q, c0 + q);
             wave_lds_sync();
             for (int q = r; q < cnt; q += G) {
                 const double c = staged_cost<D, S>(sm, q, y);
-                const int i = sm.idx[q];
-                if (c < b || (c == b && i < bi)) {
-                    s2 = b;
+                if (c < b || (c == b && c0 + q < bi)) {
                     b = c;
-                    bi = i;
-                } else {
-                    s2 = fmin(s2, c);
+                    bi = c0 + q;
                 }
             }
         }
-        if (rel_gap) group_min2(b, bi, s2, G);
-        else group_min(b, bi, G);
+        group_min(b, bi, G);
         if (bi >= g.n) bi = 0;  // no finite cost (non-finite input, reported by the prep step)
-        if (valid && r == 0) {
-            if (labels) labels[j] = bi;
-            if (mom) pixel_moments_add<D>(mom, bi, k, pixel_weight(g, j));
-            if (rel_gap) {
-                // a seed outside the list costs more than U - w_max (unshifted)
-                const double su = U - wmax;
-                rel_gap[j] = su < s2 ? gap_exact(b, su - 1e-9 * fabs(U), wmax) : gap_exact(b, s2, wmax);
-            }
-        }
+        if (valid && r == 0) pixel_moments_add<D>(mom, bi, k, pixel_weight(g, j));
     }
 }
 

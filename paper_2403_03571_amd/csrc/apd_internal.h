@@ -58,10 +58,7 @@ struct Scalars {
     double vsum;      // sum_i v_i
     double g;         // objective of eq. (2.7)
     double maxrel;    // max_i |v_i - m_i|P|| / v_i
-    // pixels queued for the double re-check and the queue's segments (with
-    // candidate lists): one 8-byte pair, taken together by one atomic
-    unsigned qcount;
-    unsigned segcount;
+    unsigned qcount;  // pixels re-evaluated in double
     float lam;        // upper bound of max_i lambda_max(A_i) (Gershgorin)
     float kap;        // upper bound of max_i lambda_G(A_i) / lambda_min(A_i)
     int bad;          // validation bits
@@ -70,9 +67,6 @@ struct Scalars {
     unsigned credited;  // tiles credited whole (boundary-aware refinement)
     double gpix;        // sum_j q_j C_{H_j j} (costs other than the squared norm)
 };
-
-static_assert(offsetof(Scalars, qcount) % 8 == 0 && offsetof(Scalars, segcount) == offsetof(Scalars, qcount) + 4,
-              "the queue counters form one aligned 8-byte pair");
 
 enum : int { kBadW = 1, kBadX = 2, kBadA = 4, kBadSPD = 8, kBadV = 16 };
 
@@ -94,10 +88,8 @@ struct BlockParts {
 // coordinates o_d = 2 k_d + 1 (exact unsigned integers)
 constexpr int moments_per_cell(int dim) { return dim == 2 ? 6 : 10; }
 
-constexpr int kCullCapDefault = 2048;  // = kCullCap, the tile lists' default capacity
-
 // A block's share of the re-check queue: queue[start, start + count) are
-// pixels of tile `tile` (of instance `tag` in the batched form).
+// pixels of tile `tile` of instance `tag`.
 struct QSeg {
     uint32_t start;
     uint32_t count;
@@ -125,36 +117,25 @@ __host__ __device__ inline double cond_bound(int dim, double lg, double det) {
 struct PassOut {
     int32_t *labels;     // [J] or nullptr
     uint64_t *mom;       // [n][K] or nullptr
-    unsigned *queue;     // [J] re-check queue (single-precision tier)
+    unsigned *queue;     // [J] re-check queue (single-precision passes over every seed) or nullptr
     uint64_t *queue64 = nullptr;  // batched form: (tag << 32 | pixel) entries
     uint32_t tag = 0;             // batched form: instance index
-    // candidate lists of the culled vector kernel, kept for the re-check:
-    // tile t's seeds in tile_lists[t * list_cap ...], their number in
-    // tile_count[t] (above list_cap: every seed); tiles of tp pixels per lane
-    int *tile_lists = nullptr;
-    int *tile_count = nullptr;
-    int list_cap = kCullCapDefault;  // entries kept per tile list
-    int tp = 0;
-    int ntile[3] = {0, 0, 0};
+    int tp = 0;  // pixels per lane of the tiles of a pass with candidate lists
     // super-tiles of sf[0] x sf[1] x sf[2] tiles (nst[] of them per axis):
     // their candidate seeds, from which the tiles pick theirs
     const int *super_list = nullptr;   // [super-tiles][super_cap]
     const int *super_count = nullptr;  // above super_cap: every seed
-    int super_cap = kCullCapDefault;
+    int super_cap = 2048;
     int sf[3] = {1, 1, 1};
     int nst[3] = {1, 1, 1};
-    // segments of the queue (one per block that queued pixels), so that the
-    // re-check can take a tile's pixels together; null: not recorded.  With
-    // segments the queue counter is the first of an 8-byte aligned pair
-    // (pixels, segments) advanced by one 64-bit atomic.
+    // batched form: segments of the queue (one per block that queued pixels),
+    // so that the re-check can take an instance's pixels together; the queue
+    // counter is then the first of an 8-byte aligned pair (pixels, segments)
+    // advanced by one 64-bit atomic; null: not recorded
     QSeg *segs = nullptr;
-    int tile_id = 0;  // this tile's index in the tile lists' layout
-    // per-pixel lower bound of the relative top-two gap (apd_assign) or
-    // null; with candidate lists the tiles also keep, in tile_U, the bound
-    // below which no seed outside their list can cost (the re-check needs
-    // it for the runner-up)
+    int tile_id = 0;  // this tile's index in its instance
+    // per-pixel lower bound of the relative top-two gap (apd_assign) or null
     float *rel_gap = nullptr;
-    double *tile_U = nullptr;
     // the hybrid kernel's seed order (k_seed_order): position q of its scan
     // holds seed seed_order[q]; null: the identity
     const int *seed_order = nullptr;
@@ -217,6 +198,8 @@ hipError_t launch_seed_order(const Geo &g, const Seeds &sd, int *ord, hipStream_
 // lists (eig from the prep kernel, tile geometry of bf16_pixels_per_lane).
 hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
+// The double re-check of the queue of a pass over every seed (passes with
+// candidate lists re-check in the tile).
 hipError_t launch_recheck(const Geo &g, const Seeds &sd, const Scalars *sc,
                           const PassOut &out, hipStream_t st);
 // Zeroes `bytes` (a multiple of 4) at device address p with a kernel.

@@ -18,11 +18,10 @@
 //                 cores) and _bf16 (bf16 matrix cores) evaluate it in local
 //                 coordinates and queue every pixel whose top-two gap is
 //                 within their rounding bound.
-//   k_recheck_*   re-runs the scan of every queued pixel in double, in
+//   k_recheck_staged  re-runs the scan of every queued pixel in double, in
 //                 the definition's own expression order, so every label
-//                 equals that of an exact double-precision argmin (_staged:
-//                 every seed, staged in LDS; _seg: a tile's candidate list,
-//                 staged once for all the tile's queued pixels).
+//                 equals that of an exact double-precision argmin (passes
+//                 over every seed; passes with lists re-check in the tile).
 //   k_finalize    blocks of cells, the last to finish combining them:
 //                 objective (2.7), gradient (2.8), maximum relative volume
 //                 error, centroids, from the moments.
@@ -189,7 +188,6 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
         sc->kap = s_k[0] * 1.0001f;
         sc->bad = s_b[0];
         sc->qcount = 0u;
-        sc->segcount = 0u;
         sc->credited = 0u;
         sc->gpix = 0.0;
         sc->g = 0.0;
@@ -459,7 +457,6 @@ __global__ __launch_bounds__(kThreads) void k_super_cull(Geo g, Seeds sd, const 
 
 // Seeds per staged chunk of the re-check kernels.
 template <int D> struct RecheckChunk { static constexpr int value = D == 2 ? 1024 : 512; };
-template <int D> struct SegChunk { static constexpr int value = 128; };  // per wave
 
 // Re-check over every seed (passes without candidate lists): the seeds are
 // staged in LDS chunk by chunk and a group of G lanes takes one queued
@@ -519,27 +516,6 @@ __global__ __launch_bounds__(kThreads) void k_recheck_staged(Geo g, Seeds sd, co
             if (out.mom) dev::pixel_moments_add<D>(out.mom, bi, k, dev::pixel_weight(g, j));
             if (out.rel_gap) out.rel_gap[j] = dev::gap_exact(b, s2, sc->wmax);
         }
-    }
-}
-
-// Re-check with the tiles' candidate lists: one wave per queue segment (the
-// queued pixels of one tile), the tile's candidates staged once for all of
-// them (dev::recheck_segment); a tile whose list overflowed scans every seed.
-template <int D>
-__global__ __launch_bounds__(kThreads) void k_recheck_seg(Geo g, Seeds sd, const Scalars *sc,
-                                                         PassOut out) {
-    constexpr int S = SegChunk<D>::value;
-    __shared__ StagedSeeds<D, S> sm[kWaves];
-    const unsigned nseg = sc->segcount;
-    const int wave = threadIdx.x >> 6;
-    for (unsigned s = blockIdx.x * kWaves + wave; s < nseg; s += gridDim.x * kWaves) {
-        const QSeg seg = out.segs[s];
-        const int cnt = out.tile_count[seg.tile];
-        const int *list = cnt <= out.list_cap ? out.tile_lists + (size_t)seg.tile * out.list_cap : nullptr;
-        const unsigned *queue = out.queue;
-        const double U = (list && out.tile_U) ? out.tile_U[seg.tile] : INFINITY;
-        recheck_segment<D, S>(g, sd, seg.start, seg.count, list, cnt, [&](unsigned q) { return queue[q]; },
-                              out.labels, out.mom, sm[wave], out.rel_gap, sc->wmax, U);
     }
 }
 
@@ -610,7 +586,6 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(Geo g, Seeds sd, const
             h->g = sc->g;
             h->maxrel = sc->maxrel;
             h->qcount = sc->qcount;
-            h->segcount = sc->segcount;
             h->lam = sc->lam;
             h->bad = sc->bad;
             h->qtotal = sc->qtotal;
@@ -776,21 +751,10 @@ hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const 
 hipError_t launch_recheck(const Geo &g, const Seeds &sd, const Scalars *sc, const PassOut &out,
                           hipStream_t st) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    // a scan over every seed: stage the seeds in LDS (three blocks of 48 KB
-    // or four of 40 KB per compute unit)
-    if (!out.tile_lists) {
-        if (g.dim == 2) k_recheck_staged<2><<<768, kThreads, 0, st>>>(g, sd, sc, out);
-        else k_recheck_staged<3><<<1024, kThreads, 0, st>>>(g, sd, sc, out);
-        return hipGetLastError();
-    }
-    // with the tiles' candidate lists: one wave per segment (a tile's
-    // queued pixels), as many as fit on the chip (a segment is a short chain
-    // of dependent loads, so concurrency sets the speed); waves past the
-    // segments leave at once
-    const int64_t tiles = (int64_t)out.ntile[0] * out.ntile[1] * out.ntile[2];
-    const unsigned nb = (unsigned)std::max<int64_t>(1, std::min<int64_t>((tiles + kWaves - 1) / kWaves, 2048));
-    if (g.dim == 2) k_recheck_seg<2><<<nb, kThreads, 0, st>>>(g, sd, sc, out);
-    else k_recheck_seg<3><<<nb, kThreads, 0, st>>>(g, sd, sc, out);
+    // the seeds staged in LDS: three blocks of 48 KB or four of 40 KB per
+    // compute unit
+    if (g.dim == 2) k_recheck_staged<2><<<768, kThreads, 0, st>>>(g, sd, sc, out);
+    else k_recheck_staged<3><<<1024, kThreads, 0, st>>>(g, sd, sc, out);
     return hipGetLastError();
 }
 

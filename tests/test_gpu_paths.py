@@ -35,3 +35,40 @@ def test_batch_work_list(ctx, count):
         assert rep[0].evals == reps[b].evals
         np.testing.assert_array_equal(one[0].cpu().numpy(), ws[b].cpu().numpy())
         assert O.evaluate(insts[b], ws[b].cpu().numpy()).maxrel < 0.05
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (70, 45)), (3, (19, 13, 21))])
+@pytest.mark.parametrize("prec", ["fp32", "bf16"])
+@pytest.mark.parametrize("ppl", [4, 8])
+def test_recheck_in_the_tile(ctx, dim, grid, prec, ppl):
+    """Every pixel of the tiles re-checked (each seed twice: exact ties), half
+    of them, or none: labels, counts (pixel weights among them) and gaps
+    against the oracle."""
+    import torch
+    for twice in (11, 5, 0):
+        inst = S.custom(dim, 11, grid, seed=twice + dim, sigma=0.3)
+        x = np.concatenate([inst.x, inst.x[:twice]])
+        A = np.concatenate([inst.A, inst.A[:twice]])
+        n = len(x)
+        w = np.random.default_rng(3).uniform(-0.01, 0.01, 11)
+        w = np.concatenate([w, w[:twice]])
+        inst = S.Instance(dim, grid, inst.lo, inst.hi, x, A, np.full(n, 1.0 / n))
+        inst.v[0] += 1.0 - inst.v.sum()
+        ctx.apd_set_pixels_per_lane(ppl)
+        try:
+            for case in (inst, S.masked(inst, S.disk_weights(grid, inst.lo, inst.hi, (0.5,) * dim, 0.45))):
+                prob = _prob(case)
+                wd = torch.as_tensor(w, device="cuda:0")
+                ref, best, second = O.assign(case, w)
+                lab, gap = ctx.apd_assign(prob, wd, prec=prec, rel_gap=True)
+                np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+                np.testing.assert_array_equal(ctx.apd_assign(prob, wd, prec=prec).cpu().numpy(), ref)
+                rel = (second - best) / (second + w.max())
+                assert np.all(gap.cpu().numpy() <= rel * (1 + 1e-6) + 1e-12)
+                out = ctx.apd_dual_objective_grad(prob, wd, prec=prec, counts=True)
+                q = np.ones(case.J, np.int64) if case.mass is None else case.mass.astype(np.int64)
+                np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, q, n).astype(np.int64))
+                if twice == 11:
+                    assert ctx.apd_last_pass_stats()["rechecked"] == case.J
+        finally:
+            ctx.apd_set_pixels_per_lane(0)
