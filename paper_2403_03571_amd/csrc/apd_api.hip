@@ -36,7 +36,8 @@ struct apd_ctx {
     int *ws_nb = nullptr;             // [cap_n][16] nearest seeds (warm-start features)
     double *cost_part = nullptr;      // [cap_parts] per-block cost sums (costs other than |.|^2_A)
     int64_t cap_parts = 0;
-    int *super_lists = nullptr;       // [cap_super][kSuperCap] candidate seeds per super-tile
+    float4 *super_lists = nullptr;    // candidate records of the super-tiles
+    size_t super_bytes = 0;
     int *super_count = nullptr;       // [cap_super]
     int64_t cap_super = 0;
     bool need_qtotal = false;          // sum the pixel weights in the next pass (validation)
@@ -213,7 +214,7 @@ struct PassBufs {
     unsigned *queue = nullptr;     // [J]
     double *eig = nullptr;         // [n][2]
     int *ord = nullptr;            // [n] seed order of the hybrid kernel
-    int *super_lists = nullptr;    // [super-tiles][super_cap]
+    float4 *super_lists = nullptr; // [super-tiles][rec_vec][super_cap]
     int *super_count = nullptr;    // [super-tiles]
     int64_t cap_super = 0;
     int super_cap = apd::kSuperCap;
@@ -328,14 +329,22 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
                 if (L.nsuper > b.cap_super)
                     return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
             } else {
-                if (L.nsuper > c->cap_super) {
+                b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, p->n);
+                const size_t rec_bytes = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim) * sizeof(float4);
+                if (rec_bytes > c->super_bytes) {
                     (void)hipFree(c->super_lists);
-                    (void)hipFree(c->super_count);
                     c->super_lists = nullptr;
+                    c->super_bytes = 0;
+                    if (hipMalloc(&c->super_lists, rec_bytes) != hipSuccess)
+                        return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
+                                    (long long)L.nsuper);
+                    c->super_bytes = rec_bytes;
+                }
+                if (L.nsuper > c->cap_super) {
+                    (void)hipFree(c->super_count);
                     c->super_count = nullptr;
                     c->cap_super = 0;
-                    if (hipMalloc(&c->super_lists, (size_t)L.nsuper * apd::kSuperCap * sizeof(int)) != hipSuccess ||
-                        hipMalloc(&c->super_count, (size_t)L.nsuper * sizeof(int)) != hipSuccess)
+                    if (hipMalloc(&c->super_count, (size_t)L.nsuper * sizeof(int)) != hipSuccess)
                         return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
                                     (long long)L.nsuper);
                     c->cap_super = L.nsuper;
@@ -349,7 +358,8 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
                 out.sf[d] = L.sf[d];
                 out.nst[d] = L.nst[d];
             }
-            if (L.sf[0] * L.sf[1] * L.sf[2] > 1) {
+            // up to a block's threads of seeds the tiles read them all at once
+            if (L.sf[0] * L.sf[1] * L.sf[2] > 1 && p->n > apd::kThreads) {
                 out.super_cap = b.super_cap;
                 HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, b.super_lists, b.super_count,
                                                   c->stream));
@@ -941,7 +951,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
                 a[3 + d] = (tl[d] + a[d] - 1) / a[d];
                 cnt *= a[3 + d];
             }
-            if (a[0] * a[1] * a[2] == 1) cnt = 0;
+            if (a[0] * a[1] * a[2] == 1 || p.n <= apd::kThreads) cnt = 0;
         }
         sfn[q] = a;
         super0[q + 1] = super0[q] + cnt;
@@ -961,7 +971,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     const size_t o_seg = bytes;
     if (!lists) bytes = align_up(bytes + (size_t)ntiles * sizeof(apd::QSeg), 256);
     const size_t o_sl = bytes;
-    bytes = align_up(bytes + (size_t)nsuper * apd::kBatchSuperCap * sizeof(int), 256);
+    bytes = align_up(bytes + (size_t)nsuper * apd::kBatchSuperCap * apd::rec_vec(dim) * sizeof(float4), 256);
     const size_t o_sc = bytes;
     bytes = align_up(bytes + (size_t)nsuper * sizeof(int), 256);
     const size_t o_s0 = bytes;
@@ -994,7 +1004,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     double **d_dst = (double **)(base + o_dst);
     uint64_t *d_queue = (uint64_t *)(base + o_q);
     apd::QSeg *d_segs = (apd::QSeg *)(base + o_seg);
-    int *d_sl = (int *)(base + o_sl);
+    float4 *d_sl = (float4 *)(base + o_sl);
     int *d_sc = (int *)(base + o_sc);
     int64_t *d_super0 = (int64_t *)(base + o_s0);
     int64_t *d_act = (int64_t *)(base + o_at);
@@ -1022,7 +1032,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         I.eig = I.rho + kBatchHist;
         I.mom = mom + off_m[q];
         const bool has_super = super0[q + 1] > super0[q];
-        I.super_lists = has_super ? d_sl + super0[q] * apd::kBatchSuperCap : nullptr;
+        I.super_lists = has_super ? d_sl + super0[q] * apd::kBatchSuperCap * apd::rec_vec(dim) : nullptr;
         I.super_count = has_super ? d_sc + super0[q] : nullptr;
         for (int d = 0; d < 3; ++d) {
             I.sf[d] = sfn[q][d];
@@ -1394,15 +1404,25 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         k.take<int>((size_t)L.tiles);
         k.take<double>((size_t)L.tiles);
         k.take<apd::QSeg>((size_t)L.tiles);
-        b.super_lists = k.take<int>((size_t)L.nsuper * kStaticSuperCap);
+        k.take<int>((size_t)L.nsuper * kStaticSuperCap);
         b.super_count = k.take<int>((size_t)L.nsuper);
         b.cap_super = L.nsuper;
-        b.super_cap = kStaticSuperCap;
     }
     if (k.off > kStaticScratch)
         return fail(c, APD_ERR_OOM,
                     "this problem needs %zu bytes of scratch; the static array holds %zu (n = %lld, J = %lld)",
                     k.off, kStaticScratch, (long long)n, (long long)J);
+    if (cull) {
+        // the super-tiles' records take the room that the limit counts for
+        // the queue, the tiles' lists and the super-tiles' (a pass with lists
+        // has no queue), as many per super-tile as fit
+        const size_t rec = (size_t)b.cap_super * apd::rec_vec(p->dim) * sizeof(float4);
+        const size_t first = (size_t)((unsigned char *)b.queue - base);
+        const size_t last = (size_t)((unsigned char *)b.super_count - base);
+        b.super_lists = reinterpret_cast<float4 *>(b.queue);
+        b.super_cap = (int)std::min<size_t>({(size_t)kStaticSuperCap, (size_t)n, (last - first) / rec});
+        b.queue = nullptr;
+    }
     // the block partials' ticket must start at zero (each launch leaves it
     // so; the array starts zeroed, but an aborted call may not have)
     HIP_TRY(c, apd::launch_zero(b.parts, sizeof(apd::BlockParts), c->stream));

@@ -26,7 +26,7 @@ struct BInst {
     int tiles1;       // tiles along axis 1
     int tiles2;       // tiles along axis 2 (3D)
     int tiles0;       // tiles along axis 0
-    int *super_lists; // [super-tiles][kBatchSuperCap] (vector kernel with lists) or null
+    float4 *super_lists; // [super-tiles][rec_vec][kBatchSuperCap] (kernels with lists) or null
     int *super_count; // [super-tiles]
     int sf[3];        // tiles per super-tile along each axis
     int nst[3];       // super-tiles along each axis

@@ -194,8 +194,7 @@ __device__ inline int find_instance(const int64_t *prefix, int B, int64_t item) 
 // (dev::super_tile_list); blocks past the active ones leave at once.
 template <int D>
 __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BState *st, BWork wk, int B) {
-    __shared__ int s_cnt;
-    __shared__ double s_red[kWaves];
+    __shared__ SuperSmem<D, kThreads> sm;
     const int64_t item = blockIdx.x;
     if (item >= wk.act_super[B]) return;
     const int b = find_instance(wk.act_super, B, item);
@@ -208,8 +207,9 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
         out.sf[d] = I.sf[d];
         out.nst[d] = I.nst[d];
     }
-    super_tile_list<D>(I.g, sd, st[b].wmax, I.eig, out, local, I.super_lists + (size_t)local * kBatchSuperCap,
-                       I.super_count + local, kBatchSuperCap, s_cnt, s_red);
+    super_tile_list<D, kThreads>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, out, local,
+                                 I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D),
+                                 I.super_count + local, kBatchSuperCap, sm);
 }
 
 // The work is split without a counter: block k takes the tiles k, k + grid,

@@ -895,8 +895,8 @@ __device__ inline void mfma_tile(const Geo &g, const Seeds &sd, double wmax, Cer
 constexpr int kPv = 8;  // pixels per lane of the vector kernel (4 on small grids)
 
 
-// The vector single-precision kernel over the seeds that can win somewhere
-// in the tile.  For the box B spanned by the tile's pixel centres,
+// Separate bounds of the costs, for the super-tiles and for the passes that
+// return the relative gaps.  For the box B spanned by the tile's pixel centres,
 //   min_{y in B} C_i(y) >= lmin_i dist(x_i, B)^2 - w_i'        = LB_i
 //   max_{y in B} C_i(y) <= lmax_i maxdist(x_i, B)^2 - w_i'     = UB_i
 // (lmin, lmax the eigenvalue range of A_i), so a seed with LB_i above
@@ -975,43 +975,23 @@ __device__ inline void cull_bounds(const Seeds &sd, const double *eig, double wm
     *ub = h - wp + slack;
 }
 
-// Block-wide: the seeds of src[0..nsrc) (of 0..nsrc-1 when src is null)
-// whose lower bound does not exceed the smallest upper bound U, written to
-// dst (at most cap of them, in any order); returns their number (which may
-// exceed cap) and U in *Uout: every seed left out costs more than U
-// everywhere in the box.  All threads of the block call it.
-template <int D, bool EXACT = true>
+// Block-wide: of the seeds id(0) .. id(nsrc - 1) those whose lower bound
+// does not exceed the smallest upper bound U, written to dst (at most cap of
+// them, in any order); returns their number (which may exceed cap) and U in
+// *Uout: every seed left out costs more than U everywhere in the box (what a
+// pass that returns the relative gaps needs).  All threads of the block call
+// it.
+template <int D, class Id>
 __device__ inline int build_candidates(const Seeds &sd, const double *eig, double wmax,
-                                       const double *blo, const double *bhi, const int *src,
+                                       const double *blo, const double *bhi, Id id,
                                        int nsrc, int *dst, int cap, int &s_cnt, double *s_red,
-                                       double *Uout = nullptr) {
+                                       double *Uout) {
     const int lane = __lane_id();
-    // a short source list keeps each thread's bounds in registers between
-    // the two passes (one read of the seed data); a long one is read twice
-    constexpr int kReg = 8;
-    const bool in_regs = src && nsrc <= kReg * kThreads;
-    double lbr[kReg];
-    int ir[kReg];
     double umin = INFINITY;
-    if (in_regs) {
-#pragma unroll
-        for (int r = 0; r < kReg; ++r) {
-            const int q = threadIdx.x + r * kThreads;
-            lbr[r] = INFINITY;
-            ir[r] = 0;
-            if (q < nsrc) {
-                double ub;
-                ir[r] = src[q];
-                cull_bounds<D, EXACT>(sd, eig, wmax, blo, bhi, ir[r], &lbr[r], &ub);
-                umin = fmin(umin, ub);
-            }
-        }
-    } else {
-        for (int q = threadIdx.x; q < nsrc; q += kThreads) {
-            double lb, ub;
-            cull_bounds<D, EXACT>(sd, eig, wmax, blo, bhi, src ? src[q] : q, &lb, &ub);
-            umin = fmin(umin, ub);
-        }
+    for (int q = threadIdx.x; q < nsrc; q += kThreads) {
+        double lb, ub;
+        cull_bounds<D, true>(sd, eig, wmax, blo, bhi, id(q), &lb, &ub);
+        umin = fmin(umin, ub);
     }
     umin = wave_min(umin);
     __syncthreads();  // s_cnt and s_red may still be read by an earlier use
@@ -1019,7 +999,7 @@ __device__ inline int build_candidates(const Seeds &sd, const double *eig, doubl
     if (lane == 0) s_red[threadIdx.x >> 6] = umin;
     __syncthreads();
     const double U = fmin(fmin(s_red[0], s_red[1]), fmin(s_red[2], s_red[3]));
-    if (Uout) *Uout = U;
+    *Uout = U;
     auto emit = [&](bool cand, int i) {
         const unsigned long long m = __ballot(cand);
         int base = 0;
@@ -1029,53 +1009,371 @@ __device__ inline int build_candidates(const Seeds &sd, const double *eig, doubl
                                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
         if (cand && base + below < cap) dst[base + below] = i;
     };
+    for (int q0 = 0; q0 < nsrc; q0 += kThreads) {
+        const int q = q0 + threadIdx.x;
+        bool cand = false;
+        int i = 0;
+        if (q < nsrc) {
+            i = id(q);
+            double lb, ub;
+            cull_bounds<D, true>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            cand = lb <= U;
+        }
+        emit(cand, i);
+    }
+    __syncthreads();
+    return s_cnt;
+}
+
+// ---- owner-difference lists
+//
+// The lists of the super-tiles, tiles and waves keep a seed only if it can
+// beat the box's owner somewhere in the box.  The owner o is the candidate of least cost at
+// the box centre; for any other candidate j the difference C_j - C_o is a
+// quadratic in the offset d from the centre, so over |d_k| <= h_k
+//   C_j - C_o >= (C_j - C_o)(0) - sum_k |g_k| h_k
+//                + sum_k min(0, m_kk) h_k^2 - sum_{r<k} |m_rk| h_r h_k,
+// g the difference of the gradients at the centre, m that of the matrices
+// (off-diagonals doubled).  A seed whose bound is above the slack costs more
+// than the owner at every point of the box, so it is not the argmin there
+// (ties included).  This is much tighter than comparing separate bounds of
+// the costs, whose ranges over the box are wide and move together: on the 3D
+// workload (256^3, N = 10^4) a 16 x 8 x 8 tile keeps 17 seeds instead of 40
+// and a wave 5.8 instead of 11.9, of which 3.8 win somewhere (2D 1024^2,
+// N = 1000: 11 instead of 20, and 3.8 instead of 8.2).
+//
+// A seed about a box centre: the offset e = x - centre (formed in double),
+// the upper triangle of A and w - w_max, in FP32.
+template <int D>
+struct SeedRec {
+    static constexpr int kTri = D * (D + 1) / 2;
+    float e[D];
+    float a[kTri];
+    float wp;
+};
+
+template <int D>
+__device__ inline SeedRec<D> seed_rec(const Seeds &sd, double wmax, const double *ctr, int i) {
+    const double *xi = sd.x + (size_t)i * D;
+    const double *ai = sd.A + (size_t)i * D * D;
+    SeedRec<D> r;
+    int t = 0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        r.e[d] = (float)(xi[d] - ctr[d]);
+#pragma unroll
+        for (int k = d; k < D; ++k) r.a[t++] = (float)ai[d * D + k];
+    }
+    r.wp = (float)(sd.w[i] - wmax);
+    return r;
+}
+
+// Its cost and gradient at the centre and its matrix (off-diagonals
+// doubled); s is its share of the slack.
+template <int D>
+struct CellQuad {
+    static constexpr int kTri = D * (D + 1) / 2;
+    float c;
+    float s;
+    float g[D];
+    float a[kTri];
+};
+
+// Cost e^T A e - w', gradient -2 A e; hh = |h|^2.  Slack: with E = |e| + |h|
+// and S = lambda_G E^2 + |w'| every term of the bound above is at most S in
+// magnitude and reaches the sum through fewer than 24 roundings of 2^-24
+// (an offset passed on from a super-tile's record carries 2 more, of its
+// own centre's scale, at most 8 E), less than 2^-18 S per seed;
+// s = 2^-15 (lam (|e|^2 + |h|^2) + |w'|) >= 2^-16 S, four times that.
+template <int D>
+__device__ inline CellQuad<D> cell_quad(const SeedRec<D> &r, float lam, float hh) {
+    CellQuad<D> q;
+    float e2 = hh, c = 0.0f;
+    int t = 0;
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+        float ae = 0.0f;
+#pragma unroll
+        for (int k = 0; k < D; ++k) {
+            const int lo = j < k ? j : k, hi = j < k ? k : j;
+            ae = fmaf(r.a[lo * D - lo * (lo - 1) / 2 + hi - lo], r.e[k], ae);
+        }
+        q.g[j] = -2.0f * ae;
+        c = fmaf(r.e[j], ae, c);
+        e2 = fmaf(r.e[j], r.e[j], e2);
+#pragma unroll
+        for (int k = j; k < D; ++k, ++t) q.a[t] = k > j ? 2.0f * r.a[t] : r.a[t];
+    }
+    q.c = c - r.wp;
+    q.s = 0x1p-15f * fmaf(lam, e2, fabsf(r.wp));
+    return q;
+}
+
+// Whether q can cost as little as the owner o somewhere in the box of half
+// extents h (NaN counts as yes).
+template <int D>
+__device__ inline bool can_beat(const CellQuad<D> &q, const CellQuad<D> &o, const float *h, float slack) {
+    float lb = q.c - o.c;
+#pragma unroll
+    for (int d = 0; d < D; ++d) lb = fmaf(-fabsf(q.g[d] - o.g[d]), h[d], lb);
+    int t = 0;
+#pragma unroll
+    for (int r = 0; r < D; ++r)
+#pragma unroll
+        for (int k = r; k < D; ++k, ++t) {
+            const float m = q.a[t] - o.a[t];
+            lb = fmaf(r == k ? fminf(m, 0.0f) : -fabsf(m), h[r] * h[k], lb);
+        }
+    return !(lb > q.s + o.s + slack);
+}
+
+// Centre (double) and half extents (rounded up) of a box.
+template <int D>
+__device__ inline float box_centre(const double *blo, const double *bhi, double *ctr, float *h) {
+    float hh = 0.0f;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        ctr[d] = 0.5 * (blo[d] + bhi[d]);
+        h[d] = (float)(0.5 * (bhi[d] - blo[d])) * (1.0f + 0x1p-20f);
+        hh = fmaf(h[d], h[d], hh);
+    }
+    return hh;
+}
+
+// Block-wide (T threads): of the seeds load(0) .. load(nsrc - 1), SeedRec
+// about the centre of a box of half extents h, those that can beat the
+// owner of the box somewhere in it, the owner included; keep(q, rec, pos) is
+// called for each with its position in the list (in any order).  Returns
+// their number.  slack: of the double costs (twice dslack_abs).
+template <int D, int T, class Load, class Keep>
+__device__ inline int owner_filter(int nsrc, Load load, const float *h, float hh, float lam, float slack, int &s_cnt,
+                                   CellQuad<D> *s_own, Keep keep) {
+    const int lane = __lane_id();
+    // a short source keeps each thread's records in registers between the
+    // two passes; a long one is read twice
+    constexpr int kReg = 2;
+    const bool in_regs = nsrc <= kReg * T;
+    SeedRec<D> rc[kReg];
+    CellQuad<D> mine;
+    mine.c = INFINITY;
     if (in_regs) {
 #pragma unroll
-        for (int r = 0; r < kReg; ++r)
-            if (r * kThreads < nsrc) emit(lbr[r] <= U, ir[r]);
-    } else {
-        for (int q0 = 0; q0 < nsrc; q0 += kThreads) {
-            const int q = q0 + threadIdx.x;
-            bool cand = false;
-            int i = 0;
+        for (int r = 0; r < kReg; ++r) {
+            const int q = threadIdx.x + r * T;
+            if (q < nsrc) rc[r] = load(q);
+        }
+#pragma unroll
+        for (int r = 0; r < kReg; ++r) {
+            const int q = threadIdx.x + r * T;
             if (q < nsrc) {
-                i = src ? src[q] : q;
-                double lb, ub;
-                cull_bounds<D, EXACT>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
-                cand = lb <= U;
+                const CellQuad<D> c = cell_quad<D>(rc[r], lam, hh);
+                if (c.c < mine.c) mine = c;
             }
-            emit(cand, i);
+        }
+    } else {
+        for (int q = threadIdx.x; q < nsrc; q += T) {
+            const CellQuad<D> c = cell_quad<D>(load(q), lam, hh);
+            if (c.c < mine.c) mine = c;
+        }
+    }
+    const unsigned long long lead = __ballot(mine.c == wave_min(mine.c));
+    __syncthreads();  // s_cnt and s_own may still be read by an earlier use
+    if (threadIdx.x == 0) s_cnt = 0;
+    if (lane == max(0, __ffsll(lead) - 1)) s_own[threadIdx.x >> 6] = mine;
+    __syncthreads();
+    int ow = 0;
+    float oc = s_own[0].c;
+#pragma unroll
+    for (int w = 1; w < T / 64; ++w) {
+        const float c = s_own[w].c;
+        ow = c < oc ? w : ow;
+        oc = fminf(oc, c);
+    }
+    const CellQuad<D> own = s_own[ow];
+    auto emit = [&](bool cand, int q, const SeedRec<D> &rec) {
+        const unsigned long long m = __ballot(cand);
+        if (!m) return;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&s_cnt, (int)__popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
+        const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        if (cand) keep(q, rec, base + below);
+    };
+    if (in_regs) {
+#pragma unroll
+        for (int r = 0; r < kReg; ++r) {
+            const int q = threadIdx.x + r * T;
+            if (r * T < nsrc)
+                emit(q < nsrc && can_beat<D>(cell_quad<D>(rc[r], lam, hh), own, h, slack), q, rc[r]);
+        }
+    } else {
+        for (int q0 = 0; q0 < nsrc; q0 += T) {
+            const int q = q0 + threadIdx.x;
+            SeedRec<D> rec = load(min(q, nsrc - 1));
+            emit(q < nsrc && can_beat<D>(cell_quad<D>(rec, lam, hh), own, h, slack), q, rec);
         }
     }
     __syncthreads();
     return s_cnt;
 }
 
-// The candidate list of super-tile st (a box of sf[0] x sf[1] x sf[2]
-// vector-kernel tiles of out.tp pixels per lane): the seeds that can attain
-// the minimum somewhere in it, at most cap of them into list, their number
-// into *count.  A seed that cannot win anywhere in the super-tile cannot win
-// in any of its tiles, and a tile's smallest upper bound over the
-// super-tile's list is at least its smallest over all seeds, so the tile
-// lists built from these lists still hold every seed that can be the exact
-// argmin (ties included).  All threads of the block call it.
+// A super-tile's list in global memory: for each seed its record about the
+// super-tile's centre and its number, packed in kRecVec float4 (16-byte pieces
+// stored piece by piece, so that consecutive lanes read consecutive pieces).
+// The tiles read their source seeds from it: gathered from the caller's
+// double arrays each candidate took 10 scattered loads, which made the short
+// lists a net loss in 3D.
 template <int D>
-__device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, const double *eig,
-                                       const PassOut &out, int st, int *list, int *count, int cap,
-                                       int &s_cnt, double *s_red) {
-    int c[3];
-    c[2] = st % out.nst[2];
-    c[1] = (st / out.nst[2]) % out.nst[1];
-    c[0] = st / (out.nst[2] * out.nst[1]);
+__device__ inline void store_rec(float4 *list, int cap, int pos, const SeedRec<D> &r, int i) {
+    const float id = __int_as_float(i);
+    if constexpr (D == 2) {
+        list[pos] = make_float4(r.e[0], r.e[1], r.wp, id);
+        list[cap + pos] = make_float4(r.a[0], r.a[1], r.a[2], 0.0f);
+    } else {
+        list[pos] = make_float4(r.e[0], r.e[1], r.e[D - 1], id);
+        list[cap + pos] = make_float4(r.a[0], r.a[1], r.a[2], r.wp);
+        list[2 * (size_t)cap + pos] = make_float4(r.a[3 % SeedRec<D>::kTri], r.a[4 % SeedRec<D>::kTri], r.a[5 % SeedRec<D>::kTri], 0.0f);
+    }
+}
+template <int D>
+__device__ inline SeedRec<D> load_rec(const float4 *list, int cap, int pos, const float *shift, int &i) {
+    SeedRec<D> r;
+    const float4 v0 = list[pos], v1 = list[cap + pos];
+    i = __float_as_int(v0.w);
+    r.e[0] = v0.x + shift[0];
+    r.e[1] = v0.y + shift[1];
+    r.a[0] = v1.x;
+    r.a[1] = v1.y;
+    r.a[2] = v1.z;
+    if constexpr (D == 2) {
+        r.wp = v0.z;
+    } else {
+        const float4 v2 = list[2 * (size_t)cap + pos];
+        r.e[D - 1] = v0.z + shift[2];
+        r.wp = v1.w;
+        r.a[3 % SeedRec<D>::kTri] = v2.x;
+        r.a[4 % SeedRec<D>::kTri] = v2.y;
+        r.a[5 % SeedRec<D>::kTri] = v2.z;
+    }
+    return r;
+}
+
+// The box of super-tile (c0, c1, c2).
+template <int D>
+__device__ inline void super_box(const Geo &g, const PassOut &out, const int *c, double *blo, double *bhi) {
     const int ext[3] = {tile_ext(D, out.tp, 0) * out.sf[0], tile_ext(D, out.tp, 1) * out.sf[1],
                         tile_ext(D, out.tp, 2) * out.sf[2]};
     int k0[3];
     for (int d = 0; d < 3; ++d) k0[d] = c[d] * ext[d];
-    double blo[3], bhi[3];
     cull_box<D>(g, k0, ext, blo, bhi);
-    // the eigenvalue bounds here: a super-tile filters every seed, and its
-    // list is only the source of the tiles' exact filters
-    const int n = build_candidates<D, false>(sd, eig, wmax, blo, bhi, nullptr, g.n, list, cap, s_cnt, s_red);
+}
+
+// LDS of super_tile_list with T threads.
+template <int D, int T>
+struct SuperSmem {
+    int list[kSuperCap];
+    CellQuad<D> own[T / 64];
+    double red[T / 64];
+    int cnt;
+};
+
+// The candidate list of super-tile st (a box of sf[0] x sf[1] x sf[2] tiles of
+// out.tp pixels per lane) into list (room for cap), their number into *count
+// (above cap: every seed).  Every seed is tested with the eigenvalue bounds
+//   lambda_min dist(x, box)^2 - w' <= U = min_k lambda_max maxdist(x_k, box)^2 - w_k',
+// then, unless the pass returns the relative gaps (whose tiles need lists
+// that bound the cost of every seed left out), the survivors by the owner's
+// difference.  A seed that cannot win anywhere in the super-tile cannot win
+// in any of its tiles.  All T threads of the block call it.  A
+// thread takes the seeds four at a time, so that their loads are in flight
+// together.
+template <int D, int T>
+__device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
+                                       const PassOut &out, int st, float4 *list, int *count, int cap,
+                                       SuperSmem<D, T> &sm) {
+    int c[3];
+    c[2] = st % out.nst[2];
+    c[1] = (st / out.nst[2]) % out.nst[1];
+    c[0] = st / (out.nst[2] * out.nst[1]);
+    double blo[3], bhi[3];
+    super_box<D>(g, out, c, blo, bhi);
+    const int lane = __lane_id();
+    constexpr int kUnroll = 4;
+    constexpr int kKeep = 12;  // a thread's lower bounds kept in registers
+    const bool in_regs = g.n <= kKeep * T;
+    float lbr[kKeep];
+    double umin = INFINITY;
+    if (in_regs) {
+#pragma unroll
+        for (int r = 0; r < kKeep; ++r) {
+            const int i = threadIdx.x + r * T;
+            lbr[r] = INFINITY;
+            if (r * T < g.n && i < g.n) {
+                double lb, ub;
+                cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+                lbr[r] = __double2float_rd(lb);
+                umin = fmin(umin, ub);
+            }
+        }
+    } else {
+#pragma unroll kUnroll
+        for (int i = threadIdx.x; i < g.n; i += T) {
+            double lb, ub;
+            cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            umin = fmin(umin, ub);
+        }
+    }
+    umin = wave_min(umin);
+    if (lane == 0) sm.red[threadIdx.x >> 6] = umin;
+    if (threadIdx.x == 0) sm.cnt = 0;
+    __syncthreads();
+    double U = sm.red[0];
+#pragma unroll
+    for (int w = 1; w < T / 64; ++w) U = fmin(U, sm.red[w]);
+    auto append = [&](bool cand, int i) {
+        const unsigned long long m = __ballot(cand);
+        if (!m) return;
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&sm.cnt, (int)__popcll(m));
+        base = __builtin_amdgcn_readfirstlane(base);
+        const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+        if (cand && base + below < kSuperCap) sm.list[base + below] = i;
+    };
+    if (in_regs) {
+#pragma unroll
+        for (int r = 0; r < kKeep; ++r)
+            if (r * T < g.n) append((int)threadIdx.x + r * T < g.n && (double)lbr[r] <= U, threadIdx.x + r * T);
+    } else {
+        for (int i0 = 0; i0 < g.n; i0 += T) {
+            const int i = i0 + threadIdx.x;
+            double lb = INFINITY, ub;
+            if (i < g.n) cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            append(i < g.n && lb <= U, i);
+        }
+    }
+    __syncthreads();
+    const int m = sm.cnt;
+    if (m > kSuperCap) {
+        if (threadIdx.x == 0) *count = cap + 1;
+        return;
+    }
+    double ctr[D];
+    float h[D];
+    const float hh = box_centre<D>(blo, bhi, ctr, h);
+    int n;
+    if (out.rel_gap) {
+        for (int q = threadIdx.x; q < min(m, cap); q += T)
+            store_rec<D>(list, cap, q, seed_rec<D>(sd, wmax, ctr, sm.list[q]), sm.list[q]);
+        n = m;
+    } else {
+        n = owner_filter<D, T>(
+            m, [&](int q) { return seed_rec<D>(sd, wmax, ctr, sm.list[q]); }, h, hh, ct.lam,
+            2.0f * dslack_abs(g, wmax, ct), sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
+                if (pos < cap) store_rec<D>(list, cap, pos, r, sm.list[q]);
+            });
+    }
     if (threadIdx.x == 0) *count = n;
 }
 
@@ -1093,127 +1391,65 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
 //    winning group)).
 //
 // With candidate lists, each wave then narrows the tile's list to the box of
-// its own P x L1 (x L2) pixels (same bounds, the tile's candidates as the
+// its own P x L1 (x L2) pixels (the same test, the tile's candidates as the
 // seed set) and scans only those; a wave whose list would not fit scans the
 // tile's list.
 constexpr int kGroupScan = 96;   // scans at least this long use group minima
 constexpr int kWaveCap = 256;    // per-wave candidate positions
 
-// Boundary-aware refinement, the owner test: does one candidate beat every
-// other candidate at every point of the box [blo, bhi] of pixel centres?
-// The owner is the candidate of least cost at the box centre c (lowest seed
-// on ties); for any other candidate j the difference D = C_j - C_i is a
-// quadratic, D(c + d) = D(c) + g.d + d^T M d with g = 2 A_j (c - x_j) -
-// 2 A_i (c - x_i) and M = A_j - A_i (indefinite in general), so over
-// |d_k| <= h_k
-//   D >= D(c) - sum_k |g_k| h_k + min(0, lambda_min(M)) |h|^2,
-// lambda_min from the closed-form eigenvalue range in 2D (widened by 1e-6 of
-// its span), bounded below by minus the Gershgorin bound of M in 3D.  The
-// owner is returned when every such bound exceeds a relative 1e-9 of the
-// terms (far above the double rounding), so the owner is the strict argmin
-// at every pixel of the box; else -1.  Lists longer than kOwnerMax are not
-// tried (such tiles meet several cells).  All threads of the block call it.
-constexpr int kOwnerMax = 8;  // longer lists: the tile meets several cells
-
-template <int D>
-__device__ inline int box_owner(const Seeds &sd, double wmax, const double *blo, const double *bhi,
-                                const int *list, int ncand, double *s_red, int *s_redi) {
-    if (ncand < 1 || ncand > kOwnerMax) return -1;
-    if (ncand == 1) return list[0];
-    double c[3], h[3];
-    for (int d = 0; d < D; ++d) {
-        c[d] = 0.5 * (blo[d] + bhi[d]);
-        h[d] = 0.5 * (bhi[d] - blo[d]);
-    }
-    const int q = threadIdx.x;
-    const int i = q < ncand ? list[q] : 0;
-    // this candidate's cost and gradient at the centre (gauge w - w_max)
-    double cc = INFINITY, gi[3] = {0.0, 0.0, 0.0};
-    if (q < ncand) {
-        const double *a = sd.A + (size_t)i * D * D;
-        double dd[3];
-        for (int d = 0; d < D; ++d) dd[d] = c[d] - sd.x[(size_t)i * D + d];
-        double qf = 0.0;
-        for (int r = 0; r < D; ++r) {
-            double ad = 0.0;
-            for (int k = 0; k < D; ++k) ad += a[(r <= k) ? r * D + k : k * D + r] * dd[k];
-            gi[r] = 2.0 * ad;
-            qf += dd[r] * ad;
-        }
-        cc = qf - (sd.w[i] - wmax);
-    }
-    // owner: least cost at the centre, lowest seed on ties
-    double v = cc;
-    int vi = q < ncand ? i : 0x7fffffff;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        const double ov = __shfl_xor(v, o);
-        const int oi = __shfl_xor(vi, o);
-        if (ov < v || (ov == v && oi < vi)) {
-            v = ov;
-            vi = oi;
+// The candidate list of a tile's box, from its super-tile's list when it has
+// one (else from every seed): into s_list, at most kCullCap seeds; returns
+// their number.  GAP: *U bounds the cost of every seed left out.
+template <int D, bool GAP, class Smem>
+__device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
+                                      const PassOut &out, int b0, int b1, int b2, const double *blo,
+                                      const double *bhi, Smem &sm, double *U) {
+    int *dst = sm.list;
+    const float4 *src = nullptr;
+    int nsrc = g.n, cap = out.super_cap;
+    const int sc[3] = {b0 / out.sf[0], b1 / out.sf[1], b2 / out.sf[2]};
+    if (out.super_list) {
+        const int st = (sc[0] * out.nst[1] + sc[1]) * out.nst[2] + sc[2];
+        const int c = out.super_count[st];
+        if (c <= cap) {
+            src = out.super_list + (size_t)st * (size_t)cap * rec_vec(D);
+            nsrc = c;
         }
     }
-    __syncthreads();  // earlier readers of the slots are done
-    if (__lane_id() == 0) {
-        s_red[threadIdx.x >> 6] = v;
-        s_redi[threadIdx.x >> 6] = vi;
+    if constexpr (GAP) {
+        return build_candidates<D>(sd, eig, wmax, blo, bhi,
+                                   [&](int q) { return src ? __float_as_int(src[q].w) : q; }, nsrc, dst, kCullCap,
+                                   sm.cnt, sm.red, U);
+    } else {
+        double ctr[D];
+        float h[D], shift[3] = {0.0f, 0.0f, 0.0f};
+        const float hh = box_centre<D>(blo, bhi, ctr, h);
+        const float slack = 2.0f * dslack_abs(g, wmax, ct);
+        if (src) {
+            double slo[3], shi[3];
+            super_box<D>(g, out, sc, slo, shi);
+            for (int d = 0; d < D; ++d) shift[d] = (float)(0.5 * (slo[d] + shi[d]) - ctr[d]);
+            return owner_filter<D, kThreads>(
+                nsrc,
+                [&](int q) {
+                    int i;
+                    return load_rec<D>(src, cap, q, shift, i);
+                },
+                h, hh, ct.lam, slack, sm.cnt, sm.own, [&](int q, const SeedRec<D> &, int pos) {
+                    if (pos < kCullCap) dst[pos] = __float_as_int(src[q].w);
+                });
+        }
+        return owner_filter<D, kThreads>(
+            nsrc, [&](int q) { return seed_rec<D>(sd, wmax, ctr, q); }, h, hh, ct.lam, slack, sm.cnt, sm.own,
+            [&](int q, const SeedRec<D> &, int pos) {
+                if (pos < kCullCap) dst[pos] = q;
+            });
     }
-    __syncthreads();
-    double ov = s_red[0];
-    int oi = s_redi[0];
-    for (int w = 1; w < kWaves; ++w)
-        if (s_red[w] < ov || (s_red[w] == ov && s_redi[w] < oi)) {
-            ov = s_red[w];
-            oi = s_redi[w];
-        }
-    // the owner's gradient and matrix, and the bound for this candidate
-    bool ok = true;
-    if (q < ncand && i != oi) {
-        const double *ao = sd.A + (size_t)oi * D * D;
-        const double *a = sd.A + (size_t)i * D * D;
-        double go[3], dd[3];
-        for (int d = 0; d < D; ++d) dd[d] = c[d] - sd.x[(size_t)oi * D + d];
-        for (int r = 0; r < D; ++r) {
-            double ad = 0.0;
-            for (int k = 0; k < D; ++k) ad += ao[(r <= k) ? r * D + k : k * D + r] * dd[k];
-            go[r] = 2.0 * ad;
-        }
-        double m[3][3];
-        for (int r = 0; r < D; ++r)
-            for (int k = 0; k < D; ++k) {
-                const int t = (r <= k) ? r * D + k : k * D + r;
-                m[r][k] = a[t] - ao[t];
-            }
-        double lmin, lmax;
-        if (D == 2) {
-            eig_range<D>(m, &lmin, &lmax);
-        } else {
-            // Gershgorin: lambda_min(M) >= -max_r sum_c |m_rc|
-            lmin = 0.0;
-            for (int r = 0; r < D; ++r) {
-                double rs = 0.0;
-                for (int k = 0; k < D; ++k) rs += fabs(m[r][k]);
-                lmin = fmin(lmin, -rs);
-            }
-        }
-        double gh = 0.0, h2 = 0.0;
-        for (int d = 0; d < D; ++d) {
-            gh += fabs(gi[d] - go[d]) * h[d];
-            h2 += h[d] * h[d];
-        }
-        const double quad = fmin(0.0, lmin) * h2;
-        const double lb = (cc - ov) - gh + quad;
-        const double slack = 1e-9 * (fabs(cc) + fabs(ov) + gh + fabs(quad) + fabs(sd.w[i] - wmax) +
-                                     fabs(sd.w[oi] - wmax));
-        ok = lb > slack;
-    }
-    return __syncthreads_and(ok) ? oi : -1;
 }
 
-// Boundary-aware refinement: a tile whose owner is L (box_owner: a single
-// candidate, or one that beats every other candidate everywhere in the
-// tile) lies inside L's cell, so its pixels are labelled L and its moments
+// Boundary-aware refinement: a tile whose list holds L alone (it beats every
+// other seed everywhere in the tile) lies inside L's cell, so its pixels are
+// labelled L and its moments
 // are added in closed form (box_moments_add) -- the pixel-level scan, the
 // certificate and the re-check are skipped; the labels and moments are
 // those of the full evaluation.  All threads of the block call it (with the
@@ -1248,32 +1484,35 @@ struct VecCfg {
     static constexpr int kChunk = CULL ? 256 : (D == 2 ? 1024 : 512);
 };
 
-// LDS of the vector tile.
-template <int D, bool CULL>
+// LDS of the vector tile (GAP: with candidate lists, the pass also returns
+// the relative gaps).
+template <int D, bool CULL, bool GAP = false>
 struct VecSmem {
-    // seed coefficients of one chunk, + a dummy slot (index kChunk); with
-    // candidate lists the free lanes of the last row hold the seed's
-    // eigenvalue range (FP32, rounded outwards)
+    // seed coefficients of one chunk, + a dummy slot (index kChunk); with GAP
+    // the free lanes of the last row hold the seed's eigenvalue range (FP32,
+    // rounded outwards)
     float4 sC[VecCfg<D, CULL>::kRows][VecCfg<D, CULL>::kChunk + 1];
-    float4 sB[CULL ? VecCfg<D, CULL>::kChunk : 1];  // (x - anchor, w - wmax) in FP32
+    float4 sB[CULL && GAP ? VecCfg<D, CULL>::kChunk : 1];  // (x - anchor, w - wmax) in FP32
     int list[CULL ? kCullCap : 1];        // candidate seeds of the tile
     int wl[kWaves][CULL ? kWaveCap : 1];  // staged positions of each wave's candidates; then its flagged pixels
+    CellQuad<D> own[kWaves];
     double red[kWaves];
-    int redi[kWaves];
     int cnt;
 };
 
-template <int D, bool CULL, int P = kPv>
+// With candidate lists they hold the seeds that can beat the box's owner
+// (owner_filter).  A pass that returns the relative gaps (GAP) needs a bound
+// of the cost of every seed it leaves out, so its lists come from separate
+// bounds of each seed's cost (build_candidates), which give one.
+template <int D, bool CULL, int P = kPv, bool GAP = false>
 __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
-                                const double *eig, int b0, int b1, int b2, VecSmem<D, CULL> &sm,
+                                const double *eig, int b0, int b1, int b2, VecSmem<D, CULL, GAP> &sm,
                                 const PassOut &out, unsigned *qcount) {
     constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
     constexpr int kVecChunk = VecCfg<D, CULL>::kChunk;
     constexpr int kDummy = kVecChunk;  // staged slot whose cost is never the minimum
     auto &sC = sm.sC;
     int *s_list = sm.list;
-    double *s_red = sm.red;
-    int &s_cnt = sm.cnt;
     const Tile<D> t = tile_at<D, P>(b0, b1, b2);
     const bool lane_ok = lane_in_grid<D>(g, t);
     int nscan = g.n;
@@ -1286,27 +1525,13 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         const int ext[3] = {E0, E1, E2};
         const int k0[3] = {t.anc[0] - E0 / 2, t.anc[1] - E1 / 2, D == 3 ? t.anc[2] - E2 / 2 : 0};
         cull_box<D>(g, k0, ext, blo, bhi);
-        const int *src = nullptr;
-        int nsrc = g.n;
-        if (out.super_list) {
-            const int st = ((b0 / out.sf[0]) * out.nst[1] + b1 / out.sf[1]) * out.nst[2] + b2 / out.sf[2];
-            const int c = out.super_count[st];
-            if (c <= out.super_cap) {
-                src = out.super_list + (size_t)st * out.super_cap;
-                nsrc = c;
-            }
-        }
-        const int ncand = build_candidates<D>(sd, eig, wmax, blo, bhi, src, nsrc, s_list, kCullCap,
-                                              s_cnt, s_red, &Utile);
+        const int ncand = tile_candidates<D, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, blo, bhi, sm, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
-        if (out.adaptive && !full && !g.mass && !out.rel_gap) {
-            const int own = box_owner<D>(sd, wmax, blo, bhi, s_list, ncand, s_red, sm.redi);
-            if (own >= 0) {
-                credit_tile<D, P>(g, t, b0, b1, b2, own, out);
-                return;
-            }
+        if (!GAP && out.adaptive && ncand == 1 && !g.mass) {
+            credit_tile<D, P>(g, t, b0, b1, b2, s_list[0], out);
+            return;
         }
     }
 
@@ -1364,7 +1589,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             double qd[6], ld[3], cd, ed[3], wpd;
             seed_terms<D>(sd, i, anc, wmax, qd, ld, &cd, ed, &wpd);
             float lmn = 0.0f, lmx = 0.0f;
-            if constexpr (CULL) {
+            if constexpr (CULL && GAP) {
                 // rounded outwards: the FP32 bounds of the wave lists stay bounds
                 lmn = (float)eig[2 * (size_t)i] * (1.0f - 0x1p-20f);
                 lmx = (float)eig[2 * (size_t)i + 1] * (1.0f + 0x1p-20f);
@@ -1491,9 +1716,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         __syncthreads();
         stage(0, nscan, padded);
         __syncthreads();
-        // the wave's box in the tile-local coordinates of the scan, and FP32
-        // bounds from the staged data, widened by a relative 1e-4 (far above
-        // their rounding), so the wave list keeps every seed that can win
+        // the wave's box in the tile-local coordinates of the scan
         float wlo[3] = {0.0f, 0.0f, 0.0f}, whi[3] = {0.0f, 0.0f, 0.0f};
         {
             const int k0w[3] = {t.org[0], t.org[1], t.org[2]};
@@ -1504,70 +1727,140 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                 whi[d] = ((float)(b - t.anc[d]) + 0.5f) * s[d];
             }
         }
-        auto wbounds = [&](int q, float &lb, float &ub) {
-            const float4 b = sm.sB[q];
-            const float4 ce = sC[VecCfg<D, CULL>::kRows - 1][q];  // .z, .w: eigenvalue range
-            const float e[3] = {b.x, b.y, b.z};
-            float dist2 = 0.0f, far2 = 0.0f;
-            for (int d = 0; d < D; ++d) {
-                const float dd = fmaxf(0.0f, fmaxf(wlo[d] - e[d], e[d] - whi[d]));
-                const float fd = fmaxf(e[d] - wlo[d], whi[d] - e[d]);
-                dist2 = fmaf(dd, dd, dist2);
-                far2 = fmaf(fd, fd, far2);
-            }
-            float l = ce.z * dist2, h = ce.w * far2;
-            const float slack = 1e-4f * (fabsf(l) + (float)D * fabsf(h) + fabsf(b.w)) + 1e-30f;
-            if constexpr (D == 2) {
-                // the exact range of the quadratic form, as cull_bounds
-                const float4 c0 = sC[0][q];  // a00, 2 a01, a11
-                quad_box_range2<float>(c0.x, c0.y, c0.z, wlo[0] - e[0], whi[0] - e[0], wlo[1] - e[1],
-                                       whi[1] - e[1], &l, &h);
-            } else {
-                // the exact maximum: the form is convex, so at a corner
-                const float4 c0 = sC[0][q];  // a00, 2 a01, 2 a02
-                const float4 c1 = sC[1][q];  // a11, 2 a12, a22
-                float hm = 0.0f;
-#pragma unroll
-                for (int v = 0; v < 8; ++v) {
-                    const float d0 = ((v & 1) ? whi[0] : wlo[0]) - e[0];
-                    const float d1 = ((v & 2) ? whi[1] : wlo[1]) - e[1];
-                    const float d2 = ((v & 4) ? whi[2] : wlo[2]) - e[2];
-                    const float qv = fmaf(fmaf(c0.x, d0, fmaf(c0.y, d1, c0.z * d2)), d0,
-                                          fmaf(fmaf(c1.x, d1, c1.y * d2), d1, c1.z * d2 * d2));
-                    hm = fmaxf(hm, qv);
-                }
-                h = hm;
-            }
-            lb = l - b.w - slack;
-            ub = h - b.w + slack;
-        };
-        float um = INFINITY;
-        for (int q = t.lane; q < nscan; q += 64) {
-            float lb, ub;
-            wbounds(q, lb, ub);
-            um = fminf(um, ub);
-        }
-        um = wave_min(um);
-        int c = 0;
-        for (int q0 = 0; q0 < nscan; q0 += 64) {
-            const int q = q0 + t.lane;
-            bool cand = false;
-            if (q < nscan) {
-                float lb, ub;
-                wbounds(q, lb, ub);
-                cand = lb <= um;
-            }
+        int c = 0;  // candidates of the wave
+        auto append = [&](bool cand, int q) {
             const unsigned long long m = __ballot(cand);
             const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
                                                               __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
             if (cand && c + below < kWaveCap) wl[c + below] = q;
             c += (int)__popcll(m);
+        };
+        if constexpr (CULL && GAP) {
+            // FP32 bounds from the staged data, widened by a relative 1e-4 (far
+            // above their rounding), so the wave list keeps every seed that
+            // can win
+            auto wbounds = [&](int q, float &lb, float &ub) {
+                const float4 b = sm.sB[q];
+                const float4 ce = sC[VecCfg<D, CULL>::kRows - 1][q];  // .z, .w: eigenvalue range
+                const float e[3] = {b.x, b.y, b.z};
+                float dist2 = 0.0f, far2 = 0.0f;
+                for (int d = 0; d < D; ++d) {
+                    const float dd = fmaxf(0.0f, fmaxf(wlo[d] - e[d], e[d] - whi[d]));
+                    const float fd = fmaxf(e[d] - wlo[d], whi[d] - e[d]);
+                    dist2 = fmaf(dd, dd, dist2);
+                    far2 = fmaf(fd, fd, far2);
+                }
+                float l = ce.z * dist2, h = ce.w * far2;
+                const float slack = 1e-4f * (fabsf(l) + (float)D * fabsf(h) + fabsf(b.w)) + 1e-30f;
+                if constexpr (D == 2) {
+                    // the exact range of the quadratic form, as cull_bounds
+                    const float4 c0 = sC[0][q];  // a00, 2 a01, a11
+                    quad_box_range2<float>(c0.x, c0.y, c0.z, wlo[0] - e[0], whi[0] - e[0], wlo[1] - e[1],
+                                           whi[1] - e[1], &l, &h);
+                } else {
+                    // the exact maximum: the form is convex, so at a corner
+                    const float4 c0 = sC[0][q];  // a00, 2 a01, 2 a02
+                    const float4 c1 = sC[1][q];  // a11, 2 a12, a22
+                    float hm = 0.0f;
+    #pragma unroll
+                    for (int v = 0; v < 8; ++v) {
+                        const float d0 = ((v & 1) ? whi[0] : wlo[0]) - e[0];
+                        const float d1 = ((v & 2) ? whi[1] : wlo[1]) - e[1];
+                        const float d2 = ((v & 4) ? whi[2] : wlo[2]) - e[2];
+                        const float qv = fmaf(fmaf(c0.x, d0, fmaf(c0.y, d1, c0.z * d2)), d0,
+                                              fmaf(fmaf(c1.x, d1, c1.y * d2), d1, c1.z * d2 * d2));
+                        hm = fmaxf(hm, qv);
+                    }
+                    h = hm;
+                }
+                lb = l - b.w - slack;
+                ub = h - b.w + slack;
+            };
+            float um = INFINITY;
+            for (int q = t.lane; q < nscan; q += 64) {
+                float lb, ub;
+                wbounds(q, lb, ub);
+                um = fminf(um, ub);
+            }
+            um = wave_min(um);
+            for (int q0 = 0; q0 < nscan; q0 += 64) {
+                const int q = q0 + t.lane;
+                bool cand = false;
+                if (q < nscan) {
+                    float lb, ub;
+                    wbounds(q, lb, ub);
+                    cand = lb <= um;
+                }
+                append(cand, q);
+            }
+            Uwave = um;  // the tile's candidates left out below cost more
+        } else if constexpr (CULL) {
+            // the owner's differences from the staged quadratics.  Each
+            // monomial of a cost reaches it, the gradient or the bound through
+            // fewer than 24 roundings of 2^-24 and their magnitudes sum to at
+            // most 3 C + 6 r^2 (the vector tile's bound), r^2 = lam |u|^2 at the
+            // tile's corner: 2^-16 (|C| + 2 r^2) is more than twice that
+            const float r2t = pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f);
+            float uc[3], h[3];
+            for (int d = 0; d < D; ++d) {
+                uc[d] = 0.5f * (wlo[d] + whi[d]);
+                h[d] = 0.5f * (whi[d] - wlo[d]) * (1.0f + 0x1p-20f);
+            }
+            auto staged_quad = [&](int q) {
+                CellQuad<D> r;
+                const float4 c0 = sC[0][q], c1 = sC[1][q];
+                if constexpr (D == 2) {
+                    r.a[0] = c0.x; r.a[1] = c0.y; r.a[2] = c0.z;
+                    const float t0 = fmaf(c0.x, uc[0], fmaf(c0.y, uc[1], c0.w)), t1 = fmaf(c0.z, uc[1], c1.x);
+                    r.c = fmaf(t0, uc[0], fmaf(t1, uc[1], c1.y));
+                    r.g[0] = fmaf(c0.x, uc[0], t0);
+                    r.g[1] = fmaf(c0.y, uc[0], fmaf(c0.z, uc[1], t1));
+                } else {
+                    const float4 c2 = sC[2][q];
+                    r.a[0] = c0.x; r.a[1] = c0.y; r.a[2] = c0.z;
+                    r.a[3] = c1.x; r.a[4] = c1.y; r.a[5] = c1.z;
+                    const float t0 = fmaf(c0.x, uc[0], fmaf(c0.y, uc[1], fmaf(c0.z, uc[2], c0.w)));
+                    const float t1 = fmaf(c1.x, uc[1], fmaf(c1.y, uc[2], c1.w));
+                    const float t2 = fmaf(c1.z, uc[2], c2.x);
+                    r.c = fmaf(t0, uc[0], fmaf(t1, uc[1], fmaf(t2, uc[2], c2.y)));
+                    r.g[0] = fmaf(c0.x, uc[0], t0);
+                    r.g[1] = fmaf(c0.y, uc[0], fmaf(c1.x, uc[1], t1));
+                    r.g[D - 1] = fmaf(c0.z, uc[0], fmaf(c1.y, uc[1], fmaf(c1.z, uc[2], t2)));
+                }
+                r.s = 0x1p-16f * (fabsf(r.c) + 2.0f * r2t);
+                return r;
+            };
+            const float sl = 2.0f * dslack_abs(g, wmax, ct);
+            // the owner: the wave's candidate of least cost at its centre
+            float best = INFINITY;
+            int bq = 0;
+            CellQuad<D> mine;
+            mine.c = INFINITY;
+            for (int q = t.lane; q < nscan; q += 64) {
+                mine = staged_quad(q);
+                if (mine.c < best) {
+                    best = mine.c;
+                    bq = q;
+                }
+            }
+            const unsigned long long lead = __ballot(best == wave_min(best));
+            const CellQuad<D> own = staged_quad(__builtin_amdgcn_readlane(bq, max(0, __ffsll(lead) - 1)));
+            if (nscan <= 64) {
+                append(t.lane < nscan && can_beat<D>(mine, own, h, sl), t.lane);
+            } else {
+                for (int q0 = 0; q0 < nscan; q0 += 64) {
+                    const int q = q0 + t.lane;
+                    append(q < nscan && can_beat<D>(staged_quad(min(q, nscan - 1)), own, h, sl), q);
+                }
+            }
         }
         const int c16 = (c + 15) & ~15;
         if (c > 0 && c16 <= kWaveCap) {
             for (int j = c + t.lane; j < c16; j += 64) wl[j] = kDummy;
             cntw = c;
-            if (c < nscan) Uwave = um;  // some of the tile's candidates were left out
+            if (c == nscan) Uwave = INFINITY;  // none of the tile's candidates was left out
+        } else {
+            Uwave = INFINITY;
         }
         // the list is read back by other lanes of the wave only
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -1617,7 +1910,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         const float thr = 2.0f * e32_bound(B1, sqrtf(r2), r2) + kbits * fmaxf(fabsf(fb[p]), fabsf(fs[p])) +
                           sab + skb * (B1 + r2);
         flag[p] = lost[p] || !((fs[p] - fb[p]) > thr);
-        if (out.rel_gap && act[p] && !flag[p]) {
+        if ((!CULL || GAP) && out.rel_gap && act[p] && !flag[p]) {
             // the winner costs at most c1u; a scanned seed at least fs minus
             // its bound, one left out of the lists more than the lists' U
             const float c1u = (fb[p] + 0x1p-19f * fabsf(fb[p]) + e32_bound(B1, sqrtf(r2), r2) + sab +
@@ -2205,7 +2498,7 @@ __device__ inline void bf16_pixel_slots(const float *f, unsigned short *out) {
 // (a00, 2a01, a11, -2(Ae)_0 | -2(Ae)_1, e^T A e - w' in 2D; the 3D rows
 // hold a00, 2a01, 2a02, -2(Ae)_0 | a11, 2a12, a22, -2(Ae)_1 | -2(Ae)_2,
 // e^T A e - w'); with candidate lists, the tile's list.
-template <int D, int C, bool CULL>
+template <int D, int C, bool CULL, bool GAP = false>
 struct Bf16Smem {
     static constexpr int kChunk = C;
     ushort8 sA[C * Bf16Slots<D>::SLOTS / 8];
@@ -2213,8 +2506,8 @@ struct Bf16Smem {
     float2 sF2[C];
     int list[CULL ? kCullCap : 1];
     uint16_t flagged[kWaves][CULL ? 64 * 4 : 1];  // recheck_flagged's pixels (at most 4 per lane)
+    CellQuad<D> own[kWaves];
     double red[kWaves];
-    int redi[kWaves];
     int cnt;
 };
 
@@ -2267,10 +2560,10 @@ template <int D> struct Bf16Rows { static constexpr int value = D == 2 ? 4 : 2; 
 // integers below 2^12 (|v| < 64).  With CULL the tile scans its candidate
 // list (built as the vector tile builds it, from its super-tile's list
 // when there is one) and keeps it for the re-check.
-template <int D, int P, int C, bool CULL>
+template <int D, int P, int C, bool CULL, bool GAP = false>
 __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
                                  const double *eig, int b0, int b1, int b2,
-                                 Bf16Smem<D, C, CULL> &sm, const PassOut &out, unsigned *qcount) {
+                                 Bf16Smem<D, C, CULL, GAP> &sm, const PassOut &out, unsigned *qcount) {
     using SL = Bf16Slots<D>;
     static_assert(C % 32 == 0, "bf16 staging");
     constexpr int NG = 2 * P;  // 32-pixel groups per wave: gi = 2 r + c
@@ -2343,27 +2636,13 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         const int ext[3] = {E0, E1, E2};
         const int k0[3] = {t.anc[0] - E0 / 2, t.anc[1] - E1 / 2, D == 3 ? t.anc[2] - E2 / 2 : 0};
         cull_box<D>(g, k0, ext, blo, bhi);
-        const int *src = nullptr;
-        int nsrc = g.n;
-        if (out.super_list) {
-            const int st = ((b0 / out.sf[0]) * out.nst[1] + b1 / out.sf[1]) * out.nst[2] + b2 / out.sf[2];
-            const int c = out.super_count[st];
-            if (c <= out.super_cap) {
-                src = out.super_list + (size_t)st * out.super_cap;
-                nsrc = c;
-            }
-        }
-        const int ncand = build_candidates<D>(sd, eig, wmax, blo, bhi, src, nsrc, sm.list, kCullCap, sm.cnt,
-                                              sm.red, &Utile);
+        const int ncand = tile_candidates<D, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, blo, bhi, sm, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
-        if (out.adaptive && !full && !g.mass && !out.rel_gap) {
-            const int own = box_owner<D>(sd, wmax, blo, bhi, sm.list, ncand, sm.red, sm.redi);
-            if (own >= 0) {
-                credit_tile<D, P>(g, t, b0, b1, b2, own, out);
-                return;
-            }
+        if (!GAP && out.adaptive && ncand == 1 && !g.mass) {
+            credit_tile<D, P>(g, t, b0, b1, b2, sm.list[0], out);
+            return;
         }
     }
 
@@ -2542,7 +2821,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             act[r] = lane_ok && (t.k0w + r) < g.grid[0];
             flag[r] = !settled;
             labe[r] = (CULL && !full) ? sm.list[pos] : min(pos, g.n - 1);
-            if (out.rel_gap && act[r] && settled) {
+            if ((!CULL || GAP) && out.rel_gap && act[r] && settled) {
                 // the winner costs at most c1u; the rest of its group at
                 // least fs, the other groups at least fo, each less its bound,
                 // and a seed left out of the list more than U

@@ -88,6 +88,9 @@ struct BlockParts {
 // coordinates o_d = 2 k_d + 1 (exact unsigned integers)
 constexpr int moments_per_cell(int dim) { return dim == 2 ? 6 : 10; }
 
+// 16-byte pieces of a super-tile list's record (store_rec)
+constexpr int rec_vec(int dim) { return dim == 2 ? 2 : 3; }
+
 // A block's share of the re-check queue: queue[start, start + count) are
 // pixels of tile `tile` of instance `tag`.
 struct QSeg {
@@ -123,7 +126,8 @@ struct PassOut {
     int tp = 0;  // pixels per lane of the tiles of a pass with candidate lists
     // super-tiles of sf[0] x sf[1] x sf[2] tiles (nst[] of them per axis):
     // their candidate seeds, from which the tiles pick theirs
-    const int *super_list = nullptr;   // [super-tiles][super_cap]
+    // (packed records, store_rec)
+    const float4 *super_list = nullptr;   // [super-tiles][rec_vec][super_cap]
     const int *super_count = nullptr;  // above super_cap: every seed
     int super_cap = 2048;
     int sf[3] = {1, 1, 1};
@@ -175,7 +179,7 @@ hipError_t launch_prep(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom
 // Candidate lists of the super-tiles described by out (sf, nst), written to
 // list / count.
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, int *list, int *count, hipStream_t st);
+                             const PassOut &out, float4 *list, int *count, hipStream_t st);
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
 hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc,

@@ -233,6 +233,9 @@ __global__ __launch_bounds__(256) void k_mass_total(int64_t J, const uint8_t *ma
     if (threadIdx.x == 0) atomicAdd(&sc->qtotal, red[0]);
 }
 
+// Seeds above which a super-tile's list is built by 1024 threads.
+constexpr int kSuperWideSeeds = 2048;
+
 // Blocks for n seeds: one seed per thread up to kMaxParts blocks.
 inline int red_blocks(int n) {
     return (int)std::min<int64_t>(kMaxParts, std::max<int64_t>(1, ((int64_t)n + kRedThreads - 1) / kRedThreads));
@@ -308,15 +311,15 @@ __global__ __launch_bounds__(kThreads) void k_assign_fp64(Geo g, Seeds sd, const
 
 // One block per tile of the vector single-precision kernel
 // (dev::vec_tile): every seed, or the tile's candidate seeds.
-template <int D, bool CULL, int P>
+template <int D, bool CULL, int P, bool GAP>
 __global__ __launch_bounds__(kThreads, (CULL && P == 4) ? 5 : 4) void k_assign_vec(Geo g, Seeds sd, Scalars *sc,
                                                         const double *eig, PassOut out) {
-    __shared__ VecSmem<D, CULL> sm;
+    __shared__ VecSmem<D, CULL, GAP> sm;
     if constexpr (D == 2)
-        vec_tile<2, CULL, P>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
+        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
                              &sc->qcount);
     else
-        vec_tile<3, CULL, P>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
+        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
                              out, &sc->qcount);
 }
 
@@ -429,28 +432,26 @@ __global__ __launch_bounds__(kThreads, D == 3 ? 3 : 4) void k_assign_hyb(Geo g, 
 // One block per tile of the vector kernel's shape with P pixels per lane
 // (dev::bf16_tile): every seed, or the tile's candidate seeds; seeds staged
 // C at a time.
-template <int D, int P, int C, bool CULL>
+template <int D, int P, int C, bool CULL, bool GAP>
 __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scalars *sc,
                                                          const double *eig, PassOut out) {
-    __shared__ dev::Bf16Smem<D, C, CULL> sm;
+    __shared__ dev::Bf16Smem<D, C, CULL, GAP> sm;
     const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
     const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
     const int b2 = D == 2 ? 0 : blockIdx.x;
-    dev::bf16_tile<D, P, C, CULL>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, b0, b1, b2, sm, out, &sc->qcount);
+    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, b0, b1, b2, sm, out, &sc->qcount);
 }
 
 // --------------------------------------------------------- k_super_cull
 
-// One block per super-tile (dev::super_tile_list).
-template <int D>
-__global__ __launch_bounds__(kThreads) void k_super_cull(Geo g, Seeds sd, const Scalars *sc,
-                                                        const double *eig, PassOut out, int *list,
-                                                        int *count) {
-    __shared__ int s_cnt;
-    __shared__ double s_red[kWaves];
+// One block of T threads per super-tile (dev::super_tile_list).
+template <int D, int T>
+__global__ __launch_bounds__(T) void k_super_cull(Geo g, Seeds sd, const Scalars *sc, const double *eig, PassOut out,
+                                                  float4 *list, int *count) {
+    __shared__ SuperSmem<D, T> sm;
     const int st = blockIdx.x;
-    super_tile_list<D>(g, sd, sc->wmax, eig, out, st, list + (size_t)st * out.super_cap, count + st,
-                       out.super_cap, s_cnt, s_red);
+    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, out, st,
+                          list + (size_t)st * (size_t)out.super_cap * rec_vec(D), count + st, out.super_cap, sm);
 }
 
 // ---------------------------------------------------------- k_recheck
@@ -608,13 +609,13 @@ dim3 tile_grid(const Geo &g) {
 // 8 pixels per lane halve the per-seed work of the lanes but give 2048-pixel
 // tiles; below 1024 such tiles (4 waves per SIMD on 256 CUs) the 4-pixel
 // form keeps the chip full.
-template <int D, bool CULL>
+template <int D, bool CULL, bool GAP = false>
 hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                       const PassOut &out, hipStream_t st) {
     if (vec_pixels_per_lane(g, CULL) == 8)
-        k_assign_vec<D, CULL, 8><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        k_assign_vec<D, CULL, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
     else
-        k_assign_vec<D, CULL, 4><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        k_assign_vec<D, CULL, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
     return hipGetLastError();
 }
 
@@ -661,18 +662,29 @@ hipError_t launch_assign_fp32(const Geo &g, const Seeds &sd, Scalars *sc, const 
                       : launch_vec<3, false>(g, sd, sc, nullptr, out, st);
 }
 
-hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, int *list, int *count, hipStream_t st) {
-    (void)hipGetLastError();
+template <int D>
+static void launch_super(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig, const PassOut &out,
+                         float4 *list, int *count, hipStream_t st) {
     const int nb = out.nst[0] * out.nst[1] * out.nst[2];
-    if (g.dim == 2) k_super_cull<2><<<nb, kThreads, 0, st>>>(g, sd, sc, eig, out, list, count);
-    else k_super_cull<3><<<nb, kThreads, 0, st>>>(g, sd, sc, eig, out, list, count);
+    // a block reads every seed: many seeds need many loads in flight
+    if (g.n > kSuperWideSeeds) k_super_cull<D, 1024><<<nb, 1024, 0, st>>>(g, sd, sc, eig, out, list, count);
+    else k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, list, count);
+}
+
+hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
+                             const PassOut &out, float4 *list, int *count, hipStream_t st) {
+    (void)hipGetLastError();
+    if (g.dim == 2) launch_super<2>(g, sd, sc, eig, out, list, count, st);
+    else launch_super<3>(g, sd, sc, eig, out, list, count, st);
     return hipGetLastError();
 }
 
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st) {
     (void)hipGetLastError();
+    if (out.rel_gap)
+        return g.dim == 2 ? launch_vec<2, true, true>(g, sd, sc, eig, out, st)
+                          : launch_vec<3, true, true>(g, sd, sc, eig, out, st);
     return g.dim == 2 ? launch_vec<2, true>(g, sd, sc, eig, out, st)
                       : launch_vec<3, true>(g, sd, sc, eig, out, st);
 }
@@ -716,7 +728,8 @@ template <int D, int P, bool CULL>
 static void launch_bf16(const Geo &g, Seeds sd, Scalars *sc, const double *eig, const PassOut &out,
                         hipStream_t st) {
     constexpr int C = (D == 2 && !CULL) ? 1024 : 256;
-    k_assign_bf16<D, P, C, CULL><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    if (CULL && out.rel_gap) k_assign_bf16<D, P, C, CULL, CULL><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    else k_assign_bf16<D, P, C, CULL, false><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
 }
 
 template <int D, bool CULL>

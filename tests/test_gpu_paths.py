@@ -72,3 +72,23 @@ def test_recheck_in_the_tile(ctx, dim, grid, prec, ppl):
                     assert ctx.apd_last_pass_stats()["rechecked"] == case.J
         finally:
             ctx.apd_set_pixels_per_lane(0)
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (200, 130)), (3, (40, 33, 50))])
+@pytest.mark.parametrize("n", [255, 256, 257, 2048, 2049, 3073, 12289])
+def test_candidate_lists_by_the_number_of_seeds(ctx, dim, grid, n):
+    """Lists from every seed in one round of a block or from super-tiles, with
+    256 or 1024 threads, a thread's bounds in registers or read again: labels
+    of both tiers and the static-scratch evaluation against the oracle, the
+    weights offset by far more than their spread."""
+    import torch
+    inst = S.custom(dim, n, grid, seed=n, sigma=0.3, amax=4.0)
+    w = np.random.default_rng(n).uniform(-0.3, 0.3, n) * n ** (-2.0 / dim) + 1e3
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    ref, _, _ = O.assign(inst, w)
+    for prec in ("fp32", "bf16"):
+        np.testing.assert_array_equal(ctx.apd_assign(prob, wd, prec=prec).cpu().numpy(), ref)
+        assert ctx.apd_last_pass_stats()["kernel"] == prec + "-lists"
+    for noalloc in (False, True):
+        out = ctx.apd_dual_objective_grad(prob, wd, counts=True, noalloc=noalloc)
+        np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, minlength=n))
