@@ -30,6 +30,8 @@ HIPCC_FLAGS = [
     "-mllvm", "-amdgpu-mfma-vgpr-form",
     "-Wall",
     "-Wno-unused-function",
+    # the constant tables of the moment products
+    "-fconstexpr-steps=20000000",
 ]
 
 

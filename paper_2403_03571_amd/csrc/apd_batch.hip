@@ -235,8 +235,8 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                                                      uint64_t *queue, QSeg *segs) {
     __shared__ union {
         float mf[kMfmaLds];
-        VecSmem<D, V == 2 || V == 4> vec;
-        Bf16Smem<D, 256, V == 5> bf;
+        VecSmem<D, V == 2 || V == 4, V == 4 ? kP : kPv> vec;
+        Bf16Smem<D, Bf16Rows<D>::value, 256, V == 5> bf;
     } sm;
     float *sC = sm.mf;
     constexpr bool kLists = V == 2 || V == 4 || V == 5;

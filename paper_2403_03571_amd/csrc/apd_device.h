@@ -243,6 +243,16 @@ __device__ inline double wave_min(double v) {
 
 // ------------------------------------------------------ tile epilogue
 
+// The labels of the settled pixels (a flagged pixel's is written by the
+// re-check).
+template <int D, int P>
+__device__ inline void write_labels(const Geo &g, const Tile<D> &t, const bool (&act)[P], const int (&lab)[P],
+                                    const bool (&flag)[P], const PassOut &out) {
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+        if (act[p] && !flag[p]) out.labels[pixel_index<D>(g, t.k0w + p, t)] = lab[p];
+}
+
 // Labels, the re-check queue (where the pass has one), and the exact
 // per-cell moments of every settled pixel.  For a cell the moments are the pixel count and the sums
 // of o_d = 2 k_d + 1 and o_d o_e over its pixels (unsigned 64-bit atomics,
@@ -255,12 +265,7 @@ __device__ inline void tile_epilogue(const Geo &g, const Tile<D> &t, const bool 
                                      const PassOut &out, unsigned *qcount) {
     constexpr int K = moments_per_cell(D);
     const int lane = t.lane;
-    // labels (a flagged pixel's is written by the re-check)
-    if (out.labels) {
-#pragma unroll
-        for (int p = 0; p < P; ++p)
-            if (act[p] && !flag[p]) out.labels[pixel_index<D>(g, t.k0w + p, t)] = lab[p];
-    }
+    if (out.labels) write_labels<D, P>(g, t, act, lab, flag, out);
     // re-check queue: one atomic per block (the counter is a single address
     // shared by every block of the pass).  Every thread of the block comes
     // here (the queue pointers are uniform), so the barriers are safe.
@@ -510,6 +515,156 @@ __device__ inline float gap_exact(double b, double s, double wmax) {
     return g > 0.0 ? __double2float_rd(g) : 0.0f;
 }
 
+// Orders this wave's LDS writes before its lanes' later reads (and earlier
+// reads before later writes): the wave's own barrier.
+__device__ inline void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ------------------------------------------- moments on the matrix cores
+
+// The moments of a tile whose pixels carry a small cell index (their
+// position in the tile's candidate list) are a contraction: for each cell the
+// sum over the pixels of (pixel in cell) times (monomials of the pixel), both
+// small exact integers.  v_mfma_i32_16x16x64_i8 forms it for 16 cells x 64
+// pixels x 16 columns: the cells' indicator on the rows (a byte compare of the
+// pixels' indices with the row's), the pixels' monomials on the columns, from
+// a constant table.  With o_d = 2 (k_d - anchor_d) + 1 the columns are 1, the
+// o_d, and for each product o_d o_e its high and low part (o_d o_e = 32 h + l,
+// 0 <= l < 32, so that both fit a signed byte up to tiles of 64 rows); the
+// sums stay far below 2^31.  The waves add their cells' sums in LDS, one slot
+// per cell of the tile's list, and the block writes each cell it holds once:
+// m, S_d and S_de shifted from the anchor to global coordinates in 64 bits.
+//
+// Before, every wave reduced each of its cells by itself (10 wave totals of
+// 11 instructions, the shift in 64 bits and 10 atomics to memory for each of
+// about 4 cells per wave): half of the instructions of the 3D kernel, which
+// went from 252 to 158 us (256^3, N = 10^4), the 2D one from 15.9 to 12.6 us
+// (1024^2, N = 1000) and the batched one from 1.32 to 1.13 ms per evaluation
+// (512 maps).  Pixel weights take the old way (they do not fit the bytes).
+constexpr int kAccSlots = 64;  // cells of a tile (longer lists: tile_epilogue)
+
+template <int D, int P>
+struct MomTab {
+    static constexpr int kSteps = P < 4 ? 4 : P;
+    static constexpr int kProd = D * (D + 1) / 2;
+    signed char v[kWaves][kSteps][64][16];
+    // step s, lane l, byte b: column l % 16 of pixel p = 4 (s / 4) + b % 4 of lane
+    // 16 (l / 16) + 4 (s % 4) + b / 4 of the wave (the order in which the rows'
+    // operand holds the pixels)
+    constexpr MomTab() : v() {
+        constexpr int E[3] = {tile_ext(D, P, 0), tile_ext(D, P, 1), tile_ext(D, P, 2)};
+        for (int w = 0; w < kWaves; ++w)
+            for (int s = 0; s < kSteps; ++s)
+                for (int q = 0; q < 64; ++q) {  // the pixels of the step: 4 groups of 16 bytes
+                    const int L = 16 * (q / 16) + 4 * (s % 4) + (q % 16) / 4, p = 4 * (s / 4) + q % 4;
+                    if (p >= P) continue;
+                    const int k0 = D == 2 ? (w >> 1) * wave_ext(D, P, 0) + (L >> 4) * P + p : w * P + p;
+                    const int k1 = D == 2 ? (w & 1) * wave_ext(D, P, 1) + (L & 15) : L >> 3;
+                    const int o[3] = {2 * (k0 - E[0] / 2) + 1, 2 * (k1 - E[1] / 2) + 1,
+                                      D == 3 ? 2 * ((L & 7) - E[2] / 2) + 1 : 0};
+                    int col[16] = {};
+                    col[0] = 1;
+                    int c = 0;
+                    for (int d = 0; d < D; ++d) {
+                        col[1 + d] = o[d];
+                        for (int e = d; e < D; ++e, ++c) {
+                            const int t = o[d] * o[e];
+                            col[1 + D + c] = t >> 5;
+                            col[1 + D + kProd + c] = t & 31;
+                        }
+                    }
+                    for (int n = 0; n < 16; ++n) v[w][s][16 * (q / 16) + n][q % 16] = (signed char)col[n];
+                }
+    }
+};
+template <int D, int P>
+static __device__ const MomTab<D, P> mom_tab{};
+
+typedef int intx4 __attribute__((ext_vector_type(4)));
+
+// LDS of the moments: the cells' sums and each wave's pixel indices.
+template <int P>
+struct MomSmem {
+    int acc[kAccSlots][16];
+    alignas(16) unsigned idx[kWaves][P > 4 ? 2 : 1][64];
+};
+
+// Zeroes the first n slots (a barrier must follow).
+template <int P>
+__device__ inline void moments_zero(MomSmem<P> &sm, int n) {
+    for (int q = threadIdx.x; q < n * 16; q += kThreads) (&sm.acc[0][0])[q] = 0;
+}
+
+// Adds this wave's pixels: idx[p] the cell index of pixel p, below ncell
+// (<= kAccSlots), or 127 (not counted); slot(j) the tile's slot of cell j.
+// Every lane of the wave must call it.
+template <int D, int P, class Slot>
+__device__ inline void moments_add(MomSmem<P> &sm, int lane, const int (&idx)[P], int ncell, Slot slot) {
+    constexpr int S = MomTab<D, P>::kSteps;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    intx4 tab[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k) tab[k] = *reinterpret_cast<const intx4 *>(&mom_tab<D, P>.v[wave][k][lane][0]);
+#pragma unroll
+    for (int hh = 0; hh < (P + 3) / 4; ++hh) {
+        unsigned v = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v |= (unsigned)(4 * hh + j < P ? idx[4 * hh + j < P ? 4 * hh + j : 0] : 127) << (8 * j);
+        sm.idx[wave][hh][lane] = v;
+    }
+    wave_lds_sync();
+    const int row = lane >> 4, col = lane & 15;
+    for (int j0 = 0; j0 < ncell; j0 += 16) {
+        const unsigned pat = (unsigned)(j0 + col) * 0x01010101u;
+        intx4 sum = {0, 0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            intx4 a = *reinterpret_cast<const intx4 *>(&sm.idx[wave][k / 4][16 * row + 4 * (k % 4)]);
+            // bytes equal to the row's index become -128, the others 0 (bytes
+            // are below 128, so the sum does not carry between them)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) a[e] = (int)(~(((unsigned)a[e] ^ pat) + 0x7f7f7f7fu) & 0x80808080u);
+            sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, tab[k], sum, 0, 0, 0);
+        }
+        // register r: cell j0 + 4 row + r, column col
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = j0 + 4 * row + r;
+            if (sum[r] != 0 && j < ncell) atomicAdd(&sm.acc[slot(j)][col], -(sum[r] >> 7));
+        }
+    }
+}
+
+// Adds the tile's cells to the moments (after a barrier): list[k] the seed of
+// slot k < n, anc the tile's anchor.
+template <int D, int P>
+__device__ inline void moments_flush(const MomSmem<P> &sm, const int *anc, const int *list, int n, uint64_t *mom) {
+    constexpr int K = moments_per_cell(D);
+    constexpr int NP = MomTab<D, P>::kProd;
+    const int q = threadIdx.x & 15;
+    // the pair (d, e) of this thread's product
+    const int c = max(0, q - 1 - D);
+    const int d = D == 2 ? (c == 2) : (c < 3 ? 0 : c < 5 ? 1 : 2);
+    const int e = D == 2 ? (c >= 1) : (c < 3 ? c : c < 5 ? c - 2 : 2);
+    auto G = [&](int k) { return (int64_t)(2 * (k == 0 ? anc[0] : k == 1 ? anc[1] : anc[2])); };
+    for (int k = threadIdx.x >> 4; k < n; k += kThreads / 16) {
+        const int *a = sm.acc[k];
+        const int m = a[0];
+        if (m == 0 || q >= K) continue;
+        int64_t val = m;
+        if (q > D) {
+            const int64_t Gd = G(d), Ge = G(e);
+            val = (int64_t)m * (Gd * Ge) + Gd * a[1 + e] + Ge * a[1 + d] + 32 * a[1 + D + c] + a[1 + D + NP + c];
+        } else if (q > 0) {
+            val = (int64_t)m * G(q - 1) + a[q];
+        }
+        atomicAdd((unsigned long long *)mom + (size_t)list[k] * K + q, (unsigned long long)val);
+    }
+}
+
 // ------------------------------------------- double re-check in the tile
 
 // (value, seed) minimum over the G lanes of a group (G a power of two up to
@@ -540,14 +695,6 @@ __device__ inline void group_min2(double &b, int &bi, double &s, int G) {
             s = fmin(s, ob);
         }
     }
-}
-
-// Orders this wave's LDS writes before its lanes' later reads (and earlier
-// reads before later writes): the wave's own barrier.
-__device__ inline void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Double re-check of a wave's flagged pixels inside the tile's kernel (passes
@@ -1486,7 +1633,7 @@ struct VecCfg {
 
 // LDS of the vector tile (GAP: with candidate lists, the pass also returns
 // the relative gaps).
-template <int D, bool CULL, bool GAP = false>
+template <int D, bool CULL, int P, bool GAP = false>
 struct VecSmem {
     // seed coefficients of one chunk, + a dummy slot (index kChunk); with GAP
     // the free lanes of the last row hold the seed's eigenvalue range (FP32,
@@ -1495,6 +1642,7 @@ struct VecSmem {
     float4 sB[CULL && GAP ? VecCfg<D, CULL>::kChunk : 1];  // (x - anchor, w - wmax) in FP32
     int list[CULL ? kCullCap : 1];        // candidate seeds of the tile
     int wl[kWaves][CULL ? kWaveCap : 1];  // staged positions of each wave's candidates; then its flagged pixels
+    MomSmem<CULL ? P : 1> mom[CULL ? 1 : 0];
     CellQuad<D> own[kWaves];
     double red[kWaves];
     int cnt;
@@ -1506,7 +1654,7 @@ struct VecSmem {
 // bounds of each seed's cost (build_candidates), which give one.
 template <int D, bool CULL, int P = kPv, bool GAP = false>
 __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
-                                const double *eig, int b0, int b1, int b2, VecSmem<D, CULL, GAP> &sm,
+                                const double *eig, int b0, int b1, int b2, VecSmem<D, CULL, P, GAP> &sm,
                                 const PassOut &out, unsigned *qcount) {
     constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
     constexpr int kVecChunk = VecCfg<D, CULL>::kChunk;
@@ -1709,12 +1857,16 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     auto ident = [](int j) { return j; };
     // per-wave lists: candidates of the tile, staged in one chunk
     const bool per_wave = CULL && !full && nscan <= kVecChunk;
+    // the pixels' positions in the tile's list index its moment slots
+    const bool slots = per_wave && nscan <= kAccSlots && !g.mass;
     int *wl = sm.wl[threadIdx.x >> 6];
     int cntw = -1;  // this wave's list length; -1: scan the tile's list
     if (per_wave) {
         const int padded = (nscan + 15) & ~15;
         __syncthreads();
         stage(0, nscan, padded);
+        if constexpr (CULL)
+            if (slots && out.mom) moments_zero(sm.mom[0], nscan);
         __syncthreads();
         // the wave's box in the tile-local coordinates of the scan
         float wlo[3] = {0.0f, 0.0f, 0.0f}, whi[3] = {0.0f, 0.0f, 0.0f};
@@ -1898,12 +2050,6 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     int lab[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        if (cntw >= 0) {
-            lab[p] = s_list[wl[min(pos[p], cntw - 1)]];
-        } else {
-            const int ps = min(pos[p], nscan - 1);
-            lab[p] = full ? ps : s_list[ps];
-        }
         const float r2 = pixel_r2(ct, u0[p], u1, u2);
         const float bb = fmaxf(fb[p], 0.0f);
         const float B1 = bb + 0x1p-10f * (bb + r2);
@@ -1926,10 +2072,40 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = fs[p] > 0.0f ? gap_lower(c1u, c2l) : 0.0f;
         }
     }
-    tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
-    if constexpr (CULL)
+    if (!slots || out.labels) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (cntw >= 0) {
+                lab[p] = s_list[wl[min(pos[p], cntw - 1)]];
+            } else {
+                const int ps = min(pos[p], nscan - 1);
+                lab[p] = full ? ps : s_list[ps];
+            }
+        }
+    }
+    if constexpr (CULL) {
+        if (slots) {
+            if (out.labels) write_labels<D, P>(g, t, act, lab, flag, out);
+            if (out.mom) {
+                // a wave's list is there unless its pixels are all flagged
+                int idx[P];
+#pragma unroll
+                for (int p = 0; p < P; ++p) idx[p] = act[p] && !flag[p] ? min(pos[p], kAccSlots - 1) : 127;
+                const bool wlist = cntw >= 0;
+                moments_add<D, P>(sm.mom[0], t.lane, idx, wlist ? cntw : nscan, [&](int j) { return wlist ? wl[j] : j; });
+            }
+        } else {
+            tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+        }
         recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : s_list, full ? g.n : nscan,
                               reinterpret_cast<uint16_t *>(wl), out, qcount, wmax, Utile);
+        if (slots && out.mom) {
+            __syncthreads();
+            moments_flush<D, P>(sm.mom[0], t.anc, s_list, nscan, out.mom);
+        }
+    } else {
+        tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+    }
 }
 
 
@@ -2498,7 +2674,7 @@ __device__ inline void bf16_pixel_slots(const float *f, unsigned short *out) {
 // (a00, 2a01, a11, -2(Ae)_0 | -2(Ae)_1, e^T A e - w' in 2D; the 3D rows
 // hold a00, 2a01, 2a02, -2(Ae)_0 | a11, 2a12, a22, -2(Ae)_1 | -2(Ae)_2,
 // e^T A e - w'); with candidate lists, the tile's list.
-template <int D, int C, bool CULL, bool GAP = false>
+template <int D, int P, int C, bool CULL, bool GAP = false>
 struct Bf16Smem {
     static constexpr int kChunk = C;
     ushort8 sA[C * Bf16Slots<D>::SLOTS / 8];
@@ -2506,6 +2682,7 @@ struct Bf16Smem {
     float2 sF2[C];
     int list[CULL ? kCullCap : 1];
     uint16_t flagged[kWaves][CULL ? 64 * 4 : 1];  // recheck_flagged's pixels (at most 4 per lane)
+    MomSmem<CULL ? P : 1> mom[CULL ? 1 : 0];
     CellQuad<D> own[kWaves];
     double red[kWaves];
     int cnt;
@@ -2563,7 +2740,7 @@ template <int D> struct Bf16Rows { static constexpr int value = D == 2 ? 4 : 2; 
 template <int D, int P, int C, bool CULL, bool GAP = false>
 __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
                                  const double *eig, int b0, int b1, int b2,
-                                 Bf16Smem<D, C, CULL, GAP> &sm, const PassOut &out, unsigned *qcount) {
+                                 Bf16Smem<D, P, C, CULL, GAP> &sm, const PassOut &out, unsigned *qcount) {
     using SL = Bf16Slots<D>;
     static_assert(C % 32 == 0, "bf16 staging");
     constexpr int NG = 2 * P;  // 32-pixel groups per wave: gi = 2 r + c
@@ -2798,7 +2975,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     // pixels of column l % 32 of those groups are its own)
     const bool lane_ok = lane_in_grid<D>(g, t);
     bool act[P], flag[P];
-    int labe[P];
+    int labe[P], idx[P];  // label, position in the list
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
         const int pb = __shfl_xor(best[gi], 32);
@@ -2821,6 +2998,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             act[r] = lane_ok && (t.k0w + r) < g.grid[0];
             flag[r] = !settled;
             labe[r] = (CULL && !full) ? sm.list[pos] : min(pos, g.n - 1);
+            idx[r] = pos;
             if ((!CULL || GAP) && out.rel_gap && act[r] && settled) {
                 // the winner costs at most c1u; the rest of its group at
                 // least fs, the other groups at least fo, each less its bound,
@@ -2840,10 +3018,29 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             }
         }
     }
-    tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
-    if constexpr (CULL)
+    if constexpr (CULL) {
+        const bool slots = !full && nscan <= kAccSlots && !g.mass;
+        if (slots) {
+            if (out.labels) write_labels<D, P>(g, t, act, labe, flag, out);
+            if (out.mom) {
+#pragma unroll
+                for (int r = 0; r < P; ++r) idx[r] = act[r] && !flag[r] ? idx[r] : 127;
+                moments_zero(sm.mom[0], nscan);
+                __syncthreads();
+                moments_add<D, P>(sm.mom[0], lane, idx, nscan, [](int j) { return j; });
+            }
+        } else {
+            tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
+        }
         recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : sm.list, full ? g.n : nscan,
                               sm.flagged[threadIdx.x >> 6], out, qcount, wmax, Utile);
+        if (slots && out.mom) {
+            __syncthreads();
+            moments_flush<D, P>(sm.mom[0], t.anc, sm.list, nscan, out.mom);
+        }
+    } else {
+        tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
+    }
 }
 
 // ------------------------------------------------------- double re-check

@@ -312,9 +312,9 @@ __global__ __launch_bounds__(kThreads) void k_assign_fp64(Geo g, Seeds sd, const
 // One block per tile of the vector single-precision kernel
 // (dev::vec_tile): every seed, or the tile's candidate seeds.
 template <int D, bool CULL, int P, bool GAP>
-__global__ __launch_bounds__(kThreads, (CULL && P == 4) ? 5 : 4) void k_assign_vec(Geo g, Seeds sd, Scalars *sc,
+__global__ __launch_bounds__(kThreads, (CULL && P == 4 && !GAP) ? 5 : 4) void k_assign_vec(Geo g, Seeds sd, Scalars *sc,
                                                         const double *eig, PassOut out) {
-    __shared__ VecSmem<D, CULL, GAP> sm;
+    __shared__ VecSmem<D, CULL, P, GAP> sm;
     if constexpr (D == 2)
         vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
                              &sc->qcount);
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kThreads, D == 3 ? 3 : 4) void k_assign_hyb(Geo g, 
 template <int D, int P, int C, bool CULL, bool GAP>
 __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scalars *sc,
                                                          const double *eig, PassOut out) {
-    __shared__ dev::Bf16Smem<D, C, CULL, GAP> sm;
+    __shared__ dev::Bf16Smem<D, P, C, CULL, GAP> sm;
     const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
     const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
     const int b2 = D == 2 ? 0 : blockIdx.x;

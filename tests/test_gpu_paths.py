@@ -92,3 +92,26 @@ def test_candidate_lists_by_the_number_of_seeds(ctx, dim, grid, n):
     for noalloc in (False, True):
         out = ctx.apd_dual_objective_grad(prob, wd, counts=True, noalloc=noalloc)
         np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, minlength=n))
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (64, 33)), (3, (32, 9, 17))])
+@pytest.mark.parametrize("n", [2, 15, 16, 17, 33, 60, 64, 65, 90])
+def test_moments_by_the_cells_of_a_tile(ctx, dim, grid, n):
+    """Few to many cells in a tile (groups of 16 on the matrix cores, up to 64
+    cells per tile there): counts, gradient and centroids of both tiers and
+    tile shapes against the oracle."""
+    import torch
+    inst = S.custom(dim, n, grid, seed=n, sigma=0.2)
+    w = np.random.default_rng(n).uniform(-0.2, 0.2, n) * n ** (-2.0 / dim)
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    ev = O.evaluate(inst, w)
+    try:
+        for prec, ppl in (("fp32", 4), ("fp32", 8), ("bf16", 4), ("bf16", 8)):
+            ctx.apd_set_pixels_per_lane(ppl)
+            out = ctx.apd_dual_objective_grad(prob, wd, prec=prec, counts=True, centroids=True)
+            np.testing.assert_array_equal(out["counts"].cpu().numpy(), ev.counts)
+            np.testing.assert_array_equal(out["grad"].cpu().numpy(), ev.grad)
+            np.testing.assert_allclose(out["centroids"].cpu().numpy(), ev.centroids, rtol=0, atol=1e-13)
+            assert out["g"] == pytest.approx(ev.g, rel=1e-12, abs=1e-15)
+    finally:
+        ctx.apd_set_pixels_per_lane(0)
