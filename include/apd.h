@@ -389,15 +389,16 @@ apd_status apd_set_culling(apd_ctx *ctx, int32_t on);
  * closed form; only tiles that meet a cell boundary are evaluated pixel by
  * pixel (the adaptive refinement the paper's discussion (Section 4)
  * proposes, here on the lists' tiles of 32 x 32 pixels (2D, 4 pixels per
- * lane) or 16 x 8 x 8 voxels (3D)).  Labels, counts, objective and gradient
+ * lane) or 16 x 8 x 8 or 16 x 16 x 8 voxels (3D)).  Labels, counts, objective and gradient
  * are unchanged.  Not applied with pixel weights or when apd_assign is
  * asked for rel_gap. */
 apd_status apd_set_adaptive(apd_ctx *ctx, int32_t on);
 
 /* Tile shape of the vector APD_FP32 kernel: pixels per lane along axis 0
  * (4 or 8; in 2D a wave is 4 x 16 lanes and a tile 2 x 2 waves, 8 times
- * that many rows x 32 columns; in 3D a tile is 4 waves x that many rows x
- * 8 x 8).  0 (the default) picks 4 with candidate lists, and over every
+ * that many rows x 32 columns; in 3D a tile is 16 x 16 x 8 voxels at 8 and
+ * 16 x 8 x 8 at 4).  0 (the default) picks 4 with candidate lists, or 8 on 3D
+ * grids of at least 2^21 voxels and 1000 voxels per seed, and over every
  * seed 8 on grids of at least 2^21 pixels, else 4.  The single-instance
  * APD_BF16 kernel takes half of a set value as its rows per lane (default
  * 4 in 2D, 2 in 3D).  The labels do not depend on it. */

@@ -1396,32 +1396,37 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         b.cost_part = k.take<double>((size_t)b.cap_parts);
     }
     if (cull) {
-        const ListGeometry L = list_geometry(p, geo, prec);
         // the call's documented limit counts a list of kStaticListCap seeds,
-        // its length and bound and a queue segment for every tile, whether or
-        // not the pass uses them
+        // its length and bound and a queue segment for every tile (of 4 pixels
+        // per lane unless set) and kStaticSuperCap seeds for every super-tile
+        // of them, whether or not the pass uses them
+        apd::Geo lim = geo;
+        if (prec == APD_FP32 && lim.vec_p == 0) lim.vec_p = apd::kP;
+        const ListGeometry L = list_geometry(p, lim, prec);
         k.take<int>((size_t)L.tiles * kStaticListCap);
         k.take<int>((size_t)L.tiles);
         k.take<double>((size_t)L.tiles);
         k.take<apd::QSeg>((size_t)L.tiles);
         k.take<int>((size_t)L.nsuper * kStaticSuperCap);
-        b.super_count = k.take<int>((size_t)L.nsuper);
-        b.cap_super = L.nsuper;
+        k.take<int>((size_t)L.nsuper);
     }
     if (k.off > kStaticScratch)
         return fail(c, APD_ERR_OOM,
                     "this problem needs %zu bytes of scratch; the static array holds %zu (n = %lld, J = %lld)",
                     k.off, kStaticScratch, (long long)n, (long long)J);
     if (cull) {
-        // the super-tiles' records take the room that the limit counts for
-        // the queue, the tiles' lists and the super-tiles' (a pass with lists
-        // has no queue), as many per super-tile as fit
-        const size_t rec = (size_t)b.cap_super * apd::rec_vec(p->dim) * sizeof(float4);
-        const size_t first = (size_t)((unsigned char *)b.queue - base);
-        const size_t last = (size_t)((unsigned char *)b.super_count - base);
-        b.super_lists = reinterpret_cast<float4 *>(b.queue);
-        b.super_cap = (int)std::min<size_t>({(size_t)kStaticSuperCap, (size_t)n, (last - first) / rec});
+        // the super-tiles' counts and records take the room that the limit
+        // counts for the queue (a pass with lists has none) and the lists, as
+        // many records per super-tile as fit
+        const int64_t nsuper = list_geometry(p, geo, prec).nsuper;
+        Carve in{reinterpret_cast<unsigned char *>(b.queue)};
         b.queue = nullptr;
+        b.cap_super = nsuper;
+        b.super_count = in.take<int>((size_t)nsuper);
+        b.super_lists = in.take<float4>(0);
+        const size_t room = (size_t)(base + k.off - reinterpret_cast<unsigned char *>(b.super_lists));
+        b.super_cap = (int)std::min<size_t>({(size_t)kStaticSuperCap, (size_t)n,
+                                             room / ((size_t)nsuper * apd::rec_vec(p->dim) * sizeof(float4))});
     }
     // the block partials' ticket must start at zero (each launch leaves it
     // so; the array starts zeroed, but an aborted call may not have)

@@ -42,6 +42,7 @@ struct BState {
     double vsum, wmax, gamma0;
     float lam;        // Gershgorin bound of every A_i (Cert::lam)
     float kap;        // condition bound of every A_i (Cert::kap)
+    float sab;        // absolute slack of the double costs at the trial point (Cert::sab)
     int phase;        // 0: first evaluation pending, 1: line search
     int npairs, head, t;
     int iters, evals;

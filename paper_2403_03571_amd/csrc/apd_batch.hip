@@ -174,7 +174,10 @@ __global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCt
     double wm = -INFINITY;
     for (int i = threadIdx.x; i < n; i += kThreads) wm = fmax(wm, I.wt[i]);
     wm = block_max(wm, red);
-    if (threadIdx.x == 0) st[b].wmax = wm;
+    if (threadIdx.x == 0) {
+        st[b].wmax = wm;
+        st[b].sab = dslack_abs(I.g, wm, st[b].lam);
+    }
 }
 
 // -------------------------------------------------------------- kb_assign
@@ -207,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
         out.sf[d] = I.sf[d];
         out.nst[d] = I.nst[d];
     }
-    super_tile_list<D, kThreads>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, out, local,
+    super_tile_list<D, kThreads>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, out, local,
                                  I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D),
                                  I.super_count + local, kBatchSuperCap, sm);
 }
@@ -266,7 +269,7 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
             b2 = r % I.tiles2;
         }
         if (V == 0) {
-            mfma_tile<D>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, b0, b1, b2, sC, out, &ctl->qcount);
+            mfma_tile<D>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, b0, b1, b2, sC, out, &ctl->qcount);
         } else {
             if (kLists) {
                 out.tp = I.tp;
@@ -282,10 +285,10 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                 }
             }
             if constexpr (V == 3 || V == 5)
-                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, b0, b1, b2,
+                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, b0, b1, b2,
                                                               sm.bf, out, kLists ? nullptr : &ctl->qcount);
             else
-                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap}, I.eig, b0, b1, b2,
+                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, b0, b1, b2,
                                                        sm.vec, out, kLists ? nullptr : &ctl->qcount);
         }
     }

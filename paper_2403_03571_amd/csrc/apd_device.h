@@ -15,7 +15,8 @@ namespace dev {
 // ------------------------------------------------------------ tile layout
 
 // A block covers a tile of pixels (tile_ext: 2D 8P x 32 as 2 x 2 waves of
-// 4 x 16 lanes, 3D 4P x 8 x 8 as 4 waves stacked along axis 0); each lane
+// 4 x 16 lanes, 3D 16 x 16 x 8 as 2 x 2 waves of 8 x 8 lanes for P = 8, else
+// 4P x 8 x 8 as 4 waves stacked along axis 0); each lane
 // owns P consecutive pixels along axis 0 and a fixed position on the other
 // axes, so consecutive lanes touch consecutive pixel indices along the
 // last axis.
@@ -55,14 +56,12 @@ __device__ inline Tile<D> tile_at(int b0, int b1, int b2) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     t.lane = lane;
     if (D == 2) {
-        t.org[0] = b0 * E0 + (wave >> 1) * wave_ext(D, P, 0);
-        t.org[1] = b1 * E1 + (wave & 1) * wave_ext(D, P, 1);
         t.org[2] = 0;
     } else {
-        t.org[0] = b0 * E0 + wave * P;
-        t.org[1] = b1 * E1;
         t.org[2] = b2 * E2;
     }
+    t.org[0] = b0 * E0 + wave_off(D, P, 0, wave);
+    t.org[1] = b1 * E1 + wave_off(D, P, 1, wave);
     lane_pixel<D, P>(t.org, lane, t.k0w, t.k[1], t.k[2]);
     t.k[0] = t.k0w;
     t.anc[0] = b0 * E0 + E0 / 2;
@@ -461,13 +460,13 @@ __device__ inline unsigned pixel_weight(const Geo &g, uint32_t j) {
 // part proportional to B as kslack() (B + r^2) (the r^2 covers the double
 // rounding of the expansion's own coefficients, seed_terms, whose terms
 // sum to at most lambda_G |e|^2 <= kappa (sqrt(B) + r)^2).
-__device__ inline float dslack_abs(const Geo &g, double wmax, Cert ct) {
+__device__ inline float dslack_abs(const Geo &g, double wmax, float lam) {
     double y2 = 0.0;
     for (int d = 0; d < g.dim; ++d) {
         const double y = fabs(g.lo[d]) + (double)g.grid[d] * g.s[d];
         y2 += y * y;
     }
-    return (float)(0x1p-44 * (fabs(wmax) + (double)ct.lam * y2));
+    return (float)(0x1p-44 * (fabs(wmax) + (double)lam * y2));
 }
 __device__ inline float kslack(Cert ct) { return 0x1p-44f * (ct.kap + 1.0f); }
 
@@ -561,8 +560,8 @@ struct MomTab {
                 for (int q = 0; q < 64; ++q) {  // the pixels of the step: 4 groups of 16 bytes
                     const int L = 16 * (q / 16) + 4 * (s % 4) + (q % 16) / 4, p = 4 * (s / 4) + q % 4;
                     if (p >= P) continue;
-                    const int k0 = D == 2 ? (w >> 1) * wave_ext(D, P, 0) + (L >> 4) * P + p : w * P + p;
-                    const int k1 = D == 2 ? (w & 1) * wave_ext(D, P, 1) + (L & 15) : L >> 3;
+                    const int k0 = wave_off(D, P, 0, w) + (D == 2 ? (L >> 4) * P : 0) + p;
+                    const int k1 = wave_off(D, P, 1, w) + (D == 2 ? L & 15 : L >> 3);
                     const int o[3] = {2 * (k0 - E[0] / 2) + 1, 2 * (k1 - E[1] / 2) + 1,
                                       D == 3 ? 2 * ((L & 7) - E[2] / 2) + 1 : 0};
                     int col[16] = {};
@@ -966,7 +965,7 @@ __device__ inline void mfma_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         }
     }
     const float r2 = ct.lam * umax2 * 1.01f;
-    const float sab = dslack_abs(g, wmax, ct), skb = kslack(ct);
+    const float sab = ct.sab, skb = kslack(ct);
     const float rr = sqrtf(r2);
     constexpr float rho = 0x1p-18f;
     int lab[kP];
@@ -1274,6 +1273,20 @@ __device__ inline bool can_beat(const CellQuad<D> &q, const CellQuad<D> &o, cons
     return !(lb > q.s + o.s + slack);
 }
 
+// Lane l's quadratic, wave-uniform.
+template <int D>
+__device__ inline CellQuad<D> lane_quad(const CellQuad<D> &q, int l) {
+    auto get = [&](float v) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); };
+    CellQuad<D> r;
+    r.c = get(q.c);
+    r.s = get(q.s);
+#pragma unroll
+    for (int d = 0; d < D; ++d) r.g[d] = get(q.g[d]);
+#pragma unroll
+    for (int t = 0; t < CellQuad<D>::kTri; ++t) r.a[t] = get(q.a[t]);
+    return r;
+}
+
 // Centre (double) and half extents (rounded up) of a box.
 template <int D>
 __device__ inline float box_centre(const double *blo, const double *bhi, double *ctr, float *h) {
@@ -1301,7 +1314,7 @@ __device__ inline int owner_filter(int nsrc, Load load, const float *h, float hh
     constexpr int kReg = 2;
     const bool in_regs = nsrc <= kReg * T;
     SeedRec<D> rc[kReg];
-    CellQuad<D> mine;
+    CellQuad<D> cq[kReg], mine;
     mine.c = INFINITY;
     if (in_regs) {
 #pragma unroll
@@ -1313,8 +1326,8 @@ __device__ inline int owner_filter(int nsrc, Load load, const float *h, float hh
         for (int r = 0; r < kReg; ++r) {
             const int q = threadIdx.x + r * T;
             if (q < nsrc) {
-                const CellQuad<D> c = cell_quad<D>(rc[r], lam, hh);
-                if (c.c < mine.c) mine = c;
+                cq[r] = cell_quad<D>(rc[r], lam, hh);
+                if (cq[r].c < mine.c) mine = cq[r];
             }
         }
     } else {
@@ -1352,7 +1365,7 @@ __device__ inline int owner_filter(int nsrc, Load load, const float *h, float hh
         for (int r = 0; r < kReg; ++r) {
             const int q = threadIdx.x + r * T;
             if (r * T < nsrc)
-                emit(q < nsrc && can_beat<D>(cell_quad<D>(rc[r], lam, hh), own, h, slack), q, rc[r]);
+                emit(q < nsrc && can_beat<D>(cq[r], own, h, slack), q, rc[r]);
         }
     } else {
         for (int q0 = 0; q0 < nsrc; q0 += T) {
@@ -1517,7 +1530,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
     } else {
         n = owner_filter<D, T>(
             m, [&](int q) { return seed_rec<D>(sd, wmax, ctr, sm.list[q]); }, h, hh, ct.lam,
-            2.0f * dslack_abs(g, wmax, ct), sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
+            2.0f * ct.sab, sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
                 if (pos < cap) store_rec<D>(list, cap, pos, r, sm.list[q]);
             });
     }
@@ -1547,11 +1560,15 @@ constexpr int kWaveCap = 256;    // per-wave candidate positions
 // The candidate list of a tile's box, from its super-tile's list when it has
 // one (else from every seed): into s_list, at most kCullCap seeds; returns
 // their number.  GAP: *U bounds the cost of every seed left out.
-template <int D, bool GAP, class Smem>
+template <int D, int P, bool GAP, class Smem>
 __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
-                                      const PassOut &out, int b0, int b1, int b2, const double *blo,
-                                      const double *bhi, Smem &sm, double *U) {
+                                      const PassOut &out, int b0, int b1, int b2, Smem &sm, double *U) {
     int *dst = sm.list;
+    auto tile_box = [&](double *blo, double *bhi) {
+        const int ext[3] = {tile_ext(D, P, 0), tile_ext(D, P, 1), tile_ext(D, P, 2)};
+        const int k0[3] = {b0 * ext[0], b1 * ext[1], b2 * ext[2]};
+        cull_box<D>(g, k0, ext, blo, bhi);
+    };
     const float4 *src = nullptr;
     int nsrc = g.n, cap = out.super_cap;
     const int sc[3] = {b0 / out.sf[0], b1 / out.sf[1], b2 / out.sf[2]};
@@ -1564,18 +1581,25 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
         }
     }
     if constexpr (GAP) {
+        double blo[3], bhi[3];
+        tile_box(blo, bhi);
         return build_candidates<D>(sd, eig, wmax, blo, bhi,
                                    [&](int q) { return src ? __float_as_int(src[q].w) : q; }, nsrc, dst, kCullCap,
                                    sm.cnt, sm.red, U);
     } else {
-        double ctr[D];
-        float h[D], shift[3] = {0.0f, 0.0f, 0.0f};
-        const float hh = box_centre<D>(blo, bhi, ctr, h);
-        const float slack = 2.0f * dslack_abs(g, wmax, ct);
+        float h[D], hh = 0.0f, shift[3] = {0.0f, 0.0f, 0.0f};
+        const float slack = 2.0f * ct.sab;
         if (src) {
-            double slo[3], shi[3];
-            super_box<D>(g, out, sc, slo, shi);
-            for (int d = 0; d < D; ++d) shift[d] = (float)(0.5 * (slo[d] + shi[d]) - ctr[d]);
+            // the boxes' centres differ by a multiple of half a pixel
+            const int tb[3] = {b0, b1, b2};
+            for (int d = 0; d < D; ++d) {
+                const int E = tile_ext(D, P, d), a = tb[d] * E, b = min(a + E, g.grid[d]) - 1;
+                const int sa = sc[d] * out.sf[d] * E, sb = min(sa + out.sf[d] * E, g.grid[d]) - 1;
+                const float s = (float)g.s[d];
+                h[d] = 0.5f * (float)(b - a) * s * (1.0f + 0x1p-20f);
+                hh = fmaf(h[d], h[d], hh);
+                shift[d] = 0.5f * (float)(sa + sb - a - b) * s;
+            }
             return owner_filter<D, kThreads>(
                 nsrc,
                 [&](int q) {
@@ -1586,6 +1610,9 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
                     if (pos < kCullCap) dst[pos] = __float_as_int(src[q].w);
                 });
         }
+        double blo[3], bhi[3], ctr[D];
+        tile_box(blo, bhi);
+        hh = box_centre<D>(blo, bhi, ctr, h);
         return owner_filter<D, kThreads>(
             nsrc, [&](int q) { return seed_rec<D>(sd, wmax, ctr, q); }, h, hh, ct.lam, slack, sm.cnt, sm.own,
             [&](int q, const SeedRec<D> &, int pos) {
@@ -1669,11 +1696,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     float Uwave = INFINITY;   // nor out of this wave's list
     if (CULL) {
         // ---- the candidate list, from the super-tile's list when it has one
-        double blo[3], bhi[3];
-        const int ext[3] = {E0, E1, E2};
-        const int k0[3] = {t.anc[0] - E0 / 2, t.anc[1] - E1 / 2, D == 3 ? t.anc[2] - E2 / 2 : 0};
-        cull_box<D>(g, k0, ext, blo, bhi);
-        const int ncand = tile_candidates<D, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, blo, bhi, sm, &Utile);
+        const int ncand = tile_candidates<D, P, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
@@ -1764,10 +1787,10 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         lost[p] = false;
     }
     // Short scan of the staged positions idx(j), j < c16 (a multiple of 16).
-    // Only the first c4 (a multiple of 4) positions are scanned: the lists
-    // are padded to 16, but a short list wastes at most 3 slots.
+    // Only the first c2 (a multiple of 2) positions are scanned: the lists
+    // are padded to 16, but a short list wastes at most 1 slot.
     bool keyed = false;  // the short scan ran: its costs lost their low 4 bits
-    auto key_scan = [&](int c4, auto idx) {
+    auto key_scan = [&](int c2, auto idx) {
         keyed = true;
         int best[P], second[P], blk[P];
 #pragma unroll
@@ -1776,14 +1799,14 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             second[p] = 0x7fffffff;
             blk[p] = 0;
         }
-        for (int q0 = 0; q0 < c4; q0 += 16) {
+        for (int q0 = 0; q0 < c2; q0 += 16) {
             int old[P];
 #pragma unroll
             for (int p = 0; p < P; ++p) old[p] = best[p];
-            for (int r4 = 0; r4 < 16 && q0 + r4 < c4; r4 += 4) {
+            for (int r2 = 0; r2 < 16 && q0 + r2 < c2; r2 += 2) {
 #pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    const int r = r4 + rr;
+                for (int rr = 0; rr < 2; ++rr) {
+                    const int r = r2 + rr;
                     float a00, beta, alpha;
                     lane_coef(idx(q0 + r), a00, beta, alpha);
 #pragma unroll
@@ -1982,7 +2005,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                 r.s = 0x1p-16f * (fabsf(r.c) + 2.0f * r2t);
                 return r;
             };
-            const float sl = 2.0f * dslack_abs(g, wmax, ct);
+            const float sl = 2.0f * ct.sab;
             // the owner: the wave's candidate of least cost at its centre
             float best = INFINITY;
             int bq = 0;
@@ -1995,11 +2018,11 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                     bq = q;
                 }
             }
-            const unsigned long long lead = __ballot(best == wave_min(best));
-            const CellQuad<D> own = staged_quad(__builtin_amdgcn_readlane(bq, max(0, __ffsll(lead) - 1)));
+            const int lead = max(0, __ffsll(__ballot(best == wave_min(best))) - 1);
             if (nscan <= 64) {
-                append(t.lane < nscan && can_beat<D>(mine, own, h, sl), t.lane);
+                append(t.lane < nscan && can_beat<D>(mine, lane_quad(mine, lead), h, sl), t.lane);
             } else {
+                const CellQuad<D> own = staged_quad(__builtin_amdgcn_readlane(bq, lead));
                 for (int q0 = 0; q0 < nscan; q0 += 64) {
                     const int q = q0 + t.lane;
                     append(q < nscan && can_beat<D>(staged_quad(min(q, nscan - 1)), own, h, sl), q);
@@ -2022,11 +2045,11 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             const int c16w = (cntw + 15) & ~15;
             auto widx = [&](int j) { return wl[j]; };
             if (cntw >= kGroupScan) group_scan(c16w, widx, 0);
-            else key_scan((cntw + 3) & ~3, widx);
+            else key_scan((cntw + 1) & ~1, widx);
         } else if (nscan >= kGroupScan) {
             group_scan(padded, ident, 0);
         } else {
-            key_scan((nscan + 3) & ~3, ident);
+            key_scan((nscan + 1) & ~1, ident);
         }
     } else if (nscan >= kGroupScan) {
         for (int base = 0; base < nscan; base += kVecChunk) {
@@ -2042,12 +2065,29 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         __syncthreads();
         stage(0, nscan, padded);
         __syncthreads();
-        key_scan((nscan + 3) & ~3, ident);
+        key_scan((nscan + 1) & ~1, ident);
     }
-    const float sab = dslack_abs(g, wmax, ct), skb = kslack(ct);
+    const float sab = ct.sab, skb = kslack(ct);
     const float kbits = keyed ? 0x1p-18f : 0.0f;
     bool flag[P];
     int lab[P];
+    // first a threshold that needs no square root and holds for the whole
+    // tile: 4 r sqrt(B) <= 2 B + 2 r^2 and r at the tile's corner, so thr <=
+    // 2^-20 (6 B1 + 12 r^2) + ..., linear in the best cost.  Nearly every wave
+    // settles all of its pixels by it (5 instructions per pixel instead of
+    // about 45 with two square roots).
+    const float r2t = pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f);
+    const float kb1 = (0x1.8p-18f + skb) * (1.0f + 0x1p-9f);
+    const float kb2 = (0x1.8p-17f + skb + 0x1p-9f * (0x1.8p-18f + skb)) * r2t * (1.0f + 0x1p-9f) + sab;
+    bool near = false;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const float thr = fmaf(fmaxf(fb[p], 0.0f), kb1, fmaf(kbits, fmaxf(fabsf(fb[p]), fabsf(fs[p])), kb2));
+        flag[p] = lost[p] || !((fs[p] - fb[p]) > thr);
+        near = near || flag[p];
+    }
+    if ((!CULL || GAP) && out.rel_gap) near = true;
+    if (__ballot(near)) {
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const float r2 = pixel_r2(ct, u0[p], u1, u2);
@@ -2071,6 +2111,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             c2l = fminf(c2l, (uc == INFINITY ? uc : uc - 0x1p-20f * fabsf(uc))) * (1.0f - 0x1p-20f);
             out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = fs[p] > 0.0f ? gap_lower(c1u, c2l) : 0.0f;
         }
+    }
     }
     if (!slots || out.labels) {
 #pragma unroll
@@ -2562,7 +2603,7 @@ __device__ inline void hyb_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     // pixel (j = NJ - 1 - p, -); the partner's seed and runner-up of those
     // pixels arrive by a swap across the half-waves
     const bool lane_ok = lane_in_grid<D>(g, t);
-    const float sab = dslack_abs(g, wmax, ct), skb = kslack(ct);
+    const float sab = ct.sab, skb = kslack(ct);
     const unsigned owin = (unsigned)__shfl_xor((int)win, 32);
     const unsigned olost = (unsigned)__shfl_xor((int)lostm, 32);
     bool act[NJ], flag[NJ];
@@ -2744,7 +2785,6 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     using SL = Bf16Slots<D>;
     static_assert(C % 32 == 0, "bf16 staging");
     constexpr int NG = 2 * P;  // 32-pixel groups per wave: gi = 2 r + c
-    constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
     constexpr int kQ = SL::SLOTS / 8;  // 16-byte operand pieces per seed
     constexpr float kPad = 1.7e38f;
 
@@ -2809,11 +2849,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     bool full = true;
     double Utile = INFINITY;  // no seed left out of the tile's list costs less
     if (CULL) {
-        double blo[3], bhi[3];
-        const int ext[3] = {E0, E1, E2};
-        const int k0[3] = {t.anc[0] - E0 / 2, t.anc[1] - E1 / 2, D == 3 ? t.anc[2] - E2 / 2 : 0};
-        cull_box<D>(g, k0, ext, blo, bhi);
-        const int ncand = tile_candidates<D, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, blo, bhi, sm, &Utile);
+        const int ncand = tile_candidates<D, P, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &Utile);
         full = ncand > kCullCap;
         nscan = full ? g.n : ncand;
         if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
@@ -2970,7 +3006,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         }
     }
 
-    const float sab = dslack_abs(g, wmax, ct), skb = kslack(ct);
+    const float sab = ct.sab, skb = kslack(ct);
     // lane l takes to the epilogue the groups of its own column half (the
     // pixels of column l % 32 of those groups are its own)
     const bool lane_ok = lane_in_grid<D>(g, t);

@@ -18,16 +18,25 @@ constexpr int kP = 4;          // pixels per lane along axis 0
 // 2D: a wave is 4 x 16 lanes (lane l at lane row l / 16, column l % 16),
 // so it covers 4p x 16 pixels, and the block's 4 waves form a 2 x 2 square
 // of waves: the tile is 8p x 32 pixels.  3D: a wave is 8 x 8 lanes on axes
-// 1 and 2; the 4 waves are stacked along axis 0: the tile is 4p x 8 x 8.
+// 1 and 2, so it covers p x 8 x 8 pixels; with p = 8 the 4 waves are a 2 x 2
+// square on axes 0 and 1 (tile 16 x 16 x 8), else they are stacked along
+// axis 0 (tile 4p x 8 x 8).
 // Square-ish wave boxes keep the candidate lists short: the upper bound a
 // candidate must beat comes from the box's far corners.
 constexpr int kHybRows3 = 16;  // rows along axis 0 of the hybrid tile: 3D (8 symmetric pairs per lane)
 constexpr int kHybRows2 = 32;  // 2D (4 pairs per lane, 4 waves)
 constexpr int tile_ext(int dim, int p, int axis) {
-    return dim == 2 ? (axis == 0 ? 8 * p : axis == 1 ? 32 : 1) : (axis == 0 ? kWaves * p : 8);
+    return dim == 2 ? (axis == 0 ? 8 * p : axis == 1 ? 32 : 1)
+           : p == 8 ? (axis < 2 ? 16 : 8)
+                    : (axis == 0 ? kWaves * p : 8);
 }
 constexpr int wave_ext(int dim, int p, int axis) {
     return dim == 2 ? (axis == 0 ? 4 * p : axis == 1 ? 16 : 1) : (axis == 0 ? p : 8);
+}
+// First pixel of wave `wave` in its tile along axes 0 and 1.
+constexpr int wave_off(int dim, int p, int axis, int wave) {
+    return (dim == 2 || p == 8) ? (axis == 0 ? wave >> 1 : wave & 1) * wave_ext(dim, p, axis)
+                                : (axis == 0 ? wave * p : 0);
 }
 
 // Problem geometry passed by value to every kernel.
@@ -61,6 +70,7 @@ struct Scalars {
     unsigned qcount;  // pixels re-evaluated in double
     float lam;        // upper bound of max_i lambda_max(A_i) (Gershgorin)
     float kap;        // upper bound of max_i lambda_G(A_i) / lambda_min(A_i)
+    float sab;        // absolute slack of the double costs (dslack_abs)
     int bad;          // validation bits
     unsigned long long qtotal;  // sum of the pixel weights (validation)
     unsigned seq;     // host copy only: the finalize's count of published passes
@@ -106,6 +116,7 @@ struct QSeg {
 struct Cert {
     float lam;
     float kap;
+    float sab;  // absolute slack of the double costs (dslack_abs)
 };
 
 // Upper bound of lambda_G(A) / lambda_min(A) for a symmetric positive

@@ -186,6 +186,7 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
         sc->vsum = s_v[0];
         sc->lam = s_l[0] * 1.0001f;
         sc->kap = s_k[0] * 1.0001f;
+        sc->sab = dslack_abs(g, s_w[0], s_l[0] * 1.0001f);
         sc->bad = s_b[0];
         sc->qcount = 0u;
         sc->credited = 0u;
@@ -316,10 +317,10 @@ __global__ __launch_bounds__(kThreads, (CULL && P == 4 && !GAP) ? 5 : 4) void k_
                                                         const double *eig, PassOut out) {
     __shared__ VecSmem<D, CULL, P, GAP> sm;
     if constexpr (D == 2)
-        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
+        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
                              &sc->qcount);
     else
-        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
+        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
                              out, &sc->qcount);
 }
 
@@ -334,9 +335,9 @@ __global__ __launch_bounds__(kThreads) void k_assign_mfma(Geo g, Seeds sd, Scala
                                                          PassOut out) {
     __shared__ __attribute__((aligned(16))) float sC[kMfmaLds];
     if (D == 2)
-        dev::mfma_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, blockIdx.y, blockIdx.x, 0, sC, out, &sc->qcount);
+        dev::mfma_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.y, blockIdx.x, 0, sC, out, &sc->qcount);
     else
-        dev::mfma_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, blockIdx.z, blockIdx.y, blockIdx.x, sC, out,
+        dev::mfma_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.z, blockIdx.y, blockIdx.x, sC, out,
                           &sc->qcount);
 }
 
@@ -421,10 +422,10 @@ __global__ __launch_bounds__(kThreads, D == 3 ? 3 : 4) void k_assign_hyb(Geo g, 
                                                                           PassOut out) {
     __shared__ __attribute__((aligned(16))) HybSmem<D> sm;
     if constexpr (D == 3)
-        hyb_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, blockIdx.z, blockIdx.y, blockIdx.x, sm, out,
+        hyb_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.z, blockIdx.y, blockIdx.x, sm, out,
                     &sc->qcount);
     else
-        hyb_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
+        hyb_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
 }
 
 // ------------------------------------------------------ k_assign_bf16
@@ -439,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scala
     const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
     const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
     const int b2 = D == 2 ? 0 : blockIdx.x;
-    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, b0, b1, b2, sm, out, &sc->qcount);
+    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, b0, b1, b2, sm, out, &sc->qcount);
 }
 
 // --------------------------------------------------------- k_super_cull
@@ -450,7 +451,7 @@ __global__ __launch_bounds__(T) void k_super_cull(Geo g, Seeds sd, const Scalars
                                                   float4 *list, int *count) {
     __shared__ SuperSmem<D, T> sm;
     const int st = blockIdx.x;
-    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap}, eig, out, st,
+    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, out, st,
                           list + (size_t)st * (size_t)out.super_cap * rec_vec(D), count + st, out.super_cap, sm);
 }
 
@@ -623,12 +624,18 @@ hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const double *
 
 int vec_pixels_per_lane(const Geo &g, bool cull) {
     if (g.vec_p == 4 || g.vec_p == 8) return g.vec_p;
-    // measured: with candidate lists the smaller wave boxes of 4 rows win
-    // (fewer candidates per wave); over every seed, 8 rows halve the
-    // per-seed work of a lane once the grid keeps the chip busy
-    if (cull) return 4;
     int64_t J = 1;
     for (int d = 0; d < g.dim; ++d) J *= g.grid[d];
+    // measured: with candidate lists the smaller wave boxes of 4 rows win
+    // (fewer candidates per wave), except in 3D on large cells, whose lists
+    // are short either way, so that halving the work per wave box pays:
+    // 16 x 16 x 8 against 16 x 8 x 8 tiles, evaluation at 1700 voxels per cell
+    // 96^3 61 / 58 us, 128^3 69 / 70, 200^3 117 / 124, 256^3 183 / 200; at 300
+    // per cell 128^3 121 / 116, 200^3 421 / 381.  2D is within 2 % at 1700
+    // pixels per cell and slower at 300 (2048^2: 153 / 135).
+    if (cull) return g.dim == 3 && J >= (int64_t)1 << 21 && J >= (int64_t)1000 * g.n ? 8 : 4;
+    // over every seed, 8 rows halve the per-seed work of a lane once the grid
+    // keeps the chip busy
     return J >= 1024 * 2048 ? 8 : 4;
 }
 
