@@ -182,15 +182,33 @@ __global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCt
 
 // -------------------------------------------------------------- kb_assign
 
+// *p for a wave-uniform p whose memory no kernel of the launch writes, by
+// scalar loads.  The compiler proves neither for a struct reached through
+// another kernel's table next to atomics, and loaded the instance's fields
+// into vector registers, with 136 bytes of scratch in kb_assign: 2.0 ms per
+// evaluation of 512 maps, 1.5 with scalar loads.
+template <class T>
+__device__ inline T uniform_load(const T *p) {
+    static_assert(sizeof(T) % 4 == 0 && __is_trivially_copyable(T), "copied by 4-byte words");
+    typedef const __attribute__((address_space(4))) unsigned Word;
+    unsigned w[sizeof(T) / 4];
+    Word *src = (Word *)p;
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(T) / 4; ++k) w[k] = src[k];
+    T r;
+    __builtin_memcpy(&r, w, sizeof(T));
+    return r;
+}
+
 // The instance of work item `item`: prefix[b] <= item < prefix[b + 1].
 __device__ inline int find_instance(const int64_t *prefix, int B, int64_t item) {
     int lo = 0, hi = B;  // prefix[lo] <= item < prefix[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (prefix[mid] <= item) lo = mid;
+        if (uniform_load(prefix + mid) <= item) lo = mid;
         else hi = mid;
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // One block per super-tile of an active instance: its candidate list
@@ -199,10 +217,11 @@ template <int D>
 __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BState *st, BWork wk, int B) {
     __shared__ SuperSmem<D, kThreads> sm;
     const int64_t item = blockIdx.x;
-    if (item >= wk.act_super[B]) return;
+    if (item >= uniform_load(wk.act_super + B)) return;
     const int b = find_instance(wk.act_super, B, item);
-    const BInst &I = inst[b];
-    const int local = (int)(item - wk.act_super[b]);
+    const BInst I = uniform_load(inst + b);
+    const BState S = uniform_load(st + b);
+    const int local = (int)(item - uniform_load(wk.act_super + b));
     Seeds sd{I.x, I.A, I.wt, I.v};
     PassOut out{nullptr, nullptr, nullptr};
     out.tp = I.tp;
@@ -210,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
         out.sf[d] = I.sf[d];
         out.nst[d] = I.nst[d];
     }
-    super_tile_list<D, kThreads>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, out, local,
+    super_tile_list<D, kThreads>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, out, local,
                                  I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D),
                                  I.super_count + local, kBatchSuperCap, sm);
 }
@@ -243,12 +262,13 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
     } sm;
     float *sC = sm.mf;
     constexpr bool kLists = V == 2 || V == 4 || V == 5;
-    const int64_t total = wk.act_tile[B];
+    const int64_t total = uniform_load(wk.act_tile + B);
     for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
         const int b = find_instance(wk.act_tile, B, item);
         __syncthreads();  // the previous tile is done with the shared memory
-        const BInst &I = inst[b];
-        const int64_t local = item - wk.act_tile[b];
+        const BInst I = uniform_load(inst + b);
+        const BState S = uniform_load(st + b);
+        const int64_t local = item - uniform_load(wk.act_tile + b);
         Seeds sd{I.x, I.A, I.wt, I.v};
         PassOut out{nullptr, I.mom, nullptr};
         if (!kLists) {
@@ -269,7 +289,7 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
             b2 = r % I.tiles2;
         }
         if (V == 0) {
-            mfma_tile<D>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, b0, b1, b2, sC, out, &ctl->qcount);
+            mfma_tile<D>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, b0, b1, b2, sC, out, &ctl->qcount);
         } else {
             if (kLists) {
                 out.tp = I.tp;
@@ -285,10 +305,10 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                 }
             }
             if constexpr (V == 3 || V == 5)
-                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, b0, b1, b2,
+                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, b0, b1, b2,
                                                               sm.bf, out, kLists ? nullptr : &ctl->qcount);
             else
-                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, st[b].wmax, Cert{st[b].lam, st[b].kap, st[b].sab}, I.eig, b0, b1, b2,
+                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, b0, b1, b2,
                                                        sm.vec, out, kLists ? nullptr : &ctl->qcount);
         }
     }

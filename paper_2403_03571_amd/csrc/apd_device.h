@@ -52,7 +52,10 @@ template <int D, int P = kP>
 __device__ inline Tile<D> tile_at(int b0, int b1, int b2) {
     constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
     Tile<D> t;
-    const int lane = __lane_id();
+    int lane = __lane_id();
+    // keeps a kernel that loops over tiles from holding every value derived
+    // from the lane in registers across the loop
+    asm volatile("" : "+v"(lane));
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     t.lane = lane;
     if (D == 2) {
