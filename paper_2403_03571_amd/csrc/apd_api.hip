@@ -1155,8 +1155,7 @@ struct apd_ws_model {
     float *P = nullptr, *G = nullptr, *M = nullptr, *V = nullptr;  // params, grad, Adam moments
     int64_t step = 0;
     int64_t cap_S = 0;
-    float *act = nullptr;   // H1, H2, H3, dA, dB [cap_S][128], y, dy [cap_S]
-    double *loss_d = nullptr;
+    float *act = nullptr;   // activations and gradient slices (apd::ws::act_floats)
     double *h_loss = nullptr;
     unsigned short *Wb = nullptr;  // BF16 weight copies for inference
     bool bf_stale = true;          // the copies predate the parameters
@@ -1164,30 +1163,15 @@ struct apd_ws_model {
 
 namespace {
 
-constexpr int kWsHid = 128;
-// floats of split weight-gradient partials after the activations
-constexpr size_t kWsPart = (size_t)apd::ws::kSplitMax * (kWsHid * kWsHid + kWsHid);
-
 apd_status ws_scratch(apd_ctx *c, apd_ws_model *m, int64_t S) {
     if (S <= m->cap_S) return APD_OK;
     (void)hipFree(m->act);
     m->act = nullptr;
     m->cap_S = 0;
-    if (hipMalloc(&m->act, ((size_t)S * (5 * kWsHid + 2) + kWsPart) * sizeof(float)) != hipSuccess)
+    if (hipMalloc(&m->act, (size_t)apd::ws::act_floats(S) * sizeof(float)) != hipSuccess)
         return fail(c, APD_ERR_OOM, "cannot allocate network activations for %lld samples", (long long)S);
     m->cap_S = S;
     return APD_OK;
-}
-
-struct WsBufs {
-    float *H1, *H2, *H3, *dA, *dB, *y, *dy, *part;
-};
-
-WsBufs ws_bufs(apd_ws_model *m) {
-    const size_t S = (size_t)m->cap_S;
-    float *a = m->act;
-    return WsBufs{a, a + S * kWsHid, a + 2 * S * kWsHid, a + 3 * S * kWsHid, a + 4 * S * kWsHid,
-                  a + 5 * S * kWsHid, a + 5 * S * kWsHid + S, a + 5 * S * kWsHid + 2 * S};
 }
 
 // Warm-start features: one pass at W = 0 gives the deficits (gradient in
@@ -1579,7 +1563,6 @@ apd_status apd_ws_create(apd_ctx *c, apd_ws_model **out, const float *params, in
     const size_t bytes = (size_t)n_params * sizeof(float);
     if (hipMalloc(&m->P, bytes) != hipSuccess || hipMalloc(&m->G, bytes) != hipSuccess ||
         hipMalloc(&m->M, bytes) != hipSuccess || hipMalloc(&m->V, bytes) != hipSuccess ||
-        hipMalloc(&m->loss_d, sizeof(double)) != hipSuccess ||
         hipMalloc(&m->Wb, (size_t)apd::ws::kBf16Count * sizeof(unsigned short)) != hipSuccess ||
         hipHostMalloc(&m->h_loss, sizeof(double), hipHostMallocDefault) != hipSuccess) {
         apd_ws_destroy(m);
@@ -1603,7 +1586,6 @@ void apd_ws_destroy(apd_ws_model *m) {
     (void)hipFree(m->M);
     (void)hipFree(m->V);
     (void)hipFree(m->act);
-    (void)hipFree(m->loss_d);
     (void)hipFree(m->Wb);
     (void)hipHostFree(m->h_loss);
     delete m;
@@ -1642,10 +1624,7 @@ apd_status apd_ws_targets(apd_ctx *c, int64_t n, const double *w, float *t) {
 apd_status apd_ws_forward(apd_ctx *c, apd_ws_model *m, const float *F, int64_t S, float *y) {
     if (!c || !m || !F || !y || S < 1 || S > 0x7fffffff) return APD_ERR_INVALID_ARG;
     c->err.clear();
-    apd_status st = ws_scratch(c, m, S);
-    if (st != APD_OK) return st;
-    WsBufs b = ws_bufs(m);
-    HIP_TRY(c, apd::ws::forward(c->stream, m->P, F, (int)S, b.H1, b.H2, b.H3, y));
+    HIP_TRY(c, apd::ws::forward(c->stream, m->P, F, (int)S, y));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return APD_OK;
 }
@@ -1665,13 +1644,7 @@ apd_status apd_ws_loss_grad(apd_ctx *c, apd_ws_model *m, const float *F, const f
     c->err.clear();
     apd_status st = ws_scratch(c, m, S);
     if (st != APD_OK) return st;
-    WsBufs b = ws_bufs(m);
-    HIP_TRY(c, apd::ws::backward(c->stream, m->P, F, t, (int)S, b.H1, b.H2, b.H3, b.y, b.dy, b.dA, b.dB,
-                                 m->G, m->loss_d, b.part));
-    if (grad)
-        HIP_TRY(c, hipMemcpyAsync(grad, m->G, (size_t)apd::ws::kParamCount * sizeof(float),
-                                  hipMemcpyDeviceToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(m->h_loss, m->loss_d, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, apd::ws::backward(c->stream, m->P, F, t, (int)S, m->act, grad ? grad : m->G, m->h_loss));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (loss) *loss = *m->h_loss;
     return APD_OK;
@@ -1683,14 +1656,10 @@ apd_status apd_ws_train_step(apd_ctx *c, apd_ws_model *m, const float *F, const 
     c->err.clear();
     apd_status st = ws_scratch(c, m, S);
     if (st != APD_OK) return st;
-    WsBufs b = ws_bufs(m);
-    HIP_TRY(c, apd::ws::backward(c->stream, m->P, F, t, (int)S, b.H1, b.H2, b.H3, b.y, b.dy, b.dA, b.dB,
-                                 m->G, m->loss_d, b.part));
     m->step += 1;
-    HIP_TRY(c, apd::ws::adam(c->stream, m->P, m->G, m->M, m->V, lr, m->step));
+    HIP_TRY(c, apd::ws::train_step(c->stream, m->P, m->M, m->V, F, t, (int)S, m->act, lr, m->step, m->h_loss));
     m->bf_stale = true;
     if (loss) {
-        HIP_TRY(c, hipMemcpyAsync(m->h_loss, m->loss_d, sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         *loss = *m->h_loss;
     }
@@ -1723,16 +1692,15 @@ apd_status apd_ws_predict(apd_ctx *c, apd_ws_model *m, const apd_problem *p, dou
     if (p->dim != 2) return fail(c, APD_ERR_INVALID_ARG, "the warm start is defined in 2D");
     if (!w_out) return fail(c, APD_ERR_INVALID_ARG, "w_out is NULL");
     const int64_t n = p->n;
-    st = ws_scratch(c, m, n + 16 * ((n + 127) / 128 + 1));
+    st = ws_scratch(c, m, n);
     if (st != APD_OK) return st;
-    WsBufs b = ws_bufs(m);
-    float *F = b.dA;  // features in the gradient scratch ([n][20] fits in [n][128])
+    float *F = m->act, *y = F + n * 20;  // features [n][20] and outputs in the activations' room
     if (hipSetDevice(c->device) != hipSuccess) return fail(c, APD_ERR_DEVICE, "hipSetDevice failed");
     st = ws_features_impl(c, p, F);
     if (st != APD_OK) return st;
-    st = ws_infer_impl(c, m, F, n, b.y);
+    st = ws_infer_impl(c, m, F, n, y);
     if (st != APD_OK) return st;
-    HIP_TRY(c, apd::ws::center(c->stream, (int)n, b.y, w_out));
+    HIP_TRY(c, apd::ws::center(c->stream, (int)n, y, w_out));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return APD_OK;
 }

@@ -229,14 +229,14 @@ extern const int64_t kParamCount;
 hipError_t features(hipStream_t s, int n, const double *x, const double *A, const double *v,
                     const double *lo, const double *hi, const double *grad0, int *nb, double *tmp,
                     float *F);
-hipError_t forward(hipStream_t s, const float *P, const float *X, int S, float *H1, float *H2,
-                   float *H3, float *y);
-// part: kSplitMax * (128 * 128 + 128) floats of scratch (split weight gradients)
-constexpr int kSplitMax = 32;
-hipError_t backward(hipStream_t s, const float *P, const float *X, const float *t, int S, float *H1,
-                    float *H2, float *H3, float *y, float *dy, float *dA, float *dB, float *G,
-                    double *loss, float *part);
-hipError_t adam(hipStream_t s, float *P, const float *G, float *M, float *V, float lr, int64_t step);
+constexpr int kSplitMax = 32;  // slices of the samples in the weight gradients
+int64_t act_floats(int64_t S);
+hipError_t forward(hipStream_t s, const float *P, const float *X, int S, float *y);
+// buf: act_floats(S) floats of scratch (256-byte aligned)
+hipError_t backward(hipStream_t s, const float *P, const float *X, const float *t, int S, float *buf, float *G,
+                    double *loss);
+hipError_t train_step(hipStream_t s, float *P, float *M, float *V, const float *X, const float *t, int S, float *buf,
+                      float lr, int64_t step, double *loss);
 // BF16 inference: transposed BF16 weight copies (kBf16Count values) and the
 // matrix-core forward pass.
 extern const int64_t kBf16Count;

@@ -147,171 +147,324 @@ __global__ __launch_bounds__(256) void kw_pool(int n, const int *nb, const doubl
     F[(size_t)i * kFeat + col] = (float)m;
 }
 
-// ------------------------------------------------------------------ GEMM
+// ------------------------------------------------- training on the matrix cores
 
-// C[m][n] = sum_k opA(m, k) opB(k, n) with opA(m, k) = TA ? A[k lda + m] :
-// A[m lda + k] and opB(k, n) = TB ? B[n ldb + k] : B[k ldb + n], then the
-// epilogue: 0 none, 1 + bias[n], 2 relu(. + bias[n]), 3 times (mask[m][n] > 0).
-// 64 x 64 output tile per block, K in slices of 16 through LDS, each thread
-// a 4 x 4 block of outputs (FP32 vector ALU; the network is small).
-template <bool TA, bool TB, int EPI>
-__global__ __launch_bounds__(256) void kw_gemm(int M, int N, int K, const float *__restrict__ A,
-                                               int lda, const float *__restrict__ B, int ldb,
-                                               float *__restrict__ C, int ldc,
-                                               const float *__restrict__ bias,
-                                               const float *__restrict__ mask, int ldm) {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int e = tid; e < 16 * 64; e += 256) {
-            const int kk = e / 64, mm = e % 64;
-            const int m = m0 + mm, k = k0 + kk;
-            float a = 0.0f;
-            if (m < M && k < K) a = TA ? A[(size_t)k * lda + m] : A[(size_t)m * lda + k];
-            As[kk][mm] = a;
-            const int n = n0 + mm;
-            float b = 0.0f;
-            if (n < N && k < K) b = TB ? B[(size_t)n * ldb + k] : B[(size_t)k * ldb + n];
-            Bs[kk][mm] = b;
-        }
-        __syncthreads();
+// Forward and backward in three launches (one for the forward alone), all
+// products on the FP32 matrix cores: v_mfma_f32_16x16x4_f32 and _32x32x2_f32
+// multiply and accumulate in FP32, at the rate of the vector ALU but without
+// its operand traffic.  The path is bound by latency, not by arithmetic
+// (0.85 GFLOP for 4096 samples, 5.6 us at the matrix cores' 153 TFLOP/s): one
+// product per launch through LDS took 21 launches and 272 us of kernels,
+// these three 34 us (kw_net 17, kw_grad 13, kw_reduce 4).
+//   kw_net       a block per 16 samples keeps their activations in LDS through
+//                the layers and back: y, the loss terms and the layers'
+//                inputs H and output gradients dZ in global memory
+//   kw_grad      the weight and bias gradients, split over the samples
+//   kw_reduce    the splits added in order (deterministic), the loss, and
+//                for a training step Adam's update
+
+typedef float floatx4_t __attribute__((ext_vector_type(4)));
+typedef float floatx16_t __attribute__((ext_vector_type(16)));
+
+constexpr int kTS = 16;         // samples per block of kw_net: 256 blocks for 4096
+constexpr int kNetThreads = 512; // its 8 waves, one per 16 columns of a layer
+constexpr int kRowF = kHid + 4; // LDS row of activations (the 16 rows of a column on distinct banks)
+
+// The contraction index of the 16x16x4 products runs over k = 16 t + 4 g + c
+// at step 4 t + c for the lanes of group g = lane / 16, on both operands, so
+// that a lane reads its activations (and, where they are contiguous in k, its
+// weights) four at a time.
+
+// out = act W (W [K][128] row-major): the wave's 16 columns n0 .. n0 + 15; rows
+// k >= KV of W and columns of act past KV are zero.
+template <int KT>
+__device__ inline floatx4_t net_tile(const float (&w)[KT][4], const float *act, int lane) {
+    const int row = lane & 15, g = lane >> 4;
+    floatx4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
+    for (int t = 0; t < KT; ++t) {
+        const floatx4_t a = *reinterpret_cast<const floatx4_t *>(act + row * kRowF + 16 * t + 4 * g);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = As[kk][ty * 4 + r];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) b[c] = Bs[kk][tx * 4 + c];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(a[r], b[c], acc[r][c]);
-        }
-        __syncthreads();
+        for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c], w[t][c], acc, 0, 0, 0);
     }
+    return acc;
+}
+template <int KT, int KV>
+__device__ inline void fwd_weights(const float *W, int n0, int lane, float (&w)[KT][4]) {
+    const int col = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + ty * 4 + r;
-        if (m >= M) continue;
+    for (int t = 0; t < KT; ++t)
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int n = n0 + tx * 4 + c;
-            if (n >= N) continue;
-            float val = acc[r][c];
-            if (EPI == 1 || EPI == 2) val += bias[n];
-            if (EPI == 2) val = fmaxf(val, 0.0f);
-            if (EPI == 3) val = mask[(size_t)m * ldm + n] > 0.0f ? val : 0.0f;
-            C[(size_t)m * ldc + n] = val;
+            const int k = 16 * t + 4 * g + c;
+            w[t][c] = (KV == 16 * KT || k < KV) ? W[(size_t)k * kHid + n0 + col] : 0.0f;
         }
+}
+// The same for out = dZ W^T (the contraction over W's columns).
+__device__ inline void bwd_weights(const float *W, int n0, int lane, float (&w)[kHid / 16][4]) {
+    const int col = lane & 15, g = lane >> 4;
+#pragma unroll
+    for (int t = 0; t < kHid / 16; ++t) {
+        const floatx4_t v = *reinterpret_cast<const floatx4_t *>(W + (size_t)(n0 + col) * kHid + 16 * t + 4 * g);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) w[t][c] = v[c];
     }
 }
 
-// Weight (and bias) gradients of one layer, split over the samples: block
-// (n tile, m tile, split) sums its slice of the samples of A^T B for a
-// 64 x 64 tile into part[split][M][N] (A [K][lda] read transposed, B
-// [K][ldb]); with BIAS the blocks of the first m tile also sum B's columns
-// over the slice into bpart[split][N].  kw_reduce_parts then adds the
-// splits in order, so the gradients are deterministic.  (One block per
-// output tile left four blocks looping over every sample.)
-template <bool BIAS>
-__global__ __launch_bounds__(256) void kw_gemm_tn_part(int M, int N, int K, int kslice,
-                                                       const float *__restrict__ A, int lda,
-                                                       const float *__restrict__ B, int ldb,
-                                                       float *__restrict__ part,
-                                                       float *__restrict__ bpart) {
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int ka = blockIdx.z * kslice, kb = min(K, ka + kslice);
-    const bool colsum = BIAS && blockIdx.y == 0;
-    float acc[4][4] = {};
-    float bsum = 0.0f;
-    for (int k0 = ka; k0 < kb; k0 += 16) {
-        for (int e = tid; e < 16 * 64; e += 256) {
-            const int kk = e / 64, mm = e % 64;
-            const int m = m0 + mm, k = k0 + kk;
-            As[kk][mm] = (m < M && k < kb) ? A[(size_t)k * lda + m] : 0.0f;
-            const int n = n0 + mm;
-            Bs[kk][mm] = (n < N && k < kb) ? B[(size_t)k * ldb + n] : 0.0f;
-        }
-        __syncthreads();
-        if (colsum && tid < 64)
-#pragma unroll
-            for (int kk = 0; kk < 16; ++kk) bsum += Bs[kk][tid];
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) a[r] = As[kk][ty * 4 + r];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) b[c] = Bs[kk][tx * 4 + c];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) acc[r][c] = fmaf(a[r], b[c], acc[r][c]);
-        }
-        __syncthreads();
-    }
-    float *out = part + (size_t)blockIdx.z * M * N;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int m = m0 + ty * 4 + r;
-        if (m >= M) continue;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            const int n = n0 + tx * 4 + c;
-            if (n < N) out[(size_t)m * N + n] = acc[r][c];
-        }
-    }
-    if (colsum && tid < 64 && n0 + tid < N) bpart[(size_t)blockIdx.z * N + n0 + tid] = bsum;
-}
+// The global activations of one pass: H1, H2, H3 and dZ1, dZ2, dZ3 [S][128],
+// dy [S], one loss term per block.
+struct NetBufs {
+    float *H[3];
+    float *dZ[3];
+    float *dy;
+    double *lossp;
+};
 
-// out[i] = sum over s < nsplit of part[s count + i], in order of s
-__global__ __launch_bounds__(256) void kw_reduce_parts(int count, int nsplit, const float *part,
-                                                       float *out) {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
-    float v = 0.0f;
-    for (int q = 0; q < nsplit; ++q) v += part[(size_t)q * count + i];
-    out[i] = v;
-}
-
-// r = y - t, loss = mean r^2 (double, fixed order), dy = 2 r / S
-__global__ __launch_bounds__(1024) void kw_loss(int S, const float *y, const float *t, float *dy,
-                                                double *loss) {
-    __shared__ double red[1024];
-    double s = 0.0;
-    for (int m = threadIdx.x; m < S; m += 1024) {
-        const float r = y[m] - t[m];
-        s += (double)r * (double)r;
-        dy[m] = 2.0f * r / (float)S;
+// Samples 16 b .. of block b through the network (and, with BWD, back):
+// wave w holds the output columns 16 w .. 16 w + 15 of every layer.
+// The weights of all layers are loaded first (loads behind stores would wait
+// for them layer by layer), and each layer's H and dZ leave LDS past the
+// caches while the next one is computed: the next kernel reads them on other
+// XCDs, and the write-back of 12.6 MB of them at the kernel's end took longer
+// than the products (4096 samples: 7 us for the forward pass alone).
+template <bool BWD>
+__global__ __launch_bounds__(kNetThreads) void kw_net(const float *__restrict__ P, const float *__restrict__ X,
+                                                      const float *__restrict__ tgt, int S, float *__restrict__ y,
+                                                      NetBufs nb) {
+    // X, H1, H2, H3, dZ3, dZ2, dZ1
+    __shared__ __attribute__((aligned(16))) float act[BWD ? 7 : 4][kTS * kRowF];
+    __shared__ float s_r[kTS];
+    const int lane = __lane_id(), tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n0 = 16 * wave, s0 = blockIdx.x * kTS;
+    const int col = lane & 15, g = lane >> 4, n = n0 + col;
+    float w1[2][4], w2[kHid / 16][4], w3[kHid / 16][4], w3t[kHid / 16][4], w2t[kHid / 16][4];
+    {
+        const int r = tid >> 5, k = tid & 31;
+        act[0][r * kRowF + k] = (k < kFeat && s0 + r < S) ? X[(size_t)(s0 + r) * kFeat + k] : 0.0f;
     }
-    red[threadIdx.x] = s;
+    fwd_weights<2, kFeat>(P + oW1, n0, lane, w1);
+    const float b1 = P[ob1 + n], b2 = P[ob2 + n], b3 = P[ob3 + n];
+    fwd_weights<kHid / 16, kHid>(P + oW2, n0, lane, w2);
+    fwd_weights<kHid / 16, kHid>(P + oW3, n0, lane, w3);
+    if constexpr (BWD) {
+        bwd_weights(P + oW3, n0, lane, w3t);
+        bwd_weights(P + oW2, n0, lane, w2t);
+    }
+    // bias and ReLU of a layer's tile
+    auto store = [&](const floatx4_t acc, float bn, float *dst) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dst[(4 * g + r) * kRowF + n] = fmaxf(acc[r] + bn, 0.0f);
+    };
+    // a thread writes 4 columns of one sample
+    auto put = [&](const float *src, float *glob) {
+        const int m = tid >> 5, c = 4 * (tid & 31);
+        if (s0 + m < S)
+            __builtin_nontemporal_store(*reinterpret_cast<const floatx4_t *>(&src[m * kRowF + c]),
+                                        reinterpret_cast<floatx4_t *>(glob + (size_t)(s0 + m) * kHid + c));
+    };
     __syncthreads();
-    for (int o = 512; o >= 1; o >>= 1) {
-        if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-        __syncthreads();
+    store(net_tile<2>(w1, act[0], lane), b1, act[1]);
+    __syncthreads();
+    if (BWD) put(act[1], nb.H[0]);
+    store(net_tile<kHid / 16>(w2, act[1], lane), b2, act[2]);
+    __syncthreads();
+    if (BWD) put(act[2], nb.H[1]);
+    store(net_tile<kHid / 16>(w3, act[2], lane), b3, act[3]);
+    __syncthreads();
+    if (BWD) put(act[3], nb.H[2]);
+    // the output: 32 threads per sample, 4 columns each
+    {
+        const int m = tid >> 5, q = tid & 31;
+        float v = 0.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v = fmaf(act[3][m * kRowF + q + 32 * k], P[oW4 + q + 32 * k], v);
+#pragma unroll
+        for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+        v += P[ob4];
+        const bool in = s0 + m < S;
+        if (q == 0 && in && y) y[s0 + m] = v;
+        if constexpr (BWD) {
+            // r, dy = 2 r / S, and dZ3 = dy W4^T where H3 > 0 (every thread of the
+            // sample holds v)
+            const float r = in ? v - tgt[s0 + m] : 0.0f;
+            const float dy = 2.0f * r / (float)S;
+            if (q == 0) {
+                s_r[m] = r;
+                if (in) nb.dy[s0 + m] = dy;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = q + 32 * k;
+                act[4][m * kRowF + c] = act[3][m * kRowF + c] > 0.0f ? dy * P[oW4 + c] : 0.0f;
+            }
+        }
     }
-    if (threadIdx.x == 0) *loss = red[0] / (double)S;
+    if constexpr (BWD) {
+        // dZ = (dZ_next W^T) where H > 0
+        auto back = [&](const floatx4_t acc, const float *H, float *dst) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = 4 * g + r;
+                dst[m * kRowF + n] = H[m * kRowF + n] > 0.0f ? acc[r] : 0.0f;
+            }
+        };
+        __syncthreads();
+        if (tid == 0) {
+            double l = 0.0;
+            for (int m = 0; m < kTS; ++m) l += (double)s_r[m] * (double)s_r[m];
+            nb.lossp[blockIdx.x] = l;
+        }
+        put(act[4], nb.dZ[2]);
+        back(net_tile<kHid / 16>(w3t, act[4], lane), act[2], act[5]);
+        __syncthreads();
+        put(act[5], nb.dZ[1]);
+        back(net_tile<kHid / 16>(w2t, act[5], lane), act[1], act[6]);
+        __syncthreads();
+        put(act[6], nb.dZ[0]);
+    }
 }
 
-// Adam with bias correction
-__global__ __launch_bounds__(256) void kw_adam(int64_t P, float *p, const float *g, float *m,
-                                               float *v, float lr, float c1, float c2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= P) return;
-    const float gi = g[i];
-    const float mi = 0.9f * m[i] + 0.1f * gi;
-    const float vi = 0.999f * v[i] + 0.001f * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+// Gradients of one slice of the samples, into part[slice][kParams].  Block
+// job 0-3 and 4-7: the 64 x 64 quarters of dW3 = H2^T dZ3 and dW2 = H1^T dZ2, a
+// wave per 32 x 32 tile; 8, 9: the halves of dW1 = X^T dZ1 (rows past 20 are
+// empty; waves 0 and 1); 10, 11: the bias gradients and the output layer's.
+// The samples come through LDS 128 at a time, every load of a chunk in flight
+// at once: the arrays were written from other XCDs, so each load goes past the
+// L2 (read straight into the products' operands 16 samples at a time the
+// kernel took 12 to 14 us for 4096 samples).
+constexpr int kGradChunk = 128;
+constexpr int kGradJobs = 12;
+
+__global__ __launch_bounds__(256) void kw_grad(const float *__restrict__ X, int S, int kslice, NetBufs nb,
+                                               float *__restrict__ part) {
+    __shared__ __attribute__((aligned(16))) float sm[2][kGradChunk][64];
+    const int job = blockIdx.x, tid = threadIdx.x, lane = __lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int ka = blockIdx.y * kslice, kb = min(S, ka + kslice);
+    float *out = part + (size_t)blockIdx.y * kParams;
+    if (job >= 10) {
+        // column n over half of the slice per thread: dW4, db3 and db4 (job
+        // 10) or db1 and db2 (11); the halves are added in LDS
+        const int n = tid & 127, half = tid >> 7;
+        const bool last = job == 10;
+        const float *U = last ? nb.H[2] : nb.dZ[0], *V = last ? nb.dZ[2] : nb.dZ[1];
+        const int mid = ka + (kb - ka + 1) / 2, k1 = half ? kb : mid;
+        float s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+        constexpr int C = 32;  // samples whose values are loaded together
+        for (int k0 = half ? mid : ka; k0 < k1; k0 += C) {
+            float u[C], v[C], d[C];
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                const bool in = k0 + q < k1;
+                u[q] = in ? U[(size_t)(k0 + q) * kHid + n] : 0.0f;
+                v[q] = in ? V[(size_t)(k0 + q) * kHid + n] : 0.0f;
+                d[q] = in && last ? nb.dy[k0 + q] : 0.0f;
+            }
+#pragma unroll
+            for (int q = 0; q < C; ++q) {
+                s1 = fmaf(u[q], last ? d[q] : 1.0f, s1);
+                s2 += v[q];
+                s3 += d[q];
+            }
+        }
+        float *red = &sm[0][0][0];
+        if (half) {
+            red[n] = s1;
+            red[128 + n] = s2;
+            if (n == 0) red[256] = s3;
+        }
+        __syncthreads();
+        if (!half) {
+            out[(last ? oW4 : ob1) + n] = s1 + red[n];
+            out[(last ? ob3 : ob2) + n] = s2 + red[128 + n];
+            if (last && n == 0) out[ob4] = s3 + red[256];
+        }
+        return;
+    }
+    const bool first = job >= 8;  // the first layer
+    const int q = job & 3;
+    const float *A = first ? X : job < 4 ? nb.H[1] : nb.H[0];
+    const float *B = first ? nb.dZ[0] : job < 4 ? nb.dZ[2] : nb.dZ[1];
+    const int lda = first ? kFeat : kHid, rows = first ? kFeat : kHid;
+    const int m0 = first ? 0 : 64 * (q >> 1), n0 = 64 * (first ? job - 8 : q & 1);
+    const int64_t o = first ? oW1 : job < 4 ? oW3 : oW2;
+    const int c = lane & 31, h = lane >> 5;
+    const int mt = first ? 0 : 32 * (wave >> 1), nt = 32 * (wave & 1);  // the wave's tile in the block's
+    floatx16_t acc{};
+    for (int k0 = ka; k0 < kb; k0 += kGradChunk) {
+        // 16 threads per sample row, 4 columns each
+        constexpr int R = kGradChunk / 16;
+        floatx4_t va[R], vb[R];
+        const int e = 4 * (tid & 15);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int k = k0 + (tid >> 4) + 16 * r;
+            const bool in = k < kb;
+            va[r] = floatx4_t{};
+            if (in && m0 + e < rows) {
+                const float *src = A + (size_t)k * lda + m0 + e;
+                if (!first) va[r] = *reinterpret_cast<const floatx4_t *>(src);
+                else  // the caller's array may lie at any float
+                    va[r] = floatx4_t{src[0], src[1], src[2], src[3]};
+            }
+            vb[r] = in ? *reinterpret_cast<const floatx4_t *>(B + (size_t)k * kHid + n0 + e) : floatx4_t{};
+        }
+        __syncthreads();  // the previous chunk's reads
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            *reinterpret_cast<floatx4_t *>(&sm[0][(tid >> 4) + 16 * r][e]) = va[r];
+            *reinterpret_cast<floatx4_t *>(&sm[1][(tid >> 4) + 16 * r][e]) = vb[r];
+        }
+        __syncthreads();
+        const int cnt = min(kGradChunk, kb - k0);
+        if (!first || wave < 2)
+            for (int k = 0; k < cnt; k += 2)
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sm[0][k + h][mt + c], sm[1][k + h][nt + c], acc, 0, 0, 0);
+    }
+    if (first && wave >= 2) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int m = m0 + mt + 8 * (r >> 2) + 4 * h + (r & 3);
+        if (m < rows) out[o + (int64_t)m * kHid + n0 + nt + c] = acc[r];
+    }
+}
+
+// Parameter i's gradient: the sum of its ns slices in order, into G, or with
+// ADAM applied (beta 0.9 / 0.999, bias correction c1, c2).  Block 0 also
+// takes the loss: the mean of the samples' squares from nl terms (double,
+// fixed order), to a device or a pinned host address.
+template <bool ADAM>
+__global__ __launch_bounds__(256) void kw_reduce(int ns, const float *__restrict__ part, float *__restrict__ G,
+                                                 float *__restrict__ p, float *__restrict__ mo, float *__restrict__ ve,
+                                                 float lr, float c1, float c2, int64_t nl, const double *lossp, int S,
+                                                 double *loss) {
+    __shared__ double red[256];
+    if (blockIdx.x == 0 && loss) {
+        double l = 0.0;
+        for (int64_t k = threadIdx.x; k < nl; k += 256) l += lossp[k];
+        red[threadIdx.x] = l;
+        __syncthreads();
+        for (int o = 128; o >= 1; o >>= 1) {
+            if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) *loss = red[0] / (double)S;
+    }
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= kParams) return;
+    float gi = 0.0f;
+#pragma unroll 8
+    for (int q = 0; q < ns; ++q) gi += part[(size_t)q * kParams + i];
+    if constexpr (ADAM) {
+        const float mi = 0.9f * mo[i] + 0.1f * gi;
+        const float vi = 0.999f * ve[i] + 0.001f * gi * gi;
+        mo[i] = mi;
+        ve[i] = vi;
+        p[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + 1e-8f);
+    } else {
+        G[i] = gi;
+    }
 }
 
 // w_i = (y_i - mean y) / N in double (one block, fixed order)
@@ -358,7 +511,6 @@ constexpr int64_t kBfW4 = kBfW3 + (int64_t)kHid * kHid;  // [128]
 constexpr int64_t kBfCount = kBfW4 + kHid;
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef unsigned short ushort8_t __attribute__((ext_vector_type(8)));
 
 // round to nearest even (the values are finite)
@@ -447,44 +599,49 @@ __global__ __launch_bounds__(256) void kw_infer_bf16(const float *P, const unsig
     if (half == 0 && s0 + row < S) y[s0 + row] = part + P[ob4];
 }
 
-template <bool TA, bool TB, int EPI>
-hipError_t gemm(hipStream_t s, int M, int N, int K, const float *A, int lda, const float *B, int ldb,
-                float *C, int ldc, const float *bias = nullptr, const float *mask = nullptr, int ldm = 0) {
-    (void)hipGetLastError();
-    dim3 grid((N + 63) / 64, (M + 63) / 64);
-    kw_gemm<TA, TB, EPI><<<grid, 256, 0, s>>>(M, N, K, A, lda, B, ldb, C, ldc, bias, mask, ldm);
-    return hipGetLastError();
+// Slices of the samples for the weight gradients: at most kSplitMax, a
+// multiple of 16 samples each.
+int grad_slice(int S) { return std::max(16, ((S + kSplitMax - 1) / kSplitMax + 15) & ~15); }
+
+// The activations of S samples in buf (act_floats(S) floats): six [S][128]
+// arrays, dy, the loss terms, the slices of the gradients.
+NetBufs net_bufs(float *buf, int S, float **part) {
+    NetBufs nb;
+    const size_t n = (size_t)S * kHid;
+    for (int k = 0; k < 3; ++k) {
+        nb.H[k] = buf + k * n;
+        nb.dZ[k] = buf + (3 + k) * n;
+    }
+    // doubles at an even offset of the (256-byte aligned) buffer
+    nb.lossp = reinterpret_cast<double *>(buf + 6 * n);
+    float *rest = buf + 6 * n + 2 * (size_t)((S + kTS - 1) / kTS);
+    nb.dy = rest;
+    *part = rest + S;
+    return nb;
 }
 
-// Splits of the samples for the weight gradients (at most kSplitMax).
-int grad_splits(int K) { return std::max(1, std::min(kSplitMax, (K + 127) / 128)); }
-
-// dW[M][N] = A^T B over K samples and, if db, db[N] = column sums of B
-// (part: kSplitMax (M N + N) floats of scratch).
-hipError_t weight_grad(hipStream_t s, int M, int N, int K, const float *A, int lda, const float *B,
-                       int ldb, float *dW, float *db, float *part) {
-    const int ns = grad_splits(K);
-    const int kslice = ((K + ns - 1) / ns + 15) & ~15;
-    float *bpart = part + (size_t)ns * M * N;
-    dim3 grid((N + 63) / 64, (M + 63) / 64, ns);
-    if (db) kw_gemm_tn_part<true><<<grid, 256, 0, s>>>(M, N, K, kslice, A, lda, B, ldb, part, bpart);
-    else kw_gemm_tn_part<false><<<grid, 256, 0, s>>>(M, N, K, kslice, A, lda, B, ldb, part, bpart);
-    kw_reduce_parts<<<(M * N + 255) / 256, 256, 0, s>>>(M * N, ns, part, dW);
-    if (db) kw_reduce_parts<<<(N + 255) / 256, 256, 0, s>>>(N, ns, bpart, db);
+// Forward, backward and the slices of the gradients.
+hipError_t gradients(hipStream_t s, const float *P, const float *X, const float *t, int S, const NetBufs &nb,
+                     float *part, int *ns) {
+    const int slice = grad_slice(S);
+    *ns = (S + slice - 1) / slice;
+    kw_net<true><<<(unsigned)((S + kTS - 1) / kTS), kNetThreads, 0, s>>>(P, X, t, S, nullptr, nb);
+    kw_grad<<<dim3(kGradJobs, (unsigned)*ns), 256, 0, s>>>(X, S, slice, nb, part);
     return hipGetLastError();
 }
 
 }  // namespace
 
-// Forward pass of S samples: H1, H2, H3 [S][128] and y [S].
-hipError_t forward(hipStream_t s, const float *P, const float *X, int S, float *H1, float *H2,
-                   float *H3, float *y) {
+// Floats of activations and gradient slices for S samples.
+int64_t act_floats(int64_t S) {
+    return S * (6 * kHid + 1) + 2 * ((S + kTS - 1) / kTS) + (int64_t)kSplitMax * kParams;
+}
+
+// y [S] of S samples.
+hipError_t forward(hipStream_t s, const float *P, const float *X, int S, float *y) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    hipError_t e;
-    if ((e = gemm<false, false, 2>(s, S, kHid, kFeat, X, kFeat, P + oW1, kHid, H1, kHid, P + ob1)) != hipSuccess) return e;
-    if ((e = gemm<false, false, 2>(s, S, kHid, kHid, H1, kHid, P + oW2, kHid, H2, kHid, P + ob2)) != hipSuccess) return e;
-    if ((e = gemm<false, false, 2>(s, S, kHid, kHid, H2, kHid, P + oW3, kHid, H3, kHid, P + ob3)) != hipSuccess) return e;
-    return gemm<false, false, 1>(s, S, 1, kHid, H3, kHid, P + oW4, 1, y, 1, P + ob4);
+    kw_net<false><<<(unsigned)((S + kTS - 1) / kTS), kNetThreads, 0, s>>>(P, X, nullptr, S, y, NetBufs{});
+    return hipGetLastError();
 }
 
 const int64_t kBf16Count = kBfCount;
@@ -502,25 +659,34 @@ hipError_t infer_bf16(hipStream_t s, const float *P, const unsigned short *Wb, c
     return hipGetLastError();
 }
 
-// Loss and gradient of the loss with respect to the flat parameters (into G).
-hipError_t backward(hipStream_t s, const float *P, const float *X, const float *t, int S, float *H1,
-                    float *H2, float *H3, float *y, float *dy, float *dA, float *dB, float *G,
-                    double *loss, float *part) {
+// Loss (if not null, written by the device: pinned or device memory) and its
+// gradient with respect to the flat parameters (into G).
+hipError_t backward(hipStream_t s, const float *P, const float *X, const float *t, int S, float *buf, float *G,
+                    double *loss) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    hipError_t e;
-    if ((e = forward(s, P, X, S, H1, H2, H3, y)) != hipSuccess) return e;
-    kw_loss<<<1, 1024, 0, s>>>(S, y, t, dy, loss);
-    // layer 4: dW4 = H3^T dy, db4 = sum dy, dH3 = dy W4^T * (H3 > 0)
-    if ((e = weight_grad(s, kHid, 1, S, H3, kHid, dy, 1, G + oW4, G + ob4, part)) != hipSuccess) return e;
-    if ((e = gemm<false, true, 3>(s, S, kHid, 1, dy, 1, P + oW4, 1, dA, kHid, nullptr, H3, kHid)) != hipSuccess) return e;
-    // layer 3
-    if ((e = weight_grad(s, kHid, kHid, S, H2, kHid, dA, kHid, G + oW3, G + ob3, part)) != hipSuccess) return e;
-    if ((e = gemm<false, true, 3>(s, S, kHid, kHid, dA, kHid, P + oW3, kHid, dB, kHid, nullptr, H2, kHid)) != hipSuccess) return e;
-    // layer 2
-    if ((e = weight_grad(s, kHid, kHid, S, H1, kHid, dB, kHid, G + oW2, G + ob2, part)) != hipSuccess) return e;
-    if ((e = gemm<false, true, 3>(s, S, kHid, kHid, dB, kHid, P + oW2, kHid, dA, kHid, nullptr, H1, kHid)) != hipSuccess) return e;
-    // layer 1
-    if ((e = weight_grad(s, kFeat, kHid, S, X, kFeat, dA, kHid, G + oW1, G + ob1, part)) != hipSuccess) return e;
+    float *part;
+    int ns;
+    const NetBufs nb = net_bufs(buf, S, &part);
+    const hipError_t e = gradients(s, P, X, t, S, nb, part, &ns);
+    if (e != hipSuccess) return e;
+    kw_reduce<false><<<(unsigned)((kParams + 255) / 256), 256, 0, s>>>(ns, part, G, nullptr, nullptr, nullptr, 0.0f,
+                                                                       1.0f, 1.0f, (S + kTS - 1) / kTS, nb.lossp, S, loss);
+    return hipGetLastError();
+}
+
+// The gradient and Adam's step number `step` on the parameters P and the
+// moments M, V.
+hipError_t train_step(hipStream_t s, float *P, float *M, float *V, const float *X, const float *t, int S, float *buf,
+                      float lr, int64_t step, double *loss) {
+    (void)hipGetLastError();  // clear a stale error left by an earlier call
+    float *part;
+    int ns;
+    const NetBufs nb = net_bufs(buf, S, &part);
+    const hipError_t e = gradients(s, P, X, t, S, nb, part, &ns);
+    if (e != hipSuccess) return e;
+    const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
+    kw_reduce<true><<<(unsigned)((kParams + 255) / 256), 256, 0, s>>>(ns, part, nullptr, P, M, V, lr, c1, c2,
+                                                                      (S + kTS - 1) / kTS, nb.lossp, S, loss);
     return hipGetLastError();
 }
 
@@ -536,13 +702,6 @@ hipError_t features(hipStream_t s, int n, const double *x, const double *A, cons
         double *out = tmp + (size_t)((h + 1) & 1) * n;
         kw_pool<<<nb1, 256, 0, s>>>(n, nb, in, out, F, 17 + h);
     }
-    return hipGetLastError();
-}
-
-hipError_t adam(hipStream_t s, float *P, const float *G, float *M, float *V, float lr, int64_t step) {
-    (void)hipGetLastError();  // clear a stale error left by an earlier call
-    const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
-    kw_adam<<<(unsigned)((kParams + 255) / 256), 256, 0, s>>>(kParams, P, G, M, V, lr, c1, c2);
     return hipGetLastError();
 }
 

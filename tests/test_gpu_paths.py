@@ -115,3 +115,35 @@ def test_moments_by_the_cells_of_a_tile(ctx, dim, grid, n):
             assert out["g"] == pytest.approx(ev.g, rel=1e-12, abs=1e-15)
     finally:
         ctx.apd_set_pixels_per_lane(0)
+
+
+@pytest.mark.parametrize("S_", [1, 15, 16, 17, 127, 129, 513, 4095, 4097])
+def test_network_by_the_number_of_samples(ctx, S_):
+    """Blocks of 16 samples, slices of the samples and chunks of 128, the
+    features at an address that is a multiple of 4 bytes only: output, loss,
+    gradient and one Adam step against the FP64 reference.  Every value passes
+    through at most four sums of 128 terms or of a slice of the samples, each
+    rounding 2^-24 of the sum of magnitudes: 2e-4 of the largest value."""
+    import torch
+    import paper_2403_03571_amd as apd
+    from oracle import mlp
+    rng = np.random.default_rng(S_)
+    p0 = (mlp.init_params(5) + 0.01 * rng.standard_normal(mlp.n_params())).astype(np.float32)
+    X = rng.standard_normal((S_, mlp.N_FEAT)).astype(np.float32)
+    t = rng.standard_normal(S_).astype(np.float32)
+    raw = torch.zeros(1 + X.size, dtype=torch.float32, device="cuda:0")
+    raw[1:] = torch.as_tensor(X.reshape(-1), device="cuda:0")
+    Xd, td = raw[1:].view(S_, mlp.N_FEAT), torch.as_tensor(t, device="cuda:0")
+    net = apd.WarmStart(ctx, p0)
+    P = p0.astype(np.float64)
+    yr, _ = mlp.forward(P, X.astype(np.float64))
+    assert np.abs(net.forward(Xd).cpu().numpy() - yr).max() <= 2e-4 * np.abs(yr).max()
+    loss, g = net.loss_grad(Xd, td)
+    lr_, gr = mlp.loss_and_grad(P, X.astype(np.float64), t.astype(np.float64))
+    assert loss == pytest.approx(lr_, rel=2e-4)
+    assert np.abs(g.cpu().numpy() - gr).max() <= 2e-4 * np.abs(gr).max()
+    # Adam's first step moves a parameter by lr g / (|g| + 1e-8 sqrt(1 - 0.999))
+    assert net.train_step(Xd, td, 1e-3) == loss
+    gd = g.cpu().numpy().astype(np.float64)
+    want = P - 1e-3 * gd / (np.abs(gd) + 1e-8)
+    assert np.abs(net.params() - want).max() <= 1e-6
