@@ -56,7 +56,8 @@ typedef enum {
  * C_ij = (y_j - x_i)^T A_i (y_j - x_i) - w_i: the faster tiers re-evaluate in
  * double every pixel whose top-two cost gap is within their rounding bound. */
 typedef enum {
-    APD_FP64 = 0, /* every pair in double precision */
+    APD_FP64 = 0, /* every cost in double precision (every pair with
+                     apd_set_culling off or when rel_gap is asked for) */
     APD_FP32 = 1, /* single precision + certified double re-check */
     APD_BF16 = 2, /* bf16 matrix cores (split hi/lo operands, fp32
                      accumulation) + certified double re-check */
@@ -375,12 +376,14 @@ apd_status apd_set_profiling(apd_ctx *ctx, int32_t on);
  * labels. */
 apd_status apd_set_variant(apd_ctx *ctx, int32_t variant);
 
-/* Per-tile candidate lists for the vector APD_FP32 kernel and the APD_BF16
- * kernel, single passes and the batched solver (1 = on, the default; 0 =
- * every seed at every pixel).  A seed is skipped in a tile when a lower
- * bound of its cost over the tile (smallest eigenvalue of A_i times the
- * squared distance to the tile, minus w_i) exceeds the smallest upper bound
- * of any seed's cost there; the labels are unchanged. */
+/* Per-tile candidate lists for the vector APD_FP32 kernel, the APD_BF16
+ * kernel (single passes and the batched solver) and the APD_FP64 kernel
+ * (1 = on, the default; 0 = every seed at every pixel).  A seed is skipped
+ * in a tile when its cost minus that of the seed of least cost at the tile's
+ * centre is positive all over the tile (a lower bound of that difference
+ * over the tile, widened for rounding; for passes that return rel_gap and for
+ * costs of another power, when a lower bound of its cost exceeds the
+ * smallest upper bound of any seed's); the labels are unchanged. */
 apd_status apd_set_culling(apd_ctx *ctx, int32_t on);
 
 /* Boundary-aware refinement (1 = on, the default; 0 = off), with the

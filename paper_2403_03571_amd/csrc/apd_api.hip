@@ -237,7 +237,8 @@ struct ListGeometry {
 
 ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, apd_precision prec) {
     ListGeometry L;
-    L.tp = prec == APD_BF16 ? apd::bf16_pixels_per_lane(g) : apd::vec_pixels_per_lane(g, true);
+    L.tp = prec == APD_BF16 ? apd::bf16_pixels_per_lane(g)
+           : prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true);
     const int ext[3] = {apd::tile_ext(p->dim, L.tp, 0), apd::tile_ext(p->dim, L.tp, 1),
                         apd::tile_ext(p->dim, L.tp, 2)};
     for (int d = 0; d < 3; ++d) L.ntile[d] = d < p->dim ? (g.grid[d] + ext[d] - 1) / ext[d] : 1;
@@ -251,6 +252,12 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, apd_precisio
         L.nsuper *= L.nst[d];
     }
     return L;
+}
+
+// Whether a pass runs over candidate lists.  The FP64 tier's relative gaps are
+// those of every pair (the runner-up may be a seed that no list holds).
+bool with_lists(const apd_ctx *c, apd_precision prec, bool rel_gap) {
+    return c->culling && ((prec == APD_FP32 && c->variant >= 1) || prec == APD_BF16 || (prec == APD_FP64 && !rel_gap));
 }
 
 // Enqueue one evaluation pass: prep, assignment (+ re-check), optional
@@ -279,7 +286,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     uint64_t *mom = moments ? b.mom : nullptr;
     if (prec != APD_FP64 && prec != APD_FP32 && prec != APD_BF16)
         return fail(c, APD_ERR_INVALID_ARG, "precision %d is not available", (int)prec);
-    const bool cull = c->culling && ((prec == APD_FP32 && c->variant >= 1) || prec == APD_BF16);
+    const bool cull = with_lists(c, prec, rel_gap != nullptr);
     const bool timing = c->profiling && !fixed;
     if (timing) HIP_TRY(c, hipEventRecord(c->ev[0], c->stream));
     HIP_TRY(c, apd::launch_prep(g, sd, b.sc, mom, cull ? b.eig : nullptr, b.parts, c->stream, w_host));
@@ -289,6 +296,52 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     out.rel_gap = rel_gap;
     if (g.power != 2 && prec != APD_FP64)
         return fail(c, APD_ERR_INVALID_ARG, "costs of power %d run in APD_FP64 only", g.power);
+    int tp = 0;  // pixels per lane of the lists' tiles
+    if (cull) {
+        const ListGeometry L = list_geometry(p, g, prec);
+        out.tp = tp = L.tp;
+        if (fixed) {
+            if (L.nsuper > b.cap_super)
+                return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
+        } else {
+            b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, p->n);
+            const size_t rec_bytes = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim) * sizeof(float4);
+            if (rec_bytes > c->super_bytes) {
+                (void)hipFree(c->super_lists);
+                c->super_lists = nullptr;
+                c->super_bytes = 0;
+                if (hipMalloc(&c->super_lists, rec_bytes) != hipSuccess)
+                    return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
+                                (long long)L.nsuper);
+                c->super_bytes = rec_bytes;
+            }
+            if (L.nsuper > c->cap_super) {
+                (void)hipFree(c->super_count);
+                c->super_count = nullptr;
+                c->cap_super = 0;
+                if (hipMalloc(&c->super_count, (size_t)L.nsuper * sizeof(int)) != hipSuccess)
+                    return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
+                                (long long)L.nsuper);
+                c->cap_super = L.nsuper;
+            }
+            b.super_lists = c->super_lists;
+            b.super_count = c->super_count;
+        }
+        out.adaptive = c->adaptive;
+        out.credited = &b.sc->credited;
+        for (int d = 0; d < 3; ++d) {
+            out.sf[d] = L.sf[d];
+            out.nst[d] = L.nst[d];
+        }
+        // up to a block's threads of seeds the tiles read them all at once
+        if (L.sf[0] * L.sf[1] * L.sf[2] > 1 && p->n > apd::kThreads) {
+            out.super_cap = b.super_cap;
+            HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, b.super_lists, b.super_count,
+                                              c->stream));
+            out.super_list = b.super_lists;
+            out.super_count = b.super_count;
+        }
+    }
     if (prec == APD_FP64) {
         if (g.power != 2 && finalize) {
             // the objective of such costs is summed pixel by pixel
@@ -305,7 +358,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
             }
             out.cost_part = fixed ? b.cost_part : c->cost_part;
         }
-        HIP_TRY(c, apd::launch_assign_fp64(g, sd, b.sc, out, c->stream));
+        HIP_TRY(c, apd::launch_assign_fp64(g, sd, b.sc, cull ? b.eig : nullptr, out, c->stream));
         if (timing) HIP_TRY(c, hipEventRecord(c->ev[2], c->stream));
         c->stats.kernel = APD_KERNEL_FP64;
         c->stats.pixels_per_lane = 0;
@@ -323,53 +376,10 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
             c->stats.kernel = APD_KERNEL_BF16_MATRIX;
             c->stats.pixels_per_lane = apd::bf16_pixels_per_lane(g);
         } else if (cull) {
-            const ListGeometry L = list_geometry(p, g, prec);
-            out.tp = L.tp;
-            if (fixed) {
-                if (L.nsuper > b.cap_super)
-                    return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
-            } else {
-                b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, p->n);
-                const size_t rec_bytes = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim) * sizeof(float4);
-                if (rec_bytes > c->super_bytes) {
-                    (void)hipFree(c->super_lists);
-                    c->super_lists = nullptr;
-                    c->super_bytes = 0;
-                    if (hipMalloc(&c->super_lists, rec_bytes) != hipSuccess)
-                        return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
-                                    (long long)L.nsuper);
-                    c->super_bytes = rec_bytes;
-                }
-                if (L.nsuper > c->cap_super) {
-                    (void)hipFree(c->super_count);
-                    c->super_count = nullptr;
-                    c->cap_super = 0;
-                    if (hipMalloc(&c->super_count, (size_t)L.nsuper * sizeof(int)) != hipSuccess)
-                        return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
-                                    (long long)L.nsuper);
-                    c->cap_super = L.nsuper;
-                }
-                b.super_lists = c->super_lists;
-                b.super_count = c->super_count;
-            }
-            out.adaptive = c->adaptive;
-            out.credited = &b.sc->credited;
-            for (int d = 0; d < 3; ++d) {
-                out.sf[d] = L.sf[d];
-                out.nst[d] = L.nst[d];
-            }
-            // up to a block's threads of seeds the tiles read them all at once
-            if (L.sf[0] * L.sf[1] * L.sf[2] > 1 && p->n > apd::kThreads) {
-                out.super_cap = b.super_cap;
-                HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, b.super_lists, b.super_count,
-                                                  c->stream));
-                out.super_list = b.super_lists;
-                out.super_count = b.super_count;
-            }
             if (prec == APD_BF16) HIP_TRY(c, apd::launch_assign_bf16(g, sd, b.sc, b.eig, out, c->stream));
             else HIP_TRY(c, apd::launch_assign_cull(g, sd, b.sc, b.eig, out, c->stream));
             c->stats.kernel = prec == APD_BF16 ? APD_KERNEL_BF16_LISTS : APD_KERNEL_FP32_LISTS;
-            c->stats.pixels_per_lane = L.tp;
+            c->stats.pixels_per_lane = tp;
         } else if (c->variant == 3 || (c->variant == 2 && hyb_by_default(p))) {
             HIP_TRY(c, apd::launch_seed_order(g, sd, b.ord, c->stream));
             out.seed_order = b.ord;
@@ -1366,7 +1376,7 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
     apd::Geo geo = make_geo(p);
     geo.vec_p = c->vec_p;
     const int64_t n = p->n, J = num_pixels(p);
-    const bool cull = c->culling && ((prec == APD_FP32 && c->variant >= 1) || prec == APD_BF16);
+    const bool cull = with_lists(c, prec, false);
     Carve k{base};
     PassBufs b;
     b.sc = k.take<apd::Scalars>(1);
@@ -1379,7 +1389,7 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         b.cap_parts = apd::fp64_blocks(geo);
         b.cost_part = k.take<double>((size_t)b.cap_parts);
     }
-    if (cull) {
+    if (cull && prec != APD_FP64) {
         // the call's documented limit counts a list of kStaticListCap seeds,
         // its length and bound and a queue segment for every tile (of 4 pixels
         // per lane unless set) and kStaticSuperCap seeds for every super-tile
@@ -1408,7 +1418,8 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         b.cap_super = nsuper;
         b.super_count = in.take<int>((size_t)nsuper);
         b.super_lists = in.take<float4>(0);
-        const size_t room = (size_t)(base + k.off - reinterpret_cast<unsigned char *>(b.super_lists));
+        const unsigned char *end = b.cost_part ? reinterpret_cast<unsigned char *>(b.cost_part) : base + k.off;
+        const size_t room = (size_t)(end - reinterpret_cast<unsigned char *>(b.super_lists));
         b.super_cap = (int)std::min<size_t>({(size_t)kStaticSuperCap, (size_t)n,
                                              room / ((size_t)nsuper * apd::rec_vec(p->dim) * sizeof(float4))});
     }

@@ -43,6 +43,7 @@ struct BState {
     float lam;        // Gershgorin bound of every A_i (Cert::lam)
     float kap;        // condition bound of every A_i (Cert::kap)
     float sab;        // absolute slack of the double costs at the trial point (Cert::sab)
+    float lsl;        // slack of the candidate lists there (Cert::lsl)
     int phase;        // 0: first evaluation pending, 1: line search
     int npairs, head, t;
     int iters, evals;

@@ -176,7 +176,9 @@ __global__ __launch_bounds__(kThreads) void kb_prep(BInst *inst, BState *st, BCt
     wm = block_max(wm, red);
     if (threadIdx.x == 0) {
         st[b].wmax = wm;
-        st[b].sab = dslack_abs(I.g, wm, st[b].lam);
+        const float sab = dslack_abs(I.g, wm, st[b].lam);
+        st[b].sab = sab;
+        st[b].lsl = list_slack(I.g, sab, st[b].lam);
     }
 }
 
@@ -229,7 +231,7 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
         out.sf[d] = I.sf[d];
         out.nst[d] = I.nst[d];
     }
-    super_tile_list<D, kThreads>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, out, local,
+    super_tile_list<D, kThreads>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, out, local,
                                  I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D),
                                  I.super_count + local, kBatchSuperCap, sm);
 }
@@ -289,7 +291,7 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
             b2 = r % I.tiles2;
         }
         if (V == 0) {
-            mfma_tile<D>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, b0, b1, b2, sC, out, &ctl->qcount);
+            mfma_tile<D>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, b0, b1, b2, sC, out, &ctl->qcount);
         } else {
             if (kLists) {
                 out.tp = I.tp;
@@ -305,10 +307,10 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                 }
             }
             if constexpr (V == 3 || V == 5)
-                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, b0, b1, b2,
+                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, b0, b1, b2,
                                                               sm.bf, out, kLists ? nullptr : &ctl->qcount);
             else
-                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab}, I.eig, b0, b1, b2,
+                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, b0, b1, b2,
                                                        sm.vec, out, kLists ? nullptr : &ctl->qcount);
         }
     }

@@ -101,6 +101,13 @@ __device__ inline double centre(const Geo &g, int d, int k) {
     return g.lo[d] + ((double)k + 0.5) * g.s[d];
 }
 
+// |y - x|_A^power from the squared norm q, clamped at 0 for power != 2.
+__device__ inline double power_of_norm(double q, int power) {
+    if (power == 2) return q;
+    const double qc = q > 0.0 ? q : 0.0;
+    return power == 1 ? sqrt(qc) : power == 3 ? qc * sqrt(qc) : qc * qc;
+}
+
 // C_ij = (y - x_i)^T A_i (y - x_i) - w_i in the definition's order: d = y - x,
 // each row of A d summed left to right, then sum_r d_r (A d)_r left to right.
 // For power p != 2 the cost is |y - x_i|_{A_i}^p - w_i, from the squared
@@ -125,11 +132,7 @@ __device__ inline double exact_cost(const double *__restrict__ x, const double *
         const double t = d[r] * row;
         q = (r == 0) ? t : q + t;
     }
-    if (power != 2) {
-        const double qc = q > 0.0 ? q : 0.0;
-        q = power == 1 ? sqrt(qc) : power == 3 ? qc * sqrt(qc) : qc * qc;
-    }
-    return q - w[i];
+    return power_of_norm(q, power) - w[i];
 }
 
 // The expanded cost of seed i about a tile anchor, for the single-precision
@@ -470,6 +473,21 @@ __device__ inline float dslack_abs(const Geo &g, double wmax, float lam) {
         y2 += y * y;
     }
     return (float)(0x1p-44 * (fabs(wmax) + (double)lam * y2));
+}
+// Slack of the owner-difference lists besides each seed's own: twice the
+// double costs', plus 2^-20 of a pixel's scale lam s^2, above what underflow in
+// FP32 can take from the terms.  Infinite (no lists) where the pixels' or the
+// box's scale leaves the range in which that holds; the FP64 tier takes
+// problems of any scale.
+__device__ inline float list_slack(const Geo &g, float sab, float lam) {
+    double smin = INFINITY, ext = 0.0;
+    for (int d = 0; d < g.dim; ++d) {
+        smin = fmin(smin, g.s[d]);
+        ext = fmax(ext, g.s[d] * (double)g.grid[d]);
+    }
+    const double px = (double)lam * smin * smin, bx = (double)lam * ext * ext;
+    const bool in = px >= 1e-31 && bx <= 1e31 && lam >= 1e-18f && lam <= 1e18f && smin >= 1e-18 && ext <= 1e18;
+    return in ? 2.0f * sab + 0x1p-20f * (float)px : INFINITY;
 }
 __device__ inline float kslack(Cert ct) { return 0x1p-44f * (ct.kap + 1.0f); }
 
@@ -1100,9 +1118,15 @@ __device__ inline void quad_box_range2(T a00, T a01x2, T a11, T p0, T P0, T p1, 
 // covers the rounding of either form: the absolute values of the form's
 // terms sum to at most D lambda_max maxdist^2 (|2 a_rc d_r d_c| <=
 // a_rr d_r^2 + a_cc d_c^2 for positive definite A).
+//
+// For costs of another power the range of the squared norm is taken to that
+// power (both grow with it).  There the rounding of the double norm counts as
+// its square root when the norm is near zero, sqrt(12 2^-53) sqrt(D lambda_max)
+// maxdist < 1e-7 h for power 1 (less for 3 and 4): the slack is 1e-6 (h + |w'|),
+// and that of an offset of the weights.
 template <int D, bool EXACT = true>
 __device__ inline void cull_bounds(const Seeds &sd, const double *eig, double wmax, const double *blo,
-                                   const double *bhi, int i, double *lb, double *ub) {
+                                   const double *bhi, int i, double *lb, double *ub, int power = 2) {
     double dist2 = 0.0, far2 = 0.0;
     for (int d = 0; d < D; ++d) {
         const double xd = sd.x[(size_t)i * D + d];
@@ -1120,6 +1144,14 @@ __device__ inline void cull_bounds(const Seeds &sd, const double *eig, double wm
         quad_box_range2<double>(a[0], 2.0 * a[1], a[3], blo[0] - x0, bhi[0] - x0, blo[1] - x1, bhi[1] - x1,
                                 &l, &h);
     }
+    if (power != 2) {
+        l = power_of_norm(l, power);
+        h = power_of_norm(h, power);
+        const double sp = 1e-6 * (h + fabs(wp)) + 0x1p-44 * fabs(wmax);
+        *lb = l - wp - sp;
+        *ub = h - wp + sp;
+        return;
+    }
     *lb = l - wp - slack;
     *ub = h - wp + slack;
 }
@@ -1134,12 +1166,12 @@ template <int D, class Id>
 __device__ inline int build_candidates(const Seeds &sd, const double *eig, double wmax,
                                        const double *blo, const double *bhi, Id id,
                                        int nsrc, int *dst, int cap, int &s_cnt, double *s_red,
-                                       double *Uout) {
+                                       double *Uout, int power = 2) {
     const int lane = __lane_id();
     double umin = INFINITY;
     for (int q = threadIdx.x; q < nsrc; q += kThreads) {
         double lb, ub;
-        cull_bounds<D, true>(sd, eig, wmax, blo, bhi, id(q), &lb, &ub);
+        cull_bounds<D, true>(sd, eig, wmax, blo, bhi, id(q), &lb, &ub, power);
         umin = fmin(umin, ub);
     }
     umin = wave_min(umin);
@@ -1165,7 +1197,7 @@ __device__ inline int build_candidates(const Seeds &sd, const double *eig, doubl
         if (q < nsrc) {
             i = id(q);
             double lb, ub;
-            cull_bounds<D, true>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            cull_bounds<D, true>(sd, eig, wmax, blo, bhi, i, &lb, &ub, power);
             cand = lb <= U;
         }
         emit(cand, i);
@@ -1446,8 +1478,8 @@ struct SuperSmem {
 // (above cap: every seed).  Every seed is tested with the eigenvalue bounds
 //   lambda_min dist(x, box)^2 - w' <= U = min_k lambda_max maxdist(x_k, box)^2 - w_k',
 // then, unless the pass returns the relative gaps (whose tiles need lists
-// that bound the cost of every seed left out), the survivors by the owner's
-// difference.  A seed that cannot win anywhere in the super-tile cannot win
+// that bound the cost of every seed left out) or its costs are of another
+// power, the survivors by the owner's difference.  A seed that cannot win anywhere in the super-tile cannot win
 // in any of its tiles.  All T threads of the block call it.  A
 // thread takes the seeds four at a time, so that their loads are in flight
 // together.
@@ -1462,6 +1494,10 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
     double blo[3], bhi[3];
     super_box<D>(g, out, c, blo, bhi);
     const int lane = __lane_id();
+    if (ct.lsl == INFINITY) {
+        if (threadIdx.x == 0) *count = cap + 1;
+        return;
+    }
     constexpr int kUnroll = 4;
     constexpr int kKeep = 12;  // a thread's lower bounds kept in registers
     const bool in_regs = g.n <= kKeep * T;
@@ -1474,7 +1510,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
             lbr[r] = INFINITY;
             if (r * T < g.n && i < g.n) {
                 double lb, ub;
-                cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+                cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
                 lbr[r] = __double2float_rd(lb);
                 umin = fmin(umin, ub);
             }
@@ -1483,7 +1519,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
 #pragma unroll kUnroll
         for (int i = threadIdx.x; i < g.n; i += T) {
             double lb, ub;
-            cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
             umin = fmin(umin, ub);
         }
     }
@@ -1512,7 +1548,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         for (int i0 = 0; i0 < g.n; i0 += T) {
             const int i = i0 + threadIdx.x;
             double lb = INFINITY, ub;
-            if (i < g.n) cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub);
+            if (i < g.n) cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
             append(i < g.n && lb <= U, i);
         }
     }
@@ -1526,14 +1562,14 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
     float h[D];
     const float hh = box_centre<D>(blo, bhi, ctr, h);
     int n;
-    if (out.rel_gap) {
+    if (out.rel_gap || g.power != 2) {
         for (int q = threadIdx.x; q < min(m, cap); q += T)
             store_rec<D>(list, cap, q, seed_rec<D>(sd, wmax, ctr, sm.list[q]), sm.list[q]);
         n = m;
     } else {
         n = owner_filter<D, T>(
             m, [&](int q) { return seed_rec<D>(sd, wmax, ctr, sm.list[q]); }, h, hh, ct.lam,
-            2.0f * ct.sab, sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
+            ct.lsl, sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
                 if (pos < cap) store_rec<D>(list, cap, pos, r, sm.list[q]);
             });
     }
@@ -1561,11 +1597,14 @@ constexpr int kGroupScan = 96;   // scans at least this long use group minima
 constexpr int kWaveCap = 256;    // per-wave candidate positions
 
 // The candidate list of a tile's box, from its super-tile's list when it has
-// one (else from every seed): into s_list, at most kCullCap seeds; returns
-// their number.  GAP: *U bounds the cost of every seed left out.
-template <int D, int P, bool GAP, class Smem>
+// one (else from every seed): into sm.list, at most kCullCap seeds; returns
+// their number.  BOUNDS: by separate bounds of each seed's cost (a pass that
+// returns the relative gaps, costs of another power); *U then bounds the cost
+// of every seed left out.
+template <int D, int P, bool BOUNDS, class Smem>
 __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
                                       const PassOut &out, int b0, int b1, int b2, Smem &sm, double *U) {
+    if (ct.lsl == INFINITY) return kCullCap + 1;
     int *dst = sm.list;
     auto tile_box = [&](double *blo, double *bhi) {
         const int ext[3] = {tile_ext(D, P, 0), tile_ext(D, P, 1), tile_ext(D, P, 2)};
@@ -1583,15 +1622,15 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
             nsrc = c;
         }
     }
-    if constexpr (GAP) {
+    if constexpr (BOUNDS) {
         double blo[3], bhi[3];
         tile_box(blo, bhi);
         return build_candidates<D>(sd, eig, wmax, blo, bhi,
                                    [&](int q) { return src ? __float_as_int(src[q].w) : q; }, nsrc, dst, kCullCap,
-                                   sm.cnt, sm.red, U);
+                                   sm.cnt, sm.red, U, g.power);
     } else {
         float h[D], hh = 0.0f, shift[3] = {0.0f, 0.0f, 0.0f};
-        const float slack = 2.0f * ct.sab;
+        const float slack = ct.lsl;
         if (src) {
             // the boxes' centres differ by a multiple of half a pixel
             const int tb[3] = {b0, b1, b2};
@@ -2008,7 +2047,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                 r.s = 0x1p-16f * (fabsf(r.c) + 2.0f * r2t);
                 return r;
             };
-            const float sl = 2.0f * ct.sab;
+            const float sl = ct.lsl;
             // the owner: the wave's candidate of least cost at its centre
             float best = INFINITY;
             int bq = 0;
@@ -3112,7 +3151,7 @@ __device__ inline void stage_seed(StagedSeeds<D, S> &sm, const Seeds &sd, int q,
 // The double cost of the staged seed at position q at y, in the expression
 // order of exact_cost (the same roundings, so the same value).
 template <int D, int S>
-__device__ inline double staged_cost(const StagedSeeds<D, S> &sm, int q, const double *y) {
+__device__ inline double staged_cost(const StagedSeeds<D, S> &sm, int q, const double *y, int power = 2) {
     double dd[D];
 #pragma unroll
     for (int e = 0; e < D; ++e) dd[e] = y[e] - sm.x[e][q];
@@ -3130,7 +3169,124 @@ __device__ inline double staged_cost(const StagedSeeds<D, S> &sm, int q, const d
         const double t = dd[e] * row;
         qf = (e == 0) ? t : qf + t;
     }
-    return qf - sm.w[q];
+    return power_of_norm(qf, power) - sm.w[q];
+}
+
+// ------------------------------------------------------- the FP64 tile
+
+// LDS of the FP64 tile.
+template <int D, bool CULL>
+struct Fp64Smem {
+    static constexpr int kChunk = 128;  // seeds staged at a time
+    StagedSeeds<D, kChunk> seeds;
+    int list[CULL ? kCullCap : 1];  // candidate seeds of the tile
+    MomSmem<CULL ? kP : 1> mom[CULL ? 1 : 0];
+    CellQuad<D> own[kWaves];
+    double red[kWaves];
+    double part[kWaves];
+    int cnt;
+};
+
+// Every cost in double precision, in the order of the definition: a lane's kP
+// pixels against the tile's candidate seeds (CULL) or every seed, staged in
+// LDS.  The kernel over every seed, one at a time through scalar loads, took
+// 190 us on 512^2 pixels with 500 seeds; with the lists 15 us (over every seed,
+// staged, 145).  For costs
+// other than the squared norm the block also sums its pixels' least costs,
+// weighted by the pixel weights, in a fixed order (per lane, a butterfly in
+// the wave, the waves in order) into *cost_part.
+template <int D, bool CULL>
+__device__ inline void fp64_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig, int b0,
+                                 int b1, int b2, Fp64Smem<D, CULL> &sm, const PassOut &out, double *cost_part) {
+    constexpr int C = Fp64Smem<D, CULL>::kChunk;
+    const Tile<D> t = tile_at<D>(b0, b1, b2);
+    const bool lane_ok = lane_in_grid<D>(g, t);
+    int nscan = g.n;
+    bool full = true;
+    if constexpr (CULL) {
+        double U;
+        const int ncand = g.power != 2 ? tile_candidates<D, kP, true>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &U)
+                                       : tile_candidates<D, kP, false>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &U);
+        full = ncand > kCullCap;
+        nscan = full ? g.n : ncand;
+        if (out.adaptive && ncand == 1 && !g.mass && !cost_part) {
+            credit_tile<D, kP>(g, t, b0, b1, b2, sm.list[0], out);
+            return;
+        }
+    }
+    bool act[kP], flag[kP];
+    double y[kP][D];
+#pragma unroll
+    for (int p = 0; p < kP; ++p) {
+        act[p] = lane_ok && (t.k0w + p) < g.grid[0];
+        flag[p] = false;
+        y[p][0] = centre(g, 0, t.k0w + p);
+        for (int d = 1; d < D; ++d) y[p][d] = centre(g, d, t.k[d]);
+    }
+    double best[kP], second[kP];
+    int pos[kP];
+#pragma unroll
+    for (int p = 0; p < kP; ++p) {
+        best[p] = INFINITY;
+        second[p] = INFINITY;
+        pos[p] = 0;
+    }
+    for (int c0 = 0; c0 < nscan; c0 += C) {
+        const int cnt = min(C, nscan - c0);
+        __syncthreads();
+        if ((int)threadIdx.x < cnt)
+            stage_seed<D, C>(sm.seeds, sd, threadIdx.x, full ? c0 + (int)threadIdx.x : sm.list[c0 + threadIdx.x]);
+        if constexpr (CULL)
+            if (c0 == 0 && out.mom) moments_zero(sm.mom[0], min(nscan, kAccSlots));
+        __syncthreads();
+#pragma unroll 2
+        for (int q = 0; q < cnt; ++q) {
+#pragma unroll
+            for (int p = 0; p < kP; ++p) {
+                const double c = staged_cost<D, C>(sm.seeds, q, y[p], g.power);
+                // equal costs go to the lowest seed: a scan over every seed
+                // meets it first, a list may hold it later
+                bool better = c < best[p];
+                if (CULL && !full && c == best[p]) better = sm.list[c0 + q] < sm.list[pos[p]];
+                if (!CULL && out.rel_gap) second[p] = better ? best[p] : fmin(second[p], c);
+                best[p] = better ? c : best[p];
+                pos[p] = better ? c0 + q : pos[p];
+            }
+        }
+    }
+    int lab[kP];
+#pragma unroll
+    for (int p = 0; p < kP; ++p) {
+        lab[p] = full ? pos[p] : nscan > 0 ? sm.list[pos[p]] : 0;
+        if (!CULL && out.rel_gap && act[p])
+            out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = gap_exact(best[p], second[p], wmax);
+    }
+    if (cost_part) {
+        double sp = 0.0;
+#pragma unroll
+        for (int p = 0; p < kP; ++p)
+            if (act[p]) sp += (double)pixel_weight(g, pixel_index<D>(g, t.k0w + p, t)) * best[p];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) sp += __shfl_xor(sp, o);
+        if (t.lane == 0) sm.part[threadIdx.x >> 6] = sp;
+        __syncthreads();
+        if (threadIdx.x == 0) *cost_part = (sm.part[0] + sm.part[1]) + (sm.part[2] + sm.part[3]);
+    }
+    if constexpr (CULL) {
+        if (nscan > 0 && nscan <= kAccSlots && !full && !g.mass) {
+            if (out.labels) write_labels<D, kP>(g, t, act, lab, flag, out);
+            if (out.mom) {
+                int idx[kP];
+#pragma unroll
+                for (int p = 0; p < kP; ++p) idx[p] = act[p] ? pos[p] : 127;
+                moments_add<D, kP>(sm.mom[0], t.lane, idx, nscan, [](int j) { return j; });
+                __syncthreads();
+                moments_flush<D, kP>(sm.mom[0], t.anc, sm.list, nscan, out.mom);
+            }
+            return;
+        }
+    }
+    tile_epilogue<D>(g, t, act, lab, flag, out, nullptr);
 }
 
 // Grid index k and centre y of pixel j (eq. (2.6)).

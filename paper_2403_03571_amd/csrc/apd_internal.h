@@ -71,6 +71,7 @@ struct Scalars {
     float lam;        // upper bound of max_i lambda_max(A_i) (Gershgorin)
     float kap;        // upper bound of max_i lambda_G(A_i) / lambda_min(A_i)
     float sab;        // absolute slack of the double costs (dslack_abs)
+    float lsl;        // slack of the candidate lists (list_slack)
     int bad;          // validation bits
     unsigned long long qtotal;  // sum of the pixel weights (validation)
     unsigned seq;     // host copy only: the finalize's count of published passes
@@ -117,6 +118,7 @@ struct Cert {
     float lam;
     float kap;
     float sab;  // absolute slack of the double costs (dslack_abs)
+    float lsl;  // slack of the candidate lists (list_slack); infinite: no lists
 };
 
 // Upper bound of lambda_G(A) / lambda_min(A) for a symmetric positive
@@ -193,7 +195,9 @@ hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, c
                              const PassOut &out, float4 *list, int *count, hipStream_t st);
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
-hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc,
+// The FP64 pass over every seed (eig null) or over the tiles' candidate lists
+// (eig from the prep kernel, tiles of kP pixels per lane).
+hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
 // Blocks of the FP64 assignment kernel (the entries of PassOut::cost_part).
 int64_t fp64_blocks(const Geo &g);

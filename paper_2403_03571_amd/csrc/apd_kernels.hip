@@ -187,6 +187,7 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
         sc->lam = s_l[0] * 1.0001f;
         sc->kap = s_k[0] * 1.0001f;
         sc->sab = dslack_abs(g, s_w[0], s_l[0] * 1.0001f);
+        sc->lsl = list_slack(g, sc->sab, s_l[0] * 1.0001f);
         sc->bad = s_b[0];
         sc->qcount = 0u;
         sc->credited = 0u;
@@ -244,68 +245,18 @@ inline int red_blocks(int n) {
 
 // ------------------------------------------------------ k_assign_fp64
 
-// For costs other than the squared norm the block also sums its pixels'
-// least costs, weighted by the pixel weights, in a fixed order (per lane,
-// a butterfly in the wave, the waves in order) into out.cost_part.
-template <int D>
-__global__ __launch_bounds__(kThreads) void k_assign_fp64(Geo g, Seeds sd, const Scalars *sc,
+// One block per tile (dev::fp64_tile): the tile's candidate seeds or every
+// seed.
+template <int D, bool CULL>
+__global__ __launch_bounds__(kThreads) void k_assign_fp64(Geo g, Seeds sd, const Scalars *sc, const double *eig,
                                                          PassOut out) {
-    const Tile<D> t = tile_of<D>(g);
-    const bool lane_ok = lane_in_grid<D>(g, t);
-    bool act[kP];
-    double y[kP][D];
-#pragma unroll
-    for (int p = 0; p < kP; ++p) {
-        act[p] = lane_ok && (t.k0w + p) < g.grid[0];
-        y[p][0] = centre(g, 0, t.k0w + p);
-        for (int d = 1; d < D; ++d) y[p][d] = centre(g, d, t.k[d]);
-    }
-    double best[kP], second[kP];
-    int lab[kP];
-#pragma unroll
-    for (int p = 0; p < kP; ++p) {
-        best[p] = INFINITY;
-        second[p] = INFINITY;
-        lab[p] = 0;
-    }
-    for (int i = 0; i < g.n; ++i) {
-#pragma unroll
-        for (int p = 0; p < kP; ++p) {
-            const double c = exact_cost<D>(sd.x, sd.A, sd.w, i, y[p], g.power);
-            if (c < best[p]) {
-                second[p] = best[p];
-                best[p] = c;
-                lab[p] = i;
-            } else {
-                second[p] = fmin(second[p], c);
-            }
-        }
-    }
-    bool flag[kP];
-#pragma unroll
-    for (int p = 0; p < kP; ++p) {
-        flag[p] = false;
-        if (out.rel_gap && act[p])
-            out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = gap_exact(best[p], second[p], sc->wmax);
-    }
-    if (out.cost_part) {
-        __shared__ double s_part[kWaves];
-        double sp = 0.0;
-#pragma unroll
-        for (int p = 0; p < kP; ++p)
-            if (act[p]) sp += (double)pixel_weight(g, pixel_index<D>(g, t.k0w + p, t)) * best[p];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) sp += __shfl_xor(sp, o);
-        if (t.lane == 0) s_part[threadIdx.x >> 6] = sp;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            const size_t b = ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-            out.cost_part[b] = (s_part[0] + s_part[1]) + (s_part[2] + s_part[3]);
-        }
-    }
-    PassOut o = out;
-    o.queue = nullptr;
-    tile_epilogue<D>(g, t, act, lab, flag, o, nullptr);
+    __shared__ Fp64Smem<D, CULL> sm;
+    const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
+    const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
+    const int b2 = D == 2 ? 0 : blockIdx.x;
+    double *part = nullptr;
+    if (out.cost_part) part = out.cost_part + ((size_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    fp64_tile<D, CULL>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, b0, b1, b2, sm, out, part);
 }
 
 // ------------------------------------------------ k_assign_fp32 / _cull
@@ -317,10 +268,10 @@ __global__ __launch_bounds__(kThreads, (CULL && P == 4 && !GAP) ? 5 : 4) void k_
                                                         const double *eig, PassOut out) {
     __shared__ VecSmem<D, CULL, P, GAP> sm;
     if constexpr (D == 2)
-        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
+        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
                              &sc->qcount);
     else
-        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
+        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
                              out, &sc->qcount);
 }
 
@@ -335,9 +286,9 @@ __global__ __launch_bounds__(kThreads) void k_assign_mfma(Geo g, Seeds sd, Scala
                                                          PassOut out) {
     __shared__ __attribute__((aligned(16))) float sC[kMfmaLds];
     if (D == 2)
-        dev::mfma_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.y, blockIdx.x, 0, sC, out, &sc->qcount);
+        dev::mfma_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, blockIdx.y, blockIdx.x, 0, sC, out, &sc->qcount);
     else
-        dev::mfma_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.z, blockIdx.y, blockIdx.x, sC, out,
+        dev::mfma_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, blockIdx.z, blockIdx.y, blockIdx.x, sC, out,
                           &sc->qcount);
 }
 
@@ -422,10 +373,10 @@ __global__ __launch_bounds__(kThreads, D == 3 ? 3 : 4) void k_assign_hyb(Geo g, 
                                                                           PassOut out) {
     __shared__ __attribute__((aligned(16))) HybSmem<D> sm;
     if constexpr (D == 3)
-        hyb_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.z, blockIdx.y, blockIdx.x, sm, out,
+        hyb_tile<3>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, blockIdx.z, blockIdx.y, blockIdx.x, sm, out,
                     &sc->qcount);
     else
-        hyb_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
+        hyb_tile<2>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
 }
 
 // ------------------------------------------------------ k_assign_bf16
@@ -440,7 +391,7 @@ __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scala
     const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
     const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
     const int b2 = D == 2 ? 0 : blockIdx.x;
-    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, b0, b1, b2, sm, out, &sc->qcount);
+    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, b0, b1, b2, sm, out, &sc->qcount);
 }
 
 // --------------------------------------------------------- k_super_cull
@@ -451,7 +402,7 @@ __global__ __launch_bounds__(T) void k_super_cull(Geo g, Seeds sd, const Scalars
                                                   float4 *list, int *count) {
     __shared__ SuperSmem<D, T> sm;
     const int st = blockIdx.x;
-    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab}, eig, out, st,
+    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, out, st,
                           list + (size_t)st * (size_t)out.super_cap * rec_vec(D), count + st, out.super_cap, sm);
 }
 
@@ -653,11 +604,16 @@ int64_t fp64_blocks(const Geo &g) {
     return (int64_t)b.x * b.y * b.z;
 }
 
-hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out,
+hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig, const PassOut &out,
                               hipStream_t st) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    if (g.dim == 2) k_assign_fp64<2><<<tile_grid<2>(g), kThreads, 0, st>>>(g, sd, sc, out);
-    else k_assign_fp64<3><<<tile_grid<3>(g), kThreads, 0, st>>>(g, sd, sc, out);
+    if (g.dim == 2) {
+        if (eig) k_assign_fp64<2, true><<<tile_grid<2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        else k_assign_fp64<2, false><<<tile_grid<2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    } else {
+        if (eig) k_assign_fp64<3, true><<<tile_grid<3>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        else k_assign_fp64<3, false><<<tile_grid<3>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    }
     if (out.cost_part) k_sum_parts<<<1, 256, 0, st>>>(out.cost_part, fp64_blocks(g), sc);
     return hipGetLastError();
 }

@@ -147,3 +147,41 @@ def test_network_by_the_number_of_samples(ctx, S_):
     gd = g.cpu().numpy().astype(np.float64)
     want = P - 1e-3 * gd / (np.abs(gd) + 1e-8)
     assert np.abs(net.params() - want).max() <= 1e-6
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (90, 70)), (3, (21, 18, 25))])
+@pytest.mark.parametrize("power", [1, 2, 3, 4])
+@pytest.mark.parametrize("n", [5, 70, 300, 3000])
+def test_fp64_lists(ctx, dim, grid, power, n):
+    """The double tier over candidate lists against the oracle and against
+    itself over every seed: all powers, pixel weights, exact ties, and a box whose
+    scale is outside single precision's range (lists off there)."""
+    import torch
+    for scale in (1.0, 1e-20):
+        inst = S.custom(dim, n, grid, seed=n + power, sigma=0.3, lo=(0.0,) * dim, hi=(scale,) * dim)
+        inst.power = power
+        inst.x[1], inst.A[1] = inst.x[0], inst.A[0]
+        r = 0.5 * scale * n ** (-1.0 / dim)
+        w = np.random.default_rng(n).uniform(-0.3, 0.3, n) * r ** power
+        w[1] = w[0]
+        masked = S.masked(inst, S.disk_weights(grid, inst.lo, inst.hi, (0.5 * scale,) * dim, 0.45 * scale))
+        masked.power = power
+        wd = torch.as_tensor(w, device="cuda:0")
+        for case in (inst, masked):
+            prob = _prob(case)
+            ref, _, _ = O.assign(case, w)
+            outs = []
+            for culling in (True, False):
+                ctx.apd_set_culling(culling)
+                try:
+                    np.testing.assert_array_equal(ctx.apd_assign(prob, wd, prec="fp64").cpu().numpy(), ref)
+                    outs.append(ctx.apd_dual_objective_grad(prob, wd, prec="fp64", counts=True, centroids=True))
+                finally:
+                    ctx.apd_set_culling(True)
+            outs.append(ctx.apd_dual_objective_grad(prob, wd, prec="fp64", counts=True, centroids=True, noalloc=True))
+            ev = O.evaluate(case, w)
+            for out in outs:
+                assert out["g"] == outs[0]["g"] and out["maxrel"] == outs[0]["maxrel"]
+                assert out["g"] == pytest.approx(ev.g, rel=1e-12, abs=1e-15 * scale ** (power + dim))
+                np.testing.assert_array_equal(out["counts"].cpu().numpy(), ev.counts)
+                np.testing.assert_array_equal(out["grad"].cpu().numpy(), ev.grad)
