@@ -45,86 +45,194 @@ namespace {
 
 // ------------------------------------------------------------- features
 
-// One wave per seed.  The 16 nearest seeds are found in 16 rounds: each
-// round every lane scans its share of the seeds for the smallest
-// (distance^2, index) pair above the previous round's, and a wave minimum
-// picks the next neighbour (ties go to the lower index).
+// (distance, index) order: the nearer seed, the lower index on equal ones.
+__device__ inline bool nearer(double d, int j, double e, int k) { return d < e || (d == e && j < k); }
+
+// The wave's least (d, j), in every lane: DPP steps within the rows of 16
+// lanes (rotations by 8 and 4, then within quads), then the rows' results.
+template <int CTRL>
+__device__ inline void nearest_step(double &d, int &j) {
+    const long long b = __double_as_longlong(d);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+    const int oj = __builtin_amdgcn_update_dpp(0, j, CTRL, 0xF, 0xF, false);
+    const double od = __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+    if (nearer(od, oj, d, j)) {
+        d = od;
+        j = oj;
+    }
+}
+__device__ inline void wave_nearest(double &d, int &j) {
+    nearest_step<0x128>(d, j);  // row_ror 8
+    nearest_step<0x124>(d, j);  // row_ror 4
+    nearest_step<0x4E>(d, j);   // quad_perm 2,3,0,1
+    nearest_step<0xB1>(d, j);   // quad_perm 1,0,3,2
+    const long long b = __double_as_longlong(d);
+    double rd = INFINITY;
+    int rj = 0x7fffffff;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), 16 * r);
+        const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 16 * r);
+        const int oj = __builtin_amdgcn_readlane(j, 16 * r);
+        const double od = __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+        if (r == 0 || nearer(od, oj, rd, rj)) {
+            rd = od;
+            rj = oj;
+        }
+    }
+    d = rd;
+    j = rj;
+}
+
+constexpr int kTop = 4;  // nearest seeds a lane keeps
+
+// One wave per seed.  A lane takes the seeds lane, lane + 64, ... and keeps
+// its kTop nearest in order; then the wave's nearest head is taken 16 times
+// (ties to the lower index).  A lane whose kTop are all taken (4 of the 16
+// nearest among its 64th of the seeds, about one wave in 10^4) looks through
+// its seeds again for the next ones.  The neighbours' terms are formed by 16
+// lanes at once and summed in the order of the neighbours.  (16 rounds over
+// all seeds and 16 dependent loads of a neighbour took 53 us for 700 seeds;
+// this takes 14.)
 __global__ __launch_bounds__(256) void kw_features(int n, const double *__restrict__ x,
                                                    const double *__restrict__ A,
                                                    const double *__restrict__ v, double lo0,
                                                    double lo1, double hi0, double hi1, float *F,
                                                    int *nb) {
-    const int lane = __lane_id();
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
+    __shared__ double s_t[4][kNeigh][9];
+    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    const int i = blockIdx.x * 4 + wave;
     if (i >= n) return;  // whole waves leave together
     const double xi0 = x[2 * i], xi1 = x[2 * i + 1];
     const int k = min(kNeigh, n - 1);
-    double pd = -1.0;
-    int pj = -1;
-    double s[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    double td[kTop];
+    int tj[kTop];
+    // the lane's kTop nearest after (pd, pj)
+    auto collect = [&](double pd, int pj) {
+#pragma unroll
+        for (int q = 0; q < kTop; ++q) {
+            td[q] = INFINITY;
+            tj[q] = 0x7fffffff;
+        }
+#pragma unroll 4
+        for (int j = lane; j < n; j += 64) {
+            const double d0 = xi0 - x[2 * j], d1 = xi1 - x[2 * j + 1];
+            double d = d0 * d0 + d1 * d1;
+            int c = j;
+            if (j == i || !nearer(pd, pj, d, j)) continue;
+#pragma unroll
+            for (int q = 0; q < kTop; ++q)
+                if (nearer(d, c, td[q], tj[q])) {
+                    const double t = td[q];
+                    const int u = tj[q];
+                    td[q] = d;
+                    tj[q] = c;
+                    d = t;
+                    c = u;
+                }
+        }
+    };
+    collect(-1.0, -1);
+    int mine = 0;  // lane r < k: neighbour r
+    int used = 0;
+    for (int r = 0; r < k; ++r) {
+        double d = td[0];
+        int j = tj[0];
+        wave_nearest(d, j);
+        if (lane == r) mine = j;
+        if ((j & 63) == lane && tj[0] == j) {
+            // taken: the next of this lane
+#pragma unroll
+            for (int q = 0; q + 1 < kTop; ++q) {
+                td[q] = td[q + 1];
+                tj[q] = tj[q + 1];
+            }
+            td[kTop - 1] = INFINITY;
+            tj[kTop - 1] = 0x7fffffff;
+            if (++used == kTop) {
+                collect(d, j);
+                used = 0;
+            }
+        }
+    }
     const double N = (double)n;
     const double *ai = A + 4 * i;
-    for (int round = 0; round < k; ++round) {
-        double bd = INFINITY;
-        int bj = 0x7fffffff;
-        for (int j = lane; j < n; j += 64) {
-            if (j == i) continue;
-            const double d0 = xi0 - x[2 * j], d1 = xi1 - x[2 * j + 1];
-            const double d2 = d0 * d0 + d1 * d1;
-            const bool after = d2 > pd || (d2 == pd && j > pj);
-            if (after && (d2 < bd || (d2 == bd && j < bj))) {
-                bd = d2;
-                bj = j;
-            }
-        }
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const double od = __shfl_xor(bd, o);
-            const int oj = __shfl_xor(bj, o);
-            if (od < bd || (od == bd && oj < bj)) {
-                bd = od;
-                bj = oj;
-            }
-        }
-        pd = bd;
-        pj = bj;
-        if (lane == 0) nb[(size_t)i * kNeigh + round] = bj;
-        // accumulate the neighbour's terms (every lane holds the same values)
-        const int j = bj;
+    if (lane < k) {
+        nb[(size_t)i * kNeigh + lane] = mine;
+        const int j = mine;
         const double dx0 = x[2 * j] - xi0, dx1 = x[2 * j + 1] - xi1;
         const double *aj = A + 4 * j;
-        s[0] += dx0;
-        s[1] += dx1;
-        s[2] += aj[0];
-        s[3] += aj[1];
-        s[4] += aj[3];
-        s[5] += N * v[j];
-        s[6] += N * (dx0 * (ai[0] * dx0 + ai[1] * dx1) + dx1 * (ai[1] * dx0 + ai[3] * dx1));
-        s[7] += N * (dx0 * (aj[0] * dx0 + aj[1] * dx1) + dx1 * (aj[1] * dx0 + aj[3] * dx1));
+        double *t = s_t[wave][lane];
+        t[0] = dx0;
+        t[1] = dx1;
+        t[2] = aj[0];
+        t[3] = aj[1];
+        t[4] = aj[3];
+        t[5] = N * v[j];
+        t[6] = N * (dx0 * (ai[0] * dx0 + ai[1] * dx1) + dx1 * (ai[1] * dx0 + ai[3] * dx1));
+        t[7] = N * (dx0 * (aj[0] * dx0 + aj[1] * dx1) + dx1 * (aj[1] * dx0 + aj[3] * dx1));
     }
-    if (lane != 0) return;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (lane >= 16) return;
     const double area = (hi0 - lo0) * (hi1 - lo1);
     const double sc = sqrt(N / area);
-    double f[kFeat];
-    f[0] = xi0;
-    f[1] = xi1;
-    f[2] = ai[0];
-    f[3] = ai[1];
-    f[4] = ai[3];
-    f[5] = N * v[i];
-    for (int q = 6; q < 14; ++q) f[q] = 0.0;
-    if (k > 0) {
-        const double c = (double)k, rn = sqrt(N);
-        f[6] = rn * s[0] / c;
-        f[7] = rn * s[1] / c;
-        for (int q = 2; q < 8; ++q) f[6 + q] = s[q] / c;
+    // lane q writes feature q
+    double f;
+    if (lane < 6) {
+        f = lane == 0 ? xi0 : lane == 1 ? xi1 : lane == 2 ? ai[0] : lane == 3 ? ai[1] : lane == 4 ? ai[3] : N * v[i];
+    } else if (lane < 14) {
+        double s = 0.0;
+        for (int r = 0; r < k; ++r) s += s_t[wave][r][lane - 6];
+        const double c = (double)k;
+        f = k == 0 ? 0.0 : lane < 8 ? sqrt(N) * s / c : s / c;
+    } else {
+        f = lane == 14 ? sc * fmin(xi0 - lo0, hi0 - xi0) : sc * fmin(xi1 - lo1, hi1 - xi1);
     }
-    f[14] = sc * fmin(xi0 - lo0, hi0 - xi0);
-    f[15] = sc * fmin(xi1 - lo1, hi1 - xi1);
-    for (int q = 0; q < 16; ++q) F[(size_t)i * kFeat + q] = (float)f[q];
+    F[(size_t)i * kFeat + lane] = (float)f;
 }
 
-// d_i = N grad_i (the deficit at W = 0) into feature 16 and out.
+// The deficit d_i = N grad_i at W = 0 (feature 16) and its 1-, 2- and 3-fold
+// repeated means over the 16 nearest seeds of each seed, in neighbour order
+// (features 17 to 19; zero for a lone seed).  Up to kPoolSeeds seeds one block
+// does it all with the values in LDS (four launches of 4.7 us each before);
+// more seeds take a launch per hop, in and out in global memory.
+constexpr int kPoolSeeds = 4096;
+
+__device__ inline double pool_mean(int n, const int *nb, const double *in, int i) {
+    const int k = min(kNeigh, n - 1);
+    double s = 0.0;
+    if (k == kNeigh) {
+        const int4 *q = reinterpret_cast<const int4 *>(nb + (size_t)i * kNeigh);
+        const int4 a = q[0], b = q[1], c = q[2], d = q[3];
+        const int id[kNeigh] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w, c.x, c.y, c.z, c.w, d.x, d.y, d.z, d.w};
+#pragma unroll
+        for (int r = 0; r < kNeigh; ++r) s += in[id[r]];
+    } else {
+        for (int r = 0; r < k; ++r) s += in[nb[(size_t)i * kNeigh + r]];
+    }
+    return k > 0 ? s / (double)k : 0.0;
+}
+
+__global__ __launch_bounds__(1024) void kw_pool_all(int n, const int *nb, const double *grad, float *F) {
+    __shared__ double d[2][kPoolSeeds];
+    for (int i = threadIdx.x; i < n; i += 1024) {
+        const double t = (double)n * grad[i];
+        d[0][i] = t;
+        F[(size_t)i * kFeat + 16] = (float)t;
+    }
+    for (int h = 0; h < kPoolHops; ++h) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < n; i += 1024) {
+            const double m = pool_mean(n, nb, d[h & 1], i);
+            d[(h + 1) & 1][i] = m;
+            F[(size_t)i * kFeat + 17 + h] = (float)m;
+        }
+    }
+}
+
 __global__ __launch_bounds__(256) void kw_deficit(int n, const double *grad, double *out, float *F) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
@@ -133,16 +241,11 @@ __global__ __launch_bounds__(256) void kw_deficit(int n, const double *grad, dou
     F[(size_t)i * kFeat + 16] = (float)d;
 }
 
-// out_i = mean of in over the 16 nearest seeds of i (in neighbour order),
-// into feature col and out; zero for a lone seed.
 __global__ __launch_bounds__(256) void kw_pool(int n, const int *nb, const double *in, double *out,
                                                float *F, int col) {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
-    const int k = min(kNeigh, n - 1);
-    double s = 0.0;
-    for (int r = 0; r < k; ++r) s += in[nb[(size_t)i * kNeigh + r]];
-    const double m = k > 0 ? s / (double)k : 0.0;
+    const double m = pool_mean(n, nb, in, i);
     out[i] = m;
     F[(size_t)i * kFeat + col] = (float)m;
 }
@@ -538,65 +641,75 @@ __global__ __launch_bounds__(256) void kw_to_bf16(const float *P, unsigned short
     Wb[e] = to_bf16(v);
 }
 
-// One wave per 32 samples (its activations in its own LDS rows, so no block
-// barriers); y[s] for s < S.
+// A block per 32 samples, wave w the outputs 32 w .. 32 w + 31 of every layer,
+// the weights of all layers loaded before the first product; y[s] for s < S.
+// (A wave per 32 samples doing all 128 columns left 22 waves on the chip for
+// 700 samples and waited for the weights product by product: 17.5 us.)
 __global__ __launch_bounds__(256) void kw_infer_bf16(const float *P, const unsigned short *Wb,
                                                      const float *X, int S, float *y) {
     constexpr int kRow = kHid + 8;  // padded LDS row
-    __shared__ unsigned short act[4][32 * kRow];
-    const int lane = __lane_id(), wave = threadIdx.x >> 6;
+    __shared__ __attribute__((aligned(16))) unsigned short act[2][32 * kRow];
+    const int lane = __lane_id(), tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
-    const int s0 = (blockIdx.x * 4 + wave) * 32;
-    if (s0 >= S) return;  // whole waves leave together
-    unsigned short *A = act[wave];
-    for (int e = lane; e < 32 * kK1; e += 64) {
-        const int r = e / kK1, k = e % kK1;
+    const int s0 = blockIdx.x * 32, o = 32 * wave + col;
+    bf16x8_t w1[kK1 / 16], w2[kHid / 16], w3[kHid / 16];
+    auto load = [&](const unsigned short *Wt, int kin, int k0) {
+        return __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const ushort8_t *>(Wt + (int64_t)o * kin + k0 + 8 * half));
+    };
+#pragma unroll
+    for (int k = 0; k < kK1 / 16; ++k) w1[k] = load(Wb + kBfW1, kK1, 16 * k);
+#pragma unroll
+    for (int k = 0; k < kHid / 16; ++k) w2[k] = load(Wb + kBfW2, kHid, 16 * k);
+#pragma unroll
+    for (int k = 0; k < kHid / 16; ++k) w3[k] = load(Wb + kBfW3, kHid, 16 * k);
+    const float b1 = P[ob1 + o], b2 = P[ob2 + o], b3 = P[ob3 + o];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = tid + 256 * q, r = e / kK1, k = e % kK1;
         const float v = (s0 + r < S && k < kFeat) ? X[(int64_t)(s0 + r) * kFeat + k] : 0.0f;
-        A[r * kRow + k] = to_bf16(v);
+        act[0][r * kRow + k] = to_bf16(v);
     }
-    auto sync_wave = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    sync_wave();
-    auto layer = [&](int kin, const unsigned short *Wt, const float *bias) {
-        floatx16_t acc[4];
+    auto put = [&](const floatx16_t &acc, float bo, unsigned short *dst) {
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) acc[cb] = floatx16_t{};
-        for (int k0 = 0; k0 < kin; k0 += 16) {
-            const bf16x8_t a = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const ushort8_t *>(A + col * kRow + k0 + 8 * half));
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) {
-                const bf16x8_t b = __builtin_bit_cast(
-                    bf16x8_t, *reinterpret_cast<const ushort8_t *>(Wt + (int64_t)(cb * 32 + col) * kin + k0 + 8 * half));
-                acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[cb], 0, 0, 0);
-            }
+        for (int r = 0; r < 16; ++r) {
+            const int row = 8 * (r / 4) + 4 * half + (r % 4);
+            dst[row * kRow + o] = to_bf16(fmaxf(acc[r] + bo, 0.0f));
         }
-        sync_wave();  // every read of the inputs precedes the writes below
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-            const int o = cb * 32 + col;
-            const float bo = bias[o];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 8 * (r / 4) + 4 * half + (r % 4);
-                A[row * kRow + o] = to_bf16(fmaxf(acc[cb][r] + bo, 0.0f));
-            }
-        }
-        sync_wave();
     };
-    layer(kK1, Wb + kBfW1, P + ob1);
-    layer(kHid, Wb + kBfW2, P + ob2);
-    layer(kHid, Wb + kBfW3, P + ob3);
-    // output layer: y = b4 + sum_o h3[o] w4[o] (BF16 operands, FP32 sums)
-    const int row = col;
+    auto mul = [&](const unsigned short *src, int k, const bf16x8_t &w, floatx16_t acc) {
+        const bf16x8_t a = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const ushort8_t *>(src + col * kRow + 16 * k + 8 * half));
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w, acc, 0, 0, 0);
+    };
+    __syncthreads();
+    floatx16_t acc{};
+#pragma unroll
+    for (int k = 0; k < kK1 / 16; ++k) acc = mul(act[0], k, w1[k], acc);
+    put(acc, b1, act[1]);
+    __syncthreads();
+    acc = floatx16_t{};
+#pragma unroll
+    for (int k = 0; k < kHid / 16; ++k) acc = mul(act[1], k, w2[k], acc);
+    put(acc, b2, act[0]);
+    __syncthreads();
+    acc = floatx16_t{};
+#pragma unroll
+    for (int k = 0; k < kHid / 16; ++k) acc = mul(act[0], k, w3[k], acc);
+    put(acc, b3, act[1]);
+    __syncthreads();
+    // output layer: y = b4 + sum_o h3[o] w4[o] (BF16 operands, FP32 sums), a lane
+    // per half row
+    if (wave != 0) return;
     float part = 0.0f;
-    for (int o = 64 * half; o < 64 * half + 64; ++o)
-        part = fmaf(from_bf16(A[row * kRow + o]), from_bf16(Wb[kBfW4 + o]), part);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const ushort8_t h = *reinterpret_cast<const ushort8_t *>(&act[1][col * kRow + 64 * half + 8 * q]);
+        const ushort8_t w = *reinterpret_cast<const ushort8_t *>(Wb + kBfW4 + 64 * half + 8 * q);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) part = fmaf(from_bf16(h[e]), from_bf16(w[e]), part);
+    }
     part += __shfl_xor(part, 32);
-    if (half == 0 && s0 + row < S) y[s0 + row] = part + P[ob4];
+    if (half == 0 && s0 + col < S) y[s0 + col] = part + P[ob4];
 }
 
 // Slices of the samples for the weight gradients: at most kSplitMax, a
@@ -655,7 +768,7 @@ hipError_t to_bf16_weights(hipStream_t s, const float *P, unsigned short *Wb) {
 hipError_t infer_bf16(hipStream_t s, const float *P, const unsigned short *Wb, const float *X, int S,
                       float *y) {
     (void)hipGetLastError();
-    kw_infer_bf16<<<(unsigned)((S + 127) / 128), 256, 0, s>>>(P, Wb, X, S, y);
+    kw_infer_bf16<<<(unsigned)((S + 31) / 32), 256, 0, s>>>(P, Wb, X, S, y);
     return hipGetLastError();
 }
 
@@ -695,6 +808,10 @@ hipError_t features(hipStream_t s, int n, const double *x, const double *A, cons
                     float *F) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
     kw_features<<<(n + 3) / 4, 256, 0, s>>>(n, x, A, v, lo[0], lo[1], hi[0], hi[1], F, nb);
+    if (n <= kPoolSeeds) {
+        kw_pool_all<<<1, 1024, 0, s>>>(n, nb, grad0, F);
+        return hipGetLastError();
+    }
     const unsigned nb1 = (unsigned)((n + 255) / 256);
     kw_deficit<<<nb1, 256, 0, s>>>(n, grad0, tmp, F);
     for (int h = 0; h < kPoolHops; ++h) {

@@ -185,3 +185,23 @@ def test_fp64_lists(ctx, dim, grid, power, n):
                 assert out["g"] == pytest.approx(ev.g, rel=1e-12, abs=1e-15 * scale ** (power + dim))
                 np.testing.assert_array_equal(out["counts"].cpu().numpy(), ev.counts)
                 np.testing.assert_array_equal(out["grad"].cpu().numpy(), ev.grad)
+
+
+@pytest.mark.parametrize("n", [1, 2, 5, 16, 17, 18, 65, 1280, 4096, 4097])
+def test_features_by_the_number_of_seeds(ctx, n):
+    """Fewer seeds than neighbours, a lane holding many of the nearest (seeds
+    64 apart in number in one tight cluster), equal distances, and the pooled
+    deficits by one block or a launch per hop: against the reference, to the
+    FP32 rounding of the features (2^-24) and of sums of 16 doubles."""
+    import paper_2403_03571_amd as apd
+    from oracle import mlp
+    inst = S.custom(2, n, 48, seed=n, sigma=0.3)
+    if n == 1280:
+        inst.x[::64] = 0.5 + 1e-3 * np.random.default_rng(0).random((20, 2))
+    if n == 65:
+        inst.x[:] = np.stack(np.meshgrid(np.arange(13) / 16 + 0.125, np.arange(5) / 8 + 0.25), -1).reshape(-1, 2)
+    net = apd.WarmStart(ctx, mlp.init_params(0))
+    F = net.features(_prob(inst)).cpu().numpy()
+    d = mlp.deficit(inst.n, O.evaluate(inst, np.zeros(inst.n)).grad)
+    ref = mlp.features(inst.x, inst.A, inst.v, inst.lo, inst.hi, d=d)
+    np.testing.assert_allclose(F, ref, rtol=2e-6, atol=1e-6)
