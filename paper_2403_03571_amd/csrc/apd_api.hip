@@ -289,7 +289,8 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     const bool cull = with_lists(c, prec, rel_gap != nullptr);
     const bool timing = c->profiling && !fixed;
     if (timing) HIP_TRY(c, hipEventRecord(c->ev[0], c->stream));
-    HIP_TRY(c, apd::launch_prep(g, sd, b.sc, mom, cull ? b.eig : nullptr, b.parts, c->stream, w_host));
+    // weights from the host: a fit's captured evaluation, after its first one
+    HIP_TRY(c, apd::launch_prep(g, sd, b.sc, mom, cull ? b.eig : nullptr, b.parts, c->stream, w_host, w_host != nullptr));
     if (g.mass && c->need_qtotal) HIP_TRY(c, apd::launch_mass_total(g, b.sc, c->stream));
     if (timing) HIP_TRY(c, hipEventRecord(c->ev[1], c->stream));
     apd::PassOut out{labels, mom, nullptr};

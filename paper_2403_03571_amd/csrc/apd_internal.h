@@ -186,9 +186,11 @@ int vec_pixels_per_lane(const Geo &g, bool cull);
 // * that many pixels long along axis 0, with the vector kernel's other axes).
 int bf16_pixels_per_lane(const Geo &g);
 // With w_src (pinned host memory) the prep kernel first copies w_src into
-// sd.w (then a device buffer of the library's), one copy fewer per pass.
+// sd.w (then a device buffer of the library's), one copy fewer per pass.  With
+// w_only the rest of sc, and eig, hold what an earlier launch for the same
+// seeds, matrices and volumes left (a fit's later evaluations).
 hipError_t launch_prep(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom, double *eig,
-                       BlockParts *bp, hipStream_t st, const double *w_src = nullptr);
+                       BlockParts *bp, hipStream_t st, const double *w_src = nullptr, bool w_only = false);
 // Candidate lists of the super-tiles described by out (sf, nst), written to
 // list / count.
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,

@@ -42,8 +42,20 @@ using namespace dev;
 
 // ------------------------------------------------------------- k_prep
 
+// Up to kOneBlock seeds the prep and finalize kernels are one block with a
+// seed per thread; above, blocks of kRedThreads whose last one to finish
+// combines the partials.  The exchange through memory (fences that reach the
+// other XCDs, the ticket, the partials read back) costs more than what the
+// blocks share: 8.2 and 7.9 us for 1000 seeds in four blocks, ONE_US in one.
 constexpr int kRedThreads = 256;
-constexpr int kRedWaves = kRedThreads / 64;
+constexpr int kOneBlock = 1024;
+
+// Groups for n seeds: one seed per thread of kRedThreads up to kMaxParts
+// groups (blocks, above kOneBlock seeds).
+__host__ __device__ inline int red_groups(int n) {
+    const int k = n / kRedThreads + (n % kRedThreads ? 1 : 0);
+    return k < 1 ? 1 : k > kMaxParts ? kMaxParts : k;
+}
 
 // Seeds [lo, hi) of block b when n seeds are split over gridDim.x blocks.
 __device__ inline void block_range(int n, int *lo, int *hi) {
@@ -53,40 +65,40 @@ __device__ inline void block_range(int n, int *lo, int *hi) {
 }
 
 // True in the last block to finish; its partials and those of every other
-// block are then visible to it.
+// block (written by the blocks' threads 0) are then visible to it.
 __device__ inline bool last_block(unsigned *ticket) {
     __shared__ bool s_last;
-    __threadfence();
+    if (threadIdx.x == 0) {
+        __threadfence();
+        s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
+        __threadfence();
+    }
     __syncthreads();
-    if (threadIdx.x == 0) s_last = atomicAdd(ticket, 1u) == gridDim.x - 1;
-    __syncthreads();
-    if (s_last) __threadfence();
     return s_last;
 }
 
 // Validation, max_i w_i, sum_i v_i, the Gershgorin bound of the largest
 // eigenvalue, the eigenvalue ranges (culling) and the zeroed moments, over
-// blocks of seeds.
-template <int D>
-__global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *sc, uint64_t *mom,
-                                                      double *eig, BlockParts *bp, const double *w_src) {
+// blocks of T seeds (a single block for T = kOneBlock).  With w_only (the
+// later evaluations of a fit) only what depends on the weights is formed
+// again; the rest stays as the fit's first evaluation left it.
+template <int D, int T>
+__global__ __launch_bounds__(T) void k_prep(Geo g, Seeds sd, Scalars *sc, uint64_t *mom, double *eig, BlockParts *bp,
+                                            const double *w_src, bool w_only) {
     constexpr int K = moments_per_cell(D);
+    constexpr int kRedWaves = T / 64;
     __shared__ double s_w[kRedWaves];
     __shared__ double s_v[kRedWaves];
     __shared__ float s_l[kRedWaves];
     __shared__ float s_k[kRedWaves];
     __shared__ int s_b[kRedWaves];
     const int tid = threadIdx.x;
-    if (mom)
-        for (size_t t = (size_t)blockIdx.x * kRedThreads + tid; t < (size_t)g.n * K;
-             t += (size_t)gridDim.x * kRedThreads)
-            mom[t] = 0ull;
     int i0, i1;
     block_range(g.n, &i0, &i1);
     double wm = -INFINITY, vs = 0.0;
     float lam = 0.0f, kap = 0.0f;
     int bad = 0;
-    for (int i = i0 + tid; i < i1; i += kRedThreads) {
+    for (int i = i0 + tid; i < i1; i += T) {
         double wi;
         if (w_src) {
             // the pass's weights, from the host; later kernels read sd.w
@@ -97,6 +109,7 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
         }
         if (!isfinite(wi)) bad |= kBadW;
         wm = fmax(wm, wi);
+        if (w_only) continue;
         for (int d = 0; d < D; ++d)
             if (!isfinite(sd.x[(size_t)i * D + d])) bad |= kBadX;
         const double *a = sd.A + (size_t)i * D * D;
@@ -139,16 +152,19 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
             vs += vi;
         }
     }
+    if (mom)
+        for (size_t t = (size_t)blockIdx.x * T + tid; t < (size_t)g.n * K; t += (size_t)gridDim.x * T) mom[t] = 0ull;
     // block reduction: a butterfly inside each wave, then the wave results
     // in wave order by thread 0 (whose slots 0 then hold the block's values)
     auto reduce = [&](double a, double v, float l, float kk, int b) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
             a = fmax(a, __shfl_xor(a, o));
+            b = b | __shfl_xor(b, o);
+            if (w_only) continue;
             v = v + __shfl_xor(v, o);
             l = fmaxf(l, __shfl_xor(l, o));
             kk = fmaxf(kk, __shfl_xor(kk, o));
-            b = b | __shfl_xor(b, o);
         }
         __syncthreads();  // earlier readers of the slots are done
         if (__lane_id() == 0) {
@@ -170,32 +186,39 @@ __global__ __launch_bounds__(kRedThreads) void k_prep(Geo g, Seeds sd, Scalars *
             }
     };
     reduce(wm, vs, lam, kap, bad);
-    if (tid == 0) {
-        bp->a[blockIdx.x] = s_w[0];
-        bp->b[blockIdx.x] = s_v[0];
-        bp->l[blockIdx.x] = s_l[0];
-        bp->k[blockIdx.x] = s_k[0];
-        bp->bad[blockIdx.x] = s_b[0];
+    if constexpr (T != kOneBlock) {
+        if (tid == 0) {
+            bp->a[blockIdx.x] = s_w[0];
+            bp->b[blockIdx.x] = s_v[0];
+            bp->l[blockIdx.x] = s_l[0];
+            bp->k[blockIdx.x] = s_k[0];
+            bp->bad[blockIdx.x] = s_b[0];
+        }
+        if (!last_block(&bp->ticket)) return;
+        const bool have = tid < (int)gridDim.x;
+        reduce(have ? bp->a[tid] : -INFINITY, have ? bp->b[tid] : 0.0, have ? bp->l[tid] : 0.0f,
+               have ? bp->k[tid] : 0.0f, have ? bp->bad[tid] : 0);
     }
-    if (!last_block(&bp->ticket)) return;
-    const bool have = tid < (int)gridDim.x;
-    reduce(have ? bp->a[tid] : -INFINITY, have ? bp->b[tid] : 0.0, have ? bp->l[tid] : 0.0f,
-           have ? bp->k[tid] : 0.0f, have ? bp->bad[tid] : 0);
     if (tid == 0) {
+        float lm = s_l[0] * 1.0001f;
+        if (w_only) {
+            lm = sc->lam;
+        } else {
+            sc->vsum = s_v[0];
+            sc->lam = lm;
+            sc->kap = s_k[0] * 1.0001f;
+        }
         sc->wmax = s_w[0];
-        sc->vsum = s_v[0];
-        sc->lam = s_l[0] * 1.0001f;
-        sc->kap = s_k[0] * 1.0001f;
-        sc->sab = dslack_abs(g, s_w[0], s_l[0] * 1.0001f);
-        sc->lsl = list_slack(g, sc->sab, s_l[0] * 1.0001f);
+        sc->sab = dslack_abs(g, s_w[0], lm);
+        sc->lsl = list_slack(g, sc->sab, lm);
         sc->bad = s_b[0];
         sc->qcount = 0u;
         sc->credited = 0u;
         sc->gpix = 0.0;
         sc->g = 0.0;
         sc->maxrel = 0.0;
-        sc->qtotal = 0ull;
-        bp->ticket = 0u;
+        if (!w_only) sc->qtotal = 0ull;
+        if constexpr (T != kOneBlock) bp->ticket = 0u;
     }
 }
 
@@ -237,11 +260,6 @@ __global__ __launch_bounds__(256) void k_mass_total(int64_t J, const uint8_t *ma
 
 // Seeds above which a super-tile's list is built by 1024 threads.
 constexpr int kSuperWideSeeds = 2048;
-
-// Blocks for n seeds: one seed per thread up to kMaxParts blocks.
-inline int red_blocks(int n) {
-    return (int)std::min<int64_t>(kMaxParts, std::max<int64_t>(1, ((int64_t)n + kRedThreads - 1) / kRedThreads));
-}
 
 // ------------------------------------------------------ k_assign_fp64
 
@@ -475,19 +493,31 @@ __global__ __launch_bounds__(kThreads) void k_recheck_staged(Geo g, Seeds sd, co
 // -------------------------------------------------------- k_finalize
 
 // Every cell's term of eq. (2.7) (dev::cell_final) and its relative volume
-// error, over blocks of cells; the terms are summed in a fixed order
-// (per block, then over blocks), so the objective is deterministic.
-template <int D>
-__global__ __launch_bounds__(kRedThreads) void k_finalize(Geo g, Seeds sd, const uint64_t *mom,
-                                                          Scalars *sc, FinalOut out, BlockParts *bp) {
+// error, over blocks of cells; the terms are summed in a fixed order (a
+// butterfly in each wave, the waves of 256 cells in order, then a butterfly
+// over these groups), the same in one block (T = kOneBlock: four groups) and
+// in several, so the objective is deterministic.
+template <int D, int T>
+__global__ __launch_bounds__(T) void k_finalize(Geo g, Seeds sd, const uint64_t *mom, Scalars *sc, FinalOut out,
+                                                BlockParts *bp) {
     constexpr int K = moments_per_cell(D);
-    __shared__ double s_g[kRedWaves];
-    __shared__ double s_m[kRedWaves];
+    constexpr int kGroupWaves = kRedThreads / 64;
+    __shared__ double s_g[T / 64];
+    __shared__ double s_m[T / 64];
     const int tid = threadIdx.x;
-    int i0, i1;
-    block_range(g.n, &i0, &i1);
+    const int groups = red_groups(g.n);  // of at most kRedThreads cells when T is kOneBlock
+    const int per = (g.n + groups - 1) / groups;
+    const int grp = T == kOneBlock ? tid / kRedThreads : (int)blockIdx.x;
+    const int i0 = min(g.n, grp * per), i1 = min(g.n, i0 + per);
+    // the scalars of the earlier kernels, loaded ahead of their use
+    Scalars pass = Scalars{};
+    unsigned published = 0u;
+    if (tid == 0) {
+        pass = *sc;
+        published = bp->published;
+    }
     double gs = 0.0, mr = 0.0;
-    for (int i = i0 + tid; i < i1; i += kRedThreads) {
+    for (int i = i0 + tid % kRedThreads; i < i1; i += kRedThreads) {
         double gi, rel, ybar[3];
         gs += dev::cell_final<D>(g, sd, mom + (size_t)i * K, i, &gi, &rel, ybar);
         mr = fmax(mr, rel);
@@ -496,7 +526,6 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(Geo g, Seeds sd, const
         if (out.centroids)
             for (int d = 0; d < D; ++d) out.centroids[(size_t)i * D + d] = ybar[d];
     }
-    // block reduction as in k_prep
     auto reduce = [&](double a, double m) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
@@ -509,43 +538,71 @@ __global__ __launch_bounds__(kRedThreads) void k_finalize(Geo g, Seeds sd, const
             s_m[tid >> 6] = m;
         }
         __syncthreads();
-        if (tid == 0)
-            for (int k = 1; k < kRedWaves; ++k) {
-                s_g[0] = s_g[0] + s_g[k];
-                s_m[0] = fmax(s_m[0], s_m[k]);
+        // thread 0 of each group (of the block, when it is one group)
+        if (tid % kRedThreads == 0)
+            for (int k = 1; k < kGroupWaves; ++k) {
+                s_g[tid >> 6] = s_g[tid >> 6] + s_g[(tid >> 6) + k];
+                s_m[tid >> 6] = fmax(s_m[tid >> 6], s_m[(tid >> 6) + k]);
             }
     };
     reduce(gs, mr);
-    if (tid == 0) {
-        bp->a[blockIdx.x] = s_g[0];
-        bp->b[blockIdx.x] = s_m[0];
-    }
-    // this block's host writes (the gradient) reach the host before the
-    // last block publishes the pass
-    if (out.host_sc) __threadfence_system();
-    if (!last_block(&bp->ticket)) return;
-    const bool have = tid < (int)gridDim.x;
-    reduce(have ? bp->a[tid] : 0.0, have ? bp->b[tid] : 0.0);
-    if (tid == 0) {
-        sc->g = g.power != 2 ? s_g[0] + g.munit * sc->gpix : s_g[0];
-        sc->maxrel = s_m[0];
-        bp->ticket = 0u;
+    // thread 0's scalars for the host, all but seq
+    auto put = [&](double gt, double mx) {
+        sc->g = gt;
+        sc->maxrel = mx;
+        if (!out.host_sc) return;
+        Scalars *h = out.host_sc;
+        h->wmax = pass.wmax;
+        h->vsum = pass.vsum;
+        h->g = gt;
+        h->maxrel = mx;
+        h->qcount = pass.qcount;
+        h->lam = pass.lam;
+        h->bad = pass.bad;
+        h->qtotal = pass.qtotal;
+        h->credited = pass.credited;
+        bp->published = published + 1u;
+    };
+    // the host waits for seq, so it goes last, after every other write of the
+    // pass (each thread's, the gradient among them) has reached the host
+    auto publish = [&] {
+        __hip_atomic_store(&out.host_sc->seq, published + 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    const double gp = g.power != 2 ? g.munit * pass.gpix : 0.0;
+    auto objective = [&](double sum) { return g.power != 2 ? sum + gp : sum; };
+    if constexpr (T == kOneBlock) {
+        // the butterfly over at most four groups; one fence covers the
+        // gradient and the scalars
+        __syncthreads();  // the groups' sums
+        if (tid == 0) {
+            double mx = s_m[0];
+            for (int k = 1; k < 4; ++k) mx = fmax(mx, s_m[k * kGroupWaves]);
+            put(objective((s_g[0] + s_g[2 * kGroupWaves]) + (s_g[kGroupWaves] + s_g[3 * kGroupWaves])), mx);
+        }
         if (out.host_sc) {
-            // every kernel of the pass before this one has finished; the
-            // host waits for seq, so it goes last
-            Scalars *h = out.host_sc;
-            h->wmax = sc->wmax;
-            h->vsum = sc->vsum;
-            h->g = sc->g;
-            h->maxrel = sc->maxrel;
-            h->qcount = sc->qcount;
-            h->lam = sc->lam;
-            h->bad = sc->bad;
-            h->qtotal = sc->qtotal;
-            h->credited = sc->credited;
             __threadfence_system();
-            const unsigned n = ++bp->published;
-            __hip_atomic_store(&out.host_sc->seq, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+            __syncthreads();
+            if (tid == 0) publish();
+        }
+    } else {
+        if (tid == 0) {
+            bp->a[blockIdx.x] = s_g[0];
+            bp->b[blockIdx.x] = s_m[0];
+        }
+        if (out.host_sc) {
+            __threadfence_system();
+            __syncthreads();
+        }
+        if (!last_block(&bp->ticket)) return;
+        const bool have = tid < (int)gridDim.x;
+        reduce(have ? bp->a[tid] : 0.0, have ? bp->b[tid] : 0.0);
+        if (tid == 0) {
+            put(objective(s_g[0]), s_m[0]);
+            bp->ticket = 0u;
+            if (out.host_sc) {
+                __threadfence_system();
+                publish();
+            }
         }
     }
 }
@@ -590,12 +647,20 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     return J >= 1024 * 2048 ? 8 : 4;
 }
 
+template <int D>
+static void launch_prep_d(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom, double *eig, BlockParts *bp,
+                          hipStream_t st, const double *w_src, bool w_only) {
+    if (g.n <= kOneBlock)
+        k_prep<D, kOneBlock><<<1, kOneBlock, 0, st>>>(g, sd, sc, mom, eig, bp, w_src, w_only);
+    else
+        k_prep<D, kRedThreads><<<red_groups(g.n), kRedThreads, 0, st>>>(g, sd, sc, mom, eig, bp, w_src, w_only);
+}
+
 hipError_t launch_prep(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom, double *eig,
-                       BlockParts *bp, hipStream_t st, const double *w_src) {
+                       BlockParts *bp, hipStream_t st, const double *w_src, bool w_only) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    const int nb = red_blocks(g.n);
-    if (g.dim == 2) k_prep<2><<<nb, kRedThreads, 0, st>>>(g, sd, sc, mom, eig, bp, w_src);
-    else k_prep<3><<<nb, kRedThreads, 0, st>>>(g, sd, sc, mom, eig, bp, w_src);
+    if (g.dim == 2) launch_prep_d<2>(g, sd, sc, mom, eig, bp, st, w_src, w_only);
+    else launch_prep_d<3>(g, sd, sc, mom, eig, bp, st, w_src, w_only);
     return hipGetLastError();
 }
 
@@ -754,9 +819,14 @@ hipError_t launch_mass_total(const Geo &g, Scalars *sc, hipStream_t st) {
 hipError_t launch_finalize(const Geo &g, const Seeds &sd, const uint64_t *mom, Scalars *sc,
                            const FinalOut &out, BlockParts *bp, hipStream_t st) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    const int nb = red_blocks(g.n);
-    if (g.dim == 2) k_finalize<2><<<nb, kRedThreads, 0, st>>>(g, sd, mom, sc, out, bp);
-    else k_finalize<3><<<nb, kRedThreads, 0, st>>>(g, sd, mom, sc, out, bp);
+    const int nb = red_groups(g.n);
+    if (g.n <= kOneBlock) {
+        if (g.dim == 2) k_finalize<2, kOneBlock><<<1, kOneBlock, 0, st>>>(g, sd, mom, sc, out, bp);
+        else k_finalize<3, kOneBlock><<<1, kOneBlock, 0, st>>>(g, sd, mom, sc, out, bp);
+    } else {
+        if (g.dim == 2) k_finalize<2, kRedThreads><<<nb, kRedThreads, 0, st>>>(g, sd, mom, sc, out, bp);
+        else k_finalize<3, kRedThreads><<<nb, kRedThreads, 0, st>>>(g, sd, mom, sc, out, bp);
+    }
     return hipGetLastError();
 }
 
