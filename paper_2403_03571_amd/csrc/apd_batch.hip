@@ -257,13 +257,15 @@ template <int D, int V>
 __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) void kb_assign(const BInst *inst, const BState *st,
                                                      BWork wk, int B, BCtl *ctl,
                                                      uint64_t *queue, QSeg *segs) {
+    constexpr bool kLists = V == 2 || V == 4 || V == 5;
+    constexpr int kLanePixels = V == 4 ? kP : kPv;
     __shared__ union {
-        float mf[kMfmaLds];
-        VecSmem<D, V == 2 || V == 4, V == 4 ? kP : kPv> vec;
-        Bf16Smem<D, Bf16Rows<D>::value, 256, V == 5> bf;
+        float mf[V == 0 ? kMfmaLds : 1];
+        VecSmem<V == 1 ? D : 2> vec[V == 1 ? 1 : 0];
+        ListSmem<D, kLanePixels, false> list[V == 2 || V == 4 ? 1 : 0];
+        Bf16Smem<D, Bf16Rows<D>::value, 256, V == 5> bf[V == 3 || V == 5 ? 1 : 0];
     } sm;
     float *sC = sm.mf;
-    constexpr bool kLists = V == 2 || V == 4 || V == 5;
     const int64_t total = uniform_load(wk.act_tile + B);
     for (int64_t item = blockIdx.x; item < total; item += gridDim.x) {
         const int b = find_instance(wk.act_tile, B, item);
@@ -290,7 +292,7 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
             b1 = r / I.tiles2;
             b2 = r % I.tiles2;
         }
-        if (V == 0) {
+        if constexpr (V == 0) {
             mfma_tile<D>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, b0, b1, b2, sC, out, &ctl->qcount);
         } else {
             if (kLists) {
@@ -306,12 +308,14 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                     out.nst[d] = I.nst[d];
                 }
             }
+            const Cert ct{S.lam, S.kap, S.sab, S.lsl};
             if constexpr (V == 3 || V == 5)
-                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, b0, b1, b2,
-                                                              sm.bf, out, kLists ? nullptr : &ctl->qcount);
+                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, ct, I.eig, b0, b1, b2, sm.bf[0], out,
+                                                              kLists ? nullptr : &ctl->qcount);
+            else if constexpr (V == 1)
+                vec_tile<D, kLanePixels>(I.g, sd, S.wmax, ct, b0, b1, b2, sm.vec[0], out, &ctl->qcount);
             else
-                vec_tile<D, kLists, V == 4 ? kP : kPv>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, b0, b1, b2,
-                                                       sm.vec, out, kLists ? nullptr : &ctl->qcount);
+                list_tile<D, kLanePixels>(I.g, sd, S.wmax, ct, I.eig, b0, b1, b2, sm.list[0], out, nullptr);
         }
     }
 }

@@ -549,8 +549,7 @@ __device__ inline void wave_lds_sync() {
 // position in the tile's candidate list) are a contraction: for each cell the
 // sum over the pixels of (pixel in cell) times (monomials of the pixel), both
 // small exact integers.  v_mfma_i32_16x16x64_i8 forms it for 16 cells x 64
-// pixels x 16 columns: the cells' indicator on the rows (a byte compare of the
-// pixels' indices with the row's), the pixels' monomials on the columns, from
+// pixels x 16 columns: the cells' indicator on the rows, the pixels' monomials on the columns, from
 // a constant table.  With o_d = 2 (k_d - anchor_d) + 1 the columns are 1, the
 // o_d, and for each product o_d o_e its high and low part (o_d o_e = 32 h + l,
 // 0 <= l < 32, so that both fit a signed byte up to tiles of 64 rows); the
@@ -571,10 +570,11 @@ struct MomTab {
     static constexpr int kSteps = P < 4 ? 4 : P;
     static constexpr int kProd = D * (D + 1) / 2;
     signed char v[kWaves][kSteps][64][16];
+    int total[kWaves][16];  // each column's sum over the wave's pixels
     // step s, lane l, byte b: column l % 16 of pixel p = 4 (s / 4) + b % 4 of lane
     // 16 (l / 16) + 4 (s % 4) + b / 4 of the wave (the order in which the rows'
     // operand holds the pixels)
-    constexpr MomTab() : v() {
+    constexpr MomTab() : v(), total() {
         constexpr int E[3] = {tile_ext(D, P, 0), tile_ext(D, P, 1), tile_ext(D, P, 2)};
         for (int w = 0; w < kWaves; ++w)
             for (int s = 0; s < kSteps; ++s)
@@ -596,7 +596,10 @@ struct MomTab {
                             col[1 + D + kProd + c] = t & 31;
                         }
                     }
-                    for (int n = 0; n < 16; ++n) v[w][s][16 * (q / 16) + n][q % 16] = (signed char)col[n];
+                    for (int n = 0; n < 16; ++n) {
+                        v[w][s][16 * (q / 16) + n][q % 16] = (signed char)col[n];
+                        total[w][n] += col[n];
+                    }
                 }
     }
 };
@@ -605,11 +608,11 @@ static __device__ const MomTab<D, P> mom_tab{};
 
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
-// LDS of the moments: the cells' sums and each wave's pixel indices.
+// LDS of the moments: the cells' sums and each wave's byte selectors.
 template <int P>
 struct MomSmem {
     int acc[kAccSlots][16];
-    alignas(16) unsigned idx[kWaves][P > 4 ? 2 : 1][64];
+    alignas(16) unsigned sel[kWaves][2][(P + 3) / 4][64];
 };
 
 // Zeroes the first n slots (a barrier must follow).
@@ -618,44 +621,68 @@ __device__ inline void moments_zero(MomSmem<P> &sm, int n) {
     for (int q = threadIdx.x; q < n * 16; q += kThreads) (&sm.acc[0][0])[q] = 0;
 }
 
-// Adds this wave's pixels: idx[p] the cell index of pixel p, below ncell
-// (<= kAccSlots), or 127 (not counted); slot(j) the tile's slot of cell j.
-// Every lane of the wave must call it.
+// Adds this wave's pixels: byte p % 4 of v[p / 4] the cell index of pixel p,
+// below ncell (<= kAccSlots), or 127 (not counted); slot(j) the tile's slot of
+// cell j.  Every lane of the wave must call it.
+//
+// The indicator operand holds 0 for a pixel of the row's cell and -1 for any
+// other, and the sums start from the columns' totals, so each sum is the
+// cell's own.  One byte permutation makes four entries: the pixels' indices
+// relative to 8 consecutive cells are its selectors (bit 7 set, which selects
+// 0xff, where the pixel is in none of them; each lane writes its own pixels'
+// selectors once) and the lane's row is a table of 8 bytes.  A byte compare in
+// the operand's layout took 3.4 instructions for four entries, 66 more per wave
+// of 512 voxels.
 template <int D, int P, class Slot>
-__device__ inline void moments_add(MomSmem<P> &sm, int lane, const int (&idx)[P], int ncell, Slot slot) {
-    constexpr int S = MomTab<D, P>::kSteps;
+__device__ inline void moments_add(MomSmem<P> &sm, int lane, const unsigned (&v)[(P + 3) / 4], int ncell, Slot slot) {
+    constexpr int S = MomTab<D, P>::kSteps, H = (P + 3) / 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = lane >> 4, col = lane & 15;
     intx4 tab[S];
 #pragma unroll
     for (int k = 0; k < S; ++k) tab[k] = *reinterpret_cast<const intx4 *>(&mom_tab<D, P>.v[wave][k][lane][0]);
-#pragma unroll
-    for (int hh = 0; hh < (P + 3) / 4; ++hh) {
-        unsigned v = 0u;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v |= (unsigned)(4 * hh + j < P ? idx[4 * hh + j < P ? 4 * hh + j : 0] : 127) << (8 * j);
-        sm.idx[wave][hh][lane] = v;
-    }
-    wave_lds_sync();
-    const int row = lane >> 4, col = lane & 15;
+    const int total = mom_tab<D, P>.total[wave][col];
+    const unsigned long long lut = ~(0xffull << (8 * (col & 7)));
     for (int j0 = 0; j0 < ncell; j0 += 16) {
-        const unsigned pat = (unsigned)(j0 + col) * 0x01010101u;
-        intx4 sum = {0, 0, 0, 0};
+        if (j0) wave_lds_sync();  // the selectors are read by other lanes
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int hh = 0; hh < H; ++hh) {
+                // bytes are below 128, so no sum carries between them
+                const unsigned y = v[hh] ^ ((unsigned)(j0 + 8 * h) * 0x01010101u);
+                sm.sel[wave][h][hh][lane] = ((y + 0x78787878u) & 0x80808080u) | y;
+            }
+        wave_lds_sync();
+        intx4 sum = {total, total, total, total};
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            intx4 a = *reinterpret_cast<const intx4 *>(&sm.idx[wave][k / 4][16 * row + 4 * (k % 4)]);
-            // bytes equal to the row's index become -128, the others 0 (bytes
-            // are below 128, so the sum does not carry between them)
+            intx4 a = *reinterpret_cast<const intx4 *>(&sm.sel[wave][col >> 3][k / 4][16 * row + 4 * (k % 4)]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) a[e] = (int)(~(((unsigned)a[e] ^ pat) + 0x7f7f7f7fu) & 0x80808080u);
+            for (int e = 0; e < 4; ++e)
+                a[e] = (int)__builtin_amdgcn_perm((unsigned)(lut >> 32), (unsigned)lut, (unsigned)a[e]);
             sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, tab[k], sum, 0, 0, 0);
         }
         // register r: cell j0 + 4 row + r, column col
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = j0 + 4 * row + r;
-            if (sum[r] != 0 && j < ncell) atomicAdd(&sm.acc[slot(j)][col], -(sum[r] >> 7));
+            if (sum[r] != 0 && j < ncell) atomicAdd(&sm.acc[slot(j)][col], sum[r]);
         }
     }
+}
+// The same from an array of indices.
+template <int D, int P, class Slot>
+__device__ inline void moments_add(MomSmem<P> &sm, int lane, const int (&idx)[P], int ncell, Slot slot) {
+    unsigned v[(P + 3) / 4];
+#pragma unroll
+    for (int hh = 0; hh < (P + 3) / 4; ++hh) {
+        v[hh] = 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[hh] |= (unsigned)(4 * hh + j < P ? idx[4 * hh + j < P ? 4 * hh + j : 0] : 127) << (8 * j);
+    }
+    moments_add<D, P>(sm, lane, v, ncell, slot);
 }
 
 // Adds the tile's cells to the moments (after a barrier): list[k] the seed of
@@ -808,6 +835,12 @@ __device__ inline void recheck_flagged(const Geo &g, const Seeds &sd, const Tile
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 __device__ inline int med3i(int a, int b, int c) { return max(min(a, b), min(max(a, b), c)); }
+// (asm: next to med3i the compiler takes min(a, b) apart and makes two of it)
+__device__ inline int min3i(int a, int b, int c) {
+    int r;
+    asm("v_min3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 
 // Single precision on the matrix cores.  The cost of seed i at pixel j in
 // tile-local coordinates is a dot product of K = 6 (2D) or 10 (3D) terms,
@@ -1580,7 +1613,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
 //  * short scans (fewer than kGroupScan seeds) keep the index of the best
 //    seed in the low 4 bits of its cost (integer min / med3 on the keys:
 //    3 operations per pixel and seed besides the 2 fused multiply-adds);
-//  * long scans take the minimum of each group of 16 seeds with 3-input
+//  * long scans (over every seed) take the minimum of each group of 16 seeds with 3-input
 //    minima (about half an operation per pixel and seed), keep the top two
 //    group minima and the group of the best, and at the end of each staged
 //    chunk re-evaluate the 16 costs of the winning group -- bit-identical
@@ -1588,13 +1621,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
 //    seed and the second-smallest cost inside that group.  The top two of
 //    all costs are then (best, min(second group minimum, second inside the
 //    winning group)).
-//
-// With candidate lists, each wave then narrows the tile's list to the box of
-// its own P x L1 (x L2) pixels (the same test, the tile's candidates as the
-// seed set) and scans only those; a wave whose list would not fit scans the
-// tile's list.
 constexpr int kGroupScan = 96;   // scans at least this long use group minima
-constexpr int kWaveCap = 256;    // per-wave candidate positions
 
 // The candidate list of a tile's box, from its super-tile's list when it has
 // one (else from every seed): into sm.list, at most kCullCap seeds; returns
@@ -1692,63 +1719,149 @@ __device__ inline void credit_tile(const Geo &g, const Tile<D> &t, int b0, int b
     }
 }
 
-// Staging of the vector tile: float4 rows per seed, seeds per chunk (the
-// 2D scan over every seed stages 1024 so that N = 1000 is one chunk).
-template <int D, bool CULL>
-struct VecCfg {
-    static constexpr int kRows = D == 2 ? 2 : 3;
-    static constexpr int kChunk = CULL ? 256 : (D == 2 ? 1024 : 512);
+// A threshold that needs no square root, holds for every pixel of a tile and is
+// linear in the best cost: 4 r sqrt(B) <= 2 B + 2 r^2 and r at the tile's corner
+// (r2t), so vec_settle's is at most 2^-20 (6 B1 + 12 r^2) + ... + kbits max(|fb|,
+// |fs|), and max(|fb|, |fs|) <= |fb| + (fs - fb).  Nearly every wave settles all
+// of its pixels by it (3 instructions per pixel instead of about 45 with two
+// square roots).
+struct LooseCert {
+    float k1, k2;
+    __device__ inline LooseCert(Cert ct, float r2t, float kbits) {
+        const float skb = kslack(ct);
+        k1 = (0x1.8p-18f + skb + kbits) * (1.0f + 0x1p-7f);
+        k2 = ((0x1.8p-17f + skb + 0x1p-9f * (0x1.8p-18f + skb)) * r2t + ct.sab) * (1.0f + 0x1p-7f);
+    }
+    __device__ inline bool settled(float fb, float fs) const { return (fs - fb) > fmaf(fabsf(fb), k1, k2); }
 };
 
-// LDS of the vector tile (GAP: with candidate lists, the pass also returns
-// the relative gaps).
-template <int D, bool CULL, int P, bool GAP = false>
+// The certificate of one pixel from its two smallest computed costs (fb, fs)
+// and, where the pass returns it (GAP, or a pass over every seed), its relative
+// gap; U bounds the cost of the seeds left out of the lists.  True: not
+// settled.
+template <int D, bool GAP>
+__device__ inline bool vec_settle(const Geo &g, const Tile<D> &t, Cert ct, const float *s, float u0, float u1,
+                                  float u2, float fb, float fs, float kbits, float U, bool act, int p,
+                                  const PassOut &out) {
+    const float sab = ct.sab, skb = kslack(ct);
+    const float r2 = pixel_r2(ct, u0, u1, u2);
+    const float bb = fmaxf(fb, 0.0f);
+    const float B1 = bb + 0x1p-10f * (bb + r2);
+    const float e1 = e32_bound(B1, sqrtf(r2), r2);
+    const float thr = 2.0f * e1 + kbits * fmaxf(fabsf(fb), fabsf(fs)) + sab + skb * (B1 + r2);
+    const bool flag = !((fs - fb) > thr);
+    if (out.rel_gap && act && !flag) {
+        // the winner costs at most c1u; a scanned seed at least fs minus its
+        // bound, one left out of the lists more than their U
+        const float c1u = (fb + 0x1p-19f * fabsf(fb) + e1 + sab + skb * (B1 + r2)) * (1.0f + 0x1p-20f);
+        const float f2 = pad_inf(fs);
+        const float bs = fmaxf(f2, 0.0f);
+        const float B2 = bs + 0x1p-10f * (bs + r2);
+        float c2l = f2 == INFINITY ? f2 : f2 - 0x1p-19f * fabsf(f2) - e32_bound(B2, sqrtf(r2), r2) - sab - skb * (B2 + r2);
+        c2l = fminf(c2l, (U == INFINITY ? U : U - 0x1p-20f * fabsf(U))) * (1.0f - 0x1p-20f);
+        out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = fs > 0.0f ? gap_lower(c1u, c2l) : 0.0f;
+    }
+    return flag;
+}
+
+// The coefficients of staged seed q along axis 0 at a lane's other
+// coordinates: its cost at u0 is (a00 u0 + beta) u0 + alpha (2 fused
+// multiply-adds per pixel after 3 (2D) or 7 (3D) per seed).  The staged rows of
+// a seed: a00, 2a01, (a11 | 2a02), l0; then in 2D l1, c and in 3D a11, 2a12,
+// a22, l1 and l2, c.
+template <int D, int R>
+__device__ inline void staged_coef(const float4 (&sC)[D][R], int q, float u1, float u2, float &a00, float &beta,
+                                   float &alpha) {
+    const float4 c0 = sC[0][q];
+    const float4 c1 = sC[1][q];
+    a00 = c0.x;
+    if constexpr (D == 2) {
+        beta = fmaf(c0.y, u1, c0.w);
+        alpha = fmaf(fmaf(c0.z, u1, c1.x), u1, c1.y);
+    } else {
+        const float4 c2 = sC[2][q];
+        beta = fmaf(c0.y, u1, fmaf(c0.z, u2, c0.w));
+        alpha = fmaf(fmaf(c1.x, u1, fmaf(c1.y, u2, c1.w)), u1, fmaf(fmaf(c1.z, u2, c2.x), u2, c2.y));
+    }
+}
+
+// Stages seed i at position q; z, w ride in the last row's free lanes.
+template <int D, int R>
+__device__ inline void stage_coef(float4 (&sC)[D][R], int q, const double *qd, const double *ld, double cd, float z,
+                                  float w) {
+    sC[0][q] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], (float)ld[0]);
+    if constexpr (D == 2) {
+        sC[1][q] = make_float4((float)ld[1], (float)cd, z, w);
+    } else {
+        sC[1][q] = make_float4((float)qd[3], (float)qd[4], (float)qd[5], (float)ld[1]);
+        sC[2][q] = make_float4((float)ld[2], (float)cd, z, w);
+    }
+}
+// A padding seed: 1.7e38 everywhere.
+template <int D, int R>
+__device__ inline void stage_pad(float4 (&sC)[D][R], int q) {
+    for (int r = 0; r < D - 1; ++r) sC[r][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    sC[D - 1][q] = make_float4(0.0f, 1.7e38f, 0.0f, 0.0f);
+}
+
+// The cost's bits with the low 4 replaced by r (wave-uniform): integer order
+// is the costs' order (one instruction, which the compiler splits in two).
+__device__ inline int cost_key(float c, int r) {
+    int k;
+    asm("v_and_or_b32 %0, %1, -16, %2" : "=v"(k) : "v"(__float_as_int(c)), "s"(r));
+    return k;
+}
+
+// Short scan of the staged positions pair(j) = idx(j) | idx(j + 1) << 16 (j
+// even) below c2 (even): per pixel the best and second key so far, and in blk
+// the block of 16 positions where the best was last lowered.
+template <int D, int R, int P, class Pair>
+__device__ inline void key_scan(const float4 (&sC)[D][R], int c2, Pair pair, const float (&u0)[P], float u1, float u2,
+                                int (&best)[P], int (&second)[P], int (&blk)[P]) {
+    unsigned next = pair(0);
+    for (int q0 = 0; q0 < c2; q0 += 16) {
+        int old[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) old[p] = best[p];
+        for (int r2 = 0; r2 < 16 && q0 + r2 < c2; r2 += 2) {
+            const unsigned two = next;
+            next = pair(q0 + r2 + 2);  // the room is padded by a pair
+            float a00, beta, alpha, b00, betb, alphb;
+            staged_coef<D>(sC, (int)(two & 0xffffu), u1, u2, a00, beta, alpha);
+            staged_coef<D>(sC, (int)(two >> 16), u1, u2, b00, betb, alphb);
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                // two candidates at a time: 3 instructions for the pair's top two
+                const int ka = cost_key(fmaf(fmaf(a00, u0[p], beta), u0[p], alpha), r2);
+                const int kb = cost_key(fmaf(fmaf(b00, u0[p], betb), u0[p], alphb), r2 + 1);
+                second[p] = min(second[p], med3i(best[p], ka, kb));
+                best[p] = min3i(best[p], ka, kb);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < P; ++p) blk[p] = (best[p] != old[p]) ? q0 : blk[p];
+    }
+}
+
+// Seeds per staged chunk of the vector tile over every seed (in 2D N = 1000 is
+// one chunk).
+template <int D> struct VecCfg { static constexpr int kChunk = D == 2 ? 1024 : 512; };
+
+template <int D>
 struct VecSmem {
-    // seed coefficients of one chunk, + a dummy slot (index kChunk); with GAP
-    // the free lanes of the last row hold the seed's eigenvalue range (FP32,
-    // rounded outwards)
-    float4 sC[VecCfg<D, CULL>::kRows][VecCfg<D, CULL>::kChunk + 1];
-    float4 sB[CULL && GAP ? VecCfg<D, CULL>::kChunk : 1];  // (x - anchor, w - wmax) in FP32
-    int list[CULL ? kCullCap : 1];        // candidate seeds of the tile
-    int wl[kWaves][CULL ? kWaveCap : 1];  // staged positions of each wave's candidates; then its flagged pixels
-    MomSmem<CULL ? P : 1> mom[CULL ? 1 : 0];
-    CellQuad<D> own[kWaves];
-    double red[kWaves];
-    int cnt;
+    float4 sC[D][VecCfg<D>::kChunk];  // seed coefficients of one chunk
 };
 
-// With candidate lists they hold the seeds that can beat the box's owner
-// (owner_filter).  A pass that returns the relative gaps (GAP) needs a bound
-// of the cost of every seed it leaves out, so its lists come from separate
-// bounds of each seed's cost (build_candidates), which give one.
-template <int D, bool CULL, int P = kPv, bool GAP = false>
-__device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
-                                const double *eig, int b0, int b1, int b2, VecSmem<D, CULL, P, GAP> &sm,
-                                const PassOut &out, unsigned *qcount) {
+// The vector tile over every seed.
+template <int D, int P = kPv>
+__device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct, int b0, int b1, int b2,
+                                VecSmem<D> &sm, const PassOut &out, unsigned *qcount) {
     constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
-    constexpr int kVecChunk = VecCfg<D, CULL>::kChunk;
-    constexpr int kDummy = kVecChunk;  // staged slot whose cost is never the minimum
+    constexpr int kVecChunk = VecCfg<D>::kChunk;
     auto &sC = sm.sC;
-    int *s_list = sm.list;
     const Tile<D> t = tile_at<D, P>(b0, b1, b2);
     const bool lane_ok = lane_in_grid<D>(g, t);
-    int nscan = g.n;
-    bool full = true;
-    double Utile = INFINITY;  // no seed left out of the tile's list costs less
-    float Uwave = INFINITY;   // nor out of this wave's list
-    if (CULL) {
-        // ---- the candidate list, from the super-tile's list when it has one
-        const int ncand = tile_candidates<D, P, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &Utile);
-        full = ncand > kCullCap;
-        nscan = full ? g.n : ncand;
-        if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
-        if (!GAP && out.adaptive && ncand == 1 && !g.mass) {
-            credit_tile<D, P>(g, t, b0, b1, b2, s_list[0], out);
-            return;
-        }
-    }
-
-    // ---- the argmin over the candidates (as k_assign_fp32)
+    const int nscan = g.n;
     float s[3];
     double anc[3];
     for (int d = 0; d < D; ++d) {
@@ -1764,62 +1877,22 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     }
     const float u1 = ((float)(t.k[1] - t.anc[1]) + 0.5f) * s[1];
     const float u2 = D == 3 ? ((float)(t.k[2] - t.anc[2]) + 0.5f) * s[2] : 0.0f;
-    // cost of staged seed q at the pixels of this lane (2 fused
-    // multiply-adds per pixel after 3 (2D) or 7 (3D) per seed)
     auto lane_coef = [&](int q, float &a00, float &beta, float &alpha) {
-        const float4 c0 = sC[0][q];
-        const float4 c1 = sC[1][q];
-        if constexpr (D == 2) {
-            a00 = c0.x;
-            beta = fmaf(c0.y, u1, c0.w);
-            alpha = fmaf(fmaf(c0.z, u1, c1.x), u1, c1.y);
-        } else {
-            const float4 c2 = sC[2][q];
-            a00 = c0.x;
-            beta = fmaf(c0.y, u1, fmaf(c0.z, u2, c0.w));
-            alpha = fmaf(fmaf(c1.x, u1, fmaf(c1.y, u2, c1.w)), u1,
-                         fmaf(fmaf(c1.z, u2, c2.x), u2, c2.y));
-        }
-    };
-    // padding entries (and the dummy slot) cost 1.7e38 everywhere
-    auto pad = [&](int q) {
-        sC[0][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if constexpr (D == 2) {
-            sC[1][q] = make_float4(0.0f, 1.7e38f, 0.0f, 0.0f);
-        } else {
-            sC[1][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            sC[2][q] = make_float4(0.0f, 1.7e38f, 0.0f, 0.0f);
-        }
+        staged_coef<D>(sC, q, u1, u2, a00, beta, alpha);
     };
     auto stage = [&](int base, int cnt, int padded) {
-        if (threadIdx.x == 0) pad(kDummy);
         for (int q = threadIdx.x; q < padded; q += kThreads) {
             if (q >= cnt) {
-                pad(q);
+                stage_pad<D>(sC, q);
                 continue;
             }
-            const int i = full ? base + q : s_list[base + q];
             double qd[6], ld[3], cd, ed[3], wpd;
-            seed_terms<D>(sd, i, anc, wmax, qd, ld, &cd, ed, &wpd);
-            float lmn = 0.0f, lmx = 0.0f;
-            if constexpr (CULL && GAP) {
-                // rounded outwards: the FP32 bounds of the wave lists stay bounds
-                lmn = (float)eig[2 * (size_t)i] * (1.0f - 0x1p-20f);
-                lmx = (float)eig[2 * (size_t)i + 1] * (1.0f + 0x1p-20f);
-                sm.sB[q] = make_float4((float)ed[0], (float)ed[1], D == 3 ? (float)ed[2] : 0.0f, (float)wpd);
-            }
-            if constexpr (D == 2) {
-                sC[0][q] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], (float)ld[0]);
-                sC[1][q] = make_float4((float)ld[1], (float)cd, lmn, lmx);
-            } else {
-                sC[0][q] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], (float)ld[0]);
-                sC[1][q] = make_float4((float)qd[3], (float)qd[4], (float)qd[5], (float)ld[1]);
-                sC[2][q] = make_float4((float)ld[2], (float)cd, lmn, lmx);
-            }
+            seed_terms<D>(sd, base + q, anc, wmax, qd, ld, &cd, ed, &wpd);
+            stage_coef<D>(sC, q, qd, ld, cd, 0.0f, 0.0f);
         }
     };
     float fb[P], fs[P];  // the two smallest costs of each pixel
-    int pos[P];          // scan position of the best seed
+    int pos[P];          // the best seed
     bool lost[P];        // the winner was not found again (never expected)
 #pragma unroll
     for (int p = 0; p < P; ++p) {
@@ -1828,51 +1901,9 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
         pos[p] = 0;
         lost[p] = false;
     }
-    // Short scan of the staged positions idx(j), j < c16 (a multiple of 16).
-    // Only the first c2 (a multiple of 2) positions are scanned: the lists
-    // are padded to 16, but a short list wastes at most 1 slot.
-    bool keyed = false;  // the short scan ran: its costs lost their low 4 bits
-    auto key_scan = [&](int c2, auto idx) {
-        keyed = true;
-        int best[P], second[P], blk[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            best[p] = 0x7fffffff;
-            second[p] = 0x7fffffff;
-            blk[p] = 0;
-        }
-        for (int q0 = 0; q0 < c2; q0 += 16) {
-            int old[P];
-#pragma unroll
-            for (int p = 0; p < P; ++p) old[p] = best[p];
-            for (int r2 = 0; r2 < 16 && q0 + r2 < c2; r2 += 2) {
-#pragma unroll
-                for (int rr = 0; rr < 2; ++rr) {
-                    const int r = r2 + rr;
-                    float a00, beta, alpha;
-                    lane_coef(idx(q0 + r), a00, beta, alpha);
-#pragma unroll
-                    for (int p = 0; p < P; ++p) {
-                        const float c = fmaf(fmaf(a00, u0[p], beta), u0[p], alpha);
-                        const int key = (__float_as_int(c) & ~15) | r;
-                        second[p] = med3i(best[p], key, second[p]);
-                        best[p] = min(best[p], key);
-                    }
-                }
-            }
-#pragma unroll
-            for (int p = 0; p < P; ++p) blk[p] = (best[p] != old[p]) ? q0 : blk[p];
-        }
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            pos[p] = blk[p] + (best[p] & 15);
-            fb[p] = __int_as_float(best[p]);
-            fs[p] = __int_as_float(second[p]);
-        }
-    };
-    // Long scan of one staged chunk (positions idx(j), j < c16), merged into
-    // the running top two; winners found here get scan position base + j.
-    auto group_scan = [&](int c16, auto idx, int base) {
+    // Long scan of one staged chunk (positions j < c16), merged into the
+    // running top two; winners found here are seeds base + j.
+    auto group_scan = [&](int c16, int base) {
         int blk[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) blk[p] = -1;
@@ -1881,7 +1912,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 float a00, beta, alpha;
-                lane_coef(idx(q0 + r), a00, beta, alpha);
+                lane_coef(q0 + r, a00, beta, alpha);
 #pragma unroll
                 for (int p = 0; p < P; ++p) {
                     const float c = fmaf(fmaf(a00, u0[p], beta), u0[p], alpha);
@@ -1908,7 +1939,7 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             int ix = -1;
             for (int r = 0; r < 16; ++r) {
                 float a00, beta, alpha;
-                lane_coef(idx(blk[p] + r), a00, beta, alpha);
+                lane_coef(blk[p] + r, a00, beta, alpha);
                 const float c = fmaf(fmaf(a00, u0[p], beta), u0[p], alpha);
                 const bool hit = ix < 0 && c == fb[p];
                 ix = hit ? r : ix;
@@ -1919,46 +1950,187 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             fs[p] = fminf(fs[p], s2);
         }
     };
-    auto ident = [](int j) { return j; };
-    // per-wave lists: candidates of the tile, staged in one chunk
-    const bool per_wave = CULL && !full && nscan <= kVecChunk;
-    // the pixels' positions in the tile's list index its moment slots
-    const bool slots = per_wave && nscan <= kAccSlots && !g.mass;
-    int *wl = sm.wl[threadIdx.x >> 6];
-    int cntw = -1;  // this wave's list length; -1: scan the tile's list
-    if (per_wave) {
-        const int padded = (nscan + 15) & ~15;
-        __syncthreads();
-        stage(0, nscan, padded);
-        if constexpr (CULL)
-            if (slots && out.mom) moments_zero(sm.mom[0], nscan);
-        __syncthreads();
-        // the wave's box in the tile-local coordinates of the scan
-        float wlo[3] = {0.0f, 0.0f, 0.0f}, whi[3] = {0.0f, 0.0f, 0.0f};
-        {
-            const int k0w[3] = {t.org[0], t.org[1], t.org[2]};
-            const int extw[3] = {wave_ext(D, P, 0), wave_ext(D, P, 1), wave_ext(D, P, 2)};
-            for (int d = 0; d < D; ++d) {
-                const int a = k0w[d], b = max(a, min(a + extw[d], g.grid[d]) - 1);
-                wlo[d] = ((float)(a - t.anc[d]) + 0.5f) * s[d];
-                whi[d] = ((float)(b - t.anc[d]) + 0.5f) * s[d];
-            }
+    const bool keyed = nscan < kGroupScan;  // the short scan's costs lose their low 4 bits
+    if (!keyed) {
+        for (int base = 0; base < nscan; base += kVecChunk) {
+            const int cnt = min(kVecChunk, nscan - base);
+            const int padded = (cnt + 15) & ~15;
+            __syncthreads();
+            stage(base, cnt, padded);
+            __syncthreads();
+            group_scan(padded, base);
         }
-        int c = 0;  // candidates of the wave
+    } else {
+        __syncthreads();
+        stage(0, nscan, (nscan + 1) & ~1);
+        __syncthreads();
+        int best[P], second[P], blk[P];
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            best[p] = 0x7fffffff;
+            second[p] = 0x7fffffff;
+            blk[p] = 0;
+        }
+        key_scan<D>(sC, (nscan + 1) & ~1, [](int j) { return (unsigned)j | (unsigned)(j + 1) << 16; }, u0, u1, u2,
+                    best, second, blk);
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            pos[p] = blk[p] + (best[p] & 15);
+            fb[p] = __int_as_float(best[p]);
+            fs[p] = __int_as_float(second[p]);
+        }
+    }
+    const float kbits = keyed ? 0x1p-18f : 0.0f;
+    bool flag[P];
+    int lab[P];
+    const LooseCert loose(ct, pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f), kbits);
+    bool near = out.rel_gap != nullptr;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        flag[p] = lost[p] || !loose.settled(fb[p], fs[p]);
+        near = near || flag[p];
+        lab[p] = min(pos[p], nscan - 1);
+    }
+    if (__ballot(near)) {
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            flag[p] = vec_settle<D, false>(g, t, ct, s, u0[p], u1, u2, fb[p], fs[p], kbits, INFINITY, act[p], p, out) ||
+                      lost[p];
+    }
+    tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+}
+
+// LDS of the list tile (GAP: the pass also returns the relative gaps).
+constexpr int kListChunk = 256;  // candidates staged at a time, one per thread
+
+template <int D, int P, bool GAP>
+struct ListSmem {
+    // coefficients of the staged candidates, + a dummy (index kListChunk) whose
+    // cost is never the minimum; with GAP the free lanes of the last row hold
+    // the seed's eigenvalue range (FP32, rounded outwards)
+    float4 sC[D][kListChunk + 1];
+    float4 sB[GAP ? kListChunk : 1];  // (x - anchor, w - wmax) in FP32
+    int list[kCullCap];               // candidate seeds of the tile
+    // each wave's staged positions (and a pair of padding); then its flagged pixels
+    alignas(4) uint16_t wl[kWaves][(64 * P > kListChunk ? 64 * P : kListChunk) + 4];
+    MomSmem<P> mom;
+    CellQuad<D> own[kWaves];
+    double red[kWaves];
+    int cnt;
+};
+
+// The vector tile over the seeds that can win somewhere in the tile: its
+// candidates (tile_candidates; every seed when the list overflows) are staged
+// in chunks of kListChunk, nearly always one; each wave narrows a chunk to the
+// seeds that can win in its own box of pixels and scans those (key_scan).  A wave
+// left with one candidate needs no scan.  A pass that returns the relative
+// gaps (GAP) needs a bound of the cost of every seed it leaves out, so its lists
+// come from separate bounds of each seed's cost, which give one.
+//
+// Bound by the issue of vector instructions: a wave of 512 voxels takes about
+// 1310 of them on 256^3 with N = 10^4 (9 candidates, 45 each; the lists about
+// 400), at 80 % of the issue rate.  So what every wave repeats is kept short
+// (the settled / outside state of its pixels as bits of one register, a
+// certificate of 3 instructions per pixel, the minima of two candidates at a
+// time) and what is rare (several chunks, an unsettled pixel) shares its code.
+// Against the form that shared the tile over every seed and its two scans
+// (1694 instructions): 112 -> 96 us there, 12.0 -> 11.2 on 1024^2 with N = 1000,
+// 429 -> 379 ms for a batched fit of 512 maps.
+template <int D, int P, bool GAP = false>
+__device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig, int b0,
+                                 int b1, int b2, ListSmem<D, P, GAP> &sm, const PassOut &out, unsigned *qcount) {
+    constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
+    constexpr int kDummy = kListChunk;
+    auto &sC = sm.sC;
+    int *s_list = sm.list;
+    const Tile<D> t = tile_at<D, P>(b0, b1, b2);
+    const bool lane_ok = lane_in_grid<D>(g, t);
+    double Utile = INFINITY;  // no seed left out of the tile's list costs less
+    float Uwave = INFINITY;   // nor out of this wave's lists
+    // ---- the candidate list, from the super-tile's list when it has one
+    const int ncand = tile_candidates<D, P, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &Utile);
+    const bool full = ncand > kCullCap;
+    const int nscan = full ? g.n : ncand;
+    if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
+    if (!GAP && out.adaptive && ncand == 1 && !g.mass) {
+        credit_tile<D, P>(g, t, b0, b1, b2, s_list[0], out);
+        return;
+    }
+    const bool one = nscan <= kListChunk;
+    // the pixels' positions in the tile's list index its moment slots
+    const bool slots = one && !full && nscan <= kAccSlots && !g.mass;
+    auto seed_at = [&](int q) { return full ? q : s_list[q]; };
+
+    float s[3];
+    double anc[3];
+    for (int d = 0; d < D; ++d) {
+        s[d] = (float)g.s[d];
+        anc[d] = g.lo[d] + (double)t.anc[d] * g.s[d];
+    }
+    float u0[P];
+    const float k0f = (float)(t.k0w - t.anc[0]);
+#pragma unroll
+    for (int p = 0; p < P; ++p) u0[p] = (k0f + ((float)p + 0.5f)) * s[0];
+    const float u1 = ((float)(t.k[1] - t.anc[1]) + 0.5f) * s[1];
+    const float u2 = D == 3 ? ((float)(t.k[2] - t.anc[2]) + 0.5f) * s[2] : 0.0f;
+    // the wave's box: pixels ka .. kb along each axis
+    int ka[3] = {0, 0, 0}, kb[3] = {0, 0, 0};
+    for (int d = 0; d < D; ++d) {
+        const int e = max(t.org[d], min(t.org[d] + wave_ext(D, P, d), g.grid[d]) - 1);
+        ka[d] = t.org[d] - t.anc[d];
+        kb[d] = e - t.anc[d];
+    }
+    const float r2t = pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f);
+    uint16_t *wl = sm.wl[threadIdx.x >> 6];
+    int best[P], second[P];  // the two smallest keys of each pixel
+    int pos[P];              // the winner: its position in the wave's list (one chunk), else its seed
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        best[p] = 0x7fffffff;
+        second[p] = 0x7fffffff;
+        pos[p] = 0;
+    }
+    int c = 0;          // candidates of the wave in the last chunk
+    bool sure = false;  // the wave has a single candidate
+    for (int base = 0; base < nscan; base += kListChunk) {
+        const int cnt = min(kListChunk, nscan - base);
+        __syncthreads();
+        if ((int)threadIdx.x < cnt) {
+            const int q = threadIdx.x, i = seed_at(base + q);
+            double qd[6], ld[3], cd, ed[3], wpd;
+            seed_terms<D>(sd, i, anc, wmax, qd, ld, &cd, ed, &wpd);
+            float lmn = 0.0f, lmx = 0.0f;
+            if constexpr (GAP) {
+                // rounded outwards: the FP32 bounds of the wave lists stay bounds
+                lmn = (float)eig[2 * (size_t)i] * (1.0f - 0x1p-20f);
+                lmx = (float)eig[2 * (size_t)i + 1] * (1.0f + 0x1p-20f);
+                sm.sB[q] = make_float4((float)ed[0], (float)ed[1], D == 3 ? (float)ed[2] : 0.0f, (float)wpd);
+            }
+            stage_coef<D>(sC, q, qd, ld, cd, lmn, lmx);
+        }
+        if (threadIdx.x == kThreads - 1) stage_pad<D>(sC, kDummy);
+        if (slots && out.mom) moments_zero(sm.mom, nscan);
+        __syncthreads();
+        c = 0;
         auto append = [&](bool cand, int q) {
             const unsigned long long m = __ballot(cand);
             const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
                                                               __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            if (cand && c + below < kWaveCap) wl[c + below] = q;
+            if (cand) wl[c + below] = (uint16_t)q;
             c += (int)__popcll(m);
         };
-        if constexpr (CULL && GAP) {
+        if constexpr (GAP) {
             // FP32 bounds from the staged data, widened by a relative 1e-4 (far
             // above their rounding), so the wave list keeps every seed that
             // can win
+            float wlo[3] = {0.0f, 0.0f, 0.0f}, whi[3] = {0.0f, 0.0f, 0.0f};
+            for (int d = 0; d < D; ++d) {
+                wlo[d] = ((float)ka[d] + 0.5f) * s[d];
+                whi[d] = ((float)kb[d] + 0.5f) * s[d];
+            }
             auto wbounds = [&](int q, float &lb, float &ub) {
                 const float4 b = sm.sB[q];
-                const float4 ce = sC[VecCfg<D, CULL>::kRows - 1][q];  // .z, .w: eigenvalue range
+                const float4 ce = sC[D - 1][q];  // .z, .w: eigenvalue range
                 const float e[3] = {b.x, b.y, b.z};
                 float dist2 = 0.0f, far2 = 0.0f;
                 for (int d = 0; d < D; ++d) {
@@ -1994,34 +2166,33 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
                 ub = h - b.w + slack;
             };
             float um = INFINITY;
-            for (int q = t.lane; q < nscan; q += 64) {
+            for (int q = t.lane; q < cnt; q += 64) {
                 float lb, ub;
                 wbounds(q, lb, ub);
                 um = fminf(um, ub);
             }
             um = wave_min(um);
-            for (int q0 = 0; q0 < nscan; q0 += 64) {
+            for (int q0 = 0; q0 < cnt; q0 += 64) {
                 const int q = q0 + t.lane;
                 bool cand = false;
-                if (q < nscan) {
+                if (q < cnt) {
                     float lb, ub;
                     wbounds(q, lb, ub);
                     cand = lb <= um;
                 }
                 append(cand, q);
             }
-            Uwave = um;  // the tile's candidates left out below cost more
-        } else if constexpr (CULL) {
+            if (c < cnt) Uwave = fminf(Uwave, um);  // the chunk's candidates left out cost more
+        } else {
             // the owner's differences from the staged quadratics.  Each
             // monomial of a cost reaches it, the gradient or the bound through
             // fewer than 24 roundings of 2^-24 and their magnitudes sum to at
             // most 3 C + 6 r^2 (the vector tile's bound), r^2 = lam |u|^2 at the
             // tile's corner: 2^-16 (|C| + 2 r^2) is more than twice that
-            const float r2t = pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f);
             float uc[3], h[3];
             for (int d = 0; d < D; ++d) {
-                uc[d] = 0.5f * (wlo[d] + whi[d]);
-                h[d] = 0.5f * (whi[d] - wlo[d]) * (1.0f + 0x1p-20f);
+                uc[d] = (float)(ka[d] + kb[d] + 1) * (0.5f * s[d]);
+                h[d] = (float)(kb[d] - ka[d]) * (0.5f * (1.0f + 0x1p-20f) * s[d]);
             }
             auto staged_quad = [&](int q) {
                 CellQuad<D> r;
@@ -2049,145 +2220,109 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
             };
             const float sl = ct.lsl;
             // the owner: the wave's candidate of least cost at its centre
-            float best = INFINITY;
-            int bq = 0;
             CellQuad<D> mine;
             mine.c = INFINITY;
-            for (int q = t.lane; q < nscan; q += 64) {
-                mine = staged_quad(q);
-                if (mine.c < best) {
-                    best = mine.c;
+            if (t.lane < cnt) mine = staged_quad(t.lane);
+            float best = mine.c;
+            int bq = t.lane;
+            for (int q = t.lane + 64; q < cnt; q += 64) {
+                const float v = staged_quad(q).c;
+                if (v < best) {
+                    best = v;
                     bq = q;
                 }
             }
             const int lead = max(0, __ffsll(__ballot(best == wave_min(best))) - 1);
-            if (nscan <= 64) {
-                append(t.lane < nscan && can_beat<D>(mine, lane_quad(mine, lead), h, sl), t.lane);
+            if (cnt <= 64) {
+                append(t.lane < cnt && can_beat<D>(mine, lane_quad(mine, lead), h, sl), t.lane);
             } else {
                 const CellQuad<D> own = staged_quad(__builtin_amdgcn_readlane(bq, lead));
-                for (int q0 = 0; q0 < nscan; q0 += 64) {
+                for (int q0 = 0; q0 < cnt; q0 += 64) {
                     const int q = q0 + t.lane;
-                    append(q < nscan && can_beat<D>(staged_quad(min(q, nscan - 1)), own, h, sl), q);
+                    append(q < cnt && can_beat<D>(staged_quad(min(q, cnt - 1)), own, h, sl), q);
                 }
             }
         }
-        const int c16 = (c + 15) & ~15;
-        if (c > 0 && c16 <= kWaveCap) {
-            for (int j = c + t.lane; j < c16; j += 64) wl[j] = kDummy;
-            cntw = c;
-            if (c == nscan) Uwave = INFINITY;  // none of the tile's candidates was left out
-        } else {
-            Uwave = INFINITY;
-        }
-        // the list is read back by other lanes of the wave only
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (cntw >= 0) {
-            const int c16w = (cntw + 15) & ~15;
-            auto widx = [&](int j) { return wl[j]; };
-            if (cntw >= kGroupScan) group_scan(c16w, widx, 0);
-            else key_scan((cntw + 1) & ~1, widx);
-        } else if (nscan >= kGroupScan) {
-            group_scan(padded, ident, 0);
-        } else {
-            key_scan((nscan + 1) & ~1, ident);
-        }
-    } else if (nscan >= kGroupScan) {
-        for (int base = 0; base < nscan; base += kVecChunk) {
-            const int cnt = min(kVecChunk, nscan - base);
-            const int padded = (cnt + 15) & ~15;
-            __syncthreads();
-            stage(base, cnt, padded);
-            __syncthreads();
-            group_scan(padded, ident, base);
-        }
-    } else {
-        const int padded = (nscan + 15) & ~15;
-        __syncthreads();
-        stage(0, nscan, padded);
-        __syncthreads();
-        key_scan((nscan + 1) & ~1, ident);
-    }
-    const float sab = ct.sab, skb = kslack(ct);
-    const float kbits = keyed ? 0x1p-18f : 0.0f;
-    bool flag[P];
-    int lab[P];
-    // first a threshold that needs no square root and holds for the whole
-    // tile: 4 r sqrt(B) <= 2 B + 2 r^2 and r at the tile's corner, so thr <=
-    // 2^-20 (6 B1 + 12 r^2) + ..., linear in the best cost.  Nearly every wave
-    // settles all of its pixels by it (5 instructions per pixel instead of
-    // about 45 with two square roots).
-    const float r2t = pixel_r2(ct, 0.5f * E0 * s[0], 0.5f * E1 * s[1], D == 3 ? 0.5f * E2 * s[2] : 0.0f);
-    const float kb1 = (0x1.8p-18f + skb) * (1.0f + 0x1p-9f);
-    const float kb2 = (0x1.8p-17f + skb + 0x1p-9f * (0x1.8p-18f + skb)) * r2t * (1.0f + 0x1p-9f) + sab;
-    bool near = false;
+        if (t.lane < 3) wl[c + t.lane] = kDummy;
+        wave_lds_sync();  // the list is read back by other lanes of the wave only
+        sure = !GAP && one && c == 1;
+        if (sure) break;
+        const unsigned *pairs = reinterpret_cast<const unsigned *>(wl);
+        auto pair = [&](int j) { return pairs[j >> 1]; };
+        int blk[P];
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const float thr = fmaf(fmaxf(fb[p], 0.0f), kb1, fmaf(kbits, fmaxf(fabsf(fb[p]), fabsf(fs[p])), kb2));
-        flag[p] = lost[p] || !((fs[p] - fb[p]) > thr);
-        near = near || flag[p];
-    }
-    if ((!CULL || GAP) && out.rel_gap) near = true;
-    if (__ballot(near)) {
+        for (int p = 0; p < P; ++p) blk[p] = one ? 0 : -1;
+        key_scan<D>(sC, (c + 1) & ~1, pair, u0, u1, u2, best, second, blk);
+        if (one) {
 #pragma unroll
-    for (int p = 0; p < P; ++p) {
-        const float r2 = pixel_r2(ct, u0[p], u1, u2);
-        const float bb = fmaxf(fb[p], 0.0f);
-        const float B1 = bb + 0x1p-10f * (bb + r2);
-        const float thr = 2.0f * e32_bound(B1, sqrtf(r2), r2) + kbits * fmaxf(fabsf(fb[p]), fabsf(fs[p])) +
-                          sab + skb * (B1 + r2);
-        flag[p] = lost[p] || !((fs[p] - fb[p]) > thr);
-        if ((!CULL || GAP) && out.rel_gap && act[p] && !flag[p]) {
-            // the winner costs at most c1u; a scanned seed at least fs minus
-            // its bound, one left out of the lists more than the lists' U
-            const float c1u = (fb[p] + 0x1p-19f * fabsf(fb[p]) + e32_bound(B1, sqrtf(r2), r2) + sab +
-                               skb * (B1 + r2)) * (1.0f + 0x1p-20f);
-            const float f2 = pad_inf(fs[p]);
-            const float bs = fmaxf(f2, 0.0f);
-            const float B2 = bs + 0x1p-10f * (bs + r2);
-            float c2l = f2 == INFINITY
-                            ? f2
-                            : f2 - 0x1p-19f * fabsf(f2) - e32_bound(B2, sqrtf(r2), r2) - sab - skb * (B2 + r2);
-            const float uc = fminf((float)Utile, Uwave);
-            c2l = fminf(c2l, (uc == INFINITY ? uc : uc - 0x1p-20f * fabsf(uc))) * (1.0f - 0x1p-20f);
-            out.rel_gap[pixel_index<D>(g, t.k0w + p, t)] = fs[p] > 0.0f ? gap_lower(c1u, c2l) : 0.0f;
+            for (int p = 0; p < P; ++p) pos[p] = blk[p] + (best[p] & 15);
+        } else {
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+                if (blk[p] >= 0) pos[p] = seed_at(base + min((int)wl[blk[p] + (best[p] & 15)], cnt - 1));
         }
     }
+    // bits of the lane's pixels: outside the grid, not settled
+    const unsigned beyond = ~0u << (lane_ok ? max(0, min(P, g.grid[0] - t.k0w)) : 0);
+    unsigned open = 0u;
+    if (!sure) {
+        constexpr float kbits = 0x1p-18f;  // the keys' low bits
+        const LooseCert loose(ct, r2t, kbits);
+        bool near = GAP;
+#pragma unroll
+        for (int p = 0; p < P; ++p)
+            near = near || !loose.settled(__int_as_float(best[p]), __int_as_float(second[p]));
+        if (__ballot(near)) {
+            const float U = fminf((float)Utile, Uwave);
+#pragma unroll
+            for (int p = 0; p < P; ++p) {
+                const float fb = __int_as_float(best[p]), fs = __int_as_float(second[p]);
+                if (GAP || __ballot(!loose.settled(fb, fs)))
+                    open |= vec_settle<D, GAP>(g, t, ct, s, u0[p], u1, u2, fb, fs, kbits, U, !(beyond >> p & 1u), p,
+                                               out)
+                                ? 1u << p
+                                : 0u;
+            }
+            open &= ~beyond;
+        }
     }
-    if (!slots || out.labels) {
+    if (slots && out.mom) {
+        unsigned v[(P + 3) / 4];
+#pragma unroll
+        for (int hh = 0; hh < (P + 3) / 4; ++hh) {
+            v[hh] = 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[hh] |= (unsigned)(4 * hh + j < P ? pos[4 * hh + j < P ? 4 * hh + j : 0] : 0) << (8 * j);
+        }
+        const unsigned off = (beyond | open) & ((1u << P) - 1u);
+        if (P % 4 != 0 || __ballot(off != 0u)) {
+            // a bit of off into the low bit of its byte
+#pragma unroll
+            for (int hh = 0; hh < (P + 3) / 4; ++hh)
+                v[hh] |= (((beyond | open) >> (4 * hh) & 15u) * 0x00204081u & 0x01010101u) * 127u;
+        }
+        moments_add<D, P>(sm.mom, t.lane, v, c, [&](int j) { return (int)wl[j]; });
+    }
+    if (!slots || out.labels || __ballot(open != 0u)) {
+        bool act[P], flag[P];
 #pragma unroll
         for (int p = 0; p < P; ++p) {
-            if (cntw >= 0) {
-                lab[p] = s_list[wl[min(pos[p], cntw - 1)]];
-            } else {
-                const int ps = min(pos[p], nscan - 1);
-                lab[p] = full ? ps : s_list[ps];
-            }
+            act[p] = !(beyond >> p & 1u);
+            flag[p] = open >> p & 1u;
         }
-    }
-    if constexpr (CULL) {
-        if (slots) {
-            if (out.labels) write_labels<D, P>(g, t, act, lab, flag, out);
-            if (out.mom) {
-                // a wave's list is there unless its pixels are all flagged
-                int idx[P];
+        if (!slots || out.labels) {
+            int lab[P];
 #pragma unroll
-                for (int p = 0; p < P; ++p) idx[p] = act[p] && !flag[p] ? min(pos[p], kAccSlots - 1) : 127;
-                const bool wlist = cntw >= 0;
-                moments_add<D, P>(sm.mom[0], t.lane, idx, wlist ? cntw : nscan, [&](int j) { return wlist ? wl[j] : j; });
-            }
-        } else {
-            tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+            for (int p = 0; p < P; ++p)
+                lab[p] = !one ? pos[p] : c > 0 ? seed_at(wl[min(pos[p], c - 1)]) : 0;  // none: all flagged
+            if (!slots) tile_epilogue<D, P>(g, t, act, lab, flag, out, nullptr);
+            else write_labels<D, P>(g, t, act, lab, flag, out);
         }
-        recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : s_list, full ? g.n : nscan,
-                              reinterpret_cast<uint16_t *>(wl), out, qcount, wmax, Utile);
-        if (slots && out.mom) {
-            __syncthreads();
-            moments_flush<D, P>(sm.mom[0], t.anc, s_list, nscan, out.mom);
-        }
-    } else {
-        tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
+        recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : s_list, nscan, wl, out, qcount, wmax, Utile);
+    }
+    if (slots && out.mom) {
+        __syncthreads();
+        moments_flush<D, P>(sm.mom, t.anc, s_list, nscan, out.mom);
     }
 }
 

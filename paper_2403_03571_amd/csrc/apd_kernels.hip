@@ -46,7 +46,7 @@ using namespace dev;
 // seed per thread; above, blocks of kRedThreads whose last one to finish
 // combines the partials.  The exchange through memory (fences that reach the
 // other XCDs, the ticket, the partials read back) costs more than what the
-// blocks share: 8.2 and 7.9 us for 1000 seeds in four blocks, ONE_US in one.
+// blocks share: prep 8.2 us for 1000 seeds in four blocks, 4.7 in one.
 constexpr int kRedThreads = 256;
 constexpr int kOneBlock = 1024;
 
@@ -279,21 +279,26 @@ __global__ __launch_bounds__(kThreads) void k_assign_fp64(Geo g, Seeds sd, const
 
 // ------------------------------------------------ k_assign_fp32 / _cull
 
-// One block per tile of the vector single-precision kernel
-// (dev::vec_tile): every seed, or the tile's candidate seeds.
-template <int D, bool CULL, int P, bool GAP>
-__global__ __launch_bounds__(kThreads, (CULL && P == 4 && !GAP) ? 5 : 4) void k_assign_vec(Geo g, Seeds sd, Scalars *sc,
-                                                        const double *eig, PassOut out) {
-    __shared__ VecSmem<D, CULL, P, GAP> sm;
-    if constexpr (D == 2)
-        vec_tile<2, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, blockIdx.y, blockIdx.x, 0, sm, out,
-                             &sc->qcount);
-    else
-        vec_tile<3, CULL, P, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm,
-                             out, &sc->qcount);
+// One block per tile of the vector single-precision kernel: every seed
+// (dev::vec_tile), or the tile's candidate seeds (dev::list_tile).
+template <int D, int P>
+__global__ __launch_bounds__(kThreads, 4) void k_assign_vec(Geo g, Seeds sd, Scalars *sc, PassOut out) {
+    __shared__ VecSmem<D> sm;
+    const Cert ct{sc->lam, sc->kap, sc->sab, sc->lsl};
+    if constexpr (D == 2) vec_tile<2, P>(g, sd, sc->wmax, ct, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
+    else vec_tile<3, P>(g, sd, sc->wmax, ct, blockIdx.z, blockIdx.y, blockIdx.x, sm, out, &sc->qcount);
 }
 
-
+template <int D, int P, bool GAP>
+__global__ __launch_bounds__(kThreads, (P == 4 && !GAP) ? 5 : 4) void k_assign_list(Geo g, Seeds sd, Scalars *sc,
+                                                                                    const double *eig, PassOut out) {
+    __shared__ ListSmem<D, P, GAP> sm;
+    const Cert ct{sc->lam, sc->kap, sc->sab, sc->lsl};
+    if constexpr (D == 2)
+        list_tile<2, P, GAP>(g, sd, sc->wmax, ct, eig, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
+    else
+        list_tile<3, P, GAP>(g, sd, sc->wmax, ct, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm, out, &sc->qcount);
+}
 
 // ------------------------------------------------------ k_assign_mfma
 
@@ -618,13 +623,20 @@ dim3 tile_grid(const Geo &g) {
 // 8 pixels per lane halve the per-seed work of the lanes but give 2048-pixel
 // tiles; below 1024 such tiles (4 waves per SIMD on 256 CUs) the 4-pixel
 // form keeps the chip full.
-template <int D, bool CULL, bool GAP = false>
-hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
-                      const PassOut &out, hipStream_t st) {
-    if (vec_pixels_per_lane(g, CULL) == 8)
-        k_assign_vec<D, CULL, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+template <int D>
+hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out, hipStream_t st) {
+    if (vec_pixels_per_lane(g, false) == 8) k_assign_vec<D, 8><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, out);
+    else k_assign_vec<D, 4><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, out);
+    return hipGetLastError();
+}
+
+template <int D, bool GAP>
+hipError_t launch_list(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig, const PassOut &out,
+                       hipStream_t st) {
+    if (vec_pixels_per_lane(g, true) == 8)
+        k_assign_list<D, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
     else
-        k_assign_vec<D, CULL, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        k_assign_list<D, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
     return hipGetLastError();
 }
 
@@ -686,8 +698,7 @@ hipError_t launch_assign_fp64(const Geo &g, const Seeds &sd, Scalars *sc, const 
 hipError_t launch_assign_fp32(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out,
                               hipStream_t st) {
     (void)hipGetLastError();  // clear a stale error left by an earlier call
-    return g.dim == 2 ? launch_vec<2, false>(g, sd, sc, nullptr, out, st)
-                      : launch_vec<3, false>(g, sd, sc, nullptr, out, st);
+    return g.dim == 2 ? launch_vec<2>(g, sd, sc, out, st) : launch_vec<3>(g, sd, sc, out, st);
 }
 
 template <int D>
@@ -711,10 +722,10 @@ hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const 
                               const PassOut &out, hipStream_t st) {
     (void)hipGetLastError();
     if (out.rel_gap)
-        return g.dim == 2 ? launch_vec<2, true, true>(g, sd, sc, eig, out, st)
-                          : launch_vec<3, true, true>(g, sd, sc, eig, out, st);
-    return g.dim == 2 ? launch_vec<2, true>(g, sd, sc, eig, out, st)
-                      : launch_vec<3, true>(g, sd, sc, eig, out, st);
+        return g.dim == 2 ? launch_list<2, true>(g, sd, sc, eig, out, st)
+                          : launch_list<3, true>(g, sd, sc, eig, out, st);
+    return g.dim == 2 ? launch_list<2, false>(g, sd, sc, eig, out, st)
+                      : launch_list<3, false>(g, sd, sc, eig, out, st);
 }
 
 hipError_t launch_assign_mfma(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out,

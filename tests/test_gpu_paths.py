@@ -117,6 +117,37 @@ def test_moments_by_the_cells_of_a_tile(ctx, dim, grid, n):
         ctx.apd_set_pixels_per_lane(0)
 
 
+@pytest.mark.parametrize("dim,grid", [(2, (64, 33)), (3, (17, 9, 33))])
+@pytest.mark.parametrize("n", [1, 3, 95, 96, 97, 255, 258, 700, 3000])
+def test_tile_scans_by_the_number_of_candidates(ctx, dim, grid, n):
+    """One candidate, one staged chunk of a tile, several, and every seed for
+    want of room in the list, short and long scans over every seed: labels,
+    counts and the certified gaps of both tile shapes against the oracle."""
+    import torch
+    inst = S.custom(dim, n, grid, seed=n, sigma=0.2)
+    w = np.random.default_rng(n).uniform(-0.2, 0.2, n) * n ** (-2.0 / dim)
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    ref, best, second = O.assign(inst, w)
+    ctx.apd_set_variant(1)  # over every seed, the vector tile at any number
+    try:
+        for ppl in (4, 8):
+            ctx.apd_set_pixels_per_lane(ppl)
+            for lists in (True, False):
+                ctx.apd_set_culling(lists)
+                np.testing.assert_array_equal(ctx.apd_assign(prob, wd, prec="fp32").cpu().numpy(), ref)
+                if n > 1:
+                    lab, gap = ctx.apd_assign(prob, wd, prec="fp32", rel_gap=True)
+                    np.testing.assert_array_equal(lab.cpu().numpy(), ref)
+                    rel = (second - best) / (second + w.max())
+                    assert np.all(gap.cpu().numpy() <= rel * (1 + 1e-6) + 1e-12)
+                out = ctx.apd_dual_objective_grad(prob, wd, counts=True)
+                np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, minlength=n))
+    finally:
+        ctx.apd_set_pixels_per_lane(0)
+        ctx.apd_set_culling(True)
+        ctx.apd_set_variant(2)
+
+
 @pytest.mark.parametrize("S_", [1, 15, 16, 17, 127, 129, 513, 4095, 4097])
 def test_network_by_the_number_of_samples(ctx, S_):
     """Blocks of 16 samples, slices of the samples and chunks of 128, the
