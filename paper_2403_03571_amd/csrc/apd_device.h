@@ -1502,7 +1502,7 @@ template <int D, int T>
 struct SuperSmem {
     int list[kSuperCap];
     CellQuad<D> own[T / 64];
-    double red[T / 64];
+    float red[T / 64];
     int cnt;
 };
 
@@ -1512,10 +1512,19 @@ struct SuperSmem {
 //   lambda_min dist(x, box)^2 - w' <= U = min_k lambda_max maxdist(x_k, box)^2 - w_k',
 // then, unless the pass returns the relative gaps (whose tiles need lists
 // that bound the cost of every seed left out) or its costs are of another
-// power, the survivors by the owner's difference.  A seed that cannot win anywhere in the super-tile cannot win
-// in any of its tiles.  All T threads of the block call it.  A
-// thread takes the seeds four at a time, so that their loads are in flight
-// together.
+// power, the survivors by the owner's difference.  A seed that cannot win
+// anywhere in the super-tile cannot win in any of its tiles.  All T threads of
+// the block call it.
+//
+// Bound by the reads of every seed's 48 bytes by every block (256^3, N = 10^4:
+// 512 blocks, 246 MB from the L2s; with the bounds in double it was bound by
+// instruction issue as well).  The bounds of squared norms are formed in FP32
+// from offsets taken in double: dist and far are off by at most 2^-22 far each,
+// so the bounds by less than 2^-19 (lambda_max far^2 + |w'|); twice that, and
+// the lists' own slack (underflow), widens them.  A thread takes the seeds four at a time without a branch between, so
+// that their loads are in flight together, and a wave reserves the places of
+// all its seeds at once.  32.5 -> 24.5 us there (512 threads, one round of
+// blocks; 1024 threads 28), 6.9 -> 5.6 on 1024^2 with N = 1000.
 template <int D, int T>
 __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
                                        const PassOut &out, int st, float4 *list, int *count, int cap,
@@ -1531,58 +1540,110 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         if (threadIdx.x == 0) *count = cap + 1;
         return;
     }
-    constexpr int kUnroll = 4;
-    constexpr int kKeep = 12;  // a thread's lower bounds kept in registers
-    const bool in_regs = g.n <= kKeep * T;
-    float lbr[kKeep];
-    double umin = INFINITY;
-    if (in_regs) {
+    double ctr[D];
+    float h[D];
+    const float hh = box_centre<D>(blo, bhi, ctr, h);
+    auto bounds_power = [&](int i, float &lb, float &ub) {
+        double l, u;
+        cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &l, &u, g.power);
+        lb = __double2float_rd(l);
+        ub = __double2float_ru(u);
+    };
+    auto bounds_square = [&](int i, float &lb, float &ub) {
+        float dist2 = 0.0f, far2 = 0.0f;
 #pragma unroll
-        for (int r = 0; r < kKeep; ++r) {
-            const int i = threadIdx.x + r * T;
-            lbr[r] = INFINITY;
-            if (r * T < g.n && i < g.n) {
-                double lb, ub;
-                cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
-                lbr[r] = __double2float_rd(lb);
-                umin = fmin(umin, ub);
+        for (int d = 0; d < D; ++d) {
+            const float e = fabsf((float)(sd.x[(size_t)i * D + d] - ctr[d]));
+            const float dd = fmaxf(0.0f, e - h[d]), fd = e + h[d];
+            dist2 = fmaf(dd, dd, dist2);
+            far2 = fmaf(fd, fd, far2);
+        }
+        const float wp = (float)(sd.w[i] - wmax);
+        const double2 ev = reinterpret_cast<const double2 *>(eig)[i];
+        const float u = (float)ev.y * far2, slack = fmaf(0x1p-18f, u + fabsf(wp), ct.lsl);
+        lb = fmaf((float)ev.x, dist2, -wp) - slack;
+        ub = (u - wp) + slack;
+    };
+    constexpr int kUnroll = 4;
+    constexpr int kKeep = T > kThreads ? 20 : 8;  // a thread's lower bounds kept in registers
+    const bool in_regs = g.n <= kKeep * T;
+    float lbr[kKeep], umin = INFINITY;
+    auto scan = [&](auto bounds) {
+        if (in_regs) {
+#pragma unroll
+            for (int r0 = 0; r0 < kKeep; r0 += kUnroll) {
+#pragma unroll
+                for (int r = r0; r < r0 + kUnroll; ++r) lbr[r] = INFINITY;
+                if (r0 * T >= g.n) continue;
+#pragma unroll
+                for (int r = r0; r < r0 + kUnroll; ++r) {
+                    // past the end the last seed again (no branch between the loads)
+                    const int i = threadIdx.x + r * T;
+                    float lb, ub;
+                    bounds(min(i, g.n - 1), lb, ub);
+                    lbr[r] = i < g.n ? lb : INFINITY;
+                    umin = fminf(umin, ub);
+                }
+            }
+        } else {
+#pragma unroll kUnroll
+            for (int i = threadIdx.x; i < g.n; i += T) {
+                float lb, ub;
+                bounds(i, lb, ub);
+                umin = fminf(umin, ub);
             }
         }
-    } else {
-#pragma unroll kUnroll
-        for (int i = threadIdx.x; i < g.n; i += T) {
-            double lb, ub;
-            cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
-            umin = fmin(umin, ub);
-        }
-    }
+    };
+    const bool square = g.power == 2;
+    if (square) scan(bounds_square);
+    else scan(bounds_power);
     umin = wave_min(umin);
     if (lane == 0) sm.red[threadIdx.x >> 6] = umin;
     if (threadIdx.x == 0) sm.cnt = 0;
     __syncthreads();
-    double U = sm.red[0];
+    float U = sm.red[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) U = fmin(U, sm.red[w]);
-    auto append = [&](bool cand, int i) {
-        const unsigned long long m = __ballot(cand);
-        if (!m) return;
+    for (int w = 1; w < T / 64; ++w) U = fminf(U, sm.red[w]);
+    auto rank = [&](unsigned long long m) {
+        return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+    };
+    auto reserve = [&](int n) {
         int base = 0;
-        if (lane == 0) base = atomicAdd(&sm.cnt, (int)__popcll(m));
-        base = __builtin_amdgcn_readfirstlane(base);
-        const int below = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                          __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-        if (cand && base + below < kSuperCap) sm.list[base + below] = i;
+        if (lane == 0) base = atomicAdd(&sm.cnt, n);
+        return __builtin_amdgcn_readfirstlane(base);
     };
     if (in_regs) {
+        // one reservation for all of a wave's seeds
+        unsigned long long keep[kKeep];
+        int n = 0;
 #pragma unroll
-        for (int r = 0; r < kKeep; ++r)
-            if (r * T < g.n) append((int)threadIdx.x + r * T < g.n && (double)lbr[r] <= U, threadIdx.x + r * T);
+        for (int r = 0; r < kKeep; ++r) {
+            keep[r] = __ballot((int)threadIdx.x + r * T < g.n && !(lbr[r] > U));
+            n += (int)__popcll(keep[r]);
+        }
+        if (n) {
+            int base = reserve(n);
+#pragma unroll
+            for (int r = 0; r < kKeep; ++r) {
+                if (!keep[r]) continue;
+                const int pos = base + rank(keep[r]);
+                if ((keep[r] >> lane & 1ull) && pos < kSuperCap) sm.list[pos] = threadIdx.x + r * T;
+                base += (int)__popcll(keep[r]);
+            }
+        }
     } else {
         for (int i0 = 0; i0 < g.n; i0 += T) {
             const int i = i0 + threadIdx.x;
-            double lb = INFINITY, ub;
-            if (i < g.n) cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &lb, &ub, g.power);
-            append(i < g.n && lb <= U, i);
+            float lb = INFINITY, ub;
+            if (i < g.n) {
+                if (square) bounds_square(i, lb, ub);
+                else bounds_power(i, lb, ub);
+            }
+            const bool cand = i < g.n && !(lb > U);
+            const unsigned long long m = __ballot(cand);
+            if (!m) continue;
+            const int pos = reserve((int)__popcll(m)) + rank(m);
+            if (cand && pos < kSuperCap) sm.list[pos] = i;
         }
     }
     __syncthreads();
@@ -1591,9 +1652,6 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         if (threadIdx.x == 0) *count = cap + 1;
         return;
     }
-    double ctr[D];
-    float h[D];
-    const float hh = box_centre<D>(blo, bhi, ctr, h);
     int n;
     if (out.rel_gap || g.power != 2) {
         for (int q = threadIdx.x; q < min(m, cap); q += T)

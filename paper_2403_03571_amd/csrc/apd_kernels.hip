@@ -258,7 +258,7 @@ __global__ __launch_bounds__(256) void k_mass_total(int64_t J, const uint8_t *ma
     if (threadIdx.x == 0) atomicAdd(&sc->qtotal, red[0]);
 }
 
-// Seeds above which a super-tile's list is built by 1024 threads.
+// Seeds above which a super-tile's list is built by 512 threads.
 constexpr int kSuperWideSeeds = 2048;
 
 // ------------------------------------------------------ k_assign_fp64
@@ -706,7 +706,7 @@ static void launch_super(const Geo &g, const Seeds &sd, const Scalars *sc, const
                          float4 *list, int *count, hipStream_t st) {
     const int nb = out.nst[0] * out.nst[1] * out.nst[2];
     // a block reads every seed: many seeds need many loads in flight
-    if (g.n > kSuperWideSeeds) k_super_cull<D, 1024><<<nb, 1024, 0, st>>>(g, sd, sc, eig, out, list, count);
+    if (g.n > kSuperWideSeeds) k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, list, count);
     else k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, list, count);
 }
 
