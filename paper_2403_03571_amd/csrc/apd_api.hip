@@ -233,6 +233,9 @@ struct ListGeometry {
     int sf[3] = {1, 1, 1};
     int nst[3] = {1, 1, 1};
     int64_t tiles = 0, nsuper = 0;
+    int hf[3] = {1, 1, 1};  // super-tiles of a region per axis
+    int nh[3] = {1, 1, 1};
+    int64_t nregion = 0;    // 0: no regions
 };
 
 ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, apd_precision prec) {
@@ -250,6 +253,18 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, apd_precisio
         L.sf[d] = std::max(1, std::min(8, f));
         L.nst[d] = (L.ntile[d] + L.sf[d] - 1) / L.sf[d];
         L.nsuper *= L.nst[d];
+    }
+    // s super-tiles each read n seeds; h regions read n and leave each
+    // super-tile about c n / h (c = 8 for the margin around the region's box):
+    // least at h = sqrt(c s)
+    if (p->power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
+        const int f = std::max(2, (int)lround(pow((double)L.nsuper / 8.0, 0.5 / p->dim)));
+        L.nregion = 1;
+        for (int d = 0; d < 3; ++d) {
+            L.hf[d] = d < p->dim ? f : 1;
+            L.nh[d] = (L.nst[d] + L.hf[d] - 1) / L.hf[d];
+            L.nregion *= L.nh[d];
+        }
     }
     return L;
 }
@@ -298,6 +313,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     if (g.power != 2 && prec != APD_FP64)
         return fail(c, APD_ERR_INVALID_ARG, "costs of power %d run in APD_FP64 only", g.power);
     int tp = 0;  // pixels per lane of the lists' tiles
+    apd::Regions rg;
     if (cull) {
         const ListGeometry L = list_geometry(p, g, prec);
         out.tp = tp = L.tp;
@@ -306,7 +322,8 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
                 return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
         } else {
             b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, p->n);
-            const size_t rec_bytes = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim) * sizeof(float4);
+            const size_t super_recs = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim);
+            const size_t rec_bytes = (super_recs + (size_t)L.nregion * 2 * apd::kRegionCap) * sizeof(float4);
             if (rec_bytes > c->super_bytes) {
                 (void)hipFree(c->super_lists);
                 c->super_lists = nullptr;
@@ -316,17 +333,26 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
                                 (long long)L.nsuper);
                 c->super_bytes = rec_bytes;
             }
-            if (L.nsuper > c->cap_super) {
+            if (L.nsuper + L.nregion > c->cap_super) {
                 (void)hipFree(c->super_count);
                 c->super_count = nullptr;
                 c->cap_super = 0;
-                if (hipMalloc(&c->super_count, (size_t)L.nsuper * sizeof(int)) != hipSuccess)
+                if (hipMalloc(&c->super_count, (size_t)(L.nsuper + L.nregion) * sizeof(int)) != hipSuccess)
                     return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
                                 (long long)L.nsuper);
-                c->cap_super = L.nsuper;
+                c->cap_super = L.nsuper + L.nregion;
             }
             b.super_lists = c->super_lists;
             b.super_count = c->super_count;
+            if (L.nregion) {
+                rg.rec = b.super_lists + super_recs;
+                rg.count = b.super_count + L.nsuper;
+                rg.cap = apd::kRegionCap;
+                for (int d = 0; d < 3; ++d) {
+                    rg.hf[d] = L.hf[d];
+                    rg.nh[d] = L.nh[d];
+                }
+            }
         }
         out.adaptive = c->adaptive;
         out.credited = &b.sc->credited;
@@ -337,7 +363,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
         // up to a block's threads of seeds the tiles read them all at once
         if (L.sf[0] * L.sf[1] * L.sf[2] > 1 && p->n > apd::kThreads) {
             out.super_cap = b.super_cap;
-            HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, b.super_lists, b.super_count,
+            HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, rg, b.super_lists, b.super_count,
                                               c->stream));
             out.super_list = b.super_lists;
             out.super_count = b.super_count;

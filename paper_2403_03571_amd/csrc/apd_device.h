@@ -1487,62 +1487,40 @@ __device__ inline SeedRec<D> load_rec(const float4 *list, int cap, int pos, cons
     return r;
 }
 
-// The box of super-tile (c0, c1, c2).
+// The box (c0, c1, c2) of f[0] x f[1] x f[2] super-tiles each.
 template <int D>
-__device__ inline void super_box(const Geo &g, const PassOut &out, const int *c, double *blo, double *bhi) {
-    const int ext[3] = {tile_ext(D, out.tp, 0) * out.sf[0], tile_ext(D, out.tp, 1) * out.sf[1],
-                        tile_ext(D, out.tp, 2) * out.sf[2]};
-    int k0[3];
-    for (int d = 0; d < 3; ++d) k0[d] = c[d] * ext[d];
+__device__ inline void super_box(const Geo &g, const PassOut &out, const int *f, const int *c, double *blo,
+                                 double *bhi) {
+    int ext[3], k0[3];
+    for (int d = 0; d < 3; ++d) {
+        ext[d] = tile_ext(D, out.tp, d) * out.sf[d] * f[d];
+        k0[d] = c[d] * ext[d];
+    }
     cull_box<D>(g, k0, ext, blo, bhi);
 }
 
-// LDS of super_tile_list with T threads.
-template <int D, int T>
-struct SuperSmem {
-    int list[kSuperCap];
-    CellQuad<D> own[T / 64];
-    float red[T / 64];
-    int cnt;
-};
-
-// The candidate list of super-tile st (a box of sf[0] x sf[1] x sf[2] tiles of
-// out.tp pixels per lane) into list (room for cap), their number into *count
-// (above cap: every seed).  Every seed is tested with the eigenvalue bounds
-//   lambda_min dist(x, box)^2 - w' <= U = min_k lambda_max maxdist(x_k, box)^2 - w_k',
-// then, unless the pass returns the relative gaps (whose tiles need lists
-// that bound the cost of every seed left out) or its costs are of another
-// power, the survivors by the owner's difference.  A seed that cannot win
-// anywhere in the super-tile cannot win in any of its tiles.  All T threads of
-// the block call it.
+// Block-wide (T threads): of the seeds 0 .. nsrc - 1 (of rec's nsrc records,
+// when given) those that the eigenvalue bounds
+//   lambda_min dist(x, box)^2 - w' <= U = min_k lambda_max maxdist(x_k, box)^2 - w_k'
+// leave a chance somewhere in the box, their numbers into list (room for cap,
+// in any order); returns how many there are.
 //
-// Bound by the reads of every seed's 48 bytes by every block (256^3, N = 10^4:
-// 512 blocks, 246 MB from the L2s; with the bounds in double it was bound by
-// instruction issue as well).  The bounds of squared norms are formed in FP32
-// from offsets taken in double: dist and far are off by at most 2^-22 far each,
-// so the bounds by less than 2^-19 (lambda_max far^2 + |w'|); twice that, and
-// the lists' own slack (underflow), widens them.  A thread takes the seeds four at a time without a branch between, so
-// that their loads are in flight together, and a wave reserves the places of
-// all its seeds at once.  32.5 -> 24.5 us there (512 threads, one round of
-// blocks; 1024 threads 28), 6.9 -> 5.6 on 1024^2 with N = 1000.
+// Bound by the reads of every seed's 48 bytes by every block.  The bounds of
+// squared norms are formed in FP32 from offsets taken in double: dist and far
+// are off by at most 2^-22 far each, so the bounds by less than 2^-19
+// (lambda_max far^2 + |w'|); twice that, and the lists' own slack (underflow),
+// widens them.  A thread takes the seeds four at a time without a branch
+// between, so that their loads are in flight together, and a wave reserves the
+// places of all its seeds at once.  Over 512 super-tiles of 256^3, N = 10^4 (246
+// MB from the L2s), against bounds in double taken one by one: 32.5 -> 24.5 us
+// with 512 threads (one round of blocks; 1024 threads 28); 6.9 -> 4.8 on
+// 1024^2, N = 1000.
 template <int D, int T>
-__device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
-                                       const PassOut &out, int st, float4 *list, int *count, int cap,
-                                       SuperSmem<D, T> &sm) {
-    int c[3];
-    c[2] = st % out.nst[2];
-    c[1] = (st / out.nst[2]) % out.nst[1];
-    c[0] = st / (out.nst[2] * out.nst[1]);
-    double blo[3], bhi[3];
-    super_box<D>(g, out, c, blo, bhi);
+__device__ inline int box_survivors(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
+                                    const double *blo, const double *bhi, const double *ctr, const float *h,
+                                    const float4 *rec, int rec_cap, const float *shift, int nsrc, int *list, int cap,
+                                    int &s_cnt, float *s_red) {
     const int lane = __lane_id();
-    if (ct.lsl == INFINITY) {
-        if (threadIdx.x == 0) *count = cap + 1;
-        return;
-    }
-    double ctr[D];
-    float h[D];
-    const float hh = box_centre<D>(blo, bhi, ctr, h);
     auto bounds_power = [&](int i, float &lb, float &ub) {
         double l, u;
         cull_bounds<D, false>(sd, eig, wmax, blo, bhi, i, &l, &u, g.power);
@@ -1564,9 +1542,30 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         lb = fmaf((float)ev.x, dist2, -wp) - slack;
         ub = (u - wp) + slack;
     };
+    // from a region's record: x about its centre, w - w_max, the eigenvalue
+    // range.  The offset's rounding is at most 2^-22 of its size, covered like
+    // that of the others, and 2^-22 of the shift, which widens the box
+    float hr[D];
+#pragma unroll
+    for (int d = 0; d < D; ++d) hr[d] = rec ? fmaf(0x1p-22f, fabsf(shift[d]), h[d]) * (1.0f + 0x1p-20f) : h[d];
+    auto bounds_rec = [&](int q, float &lb, float &ub) {
+        const float4 r = rec[q], v = rec[rec_cap + q];
+        const float e[3] = {r.x + shift[0], r.y + shift[1], r.z + shift[2]};
+        float dist2 = 0.0f, far2 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const float dd = fmaxf(0.0f, fabsf(e[d]) - hr[d]), fd = fabsf(e[d]) + hr[d];
+            dist2 = fmaf(dd, dd, dist2);
+            far2 = fmaf(fd, fd, far2);
+        }
+        const float u = v.y * far2, slack = fmaf(0x1p-18f, u + fabsf(r.w), ct.lsl);
+        lb = fmaf(v.x, dist2, -r.w) - slack;
+        ub = (u - r.w) + slack;
+    };
+    auto seed_at = [&](int q) { return rec ? __float_as_int(rec[rec_cap + q].z) : q; };
     constexpr int kUnroll = 4;
     constexpr int kKeep = T > kThreads ? 20 : 8;  // a thread's lower bounds kept in registers
-    const bool in_regs = g.n <= kKeep * T;
+    const bool in_regs = nsrc <= kKeep * T;
     float lbr[kKeep], umin = INFINITY;
     auto scan = [&](auto bounds) {
         if (in_regs) {
@@ -1574,20 +1573,20 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
             for (int r0 = 0; r0 < kKeep; r0 += kUnroll) {
 #pragma unroll
                 for (int r = r0; r < r0 + kUnroll; ++r) lbr[r] = INFINITY;
-                if (r0 * T >= g.n) continue;
+                if (r0 * T >= nsrc) continue;
 #pragma unroll
                 for (int r = r0; r < r0 + kUnroll; ++r) {
                     // past the end the last seed again (no branch between the loads)
                     const int i = threadIdx.x + r * T;
                     float lb, ub;
-                    bounds(min(i, g.n - 1), lb, ub);
-                    lbr[r] = i < g.n ? lb : INFINITY;
+                    bounds(min(i, nsrc - 1), lb, ub);
+                    lbr[r] = i < nsrc ? lb : INFINITY;
                     umin = fminf(umin, ub);
                 }
             }
         } else {
 #pragma unroll kUnroll
-            for (int i = threadIdx.x; i < g.n; i += T) {
+            for (int i = threadIdx.x; i < nsrc; i += T) {
                 float lb, ub;
                 bounds(i, lb, ub);
                 umin = fminf(umin, ub);
@@ -1595,21 +1594,22 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         }
     };
     const bool square = g.power == 2;
-    if (square) scan(bounds_square);
+    if (rec) scan(bounds_rec);
+    else if (square) scan(bounds_square);
     else scan(bounds_power);
     umin = wave_min(umin);
-    if (lane == 0) sm.red[threadIdx.x >> 6] = umin;
-    if (threadIdx.x == 0) sm.cnt = 0;
+    if (lane == 0) s_red[threadIdx.x >> 6] = umin;
+    if (threadIdx.x == 0) s_cnt = 0;
     __syncthreads();
-    float U = sm.red[0];
+    float U = s_red[0];
 #pragma unroll
-    for (int w = 1; w < T / 64; ++w) U = fminf(U, sm.red[w]);
+    for (int w = 1; w < T / 64; ++w) U = fminf(U, s_red[w]);
     auto rank = [&](unsigned long long m) {
         return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
     };
     auto reserve = [&](int n) {
         int base = 0;
-        if (lane == 0) base = atomicAdd(&sm.cnt, n);
+        if (lane == 0) base = atomicAdd(&s_cnt, n);
         return __builtin_amdgcn_readfirstlane(base);
     };
     if (in_regs) {
@@ -1618,7 +1618,7 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
         int n = 0;
 #pragma unroll
         for (int r = 0; r < kKeep; ++r) {
-            keep[r] = __ballot((int)threadIdx.x + r * T < g.n && !(lbr[r] > U));
+            keep[r] = __ballot((int)threadIdx.x + r * T < nsrc && !(lbr[r] > U));
             n += (int)__popcll(keep[r]);
         }
         if (n) {
@@ -1627,27 +1627,115 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
             for (int r = 0; r < kKeep; ++r) {
                 if (!keep[r]) continue;
                 const int pos = base + rank(keep[r]);
-                if ((keep[r] >> lane & 1ull) && pos < kSuperCap) sm.list[pos] = threadIdx.x + r * T;
+                if ((keep[r] >> lane & 1ull) && pos < cap) list[pos] = seed_at(threadIdx.x + r * T);
                 base += (int)__popcll(keep[r]);
             }
         }
     } else {
-        for (int i0 = 0; i0 < g.n; i0 += T) {
+        for (int i0 = 0; i0 < nsrc; i0 += T) {
             const int i = i0 + threadIdx.x;
             float lb = INFINITY, ub;
-            if (i < g.n) {
-                if (square) bounds_square(i, lb, ub);
+            if (i < nsrc) {
+                if (rec) bounds_rec(i, lb, ub);
+                else if (square) bounds_square(i, lb, ub);
                 else bounds_power(i, lb, ub);
             }
-            const bool cand = i < g.n && !(lb > U);
+            const bool cand = i < nsrc && !(lb > U);
             const unsigned long long m = __ballot(cand);
             if (!m) continue;
             const int pos = reserve((int)__popcll(m)) + rank(m);
-            if (cand && pos < kSuperCap) sm.list[pos] = i;
+            if (cand && pos < cap) list[pos] = seed_at(i);
         }
     }
     __syncthreads();
-    const int m = sm.cnt;
+    return s_cnt;
+}
+
+// The seeds of region rg (a box of hf[0] x hf[1] x hf[2] super-tiles) that its
+// super-tiles start from: with many of both, the super-tiles' reads of every
+// seed would outweigh the rest of the pass (4000^2, N = 53333: 650 of 832 us; the
+// regions take 58 and the super-tiles then 67).  Packed about the region's centre
+// (box_survivors' bounds_rec).  All T threads of the block call it.
+template <int D, int T>
+__device__ inline void region_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
+                                   const PassOut &out, const Regions &rg, int id, int *s_list, int &s_cnt,
+                                   float *s_red) {
+    float4 *rec = rg.rec + (size_t)id * 2 * rg.cap;
+    int *count = rg.count + id;
+    if (ct.lsl == INFINITY) {
+        if (threadIdx.x == 0) *count = rg.cap + 1;
+        return;
+    }
+    const int c[3] = {id / (rg.nh[2] * rg.nh[1]), id / rg.nh[2] % rg.nh[1], id % rg.nh[2]};
+    double blo[3], bhi[3], ctr[D];
+    float h[D];
+    super_box<D>(g, out, rg.hf, c, blo, bhi);
+    box_centre<D>(blo, bhi, ctr, h);
+    const int m = box_survivors<D, T>(g, sd, wmax, ct, eig, blo, bhi, ctr, h, nullptr, 0, nullptr, g.n, s_list,
+                                      rg.cap, s_cnt, s_red);
+    if (threadIdx.x == 0) *count = m;
+    if (m > rg.cap) return;
+    for (int q = threadIdx.x; q < m; q += T) {
+        const int i = s_list[q];
+        const double *x = sd.x + (size_t)i * D;
+        rec[q] = make_float4((float)(x[0] - ctr[0]), (float)(x[1] - ctr[1]), D == 3 ? (float)(x[D - 1] - ctr[D - 1]) : 0.0f,
+                             (float)(sd.w[i] - wmax));
+        rec[rg.cap + q] = make_float4((float)eig[2 * (size_t)i], (float)eig[2 * (size_t)i + 1], __int_as_float(i), 0.0f);
+    }
+}
+
+// LDS of super_tile_list with T threads.
+template <int D, int T>
+struct SuperSmem {
+    int list[kSuperCap];
+    CellQuad<D> own[T / 64];
+    float red[T / 64];
+    int cnt;
+};
+
+// The candidate list of super-tile st (a box of sf[0] x sf[1] x sf[2] tiles of
+// out.tp pixels per lane) into list (room for cap), their number into *count
+// (above cap: every seed): the survivors of its box (box_survivors, from its
+// region's list where the pass has regions), then, unless the pass returns the
+// relative gaps (whose tiles need lists that bound the cost of every seed left
+// out) or its costs are of another power, of these by the owner's difference.
+// A seed that cannot win anywhere in the super-tile cannot win in any of its
+// tiles.  All T threads of the block call it.
+template <int D, int T>
+__device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
+                                       const PassOut &out, const Regions &rg, int st, float4 *list, int *count,
+                                       int cap, SuperSmem<D, T> &sm) {
+    int c[3];
+    c[2] = st % out.nst[2];
+    c[1] = (st / out.nst[2]) % out.nst[1];
+    c[0] = st / (out.nst[2] * out.nst[1]);
+    if (ct.lsl == INFINITY) {
+        if (threadIdx.x == 0) *count = cap + 1;
+        return;
+    }
+    constexpr int kOne[3] = {1, 1, 1};
+    double blo[3], bhi[3], ctr[D];
+    float h[D];
+    super_box<D>(g, out, kOne, c, blo, bhi);
+    const float hh = box_centre<D>(blo, bhi, ctr, h);
+    const float4 *rec = nullptr;
+    int nsrc = g.n;
+    float shift[3] = {0.0f, 0.0f, 0.0f};
+    if (rg.rec) {
+        const int rc[3] = {c[0] / rg.hf[0], c[1] / rg.hf[1], c[2] / rg.hf[2]};
+        const int id = (rc[0] * rg.nh[1] + rc[1]) * rg.nh[2] + rc[2];
+        if (rg.count[id] <= rg.cap) {
+            rec = rg.rec + (size_t)id * 2 * rg.cap;
+            nsrc = rg.count[id];
+            double rlo[3], rhi[3], rctr[D];
+            float rh[D];
+            super_box<D>(g, out, rg.hf, rc, rlo, rhi);
+            box_centre<D>(rlo, rhi, rctr, rh);
+            for (int d = 0; d < D; ++d) shift[d] = (float)(rctr[d] - ctr[d]);
+        }
+    }
+    const int m = box_survivors<D, T>(g, sd, wmax, ct, eig, blo, bhi, ctr, h, rec, rg.cap, shift, nsrc, sm.list,
+                                      kSuperCap, sm.cnt, sm.red);
     if (m > kSuperCap) {
         if (threadIdx.x == 0) *count = cap + 1;
         return;

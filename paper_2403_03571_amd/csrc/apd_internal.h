@@ -166,6 +166,23 @@ struct PassOut {
     double *cost_part = nullptr;
 };
 
+// Regions of hf[0] x hf[1] x hf[2] super-tiles (nh[] of them per axis) with
+// lists of their own, or none (rec null).
+struct Regions {
+    float4 *rec = nullptr;  // [regions][2][cap]
+    int *count = nullptr;   // [regions]; above cap: every seed
+    int cap = 0;
+    int hf[3] = {1, 1, 1};
+    int nh[3] = {1, 1, 1};
+};
+constexpr int kRegionCap = 4096;  // candidate seeds kept per region
+// Regions from so many pairs of super-tile and seed: below, the second kernel
+// costs more than the shorter lists save.  Evaluation without / with regions:
+// 256^3, N = 10^4 (5.1e6 pairs) 154 / 164 us; 4000^2, 9411 (9.6e6) 133 / 133;
+// 2048^2, 13981 (1.43e7) 120 / 96; 200^3, 26666 352 / 341; 4000^2, 53333 (2.1e8)
+// 832 / 262.
+constexpr int64_t kRegionPairs = (int64_t)3 << 22;
+
 constexpr int kMfmaLds = kChunk * 16;  // floats of LDS staging of the matrix-core tile
 constexpr int kCullCap = 2048;         // candidate seeds kept per tile
 constexpr int kSuperCap = 2048;        // candidate seeds kept per super-tile
@@ -194,7 +211,7 @@ hipError_t launch_prep(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom
 // Candidate lists of the super-tiles described by out (sf, nst), written to
 // list / count.
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, float4 *list, int *count, hipStream_t st);
+                             const PassOut &out, const Regions &rg, float4 *list, int *count, hipStream_t st);
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
 // The FP64 pass over every seed (eig null) or over the tiles' candidate lists

@@ -422,11 +422,23 @@ __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scala
 // One block of T threads per super-tile (dev::super_tile_list).
 template <int D, int T>
 __global__ __launch_bounds__(T) void k_super_cull(Geo g, Seeds sd, const Scalars *sc, const double *eig, PassOut out,
-                                                  float4 *list, int *count) {
+                                                  Regions rg, float4 *list, int *count) {
     __shared__ SuperSmem<D, T> sm;
     const int st = blockIdx.x;
-    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, out, st,
+    super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, out, rg, st,
                           list + (size_t)st * (size_t)out.super_cap * rec_vec(D), count + st, out.super_cap, sm);
+}
+
+// One block per region (dev::region_list).
+constexpr int kRegionThreads = 1024;
+template <int D>
+__global__ __launch_bounds__(kRegionThreads) void k_region_cull(Geo g, Seeds sd, const Scalars *sc, const double *eig,
+                                                                PassOut out, Regions rg) {
+    __shared__ int s_list[kRegionCap];
+    __shared__ float s_red[kRegionThreads / 64];
+    __shared__ int s_cnt;
+    region_list<D, kRegionThreads>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, out, rg,
+                                   blockIdx.x, s_list, s_cnt, s_red);
 }
 
 // ---------------------------------------------------------- k_recheck
@@ -711,18 +723,24 @@ hipError_t launch_assign_fp32(const Geo &g, const Seeds &sd, Scalars *sc, const 
 
 template <int D>
 static void launch_super(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig, const PassOut &out,
-                         float4 *list, int *count, hipStream_t st) {
+                         const Regions &rg, float4 *list, int *count, hipStream_t st) {
     const int nb = out.nst[0] * out.nst[1] * out.nst[2];
-    // a block reads every seed: many seeds need many loads in flight
-    if (g.n > kSuperWideSeeds) k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, list, count);
-    else k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, list, count);
+    if (rg.rec) {
+        k_region_cull<D><<<rg.nh[0] * rg.nh[1] * rg.nh[2], kRegionThreads, 0, st>>>(g, sd, sc, eig, out, rg);
+        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+    } else if (g.n > kSuperWideSeeds) {
+        // a block reads every seed: many seeds need many loads in flight
+        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+    } else {
+        k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+    }
 }
 
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, float4 *list, int *count, hipStream_t st) {
+                             const PassOut &out, const Regions &rg, float4 *list, int *count, hipStream_t st) {
     (void)hipGetLastError();
-    if (g.dim == 2) launch_super<2>(g, sd, sc, eig, out, list, count, st);
-    else launch_super<3>(g, sd, sc, eig, out, list, count, st);
+    if (g.dim == 2) launch_super<2>(g, sd, sc, eig, out, rg, list, count, st);
+    else launch_super<3>(g, sd, sc, eig, out, rg, list, count, st);
     return hipGetLastError();
 }
 

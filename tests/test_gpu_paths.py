@@ -94,6 +94,30 @@ def test_candidate_lists_by_the_number_of_seeds(ctx, dim, grid, n):
         np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, minlength=n))
 
 
+@pytest.mark.parametrize("dim,grid,n", [(2, (2100, 1999), 15000), (3, (130, 121, 129), 29000)])
+@pytest.mark.parametrize("spread", [1.0, 0.04])
+def test_regions_of_super_tiles(ctx, dim, grid, n, spread):
+    """Many super-tiles and seeds: lists by way of regions, the seeds spread
+    evenly or so close together that the regions' lists overflow; labels, gaps
+    and counts against the passes over every seed."""
+    import torch
+    inst = S.custom(dim, n, grid, seed=n, sigma=0.2)
+    inst.x[:] = np.asarray(inst.lo) + spread * (inst.x - np.asarray(inst.lo))
+    w = np.random.default_rng(n).uniform(-0.2, 0.2, n) * n ** (-2.0 / dim) * spread ** 2
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    try:
+        ctx.apd_set_culling(False)
+        ref, exact = ctx.apd_assign(prob, wd, prec="fp64", rel_gap=True)
+    finally:
+        ctx.apd_set_culling(True)
+    for prec in ("fp32", "bf16", "fp64"):
+        assert torch.equal(ctx.apd_assign(prob, wd, prec=prec), ref)
+    lab, gap = ctx.apd_assign(prob, wd, prec="fp32", rel_gap=True)
+    assert torch.equal(lab, ref) and bool((gap <= exact * (1 + 1e-6) + 1e-12).all())
+    out = ctx.apd_dual_objective_grad(prob, wd, counts=True)
+    assert torch.equal(out["counts"].cpu(), torch.bincount(ref.cpu().long(), minlength=n))
+
+
 @pytest.mark.parametrize("dim,grid", [(2, (64, 33)), (3, (32, 9, 17))])
 @pytest.mark.parametrize("n", [2, 15, 16, 17, 33, 60, 64, 65, 90])
 def test_moments_by_the_cells_of_a_tile(ctx, dim, grid, n):
