@@ -667,13 +667,13 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     int64_t J = 1;
     for (int d = 0; d < g.dim; ++d) J *= g.grid[d];
     // measured: with candidate lists the smaller wave boxes of 4 rows win
-    // (fewer candidates per wave), except in 3D on large cells, whose lists
-    // are short either way, so that halving the work per wave box pays:
-    // 16 x 16 x 8 against 16 x 8 x 8 tiles, evaluation at 1700 voxels per cell
-    // 96^3 61 / 58 us, 128^3 69 / 70, 200^3 117 / 124, 256^3 183 / 200; at 300
-    // per cell 128^3 121 / 116, 200^3 421 / 381.  2D is within 2 % at 1700
-    // pixels per cell and slower at 300 (2048^2: 153 / 135).
-    if (cull) return g.dim == 3 && J >= (int64_t)1 << 21 && J >= (int64_t)1000 * g.n ? 8 : 4;
+    // (fewer candidates per wave), except on large grids of large cells, whose
+    // lists are short either way, so that halving the work per wave box pays.
+    // Evaluation in us, 4 / 8 rows, at 1700 pixels per cell: 96^3 54.6 / 56.3,
+    // 128^3 66.6 / 64.1, 200^3 113.8 / 100.8, 1024^2 50.2 / 50.0, 2048^2 64.9 /
+    // 62.2, 4000^2 132.8 / 116.4; at 300 per cell: 128^3 109.4 / 112.5, 200^3
+    // 352 / 375, 2048^2 120.7 / 136.1, 4000^2 262 / 305.
+    if (cull) return J >= (int64_t)1 << (g.dim == 2 ? 22 : 21) && J >= (int64_t)1000 * g.n ? 8 : 4;
     // over every seed, 8 rows halve the per-seed work of a lane once the grid
     // keeps the chip busy
     return J >= 1024 * 2048 ? 8 : 4;
