@@ -290,7 +290,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_assign_vec(Geo g, Seeds sd, Sca
 }
 
 template <int D, int P, bool GAP>
-__global__ __launch_bounds__(kThreads, (P == 4 && !GAP) ? 5 : 4) void k_assign_list(Geo g, Seeds sd, Scalars *sc,
+__global__ __launch_bounds__(kThreads, (P <= 4 && !GAP) ? 5 : 4) void k_assign_list(Geo g, Seeds sd, Scalars *sc,
                                                                                     const double *eig, PassOut out) {
     __shared__ ListSmem<D, P, GAP> sm;
     const Cert ct{sc->lam, sc->kap, sc->sab, sc->lsl};
@@ -653,10 +653,11 @@ hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut 
 template <int D, bool GAP>
 hipError_t launch_list(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig, const PassOut &out,
                        hipStream_t st) {
-    if (vec_pixels_per_lane(g, true) == 8)
-        k_assign_list<D, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
-    else
-        k_assign_list<D, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    switch (vec_pixels_per_lane(g, true)) {
+    case 8: k_assign_list<D, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
+    case 4: k_assign_list<D, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
+    default: k_assign_list<D, 2, GAP><<<tile_grid<D, 2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    }
     return hipGetLastError();
 }
 
@@ -673,6 +674,14 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     // 128^3 66.6 / 64.1, 200^3 113.8 / 100.8, 1024^2 50.2 / 50.0, 2048^2 64.9 /
     // 62.2, 4000^2 132.8 / 116.4; at 300 per cell: 128^3 109.4 / 112.5, 200^3
     // 352 / 375, 2048^2 120.7 / 136.1, 4000^2 262 / 305.
+    // In 3D 2 rows (8^3 tiles) on small grids, where 16 x 8 x 8 tiles leave
+    // compute units idle, and on small cells, whose wave lists they keep
+    // short: 2 / 4 rows at 300 per cell 40^3 36.4 / 44.1, 64^3 53.5 / 62.3,
+    // 128^3 96 / 106, 256^3 749 / 871; at 600 56^3 47.9 / 48.5, 80^3 55.1 / 60.4,
+    // 128^3 78.2 / 74.3, 256^3 393 / 357; at 1700 48^3 35.3 / 36.1, 80^3 48.6 /
+    // 48.7, 96^3 55.7 / 52.3.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
+    // 46.4 / 43.0: 4 rows.)
+    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || J < (int64_t)450 * g.n)) return 2;
     if (cull) return J >= (int64_t)1 << (g.dim == 2 ? 22 : 21) && J >= (int64_t)1000 * g.n ? 8 : 4;
     // over every seed, 8 rows halve the per-seed work of a lane once the grid
     // keeps the chip busy

@@ -94,6 +94,28 @@ def test_candidate_lists_by_the_number_of_seeds(ctx, dim, grid, n):
         np.testing.assert_array_equal(out["counts"].cpu().numpy(), np.bincount(ref, minlength=n))
 
 
+@pytest.mark.parametrize("dim,grid,n,rows", [
+    (3, (79, 80, 82), 3, 2), (3, (81, 80, 82), 1300, 2), (3, (81, 80, 82), 1100, 4), (3, (129, 128, 128), 2100, 8),
+    (3, (9, 7, 3), 40, 2), (2, (2048, 2049), 4100, 8), (2, (2048, 2047), 4100, 4), (2, (17, 5), 300, 4)])
+def test_rows_per_lane_by_grid_and_seeds(ctx, dim, grid, n, rows):
+    """Either side of each line of the rule for the rows per lane of the
+    listed tile: the rows taken, labels and counts against every seed."""
+    import torch
+    inst = S.custom(dim, n, grid, seed=n, sigma=0.2)
+    w = np.random.default_rng(n).uniform(-0.2, 0.2, n) * n ** (-2.0 / dim)
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    try:
+        ctx.apd_set_culling(False)
+        ref = ctx.apd_assign(prob, wd, prec="fp64")
+    finally:
+        ctx.apd_set_culling(True)
+    assert torch.equal(ctx.apd_assign(prob, wd, prec="fp32"), ref)
+    assert ctx.apd_last_pass_stats()["pixels_per_lane"] == rows
+    for noalloc in (False, True):
+        out = ctx.apd_dual_objective_grad(prob, wd, counts=True, noalloc=noalloc)
+        assert torch.equal(out["counts"].cpu(), torch.bincount(ref.cpu().long(), minlength=n))
+
+
 @pytest.mark.parametrize("dim,grid,n", [(2, (2100, 1999), 15000), (3, (130, 121, 129), 29000)])
 @pytest.mark.parametrize("spread", [1.0, 0.04])
 def test_regions_of_super_tiles(ctx, dim, grid, n, spread):
