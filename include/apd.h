@@ -60,7 +60,8 @@ typedef enum {
                      apd_set_culling off or when rel_gap is asked for) */
     APD_FP32 = 1, /* single precision + certified double re-check */
     APD_BF16 = 2, /* bf16 matrix cores (split hi/lo operands, fp32
-                     accumulation) + certified double re-check */
+                     accumulation; candidate lists in fp32) + certified
+                     double re-check */
     APD_BF16_RECHECK = APD_BF16  /* the same tier, by its boundary name */
 } apd_precision;
 
@@ -332,7 +333,10 @@ typedef enum {
     APD_KERNEL_FP32_VECTOR = 1,  /* FP32 vector ALU over every seed            */
     APD_KERNEL_FP32_LISTS = 2,   /* FP32 vector ALU over tile candidate lists  */
     APD_KERNEL_BF16_MATRIX = 3,  /* bf16 matrix cores over every seed          */
-    APD_KERNEL_BF16_LISTS = 4,   /* bf16 matrix cores over candidate lists     */
+    APD_KERNEL_BF16_LISTS = 4,   /* the APD_BF16 tier over candidate lists (the
+                                    lists are too short for blocks of 32 seeds
+                                    on the matrix cores: their costs are formed
+                                    in FP32, as APD_KERNEL_FP32_LISTS does)    */
     APD_KERNEL_FP64 = 5,         /* the FP64 tier                              */
     APD_KERNEL_FP32_HYBRID = 6   /* FP32 over every seed: matrix cores form each
                                     position's quadratic in u0, the vector ALU
@@ -405,8 +409,8 @@ apd_status apd_set_adaptive(apd_ctx *ctx, int32_t on);
  * per seed, 2 (8 x 8 x 8 voxels) on 3D grids under 2^19 voxels or 450 voxels
  * per seed, else 4; over every seed 8 on grids of at least 2^21 pixels, else
  * 4.  The single-instance
- * APD_BF16 kernel takes half of a set value as its rows per lane (default
- * 4 in 2D, 2 in 3D).  The labels do not depend on it. */
+ * APD_BF16 kernel over every seed takes half of a set value as its rows per
+ * lane (default 4 in 2D, 2 in 3D).  The labels do not depend on it. */
 apd_status apd_set_pixels_per_lane(apd_ctx *ctx, int32_t p);
 
 /* Kernel choice for a class of problems: times every exact kernel of the

@@ -238,10 +238,13 @@ struct ListGeometry {
     int64_t nregion = 0;    // 0: no regions
 };
 
-ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, apd_precision prec) {
+int list_rows(const apd::Geo &g, apd_precision prec) {
+    return prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true);
+}
+
+ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
     ListGeometry L;
-    L.tp = prec == APD_BF16 ? apd::bf16_pixels_per_lane(g)
-           : prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true);
+    L.tp = rows;
     const int ext[3] = {apd::tile_ext(p->dim, L.tp, 0), apd::tile_ext(p->dim, L.tp, 1),
                         apd::tile_ext(p->dim, L.tp, 2)};
     for (int d = 0; d < 3; ++d) L.ntile[d] = d < p->dim ? (g.grid[d] + ext[d] - 1) / ext[d] : 1;
@@ -315,7 +318,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     int tp = 0;  // pixels per lane of the lists' tiles
     apd::Regions rg;
     if (cull) {
-        const ListGeometry L = list_geometry(p, g, prec);
+        const ListGeometry L = list_geometry(p, g, list_rows(g, prec));
         out.tp = tp = L.tp;
         if (fixed) {
             if (L.nsuper > b.cap_super)
@@ -399,12 +402,11 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
             out.queue = b.queue;
         }
         if (prec == APD_BF16 && !cull) {
-            HIP_TRY(c, apd::launch_assign_bf16(g, sd, b.sc, nullptr, out, c->stream));
+            HIP_TRY(c, apd::launch_assign_bf16(g, sd, b.sc, out, c->stream));
             c->stats.kernel = APD_KERNEL_BF16_MATRIX;
             c->stats.pixels_per_lane = apd::bf16_pixels_per_lane(g);
         } else if (cull) {
-            if (prec == APD_BF16) HIP_TRY(c, apd::launch_assign_bf16(g, sd, b.sc, b.eig, out, c->stream));
-            else HIP_TRY(c, apd::launch_assign_cull(g, sd, b.sc, b.eig, out, c->stream));
+            HIP_TRY(c, apd::launch_assign_cull(g, sd, b.sc, b.eig, out, c->stream));
             c->stats.kernel = prec == APD_BF16 ? APD_KERNEL_BF16_LISTS : APD_KERNEL_FP32_LISTS;
             c->stats.pixels_per_lane = tp;
         } else if (c->variant == 3 || (c->variant == 2 && hyb_by_default(p))) {
@@ -929,7 +931,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
     const int bvariant = trial ? trial->kernel : c->batch_kernel >= 0 ? c->batch_kernel
                          : o->prec == APD_BF16 ? (c->culling ? 5 : 3)
                          : (c->variant == 0 ? 0 : (c->culling ? (c->vec_p == 4 ? 4 : 2) : 1));
-    const bool bf = bvariant == 3 || bvariant == 5;
+    const bool bf = bvariant == 3;
     const int btp = bvariant == 4 ? apd::kP : bf ? (dim == 2 ? 4 : 2) : 8;
     // work list: largest instances first
     std::vector<int> order(B);
@@ -955,7 +957,7 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         // the batched tiles build their candidate lists from every seed of
         // the instance, so fewer, larger tiles pay less for them --
         // measured); bf16 32 x 32 / 8 x 8 x 8
-        const bool vec = bvariant == 1 || bvariant == 2 || bvariant == 4 || bf;
+        const bool vec = bvariant != 0;
         const int e0 = vec ? apd::tile_ext(dim, btp, 0) : apd::kWaves * apd::kP;
         const int e1 = vec ? apd::tile_ext(dim, btp, 1) : (dim == 2 ? 32 : 4);
         const int e2 = 8;
@@ -1421,9 +1423,8 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         // its length and bound and a queue segment for every tile (of 4 pixels
         // per lane unless set) and kStaticSuperCap seeds for every super-tile
         // of them, whether or not the pass uses them
-        apd::Geo lim = geo;
-        if (prec == APD_FP32 && lim.vec_p == 0) lim.vec_p = apd::kP;
-        const ListGeometry L = list_geometry(p, lim, prec);
+        const ListGeometry L = list_geometry(p, geo, prec == APD_BF16 ? apd::bf16_pixels_per_lane(geo)
+                                                     : geo.vec_p ? geo.vec_p : apd::kP);
         k.take<int>((size_t)L.tiles * kStaticListCap);
         k.take<int>((size_t)L.tiles);
         k.take<double>((size_t)L.tiles);
@@ -1439,7 +1440,7 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         // the super-tiles' counts and records take the room that the limit
         // counts for the queue (a pass with lists has none) and the lists, as
         // many records per super-tile as fit
-        const int64_t nsuper = list_geometry(p, geo, prec).nsuper;
+        const int64_t nsuper = list_geometry(p, geo, list_rows(geo, prec)).nsuper;
         Carve in{reinterpret_cast<unsigned char *>(b.queue)};
         b.queue = nullptr;
         b.cap_super = nsuper;
@@ -1896,7 +1897,7 @@ apd_status apd_autotune_batched(apd_ctx *c, const apd_problem *probs, int32_t B,
     c->batch_kernel = cand[best];
     res->kernel = c->stats.kernel = batch_public_kernel(cand[best]);
     const int dim = probs[0].dim;
-    res->pixels_per_lane = cand[best] == 0 ? 0 : cand[best] == 4 ? apd::kP : (cand[best] == 3 || cand[best] == 5) ? (dim == 2 ? 4 : 2) : 8;
+    res->pixels_per_lane = cand[best] == 0 ? 0 : cand[best] == 4 ? apd::kP : cand[best] == 3 ? (dim == 2 ? 4 : 2) : 8;
     c->stats.pixels_per_lane = res->pixels_per_lane;
     return APD_OK;
 }

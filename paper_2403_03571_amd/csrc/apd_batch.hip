@@ -249,21 +249,18 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
 //
 // V: 0 fp32 matrix cores, 1 fp32 vector, 2 fp32 vector with candidate
 // lists (8 pixels per lane), 3 bf16 matrix cores, 4 fp32 vector with
-// candidate lists (4 pixels per lane), 5 bf16 matrix cores with candidate
-// lists (both bf16 forms with Bf16Rows<D> pixel rows per lane; at two
-// waves per SIMD the 2D form spills a few registers, and still runs the
-// batched C4-type solve 1.5 times faster than at one wave -- measured)
+// candidate lists (4 pixels per lane); 3 with Bf16Rows<D> pixel rows per lane.
 template <int D, int V>
-__global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) void kb_assign(const BInst *inst, const BState *st,
+__global__ __launch_bounds__(kThreads, (D == 2 && V != 3) ? 4 : 2) void kb_assign(const BInst *inst, const BState *st,
                                                      BWork wk, int B, BCtl *ctl,
                                                      uint64_t *queue, QSeg *segs) {
-    constexpr bool kLists = V == 2 || V == 4 || V == 5;
+    constexpr bool kLists = V == 2 || V == 4;
     constexpr int kLanePixels = V == 4 ? kP : kPv;
     __shared__ union {
         float mf[V == 0 ? kMfmaLds : 1];
         VecSmem<V == 1 ? D : 2> vec[V == 1 ? 1 : 0];
         ListSmem<D, kLanePixels, false> list[V == 2 || V == 4 ? 1 : 0];
-        Bf16Smem<D, Bf16Rows<D>::value, 256, V == 5> bf[V == 3 || V == 5 ? 1 : 0];
+        Bf16Smem<D, 256> bf[V == 3 ? 1 : 0];
     } sm;
     float *sC = sm.mf;
     const int64_t total = uniform_load(wk.act_tile + B);
@@ -309,9 +306,8 @@ __global__ __launch_bounds__(kThreads, (D == 2 && V != 3 && V != 5) ? 4 : 2) voi
                 }
             }
             const Cert ct{S.lam, S.kap, S.sab, S.lsl};
-            if constexpr (V == 3 || V == 5)
-                bf16_tile<D, Bf16Rows<D>::value, 256, V == 5>(I.g, sd, S.wmax, ct, I.eig, b0, b1, b2, sm.bf[0], out,
-                                                              kLists ? nullptr : &ctl->qcount);
+            if constexpr (V == 3)
+                bf16_tile<D, Bf16Rows<D>::value, 256>(I.g, sd, S.wmax, ct, b0, b1, b2, sm.bf[0], out, &ctl->qcount);
             else if constexpr (V == 1)
                 vec_tile<D, kLanePixels>(I.g, sd, S.wmax, ct, b0, b1, b2, sm.vec[0], out, &ctl->qcount);
             else
@@ -578,9 +574,9 @@ void batch_assign(int variant, dim3 grid, BInst *inst, BState *st, BWork wk, int
     switch (variant) {
     case 0: kb_assign<D, 0><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
     case 1: kb_assign<D, 1><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
-    case 2: kb_assign<D, 2><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
     case 4: kb_assign<D, 4><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
-    case 5: kb_assign<D, 5><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
+    case 5:  // the bf16 tier's lists are scanned in FP32 (launch_assign_cull)
+    case 2: kb_assign<D, 2><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
     default: kb_assign<D, 3><<<grid, kThreads, 0, s>>>(inst, st, wk, B, ctl, queue, segs); break;
     }
 }

@@ -3037,28 +3037,21 @@ __device__ inline void bf16_pixel_slots(const float *f, unsigned short *out) {
 // load) and its FP32 coefficients in the layout of the vector tile
 // (a00, 2a01, a11, -2(Ae)_0 | -2(Ae)_1, e^T A e - w' in 2D; the 3D rows
 // hold a00, 2a01, 2a02, -2(Ae)_0 | a11, 2a12, a22, -2(Ae)_1 | -2(Ae)_2,
-// e^T A e - w'); with candidate lists, the tile's list.
-template <int D, int P, int C, bool CULL, bool GAP = false>
+// e^T A e - w').
+template <int D, int C>
 struct Bf16Smem {
     static constexpr int kChunk = C;
     ushort8 sA[C * Bf16Slots<D>::SLOTS / 8];
     float4 sF4[D - 1][C];
     float2 sF2[C];
-    int list[CULL ? kCullCap : 1];
-    uint16_t flagged[kWaves][CULL ? 64 * 4 : 1];  // recheck_flagged's pixels (at most 4 per lane)
-    MomSmem<CULL ? P : 1> mom[CULL ? 1 : 0];
-    CellQuad<D> own[kWaves];
-    double red[kWaves];
-    int cnt;
 };
 
 // Rows per lane of the bf16 tile: 4 in 2D, 2 in 3D (its two matrix-core
 // operands per block need twice the registers).
 template <int D> struct Bf16Rows { static constexpr int value = D == 2 ? 4 : 2; };
 
-// The bf16 tier of one tile, in the vector tile's geometry (tile_at: P
-// pixels per lane along axis 0), so that it shares the candidate lists, the
-// super-tiles and the re-check's tile layout.  A wave's pixels form 2P
+// The bf16 tier of one tile over every seed, in the vector tile's geometry
+// (tile_at: P pixels per lane along axis 0).  A wave's pixels form 2P
 // groups of 32: group 2r + c holds pixel r of lanes 32c .. 32c + 31, its
 // column col that of lane 32c + col.  A 32-seed x 32-pixel block of costs
 // is one (2D) or two (3D) v_mfma_f32_32x32x16_bf16 with the seeds on rows,
@@ -3098,13 +3091,10 @@ template <int D> struct Bf16Rows { static constexpr int value = D == 2 ? 4 : 2; 
 //    gap, so such pixels are never settled.  Other pixels go to the double
 //    re-check.
 // The features are exact bf16 hi + lo pairs: in half-pixel units they are
-// integers below 2^12 (|v| < 64).  With CULL the tile scans its candidate
-// list (built as the vector tile builds it, from its super-tile's list
-// when there is one) and keeps it for the re-check.
-template <int D, int P, int C, bool CULL, bool GAP = false>
-__device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct,
-                                 const double *eig, int b0, int b1, int b2,
-                                 Bf16Smem<D, P, C, CULL, GAP> &sm, const PassOut &out, unsigned *qcount) {
+// integers below 2^12 (|v| < 64).
+template <int D, int P, int C>
+__device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct, int b0, int b1, int b2,
+                                 Bf16Smem<D, C> &sm, const PassOut &out, unsigned *qcount) {
     using SL = Bf16Slots<D>;
     static_assert(C % 32 == 0, "bf16 staging");
     constexpr int NG = 2 * P;  // 32-pixel groups per wave: gi = 2 r + c
@@ -3167,21 +3157,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         }
     }
 
-    // ---- the candidate list, from the super-tile's list when it has one
-    int nscan = g.n;
-    bool full = true;
-    double Utile = INFINITY;  // no seed left out of the tile's list costs less
-    if (CULL) {
-        const int ncand = tile_candidates<D, P, GAP>(g, sd, wmax, ct, eig, out, b0, b1, b2, sm, &Utile);
-        full = ncand > kCullCap;
-        nscan = full ? g.n : ncand;
-        if (full || ncand >= g.n) Utile = INFINITY;  // no seed was left out
-        if (!GAP && out.adaptive && ncand == 1 && !g.mass) {
-            credit_tile<D, P>(g, t, b0, b1, b2, sm.list[0], out);
-            return;
-        }
-    }
-
+    const int nscan = g.n;
     // staging of scan positions [base, base + cnt), padded to a multiple of
     // 32 with entries that cost 1.7e38 everywhere
     auto stage = [&](int base, int cnt, int padded) {
@@ -3194,9 +3170,8 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
                 for (int r = 0; r < D - 1; ++r) sm.sF4[r][q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
                 sm.sF2[q] = make_float2(0.0f, kPad);
             } else {
-                const int i = (CULL && !full) ? sm.list[base + q] : base + q;
                 double qd[6], ld[3], cd, ed[3], wpd;
-                seed_terms<D>(sd, i, ancd, wmax, qd, ld, &cd, ed, &wpd);
+                seed_terms<D>(sd, base + q, ancd, wmax, qd, ld, &cd, ed, &wpd);
                 const double h0 = 0.5 * g.s[0], h1 = 0.5 * g.s[1], h2 = D == 3 ? 0.5 * g.s[2] : 0.0;
                 if (D == 2) {
                     sm.sF4[0][q] = make_float4((float)qd[0], (float)qd[1], (float)qd[2], (float)ld[0]);
@@ -3334,7 +3309,7 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     // pixels of column l % 32 of those groups are its own)
     const bool lane_ok = lane_in_grid<D>(g, t);
     bool act[P], flag[P];
-    int labe[P], idx[P];  // label, position in the list
+    int labe[P];
 #pragma unroll
     for (int gi = 0; gi < NG; ++gi) {
         const int pb = __shfl_xor(best[gi], 32);
@@ -3353,15 +3328,12 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         const bool settled = (fs - fb) > thr32 && (fo - fb) > thr16;
         const int r = gi >> 1;
         if ((gi & 1) == half) {
-            const int pos = min(lab[gi], nscan - 1);
             act[r] = lane_ok && (t.k0w + r) < g.grid[0];
             flag[r] = !settled;
-            labe[r] = (CULL && !full) ? sm.list[pos] : min(pos, g.n - 1);
-            idx[r] = pos;
-            if ((!CULL || GAP) && out.rel_gap && act[r] && settled) {
+            labe[r] = min(lab[gi], nscan - 1);
+            if (out.rel_gap && act[r] && settled) {
                 // the winner costs at most c1u; the rest of its group at
-                // least fs, the other groups at least fo, each less its bound,
-                // and a seed left out of the list more than U
+                // least fs, the other groups at least fo, each less its bound
                 const float c1u = (fb + 0x1p-19f * fabsf(fb) + e32 + slack) * (1.0f + 0x1p-20f);
                 const float f2 = pad_inf(fs), fo2 = pad_inf(fo);
                 const float bs = fmaxf(f2, 0.0f), bo = fmaxf(fo2, 0.0f);
@@ -3370,36 +3342,13 @@ __device__ inline void bf16_tile(const Geo &g, const Seeds &sd, double wmax, Cer
                                      ? f2
                                      : f2 - 0x1p-19f * fabsf(f2) - e32_bound(Bs, rr, r2) - sab - skb * (Bs + r2);
                 const float co = fo2 == INFINITY ? fo2 : fo2 - e16_bound(Bo, rr, r2) - sab - skb * (Bo + r2);
-                const float uc = (float)Utile;
-                const float c2l = fminf(fminf(cs, co), (uc == INFINITY ? uc : uc - 0x1p-20f * fabsf(uc))) * (1.0f - 0x1p-20f);
+                const float c2l = fminf(cs, co) * (1.0f - 0x1p-20f);
                 out.rel_gap[pixel_index<D>(g, t.k0w + r, t)] =
                     (fs > 0.0f && fo > 0.0f) ? gap_lower(c1u, c2l) : 0.0f;
             }
         }
     }
-    if constexpr (CULL) {
-        const bool slots = !full && nscan <= kAccSlots && !g.mass;
-        if (slots) {
-            if (out.labels) write_labels<D, P>(g, t, act, labe, flag, out);
-            if (out.mom) {
-#pragma unroll
-                for (int r = 0; r < P; ++r) idx[r] = act[r] && !flag[r] ? idx[r] : 127;
-                moments_zero(sm.mom[0], nscan);
-                __syncthreads();
-                moments_add<D, P>(sm.mom[0], lane, idx, nscan, [](int j) { return j; });
-            }
-        } else {
-            tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
-        }
-        recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : sm.list, full ? g.n : nscan,
-                              sm.flagged[threadIdx.x >> 6], out, qcount, wmax, Utile);
-        if (slots && out.mom) {
-            __syncthreads();
-            moments_flush<D, P>(sm.mom[0], t.anc, sm.list, nscan, out.mom);
-        }
-    } else {
-        tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
-    }
+    tile_epilogue<D, P>(g, t, act, labe, flag, out, qcount);
 }
 
 // ------------------------------------------------------- double re-check

@@ -199,7 +199,7 @@ struct FinalOut {
 // Pixels per lane of the vector kernel on this grid, with or without
 // candidate lists (its tiles are kWaves * that many pixels long along axis 0).
 int vec_pixels_per_lane(const Geo &g, bool cull);
-// Pixel rows per lane of the bf16 kernel on this grid (its tiles are kWaves
+// Pixel rows per lane of the bf16 kernel over every seed on this grid (its tiles are kWaves
 // * that many pixels long along axis 0, with the vector kernel's other axes).
 int bf16_pixels_per_lane(const Geo &g);
 // With w_src (pinned host memory) the prep kernel first copies w_src into
@@ -232,10 +232,8 @@ hipError_t launch_assign_hyb(const Geo &g, const Seeds &sd, Scalars *sc,
 // The seeds in the order of a space-filling curve over the box (ord [n]),
 // for the hybrid kernel's super-blocks.
 hipError_t launch_seed_order(const Geo &g, const Seeds &sd, int *ord, hipStream_t st);
-// The bf16 pass over every seed (eig null) or over the tiles' candidate
-// lists (eig from the prep kernel, tile geometry of bf16_pixels_per_lane).
-hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
-                              const PassOut &out, hipStream_t st);
+// The bf16 pass over every seed.
+hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out, hipStream_t st);
 // The double re-check of the queue of a pass over every seed (passes with
 // candidate lists re-check in the tile).
 hipError_t launch_recheck(const Geo &g, const Seeds &sd, const Scalars *sc,

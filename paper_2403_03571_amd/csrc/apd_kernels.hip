@@ -405,16 +405,14 @@ __global__ __launch_bounds__(kThreads, D == 3 ? 3 : 4) void k_assign_hyb(Geo g, 
 // ------------------------------------------------------ k_assign_bf16
 
 // One block per tile of the vector kernel's shape with P pixels per lane
-// (dev::bf16_tile): every seed, or the tile's candidate seeds; seeds staged
-// C at a time.
-template <int D, int P, int C, bool CULL, bool GAP>
-__global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scalars *sc,
-                                                         const double *eig, PassOut out) {
-    __shared__ dev::Bf16Smem<D, P, C, CULL, GAP> sm;
+// (dev::bf16_tile), over every seed, staged C at a time.
+template <int D, int P, int C>
+__global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scalars *sc, PassOut out) {
+    __shared__ dev::Bf16Smem<D, C> sm;
     const int b0 = D == 2 ? blockIdx.y : blockIdx.z;
     const int b1 = D == 2 ? blockIdx.x : blockIdx.y;
     const int b2 = D == 2 ? 0 : blockIdx.x;
-    dev::bf16_tile<D, P, C, CULL, GAP>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, b0, b1, b2, sm, out, &sc->qcount);
+    dev::bf16_tile<D, P, C>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, b0, b1, b2, sm, out, &sc->qcount);
 }
 
 // --------------------------------------------------------- k_super_cull
@@ -679,9 +677,10 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     // short: 2 / 4 rows at 300 per cell 40^3 36.4 / 44.1, 64^3 53.5 / 62.3,
     // 128^3 96 / 106, 256^3 749 / 871; at 600 56^3 47.9 / 48.5, 80^3 55.1 / 60.4,
     // 128^3 78.2 / 74.3, 256^3 393 / 357; at 1700 48^3 35.3 / 36.1, 80^3 48.6 /
-    // 48.7, 96^3 55.7 / 52.3.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
+    // 48.7, 96^3 55.7 / 52.3; with pixel weights, whose moments each wave adds
+    // by itself, at 300 96^3 102 / 93, 200^3 480 / 391.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
     // 46.4 / 43.0: 4 rows.)
-    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || J < (int64_t)450 * g.n)) return 2;
+    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || (!g.mass && J < (int64_t)450 * g.n))) return 2;
     if (cull) return J >= (int64_t)1 << (g.dim == 2 ? 22 : 21) && J >= (int64_t)1000 * g.n ? 8 : 4;
     // over every seed, 8 rows halve the per-seed work of a lane once the grid
     // keeps the chip busy
@@ -753,6 +752,12 @@ hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, c
     return hipGetLastError();
 }
 
+// Both single-precision tiers' passes over candidate lists.  The bf16 tier's
+// lists are as short as the FP32 tier's (9 seeds per wave of 512 voxels), where
+// blocks of 32 seeds on the matrix cores are mostly padding and their looser
+// bound asks for FP32 costs all the same, so it scans them in FP32 as well:
+// evaluation in us, bf16 blocks / FP32 scan, 1024^2 with 1000 cells 65.6 / 50.0,
+// 2048^2 with 2467 127 / 62, 128^3 with 1233 120 / 62, 256^3 with 10^4 631 / 153.
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st) {
     (void)hipGetLastError();
@@ -796,21 +801,17 @@ hipError_t launch_seed_order(const Geo &g, const Seeds &sd, int *ord, hipStream_
     return hipGetLastError();
 }
 
-// Seeds per staged chunk of the bf16 tile: 1024 in 2D over every seed
-// (N = 1000 is one chunk), 256 in 3D or with candidate lists.
-template <int D, int P, bool CULL>
-static void launch_bf16(const Geo &g, Seeds sd, Scalars *sc, const double *eig, const PassOut &out,
-                        hipStream_t st) {
-    constexpr int C = (D == 2 && !CULL) ? 1024 : 256;
-    if (CULL && out.rel_gap) k_assign_bf16<D, P, C, CULL, CULL><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
-    else k_assign_bf16<D, P, C, CULL, false><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+// Seeds per staged chunk of the bf16 tile: 1024 in 2D (N = 1000 is one chunk),
+// 256 in 3D.
+template <int D, int P>
+static void launch_bf16(const Geo &g, Seeds sd, Scalars *sc, const PassOut &out, hipStream_t st) {
+    k_assign_bf16<D, P, D == 2 ? 1024 : 256><<<tile_grid<D, P>(g), kThreads, 0, st>>>(g, sd, sc, out);
 }
 
-template <int D, bool CULL>
-static void launch_bf16_rows(const Geo &g, Seeds sd, Scalars *sc, const double *eig, const PassOut &out,
-                             hipStream_t st) {
-    if (bf16_pixels_per_lane(g) == 4) launch_bf16<D, 4, CULL>(g, sd, sc, eig, out, st);
-    else launch_bf16<D, 2, CULL>(g, sd, sc, eig, out, st);
+template <int D>
+static void launch_bf16_rows(const Geo &g, Seeds sd, Scalars *sc, const PassOut &out, hipStream_t st) {
+    if (bf16_pixels_per_lane(g) == 4) launch_bf16<D, 4>(g, sd, sc, out, st);
+    else launch_bf16<D, 2>(g, sd, sc, out, st);
 }
 
 // Pixel rows per lane of the bf16 tile: 4 in 2D and 2 in 3D (where the
@@ -821,17 +822,10 @@ int bf16_pixels_per_lane(const Geo &g) {
     return g.dim == 2 ? 4 : 2;
 }
 
-hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
-                              const PassOut &out, hipStream_t st) {
+hipError_t launch_assign_bf16(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut &out, hipStream_t st) {
     (void)hipGetLastError();
-    const bool cull = eig != nullptr;
-    if (g.dim == 2) {
-        if (cull) launch_bf16_rows<2, true>(g, sd, sc, eig, out, st);
-        else launch_bf16_rows<2, false>(g, sd, sc, eig, out, st);
-    } else {
-        if (cull) launch_bf16_rows<3, true>(g, sd, sc, eig, out, st);
-        else launch_bf16_rows<3, false>(g, sd, sc, eig, out, st);
-    }
+    if (g.dim == 2) launch_bf16_rows<2>(g, sd, sc, out, st);
+    else launch_bf16_rows<3>(g, sd, sc, out, st);
     return hipGetLastError();
 }
 
