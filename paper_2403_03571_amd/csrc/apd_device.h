@@ -562,7 +562,7 @@ __device__ inline void wave_lds_sync() {
 // about 4 cells per wave): half of the instructions of the 3D kernel, which
 // went from 252 to 158 us (256^3, N = 10^4), the 2D one from 15.9 to 12.6 us
 // (1024^2, N = 1000) and the batched one from 1.32 to 1.13 ms per evaluation
-// (512 maps).  Pixel weights take the old way (they do not fit the bytes).
+// (512 maps).
 constexpr int kAccSlots = 64;  // cells of a tile (longer lists: tile_epilogue)
 
 template <int D, int P>
@@ -609,15 +609,16 @@ static __device__ const MomTab<D, P> mom_tab{};
 typedef int intx4 __attribute__((ext_vector_type(4)));
 
 // LDS of the moments: the cells' sums and each wave's byte selectors.
-template <int P>
+template <int P, bool W = false>
 struct MomSmem {
     int acc[kAccSlots][16];
     alignas(16) unsigned sel[kWaves][2][(P + 3) / 4][64];
+    alignas(16) unsigned wgt[W ? kWaves : 0][2][(P + 3) / 4][64];  // the weights' low and high 4 bits
 };
 
 // Zeroes the first n slots (a barrier must follow).
-template <int P>
-__device__ inline void moments_zero(MomSmem<P> &sm, int n) {
+template <int P, bool W>
+__device__ inline void moments_zero(MomSmem<P, W> &sm, int n) {
     for (int q = threadIdx.x; q < n * 16; q += kThreads) (&sm.acc[0][0])[q] = 0;
 }
 
@@ -633,8 +634,15 @@ __device__ inline void moments_zero(MomSmem<P> &sm, int n) {
 // selectors once) and the lane's row is a table of 8 bytes.  A byte compare in
 // the operand's layout took 3.4 instructions for four entries, 66 more per wave
 // of 512 voxels.
-template <int D, int P, class Slot>
-__device__ inline void moments_add(MomSmem<P> &sm, int lane, const unsigned (&v)[(P + 3) / 4], int ncell, Slot slot) {
+//
+// With pixel weights (W: mass, bytes; pix(p) the index of pixel p, below 0
+// outside the grid) the entries of the row's cell are the weights' low and then
+// their high 4 bits, in two products, and the sums start from zero (each wave
+// reducing its cells by itself: 256^3, N = 10^4 270 us, so 193; 4000^2, N = 9411
+// 182, 159).
+template <int D, int P, bool W, class Slot, class Pix>
+__device__ inline void moments_add(MomSmem<P, W> &sm, int lane, const unsigned (&v)[(P + 3) / 4], int ncell, Slot slot,
+                                   const uint8_t *mass, Pix pix) {
     constexpr int S = MomTab<D, P>::kSteps, H = (P + 3) / 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = lane >> 4, col = lane & 15;
@@ -643,6 +651,25 @@ __device__ inline void moments_add(MomSmem<P> &sm, int lane, const unsigned (&v)
     for (int k = 0; k < S; ++k) tab[k] = *reinterpret_cast<const intx4 *>(&mom_tab<D, P>.v[wave][k][lane][0]);
     const int total = mom_tab<D, P>.total[wave][col];
     const unsigned long long lut = ~(0xffull << (8 * (col & 7)));
+    auto mask = [&](unsigned sel) { return __builtin_amdgcn_perm((unsigned)(lut >> 32), (unsigned)lut, sel); };
+    if constexpr (W) {
+#pragma unroll
+        for (int hh = 0; hh < H; ++hh) {
+            unsigned q[4], lo = 0u, hi = 0u;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int64_t k = 4 * hh + j < P ? pix(4 * hh + j) : -1;
+                q[j] = k >= 0 ? mass[k] : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                lo |= (q[j] & 15u) << (8 * j);
+                hi |= (q[j] >> 4) << (8 * j);
+            }
+            sm.wgt[wave][0][hh][lane] = lo;
+            sm.wgt[wave][1][hh][lane] = hi;
+        }
+    }
     for (int j0 = 0; j0 < ncell; j0 += 16) {
         if (j0) wave_lds_sync();  // the selectors are read by other lanes
 #pragma unroll
@@ -654,14 +681,29 @@ __device__ inline void moments_add(MomSmem<P> &sm, int lane, const unsigned (&v)
                 sm.sel[wave][h][hh][lane] = ((y + 0x78787878u) & 0x80808080u) | y;
             }
         wave_lds_sync();
-        intx4 sum = {total, total, total, total};
+        const int start = W ? 0 : total;
+        intx4 sum = {start, start, start, start}, high = {0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            intx4 a = *reinterpret_cast<const intx4 *>(&sm.sel[wave][col >> 3][k / 4][16 * row + 4 * (k % 4)]);
+            const int at = 16 * row + 4 * (k % 4);
+            intx4 a = *reinterpret_cast<const intx4 *>(&sm.sel[wave][col >> 3][k / 4][at]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                a[e] = (int)__builtin_amdgcn_perm((unsigned)(lut >> 32), (unsigned)lut, (unsigned)a[e]);
+            for (int e = 0; e < 4; ++e) a[e] = (int)mask((unsigned)a[e]);
+            if constexpr (W) {
+                intx4 lo = *reinterpret_cast<const intx4 *>(&sm.wgt[wave][0][k / 4][at]);
+                intx4 hi = *reinterpret_cast<const intx4 *>(&sm.wgt[wave][1][k / 4][at]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    hi[e] &= ~a[e];
+                    a[e] = lo[e] & ~a[e];
+                }
+                high = __builtin_amdgcn_mfma_i32_16x16x64_i8(hi, tab[k], high, 0, 0, 0);
+            }
             sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, tab[k], sum, 0, 0, 0);
+        }
+        if constexpr (W) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) sum[r] += 16 * high[r];
         }
         // register r: cell j0 + 4 row + r, column col
 #pragma unroll
@@ -682,13 +724,13 @@ __device__ inline void moments_add(MomSmem<P> &sm, int lane, const int (&idx)[P]
         for (int j = 0; j < 4; ++j)
             v[hh] |= (unsigned)(4 * hh + j < P ? idx[4 * hh + j < P ? 4 * hh + j : 0] : 127) << (8 * j);
     }
-    moments_add<D, P>(sm, lane, v, ncell, slot);
+    moments_add<D, P, false>(sm, lane, v, ncell, slot, nullptr, [](int) { return (int64_t)-1; });
 }
 
 // Adds the tile's cells to the moments (after a barrier): list[k] the seed of
 // slot k < n, anc the tile's anchor.
-template <int D, int P>
-__device__ inline void moments_flush(const MomSmem<P> &sm, const int *anc, const int *list, int n, uint64_t *mom) {
+template <int D, int P, bool W>
+__device__ inline void moments_flush(const MomSmem<P, W> &sm, const int *anc, const int *list, int n, uint64_t *mom) {
     constexpr int K = moments_per_cell(D);
     constexpr int NP = MomTab<D, P>::kProd;
     const int q = threadIdx.x & 15;
@@ -704,7 +746,7 @@ __device__ inline void moments_flush(const MomSmem<P> &sm, const int *anc, const
         int64_t val = m;
         if (q > D) {
             const int64_t Gd = G(d), Ge = G(e);
-            val = (int64_t)m * (Gd * Ge) + Gd * a[1 + e] + Ge * a[1 + d] + 32 * a[1 + D + c] + a[1 + D + NP + c];
+            val = (int64_t)m * (Gd * Ge) + Gd * a[1 + e] + Ge * a[1 + d] + (int64_t)32 * a[1 + D + c] + a[1 + D + NP + c];
         } else if (q > 0) {
             val = (int64_t)m * G(q - 1) + a[q];
         }
@@ -2146,10 +2188,11 @@ __device__ inline void vec_tile(const Geo &g, const Seeds &sd, double wmax, Cert
     tile_epilogue<D, P>(g, t, act, lab, flag, out, qcount);
 }
 
-// LDS of the list tile (GAP: the pass also returns the relative gaps).
+// LDS of the list tile (GAP: the pass also returns the relative gaps; W: it
+// forms moments with pixel weights).
 constexpr int kListChunk = 256;  // candidates staged at a time, one per thread
 
-template <int D, int P, bool GAP>
+template <int D, int P, bool GAP, bool W = false>
 struct ListSmem {
     // coefficients of the staged candidates, + a dummy (index kListChunk) whose
     // cost is never the minimum; with GAP the free lanes of the last row hold
@@ -2159,7 +2202,7 @@ struct ListSmem {
     int list[kCullCap];               // candidate seeds of the tile
     // each wave's staged positions (and a pair of padding); then its flagged pixels
     alignas(4) uint16_t wl[kWaves][(64 * P > kListChunk ? 64 * P : kListChunk) + 4];
-    MomSmem<P> mom;
+    MomSmem<P, W> mom[GAP ? 0 : 1];  // a pass that returns gaps forms no moments
     CellQuad<D> own[kWaves];
     double red[kWaves];
     int cnt;
@@ -2182,9 +2225,9 @@ struct ListSmem {
 // Against the form that shared the tile over every seed and its two scans
 // (1694 instructions): 112 -> 96 us there, 12.0 -> 11.2 on 1024^2 with N = 1000,
 // 429 -> 379 ms for a batched fit of 512 maps.
-template <int D, int P, bool GAP = false>
+template <int D, int P, bool GAP = false, bool W = false>
 __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig, int b0,
-                                 int b1, int b2, ListSmem<D, P, GAP> &sm, const PassOut &out, unsigned *qcount) {
+                                 int b1, int b2, ListSmem<D, P, GAP, W> &sm, const PassOut &out, unsigned *qcount) {
     constexpr int E0 = tile_ext(D, P, 0), E1 = tile_ext(D, P, 1), E2 = tile_ext(D, P, 2);
     constexpr int kDummy = kListChunk;
     auto &sC = sm.sC;
@@ -2204,7 +2247,7 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
     }
     const bool one = nscan <= kListChunk;
     // the pixels' positions in the tile's list index its moment slots
-    const bool slots = one && !full && nscan <= kAccSlots && !g.mass;
+    const bool slots = one && !full && nscan <= kAccSlots;
     auto seed_at = [&](int q) { return full ? q : s_list[q]; };
 
     float s[3];
@@ -2255,7 +2298,8 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             stage_coef<D>(sC, q, qd, ld, cd, lmn, lmx);
         }
         if (threadIdx.x == kThreads - 1) stage_pad<D>(sC, kDummy);
-        if (slots && out.mom) moments_zero(sm.mom, nscan);
+        if constexpr (!GAP)
+            if (slots && out.mom) moments_zero(sm.mom[0], nscan);
         __syncthreads();
         c = 0;
         auto append = [&](bool cand, int q) {
@@ -2432,22 +2476,26 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             open &= ~beyond;
         }
     }
-    if (slots && out.mom) {
-        unsigned v[(P + 3) / 4];
+    if constexpr (!GAP) {
+        if (slots && out.mom) {
+            unsigned v[(P + 3) / 4];
 #pragma unroll
-        for (int hh = 0; hh < (P + 3) / 4; ++hh) {
-            v[hh] = 0u;
+            for (int hh = 0; hh < (P + 3) / 4; ++hh) {
+                v[hh] = 0u;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) v[hh] |= (unsigned)(4 * hh + j < P ? pos[4 * hh + j < P ? 4 * hh + j : 0] : 0) << (8 * j);
+                for (int j = 0; j < 4; ++j) v[hh] |= (unsigned)(4 * hh + j < P ? pos[4 * hh + j < P ? 4 * hh + j : 0] : 0) << (8 * j);
+            }
+            const unsigned off = (beyond | open) & ((1u << P) - 1u);
+            if (P % 4 != 0 || __ballot(off != 0u)) {
+                // a bit of off into the low bit of its byte
+#pragma unroll
+                for (int hh = 0; hh < (P + 3) / 4; ++hh)
+                    v[hh] |= (((beyond | open) >> (4 * hh) & 15u) * 0x00204081u & 0x01010101u) * 127u;
+            }
+            auto slot = [&](int j) { return (int)wl[j]; };
+            auto pix = [&](int p) { return beyond >> p & 1u ? (int64_t)-1 : (int64_t)pixel_index<D>(g, t.k0w + p, t); };
+            moments_add<D, P, W>(sm.mom[0], t.lane, v, c, slot, g.mass, pix);
         }
-        const unsigned off = (beyond | open) & ((1u << P) - 1u);
-        if (P % 4 != 0 || __ballot(off != 0u)) {
-            // a bit of off into the low bit of its byte
-#pragma unroll
-            for (int hh = 0; hh < (P + 3) / 4; ++hh)
-                v[hh] |= (((beyond | open) >> (4 * hh) & 15u) * 0x00204081u & 0x01010101u) * 127u;
-        }
-        moments_add<D, P>(sm.mom, t.lane, v, c, [&](int j) { return (int)wl[j]; });
     }
     if (!slots || out.labels || __ballot(open != 0u)) {
         bool act[P], flag[P];
@@ -2466,9 +2514,11 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
         }
         recheck_flagged<D, P>(g, sd, t, act, flag, full ? nullptr : s_list, nscan, wl, out, qcount, wmax, Utile);
     }
-    if (slots && out.mom) {
-        __syncthreads();
-        moments_flush<D, P>(sm.mom, t.anc, s_list, nscan, out.mom);
+    if constexpr (!GAP) {
+        if (slots && out.mom) {
+            __syncthreads();
+            moments_flush<D, P>(sm.mom[0], t.anc, s_list, nscan, out.mom);
+        }
     }
 }
 

@@ -289,15 +289,15 @@ __global__ __launch_bounds__(kThreads, 4) void k_assign_vec(Geo g, Seeds sd, Sca
     else vec_tile<3, P>(g, sd, sc->wmax, ct, blockIdx.z, blockIdx.y, blockIdx.x, sm, out, &sc->qcount);
 }
 
-template <int D, int P, bool GAP>
+template <int D, int P, bool GAP, bool W>
 __global__ __launch_bounds__(kThreads, (P <= 4 && !GAP) ? 5 : 4) void k_assign_list(Geo g, Seeds sd, Scalars *sc,
                                                                                     const double *eig, PassOut out) {
-    __shared__ ListSmem<D, P, GAP> sm;
+    __shared__ ListSmem<D, P, GAP, W> sm;
     const Cert ct{sc->lam, sc->kap, sc->sab, sc->lsl};
     if constexpr (D == 2)
-        list_tile<2, P, GAP>(g, sd, sc->wmax, ct, eig, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
+        list_tile<2, P, GAP, W>(g, sd, sc->wmax, ct, eig, blockIdx.y, blockIdx.x, 0, sm, out, &sc->qcount);
     else
-        list_tile<3, P, GAP>(g, sd, sc->wmax, ct, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm, out, &sc->qcount);
+        list_tile<3, P, GAP, W>(g, sd, sc->wmax, ct, eig, blockIdx.z, blockIdx.y, blockIdx.x, sm, out, &sc->qcount);
 }
 
 // ------------------------------------------------------ k_assign_mfma
@@ -648,13 +648,13 @@ hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut 
     return hipGetLastError();
 }
 
-template <int D, bool GAP>
+template <int D, bool GAP, bool W = false>
 hipError_t launch_list(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig, const PassOut &out,
                        hipStream_t st) {
     switch (vec_pixels_per_lane(g, true)) {
-    case 8: k_assign_list<D, 8, GAP><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
-    case 4: k_assign_list<D, 4, GAP><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
-    default: k_assign_list<D, 2, GAP><<<tile_grid<D, 2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    case 8: k_assign_list<D, 8, GAP, W><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
+    case 4: k_assign_list<D, 4, GAP, W><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
+    default: k_assign_list<D, 2, GAP, W><<<tile_grid<D, 2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
     }
     return hipGetLastError();
 }
@@ -677,10 +677,9 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     // short: 2 / 4 rows at 300 per cell 40^3 36.4 / 44.1, 64^3 53.5 / 62.3,
     // 128^3 96 / 106, 256^3 749 / 871; at 600 56^3 47.9 / 48.5, 80^3 55.1 / 60.4,
     // 128^3 78.2 / 74.3, 256^3 393 / 357; at 1700 48^3 35.3 / 36.1, 80^3 48.6 /
-    // 48.7, 96^3 55.7 / 52.3; with pixel weights, whose moments each wave adds
-    // by itself, at 300 96^3 102 / 93, 200^3 480 / 391.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
+    // 48.7, 96^3 55.7 / 52.3.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
     // 46.4 / 43.0: 4 rows.)
-    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || (!g.mass && J < (int64_t)450 * g.n))) return 2;
+    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || J < (int64_t)450 * g.n)) return 2;
     if (cull) return J >= (int64_t)1 << (g.dim == 2 ? 22 : 21) && J >= (int64_t)1000 * g.n ? 8 : 4;
     // over every seed, 8 rows halve the per-seed work of a lane once the grid
     // keeps the chip busy
@@ -764,6 +763,9 @@ hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const 
     if (out.rel_gap)
         return g.dim == 2 ? launch_list<2, true>(g, sd, sc, eig, out, st)
                           : launch_list<3, true>(g, sd, sc, eig, out, st);
+    if (g.mass && out.mom)
+        return g.dim == 2 ? launch_list<2, false, true>(g, sd, sc, eig, out, st)
+                          : launch_list<3, false, true>(g, sd, sc, eig, out, st);
     return g.dim == 2 ? launch_list<2, false>(g, sd, sc, eig, out, st)
                       : launch_list<3, false>(g, sd, sc, eig, out, st);
 }

@@ -194,6 +194,31 @@ def test_tile_scans_by_the_number_of_candidates(ctx, dim, grid, n):
         ctx.apd_set_variant(2)
 
 
+@pytest.mark.parametrize("dim,grid", [(2, (64, 33)), (3, (32, 9, 17))])
+@pytest.mark.parametrize("n", [2, 17, 64, 65, 300])
+def test_weighted_moments_by_the_cells_of_a_tile(ctx, dim, grid, n):
+    """Pixel weights over the whole range of a byte, few to many cells in a
+    tile: counts exactly, gradient, objective and centroids, both tile shapes
+    and the static-scratch evaluation, against the oracle."""
+    import torch
+    q = np.random.default_rng(n).integers(0, 256, grid).astype(np.uint8)
+    q.reshape(-1)[:70] = 255
+    inst = S.masked(S.custom(dim, n, grid, seed=n, sigma=0.2), q)
+    w = np.random.default_rng(n).uniform(-0.2, 0.2, n) * n ** (-2.0 / dim)
+    prob, wd = _prob(inst), torch.as_tensor(w, device="cuda:0")
+    ev = O.evaluate(inst, w)
+    try:
+        for ppl, noalloc in ((0, False), (4, False), (8, False), (0, True)):
+            ctx.apd_set_pixels_per_lane(ppl)
+            out = ctx.apd_dual_objective_grad(prob, wd, counts=True, centroids=True, noalloc=noalloc)
+            np.testing.assert_array_equal(out["counts"].cpu().numpy(), ev.counts)
+            np.testing.assert_allclose(out["grad"].cpu().numpy(), ev.grad, rtol=0, atol=1e-15)
+            np.testing.assert_allclose(out["centroids"].cpu().numpy(), ev.centroids, rtol=0, atol=1e-13)
+            assert out["g"] == pytest.approx(ev.g, rel=1e-12, abs=1e-15)
+    finally:
+        ctx.apd_set_pixels_per_lane(0)
+
+
 @pytest.mark.parametrize("S_", [1, 15, 16, 17, 127, 129, 513, 4095, 4097])
 def test_network_by_the_number_of_samples(ctx, S_):
     """Blocks of 16 samples, slices of the samples and chunks of 128, the
