@@ -38,8 +38,7 @@ constexpr int kHist = 10;  // stored curvature pairs (the solver's memory)
 // ------------------------------------------------------------ block helpers
 
 __device__ inline double block_sum(double v, double *red) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    v = wave_sum(v);
     const int w = threadIdx.x >> 6;
     __syncthreads();
     if (__lane_id() == 0) red[w] = v;
@@ -50,8 +49,7 @@ __device__ inline double block_sum(double v, double *red) {
 }
 
 __device__ inline double block_max(double v, double *red) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o));
+    v = wave_max(v);
     const int w = threadIdx.x >> 6;
     __syncthreads();
     if (__lane_id() == 0) red[w] = v;

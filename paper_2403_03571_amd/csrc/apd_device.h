@@ -246,6 +246,33 @@ __device__ inline double wave_min(double v) {
     return fmin(fmin(lane_double(v, 0), lane_double(v, 16)), fmin(lane_double(v, 32), lane_double(v, 48)));
 }
 
+// The butterfly v = f(v, v of lane ^ o), o = 32, 16, 8, 4, 2, 1, for a
+// commutative f, without the LDS round trips of __shfl_xor (two per step and
+// double, about 100 cycles each): a half (row) swap leaves the pair's lower
+// lane in one register and its upper lane in the other.  With it the prep and
+// finalize of an evaluation in one block take 3.8 + 4.0 instead of 4.3 + 4.8 us.
+template <class F>
+__device__ inline double wave_butterfly(double v, F f) {
+    auto swapped = [&](auto swap) {
+        const long long b = __double_as_longlong(v);
+        const auto lo = swap((unsigned)(b & 0xffffffffll)), hi = swap((unsigned)(b >> 32));
+        auto join = [](unsigned l, unsigned h) { return __longlong_as_double(((long long)h << 32) | (long long)l); };
+        return f(join(lo[0], hi[0]), join(lo[1], hi[1]));
+    };
+    v = swapped([](unsigned x) { return __builtin_amdgcn_permlane32_swap(x, x, false, false); });
+    v = swapped([](unsigned x) { return __builtin_amdgcn_permlane16_swap(x, x, false, false); });
+    v = f(v, dpp_double<0x128>(v));                    // row_ror:8
+    v = f(v, dpp_double<0x1B>(dpp_double<0x141>(v)));  // ^ 7, then ^ 3
+    v = f(v, dpp_double<0x4E>(v));
+    return f(v, dpp_double<0xB1>(v));
+}
+__device__ inline double wave_sum(double v) {
+    return wave_butterfly(v, [](double a, double b) { return a + b; });
+}
+__device__ inline double wave_max(double v) {
+    return wave_butterfly(v, [](double a, double b) { return fmax(a, b); });
+}
+
 // ------------------------------------------------------ tile epilogue
 
 // The labels of the settled pixels (a flagged pixel's is written by the

@@ -79,7 +79,7 @@ struct Scalars {
     double gpix;        // sum_j q_j C_{H_j j} (costs other than the squared norm)
 };
 
-enum : int { kBadW = 1, kBadX = 2, kBadA = 4, kBadSPD = 8, kBadV = 16 };
+enum : int { kBadW = 1, kBadX = 2, kBadA = 4, kBadSPD = 8, kBadV = 16, kBadAll = 31 };
 
 // Per-block partial results of the multi-block prep and finalize kernels;
 // the last block to finish (ticket) combines them in block order, so the

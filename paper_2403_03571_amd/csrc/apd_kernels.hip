@@ -157,14 +157,15 @@ __global__ __launch_bounds__(T) void k_prep(Geo g, Seeds sd, Scalars *sc, uint64
     // block reduction: a butterfly inside each wave, then the wave results
     // in wave order by thread 0 (whose slots 0 then hold the block's values)
     auto reduce = [&](double a, double v, float l, float kk, int b) {
+        a = wave_max(a);
+        int any = 0;
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            a = fmax(a, __shfl_xor(a, o));
-            b = b | __shfl_xor(b, o);
-            if (w_only) continue;
-            v = v + __shfl_xor(v, o);
-            l = fmaxf(l, __shfl_xor(l, o));
-            kk = fmaxf(kk, __shfl_xor(kk, o));
+        for (int bit = 1; bit <= kBadAll; bit <<= 1) any |= __ballot((b & bit) != 0) ? bit : 0;
+        b = any;
+        if (!w_only) {
+            v = wave_sum(v);
+            l = (float)wave_max((double)l);
+            kk = (float)wave_max((double)kk);
         }
         __syncthreads();  // earlier readers of the slots are done
         if (__lane_id() == 0) {
@@ -549,11 +550,8 @@ __global__ __launch_bounds__(T) void k_finalize(Geo g, Seeds sd, const uint64_t 
             for (int d = 0; d < D; ++d) out.centroids[(size_t)i * D + d] = ybar[d];
     }
     auto reduce = [&](double a, double m) {
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            a = a + __shfl_xor(a, o);
-            m = fmax(m, __shfl_xor(m, o));
-        }
+        a = wave_sum(a);
+        m = wave_max(m);
         __syncthreads();
         if (__lane_id() == 0) {
             s_g[tid >> 6] = a;
