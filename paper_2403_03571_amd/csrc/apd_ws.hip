@@ -494,7 +494,7 @@ __global__ __launch_bounds__(256) void kw_grad(const float *__restrict__ X, int 
     const int64_t o = first ? oW1 : job < 4 ? oW3 : oW2;
     const int c = lane & 31, h = lane >> 5;
     const int mt = first ? 0 : 32 * (wave >> 1), nt = 32 * (wave & 1);  // the wave's tile in the block's
-    floatx16_t acc{};
+    floatx16_t acc{}, odd{};  // two chains: half the roundings, and no wait between products
     for (int k0 = ka; k0 < kb; k0 += kGradChunk) {
         // 16 threads per sample row, 4 columns each
         constexpr int R = kGradChunk / 16;
@@ -522,14 +522,17 @@ __global__ __launch_bounds__(256) void kw_grad(const float *__restrict__ X, int 
         __syncthreads();
         const int cnt = min(kGradChunk, kb - k0);
         if (!first || wave < 2)
-            for (int k = 0; k < cnt; k += 2)
+            for (int k = 0; k < cnt; k += 4) {  // rows past the slice are zero
                 acc = __builtin_amdgcn_mfma_f32_32x32x2f32(sm[0][k + h][mt + c], sm[1][k + h][nt + c], acc, 0, 0, 0);
+                odd = __builtin_amdgcn_mfma_f32_32x32x2f32(sm[0][k + 2 + h][mt + c], sm[1][k + 2 + h][nt + c], odd, 0, 0,
+                                                           0);
+            }
     }
     if (first && wave >= 2) return;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const int m = m0 + mt + 8 * (r >> 2) + 4 * h + (r & 3);
-        if (m < rows) out[o + (int64_t)m * kHid + n0 + nt + c] = acc[r];
+        if (m < rows) out[o + (int64_t)m * kHid + n0 + nt + c] = acc[r] + odd[r];
     }
 }
 
@@ -556,9 +559,11 @@ __global__ __launch_bounds__(256) void kw_reduce(int ns, const float *__restrict
     }
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= kParams) return;
-    float gi = 0.0f;
+    // in double: it costs nothing beside the loads
+    double sum = 0.0;
 #pragma unroll 8
-    for (int q = 0; q < ns; ++q) gi += part[(size_t)q * kParams + i];
+    for (int q = 0; q < ns; ++q) sum += (double)part[(size_t)q * kParams + i];
+    const float gi = (float)sum;
     if constexpr (ADAM) {
         const float mi = 0.9f * mo[i] + 0.1f * gi;
         const float vi = 0.999f * ve[i] + 0.001f * gi * gi;
