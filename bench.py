@@ -60,7 +60,7 @@ MEASURED_TRAFFIC = {
     ("k_assign_hyb<3>", "c3"): {
         "fetch_kib": 5692.0, "write_kib": 20526.7, "fetch_factor": 1048576 / 524302.5, "write_factor": 1.0,
         "sources_sha256": "d6e1432f3ee2cf41122062e0506e6c059bd5ca704adf47dfbddb357b20ae9a4e"},
-    ("k_assign_vec<2, false, 4>", "c2"): {
+    ("k_assign_vec<2, 4>", "c2"): {
         "fetch_kib": 366.0, "write_kib": 715.9, "fetch_factor": 1048576 / 524302.5, "write_factor": 1.0,
         "sources_sha256": "d6e1432f3ee2cf41122062e0506e6c059bd5ca704adf47dfbddb357b20ae9a4e"},
 }
@@ -109,21 +109,27 @@ def hyb_by_default(inst) -> bool:
 def kernel_name(args, inst, cull=False) -> str:
     """The assignment kernel a pass of this configuration launches."""
     d = inst.dim
+    p = getattr(args, "pixels_per_lane", 0)
     if args.prec == "fp64":
-        return f"k_assign_fp64<{d}>"
+        return f"k_assign_fp64<{d}, {'true' if cull else 'false'}>"
+    if cull:
+        if p not in (4, 8):
+            if d == 3 and (inst.J < 1 << 19 or inst.J < 450 * inst.n):
+                p = 2
+            else:
+                large = inst.J >= 1 << (22 if d == 2 else 21) and inst.J >= 1000 * inst.n
+                p = 8 if large and (d == 3 or inst.J < 8000 * inst.n) else 4
+        return f"k_assign_list<{d}, {p}>"
     if args.prec == "bf16":
-        p = getattr(args, "pixels_per_lane", 0)
         rows = p // 2 if p in (4, 8) else (4 if d == 2 else 2)
-        chunk = 1024 if d == 2 and not cull else 256
-        return f"k_assign_bf16<{d}, {rows}, {chunk}, {'true' if cull else 'false'}>"
+        return f"k_assign_bf16<{d}, {rows}, {1024 if d == 2 else 256}>"
     if args.variant == 0:
         return f"k_assign_mfma<{d}>"
-    if not cull and (args.variant == 3 or (args.variant == 2 and hyb_by_default(inst))):
+    if args.variant == 3 or (args.variant == 2 and hyb_by_default(inst)):
         return f"k_assign_hyb<{d}>"
-    p = getattr(args, "pixels_per_lane", 0)
     if p not in (4, 8):
-        p = 4 if cull else (8 if inst.J >= 1024 * 2048 else 4)
-    return f"k_assign_vec<{d}, {'true' if cull else 'false'}, {p}>"
+        p = 8 if inst.J >= 1024 * 2048 else 4
+    return f"k_assign_vec<{d}, {p}>"
 
 
 def cpu_baseline(inst, w, budget_s: float = 15.0):
