@@ -1363,11 +1363,11 @@ struct CellQuad {
 };
 
 // Cost e^T A e - w', gradient -2 A e; hh = |h|^2.  Slack: with E = |e| + |h|
-// and S = lambda_G E^2 + |w'| every term of the bound above is at most S in
-// magnitude and reaches the sum through fewer than 24 roundings of 2^-24
-// (an offset passed on from a super-tile's record carries 2 more, of its
-// own centre's scale, at most 8 E), less than 2^-18 S per seed;
-// s = 2^-15 (lam (|e|^2 + |h|^2) + |w'|) >= 2^-16 S, four times that.
+// and S = lambda_G E^2 + |w'| the terms of the bound above sum to at most S in
+// magnitude and reach it through fewer than 24 roundings of 2^-24, less than
+// 2^-18 S per seed; s = 2^-15 (lam (|e|^2 + |h|^2) + |w'|) >= 2^-16 S, four times
+// that.  An offset that is shifted from another centre (shift_slack) carries
+// that shift's error besides.
 template <int D>
 __device__ inline CellQuad<D> cell_quad(const SeedRec<D> &r, float lam, float hh) {
     CellQuad<D> q;
@@ -1390,6 +1390,21 @@ __device__ inline CellQuad<D> cell_quad(const SeedRec<D> &r, float lam, float hh
     q.c = c - r.wp;
     q.s = 0x1p-15f * fmaf(lam, e2, fabsf(r.wp));
     return q;
+}
+
+// What hh grows by for offsets formed from those about another centre, `shift`
+// away, by an addition in FP32.  The stored offset, the shift and their sum leave
+// at most t = 2^-22 |shift| in e besides relative roundings of e itself, and
+// |shift| can be many times E: a last tile of one pixel under a super-tile of
+// eight has h = 0.  The terms are then off by at most 2 lambda_G t E + lambda_G t^2
+// more.  With 2^-10 |shift|^2 added to hh, the three quarters of s that the
+// roundings leave hold 2^-15 lambda_G (3/8 E^2 + 2^-10 |shift|^2) >= 2^-19.7 lambda_G
+// E |shift|, against 2^-21 lambda_G E |shift| (1 + 2^-20).
+template <int D>
+__device__ inline float shift_slack(const float *shift, float hh) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) hh = fmaf(0x1p-10f * shift[d], shift[d], hh);
+    return hh;
 }
 
 // Whether q can cost as little as the owner o somewhere in the box of half
@@ -1890,7 +1905,7 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
                     int i;
                     return load_rec<D>(src, cap, q, shift, i);
                 },
-                h, hh, ct.lam, slack, sm.cnt, sm.own, [&](int q, const SeedRec<D> &, int pos) {
+                h, shift_slack<D>(shift, hh), ct.lam, slack, sm.cnt, sm.own, [&](int q, const SeedRec<D> &, int pos) {
                     if (pos < kCullCap) dst[pos] = __float_as_int(src[q].w);
                 });
         }

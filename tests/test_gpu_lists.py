@@ -1,0 +1,72 @@
+"""GPU: candidate lists where their rounding slack is what keeps a winner, and
+calls at the limits of the lists' room and of a launch, against every seed."""
+import numpy as np
+import pytest
+
+import apd_synth as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import paper_2403_03571_amd as apd
+    return apd.Context(0)
+
+
+def _prob(inst):
+    import paper_2403_03571_amd as apd
+    return apd.Problem.from_instance(inst, "cuda:0")
+
+
+def _instance(grid, x, A):
+    dim, n = x.shape[1], len(x)
+    v = np.full(n, 1.0 / n)
+    v[0] += 1.0 - v.sum()
+    return S.Instance(dim, grid, np.zeros(dim), np.ones(dim), x, A, v)
+
+
+def _every_seed(ctx, prob, w):
+    ctx.apd_set_culling(False)
+    try:
+        return ctx.apd_assign(prob, w, prec="fp64")
+    finally:
+        ctx.apd_set_culling(True)
+
+
+@pytest.mark.parametrize("grid,rows", [((65536, 225), 32), ((225, 65536), 32), ((65537, 1, 9), 32)])
+def test_near_ties_beside_clipped_tiles(ctx, grid, rows):
+    """Pairs of seeds beside the grid's last tiles, which hold one column (row,
+    layer) of very uneven pixels: the costs of a pair differ by 10^-9 to 10^-4 of
+    themselves, far above the double rounding and far below that of an offset
+    taken from the super-tile's centre in FP32."""
+    import torch
+    rng = np.random.default_rng(5)
+    dim = len(grid)
+    long = int(np.argmax(grid))
+    thin = dim - 1 if long == 0 else 0
+    side = 1.0 / grid[long]
+    m = grid[long] // (2 * rows)
+    x = np.full((m, 2, dim), 0.5)
+    x[:, :, long] = ((2 * rows * np.arange(m) + rows / 2 + rng.uniform(-rows / 4, rows / 4, m)) * side)[:, None]
+    mid = 1.0 - 0.5 / grid[thin]
+    x[:, :, thin] = mid + rng.choice([-1, 1], (m, 2)) * rng.uniform(0.15, 1.0, (m, 2)) * rows * side
+    r2 = (x[:, :, thin] - mid) ** 2
+    w = np.zeros((m, 2))
+    w[:, 1] = r2[:, 1] - r2[:, 0] + np.exp(rng.uniform(np.log(1e-9), np.log(1e-4), m)) * r2.max(1) * \
+        rng.choice([-1.0, 1.0], m)
+    n = 2 * m
+    assert n > 256
+    inst = _instance(grid, x.reshape(n, dim), np.tile(np.eye(dim), (n, 1, 1)))
+    prob, wd = _prob(inst), torch.as_tensor(w.reshape(n), device="cuda:0")
+    ref = _every_seed(ctx, prob, wd)
+    try:
+        for ppl in (0, 4, 8):
+            ctx.apd_set_pixels_per_lane(ppl)
+            for prec in ("fp32", "bf16", "fp64"):
+                bad = int((ctx.apd_assign(prob, wd, prec=prec) != ref).sum())
+                assert bad == 0, (ppl, prec, bad)
+                out = ctx.apd_dual_objective_grad(prob, wd, prec=prec, counts=True)
+                assert torch.equal(out["counts"].cpu(), torch.bincount(ref.reshape(-1).cpu().long(), minlength=n))
+    finally:
+        ctx.apd_set_pixels_per_lane(0)
