@@ -2420,12 +2420,16 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
             // monomial of a cost reaches it, the gradient or the bound through
             // fewer than 24 roundings of 2^-24 and their magnitudes sum to at
             // most 3 C + 6 r^2 (the vector tile's bound), r^2 = lam |u|^2 at the
-            // tile's corner: 2^-16 (|C| + 2 r^2) is more than twice that
+            // tile's corner: 2^-16 (|C| + 2 r^2) is more than twice that.  The
+            // double rounding of the costs and of their coefficients is relative
+            // to lam |d|^2, up to kappa times C: kslack (|C| + 2 r^2), four times
+            // its 2^-46 (kappa + 1) (C + r^2), counts from kappa of about 2^30
             float uc[3], h[3];
             for (int d = 0; d < D; ++d) {
                 uc[d] = (float)(ka[d] + kb[d] + 1) * (0.5f * s[d]);
                 h[d] = (float)(kb[d] - ka[d]) * (0.5f * (1.0f + 0x1p-20f) * s[d]);
             }
+            const float ks = 0x1p-16f + kslack(ct);
             auto staged_quad = [&](int q) {
                 CellQuad<D> r;
                 const float4 c0 = sC[0][q], c1 = sC[1][q];
@@ -2447,7 +2451,7 @@ __device__ inline void list_tile(const Geo &g, const Seeds &sd, double wmax, Cer
                     r.g[1] = fmaf(c0.y, uc[0], fmaf(c1.x, uc[1], t1));
                     r.g[D - 1] = fmaf(c0.z, uc[0], fmaf(c1.y, uc[1], fmaf(c1.z, uc[2], t2)));
                 }
-                r.s = 0x1p-16f * (fabsf(r.c) + 2.0f * r2t);
+                r.s = ks * (fabsf(r.c) + 2.0f * r2t);
                 return r;
             };
             const float sl = ct.lsl;

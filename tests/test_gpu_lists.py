@@ -70,3 +70,29 @@ def test_near_ties_beside_clipped_tiles(ctx, grid, rows):
                 assert torch.equal(out["counts"].cpu(), torch.bincount(ref.reshape(-1).cpu().long(), minlength=n))
     finally:
         ctx.apd_set_pixels_per_lane(0)
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (64, 70)), (3, (17, 20, 33))])
+@pytest.mark.parametrize("n", [2, 6])
+def test_ill_conditioned_seeds_far_away(ctx, dim, grid, n):
+    """Pairs of seeds 10^6 box sides away on either side along the least
+    eigenvalue's direction of matrices of condition number 10^12: their costs tie
+    up to the rounding of the double evaluation, which decides the labels."""
+    import torch
+    rng = np.random.default_rng(n)
+    R = np.linalg.qr(rng.normal(size=(n // 2, dim, dim)))[0]
+    ev = np.array([1e-12] + [1.0] * (dim - 1))
+    A = (R * ev) @ np.swapaxes(R, -1, -2)
+    A = np.repeat(0.5 * (A + np.swapaxes(A, -1, -2)), 2, axis=0)
+    x = 0.5 + 1e6 * np.array([1.0, -1.0])[None, :, None] * R[:, None, :, 0]
+    inst = _instance(grid, x.reshape(n, dim), A)
+    prob, wd = _prob(inst), torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    ref = _every_seed(ctx, prob, wd)
+    assert len(ref.unique()) > 1
+    try:
+        for ppl in (0, 4, 8):
+            ctx.apd_set_pixels_per_lane(ppl)
+            for prec in ("fp32", "bf16", "fp64"):
+                assert torch.equal(ctx.apd_assign(prob, wd, prec=prec), ref), (ppl, prec)
+    finally:
+        ctx.apd_set_pixels_per_lane(0)

@@ -9,11 +9,12 @@ off: 2^-49 (lambda_G |d|^2 + |w| + lambda_G sum_d Y_d^2) per seed, |d| the
 largest distance to the box and Y_d the largest coordinate.  The exact values are
 formed in extended precision (2^-64) from the exact box.
 
-The bound is replayed for a box's seeds from the caller's arrays and for a tile's
-from its super-tile's records (their offsets shifted to the tile's centre in
-FP32); on whole tiles and on last tiles that the grid's end clips to a column or a
-single pixel, boxes with very uneven pixels and away from the origin, seeds near
-and far, condition numbers up to 10^6 and a large common offset of the weights.
+Three forms of the bound are replayed: a box's seeds from the caller's arrays, a
+tile's from its super-tile's records (their offsets shifted to the tile's centre
+in FP32), and a wave's from the tile's staged coefficients; on whole tiles and on
+last tiles that the grid's end clips to a column or a single pixel, boxes with
+very uneven pixels and away from the origin, seeds near and far, condition
+numbers up to 10^12 and a large common offset of the weights.
 """
 from __future__ import annotations
 
@@ -36,7 +37,7 @@ def tile_ext(dim, p):
 class Case:
     """A tile of a grid, the super-tile that holds it, and m pairs of seeds."""
 
-    def __init__(self, rng, dim, grid, lo, hi, p, sf, tile, m, kappa, reach, offset=0.0):
+    def __init__(self, rng, dim, grid, lo, hi, p, sf, tile, m, kappa, reach, offset=0.0, soft=False):
         self.dim, self.m = dim, m
         self.ext = tile_ext(dim, p)
         self.lo, self.grid = lo, grid
@@ -52,10 +53,12 @@ class Case:
         u = rng.normal(size=(m, 2, dim))
         u /= np.linalg.norm(u, axis=-1, keepdims=True)
         scale = np.where(rng.random((m, 1, 1)) < 0.5, min(self.s), np.asarray(self.s))
-        self.x = y[:, None, :] + far * u * scale
         k = np.exp(rng.uniform(0.0, np.log(kappa), (m, 2)))
         ev = np.stack([k ** (t / (dim - 1)) for t in range(dim)], -1) * k[..., None] ** -0.5
         R = np.linalg.qr(rng.normal(size=(m, 2, dim, dim)))[0]
+        if soft:  # along the direction of the least eigenvalue
+            u, scale = R[..., 0], min(self.s)
+        self.x = y[:, None, :] + far * u * scale
         A = (R * ev[..., None, :]) @ np.swapaxes(R, -1, -2)
         self.A = 0.5 * (A + np.swapaxes(A, -1, -2))
         self.w = np.zeros((m, 2))
@@ -169,6 +172,47 @@ class Case:
                              for d in range(self.dim)], q, hh) for q in (0, 1)]
         return self.bound(Q, h), self.exact(self.a, self.b)
 
+    def from_staged(self, wa, wb):
+        """A wave's seeds (its box the pixels wa .. wb) from the staged
+        coefficients of the tile."""
+        dim = self.dim
+        anc_k = [self.a[d] + self.ext[d] // 2 for d in range(dim)]
+        s = [f4(v) for v in self.s]
+        r2t = f4(0)
+        for d in reversed(range(dim)):
+            half = f4(0.5 * self.ext[d]) * s[d]
+            r2t = fma(half, half, r2t)
+        r2t = self.lam * r2t * f4(1.01)
+        uc = [f4(wa[d] + wb[d] + 1 - 2 * anc_k[d]) * (f4(0.5) * s[d]) for d in range(dim)]
+        h = [f4(wb[d] - wa[d]) * (f4(0.5 * (1 + 2.0 ** -20)) * s[d]) for d in range(dim)]
+        kslack = f4(2.0 ** -44) * (self.kap + f4(1))
+        Q = []
+        for q in (0, 1):
+            e = [self.x[:, q, d] - (self.lo[d] + anc_k[d] * self.s[d]) for d in range(dim)]
+            ee, lin = 0.0, []
+            for r in range(dim):
+                ae = 0.0
+                for k in range(dim):
+                    ae = ae + self.A[:, q, min(r, k), max(r, k)] * e[k]
+                lin.append((-2.0 * ae).astype(f4))
+                ee = ee + e[r] * ae
+            c0 = (ee - (self.w[:, q] - self.wmax)).astype(f4)
+            a = [((1.0 if r == t else 2.0) * self.A[:, q, r, t]).astype(f4) for r in range(dim) for t in range(r, dim)]
+            if dim == 2:
+                t0 = fma(a[0], uc[0], fma(a[1], uc[1], lin[0]))
+                t1 = fma(a[2], uc[1], lin[1])
+                c = fma(t0, uc[0], fma(t1, uc[1], c0))
+                g = [fma(a[0], uc[0], t0), fma(a[1], uc[0], fma(a[2], uc[1], t1))]
+            else:
+                t0 = fma(a[0], uc[0], fma(a[1], uc[1], fma(a[2], uc[2], lin[0])))
+                t1 = fma(a[3], uc[1], fma(a[4], uc[2], lin[1]))
+                t2 = fma(a[5], uc[2], lin[2])
+                c = fma(t0, uc[0], fma(t1, uc[1], fma(t2, uc[2], c0)))
+                g = [fma(a[0], uc[0], t0), fma(a[1], uc[0], fma(a[3], uc[1], t1)),
+                     fma(a[2], uc[0], fma(a[4], uc[1], fma(a[5], uc[2], t2)))]
+            Q.append((c, (f4(2.0 ** -16) + kslack) * (np.abs(c) + f4(2) * r2t), g, a))
+        return self.bound(Q, h), self.exact(wa, wb)
+
 
 def worst(result):
     """Largest (computed bound - exact bound + what the double costs can be
@@ -225,3 +269,29 @@ def test_pairs_beside_a_clipped_tile(box):
         c = case.cost(y)
         (lb0, t0), (lb1, t1) = case.from_records()[0]
         assert not np.any((lb0 > t0) & (c[:, 0] <= c[:, 1])) and not np.any((lb1 > t1) & (c[:, 1] <= c[:, 0]))
+
+
+def waves_of(case, p):
+    """The pixels of the tile's waves."""
+    dim = case.dim
+    we = (4 * p, 16) if dim == 2 else (p, 8, 8)
+    for w in range(4):
+        if dim == 2 or p == 8:
+            off = ((w >> 1) * we[0], (w & 1) * we[1], 0)
+        else:
+            off = (w * p, 0, 0)
+        a = [case.a[d] + off[d] for d in range(dim)]
+        yield a, [max(a[d], min(a[d] + we[d], case.grid[d]) - 1) for d in range(dim)]
+
+
+@pytest.mark.parametrize("box", range(len(BOXES)))
+@pytest.mark.parametrize("kappa,reach,offset,soft", [(9.0, (0.05, 40.0), 0.0, False), (9.0, (0.5, 400.0), 1e3, False),
+                                                     (1e6, (0.05, 400.0), 0.0, True), (1e12, (1e3, 1e9), 0.0, True)])
+def test_lists_of_a_wave(box, kappa, reach, offset, soft):
+    """A wave's seeds from the tile's staged coefficients.  Far along the least
+    eigenvalue's direction of an ill-conditioned matrix a cost is small against the
+    terms of its double evaluation, whose rounding the slack has to cover."""
+    rng = np.random.default_rng(300 + box)
+    case = Case(rng, *BOXES[box], m=20000, kappa=kappa, reach=reach, offset=offset, soft=soft)
+    for wa, wb in waves_of(case, BOXES[box][4]):
+        assert worst(case.from_staged(wa, wb)) <= 1.0
