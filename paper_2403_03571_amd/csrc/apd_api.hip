@@ -260,7 +260,7 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
     // s super-tiles each read n seeds; h regions read n and leave each
     // super-tile about c n / h (c = 8 for the margin around the region's box):
     // least at h = sqrt(c s)
-    if (p->power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
+    if (g.power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
         const int f = std::max(2, (int)lround(pow((double)L.nsuper / 8.0, 0.5 / p->dim)));
         L.nregion = 1;
         for (int d = 0; d < 3; ++d) {

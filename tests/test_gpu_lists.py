@@ -96,3 +96,33 @@ def test_ill_conditioned_seeds_far_away(ctx, dim, grid, n):
                 assert torch.equal(ctx.apd_assign(prob, wd, prec=prec), ref), (ppl, prec)
     finally:
         ctx.apd_set_pixels_per_lane(0)
+
+
+def _seconds(f, reps=5):
+    import time
+
+    import torch
+    f()
+    best = float("inf")
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t0)
+    return best
+
+
+def test_regions_whichever_way_the_power_is_given(ctx):
+    """power = 0 (the header's name of the squared norm, what a zeroed struct
+    holds) takes the same way as power = 2: the super-tiles' lists by way of
+    regions, without which this call takes three times as long."""
+    import torch
+    inst = S.custom(2, 53333, (4000, 4000), seed=1, sigma=0.2)
+    prob, wd = _prob(inst), torch.zeros(inst.n, dtype=torch.float64, device="cuda:0")
+    took, labels = [], []
+    for power in (2, 0):
+        prob.power = power
+        took.append(_seconds(lambda: ctx.apd_assign(prob, wd)))
+        labels.append(ctx.apd_assign(prob, wd))
+    assert torch.equal(*labels) and took[1] < 1.5 * took[0], took
