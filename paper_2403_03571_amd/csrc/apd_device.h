@@ -765,7 +765,7 @@ __device__ inline void moments_flush(const MomSmem<P, W> &sm, const int *anc, co
     const int c = max(0, q - 1 - D);
     const int d = D == 2 ? (c == 2) : (c < 3 ? 0 : c < 5 ? 1 : 2);
     const int e = D == 2 ? (c >= 1) : (c < 3 ? c : c < 5 ? c - 2 : 2);
-    auto G = [&](int k) { return (int64_t)(2 * (k == 0 ? anc[0] : k == 1 ? anc[1] : anc[2])); };
+    auto G = [&](int k) { return 2 * (int64_t)(k == 0 ? anc[0] : k == 1 ? anc[1] : anc[2]); };
     for (int k = threadIdx.x >> 4; k < n; k += kThreads / 16) {
         const int *a = sm.acc[k];
         const int m = a[0];
@@ -1897,7 +1897,7 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
                 const float s = (float)g.s[d];
                 h[d] = 0.5f * (float)(b - a) * s * (1.0f + 0x1p-20f);
                 hh = fmaf(h[d], h[d], hh);
-                shift[d] = 0.5f * (float)(sa + sb - a - b) * s;
+                shift[d] = 0.5f * (float)((sa - a) + (sb - b)) * s;
             }
             return owner_filter<D, kThreads>(
                 nsrc,

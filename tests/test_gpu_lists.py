@@ -126,3 +126,20 @@ def test_regions_whichever_way_the_power_is_given(ctx):
         took.append(_seconds(lambda: ctx.apd_assign(prob, wd)))
         labels.append(ctx.apd_assign(prob, wd))
     assert torch.equal(*labels) and took[1] < 1.5 * took[0], took
+
+
+def test_first_moments_of_a_very_long_axis(ctx):
+    """An axis of more than 2^30 pixels: counts and centroids of the two halves
+    of a row (their second moments leave 64 bits there)."""
+    import torch
+    M = 1200000000
+    x = np.array([[0.85, 0.5], [0.97, 0.5]])
+    prob = _prob(_instance((M, 1), x, np.tile(np.eye(2), (2, 1, 1))))
+    cut = int(round(0.91 * M))
+    for prec in ("fp32", "fp64"):
+        out = ctx.apd_dual_objective_grad(prob, torch.zeros(2, dtype=torch.float64, device="cuda:0"), prec=prec,
+                                          counts=True, centroids=True)
+        k = out["counts"].cpu().numpy()
+        assert abs(int(k[0]) - cut) <= 1 and k.sum() == M
+        want = np.array([0.5 * k[0], k[0] + 0.5 * k[1]]) / M
+        np.testing.assert_allclose(out["centroids"].cpu().numpy()[:, 0], want, rtol=1e-12, atol=0)
