@@ -167,9 +167,9 @@ apd_status apd_dual_objective_grad(apd_ctx *ctx, const apd_problem *prob, const 
  * about (100 n + 4 J) bytes plus, with candidate lists, 1 KiB per tile of
  * 1024 pixels and 2 KiB per super-tile: up to about 2 * 10^7 pixels at
  * n = 10^4 -- are rejected with APD_ERR_OOM and a message giving the size
- * needed.  Candidate lists keep at most 256 seeds per tile and 512 per
- * super-tile (longer lists fall back to every seed, as with the regular
- * call).  Every call on a device shares that device's array: calls that
+ * needed.  The super-tiles' candidate lists take what the array has left, up
+ * to 2048 seeds each as with the regular call (longer lists fall back to
+ * every seed).  Every call on a device shares that device's array: calls that
  * overlap in time on one device (other threads, other streams) race and
  * must be serialised by the caller.
  * Errors: as apd_dual_objective_grad, plus OOM for problems too large. */

@@ -36,8 +36,9 @@ struct apd_ctx {
     int *ws_nb = nullptr;             // [cap_n][16] nearest seeds (warm-start features)
     double *cost_part = nullptr;      // [cap_parts] per-block cost sums (costs other than |.|^2_A)
     int64_t cap_parts = 0;
-    float4 *super_lists = nullptr;    // candidate records of the super-tiles
+    float4 *super_lists = nullptr;    // candidate records (or numbers) of the super-tiles and regions
     size_t super_bytes = 0;
+    bool super_ids_only = false;      // the last eager pass kept numbers alone
     int *super_count = nullptr;       // [cap_super]
     int64_t cap_super = 0;
     bool need_qtotal = false;          // sum the pixel weights in the next pass (validation)
@@ -215,6 +216,7 @@ struct PassBufs {
     double *eig = nullptr;         // [n][2]
     int *ord = nullptr;            // [n] seed order of the hybrid kernel
     float4 *super_lists = nullptr; // [super-tiles][rec_vec][super_cap]
+    int *super_ids = nullptr;      // or [super-tiles][super_cap]
     int *super_count = nullptr;    // [super-tiles]
     int64_t cap_super = 0;
     int super_cap = apd::kSuperCap;
@@ -236,7 +238,21 @@ struct ListGeometry {
     int hf[3] = {1, 1, 1};  // super-tiles of a region per axis
     int nh[3] = {1, 1, 1};
     int64_t nregion = 0;    // 0: no regions
+    bool super = false;     // the tiles pick their seeds from the super-tiles' lists
+    bool single() const { return sf[0] * sf[1] * sf[2] == 1; }  // a super-tile is one tile
 };
+
+// Seeds so dense that a super-tile of three cell diameters is one tile get lists
+// all the same from so many pairs of tile and seed: a tile that starts from every
+// seed reads 104 bytes of each, twice, the lists' kernel 48 (or its region's).
+// Evaluation without / with them: 2048^2 with 34952 seeds 688 / 201 us, 139810
+// 2573 / 2185; 512^2 with 8738 (2.2e6 pairs, so without) 91; in 3D, with super-tiles
+// of two or four tiles, 128^3 with 34952 1220 / 413, 256^3 with 279620 202 / 16.3
+// ms (with one tile each 53), 64^3 with 13107 (6.7e6) 146 / 136.
+constexpr int64_t kTileListPairs = (int64_t)1 << 22;
+// A box of 3.7 cell diameters (3D) leaves 1350 seeds to its eigenvalue bounds on
+// average, one of four 1609 and at times more than the 2048 of kSuperCap.
+constexpr double kDenseCells = 52.0;
 
 int list_rows(const apd::Geo &g, apd_precision prec) {
     return prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true);
@@ -250,17 +266,29 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
     for (int d = 0; d < 3; ++d) L.ntile[d] = d < p->dim ? (g.grid[d] + ext[d] - 1) / ext[d] : 1;
     L.tiles = (int64_t)L.ntile[0] * L.ntile[1] * L.ntile[2];
     const double diam = pow((double)num_pixels(p) / (double)p->n, 1.0 / p->dim);
+    for (int d = 0; d < p->dim; ++d) L.sf[d] = std::max(1, std::min(8, (int)lround(3.0 * diam / ext[d])));
+    // dense seeds in 3D, where regions hold more seeds than they have room for: a
+    // super-tile of two or four tiles, as long as it holds at most kDenseCells cells
+    if (p->dim == 3 && L.single() && L.tiles * p->n >= kTileListPairs) {
+        double cells = (double)p->n / (double)num_pixels(p);
+        for (int d = 0; d < p->dim; ++d) cells *= ext[d];
+        for (int d = p->dim - 1; d >= 0 && cells * 2.0 <= kDenseCells; --d)
+            if (L.ntile[d] > 1) {
+                L.sf[d] = 2;
+                cells *= 2.0;
+            }
+    }
     L.nsuper = 1;
     for (int d = 0; d < 3; ++d) {
-        const int f = d < p->dim ? (int)lround(3.0 * diam / ext[d]) : 1;
-        L.sf[d] = std::max(1, std::min(8, f));
         L.nst[d] = (L.ntile[d] + L.sf[d] - 1) / L.sf[d];
         L.nsuper *= L.nst[d];
     }
+    // up to a block's threads of seeds the tiles read them all at once
+    L.super = p->n > apd::kThreads && (!L.single() || L.tiles * p->n >= kTileListPairs);
     // s super-tiles each read n seeds; h regions read n and leave each
     // super-tile about c n / h (c = 8 for the margin around the region's box):
     // least at h = sqrt(c s)
-    if (g.power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
+    if (L.super && g.power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
         const int f = std::max(2, (int)lround(pow((double)L.nsuper / 8.0, 0.5 / p->dim)));
         L.nregion = 1;
         for (int d = 0; d < 3; ++d) {
@@ -270,6 +298,62 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
         }
     }
     return L;
+}
+
+// The context's room for the super-tiles' and regions' lists of a pass.  Where a
+// super-tile is one tile its list is read once and holds the seeds' numbers alone
+// (8 KiB per tile; the records, 96, save the gathers of the tiles that share
+// them), and so it does where the records don't fit in the device's memory.  That
+// is settled by an eager pass: a captured one, which must not allocate, takes what
+// the eager pass before it took.
+bool grow_super(apd_ctx *c, size_t bytes) {
+    if (bytes <= c->super_bytes) return true;
+    (void)hipFree(c->super_lists);
+    c->super_lists = nullptr;
+    c->super_bytes = 0;
+    if (hipMalloc(&c->super_lists, bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        c->super_lists = nullptr;
+        return false;
+    }
+    c->super_bytes = bytes;
+    return true;
+}
+
+apd_status ensure_super(apd_ctx *c, const ListGeometry &L, int dim, int64_t n, bool captured, PassBufs &b,
+                        apd::Regions &rg) {
+    b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, n);
+    const size_t region = (size_t)L.nregion * 2 * apd::kRegionCap * sizeof(float4);
+    const size_t seeds = (size_t)L.nsuper * b.super_cap;
+    bool records = !L.single() && !(captured && c->super_ids_only);
+    if (records) records = grow_super(c, region + seeds * apd::rec_vec(dim) * sizeof(float4));
+    if (!captured) c->super_ids_only = !records;
+    bool ok = records || grow_super(c, region + seeds * sizeof(int));
+    const int64_t counts = L.nsuper + L.nregion;
+    if (ok && counts > c->cap_super) {
+        (void)hipFree(c->super_count);
+        c->super_count = nullptr;
+        c->cap_super = 0;
+        ok = hipMalloc(&c->super_count, (size_t)counts * sizeof(int)) == hipSuccess;
+        if (ok) c->cap_super = counts;
+        else c->super_count = nullptr;
+    }
+    if (!ok)
+        return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles", (long long)L.nsuper);
+    float4 *lists = c->super_lists + region / sizeof(float4);
+    if (records) b.super_lists = lists;
+    else b.super_ids = reinterpret_cast<int *>(lists);
+    b.super_count = c->super_count;
+    if (L.nregion) {
+        rg.rec = c->super_lists;
+        rg.count = b.super_count + L.nsuper;
+        rg.cap = apd::kRegionCap;
+        for (int d = 0; d < 3; ++d) {
+            rg.hf[d] = L.hf[d];
+            rg.nh[d] = L.nh[d];
+        }
+    }
+    return APD_OK;
 }
 
 // Whether a pass runs over candidate lists.  The FP64 tier's relative gaps are
@@ -320,55 +404,25 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     if (cull) {
         const ListGeometry L = list_geometry(p, g, list_rows(g, prec));
         out.tp = tp = L.tp;
-        if (fixed) {
-            if (L.nsuper > b.cap_super)
-                return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
-        } else {
-            b.super_cap = (int)std::min<int64_t>(apd::kSuperCap, p->n);
-            const size_t super_recs = (size_t)L.nsuper * b.super_cap * apd::rec_vec(p->dim);
-            const size_t rec_bytes = (super_recs + (size_t)L.nregion * 2 * apd::kRegionCap) * sizeof(float4);
-            if (rec_bytes > c->super_bytes) {
-                (void)hipFree(c->super_lists);
-                c->super_lists = nullptr;
-                c->super_bytes = 0;
-                if (hipMalloc(&c->super_lists, rec_bytes) != hipSuccess)
-                    return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
-                                (long long)L.nsuper);
-                c->super_bytes = rec_bytes;
-            }
-            if (L.nsuper + L.nregion > c->cap_super) {
-                (void)hipFree(c->super_count);
-                c->super_count = nullptr;
-                c->cap_super = 0;
-                if (hipMalloc(&c->super_count, (size_t)(L.nsuper + L.nregion) * sizeof(int)) != hipSuccess)
-                    return fail(c, APD_ERR_OOM, "cannot allocate candidate lists for %lld super-tiles",
-                                (long long)L.nsuper);
-                c->cap_super = L.nsuper + L.nregion;
-            }
-            b.super_lists = c->super_lists;
-            b.super_count = c->super_count;
-            if (L.nregion) {
-                rg.rec = b.super_lists + super_recs;
-                rg.count = b.super_count + L.nsuper;
-                rg.cap = apd::kRegionCap;
-                for (int d = 0; d < 3; ++d) {
-                    rg.hf[d] = L.hf[d];
-                    rg.nh[d] = L.nh[d];
-                }
-            }
-        }
         out.adaptive = c->adaptive;
         out.credited = &b.sc->credited;
         for (int d = 0; d < 3; ++d) {
             out.sf[d] = L.sf[d];
             out.nst[d] = L.nst[d];
         }
-        // up to a block's threads of seeds the tiles read them all at once
-        if (L.sf[0] * L.sf[1] * L.sf[2] > 1 && p->n > apd::kThreads) {
+        if (L.super) {
+            if (fixed) {
+                if (L.nsuper > b.cap_super)
+                    return fail(c, APD_ERR_INVALID_ARG, "candidate lists exceed the fixed scratch");
+            } else {
+                const apd_status ss = ensure_super(c, L, p->dim, p->n, w_host != nullptr, b, rg);
+                if (ss != APD_OK) return ss;
+            }
             out.super_cap = b.super_cap;
-            HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, rg, b.super_lists, b.super_count,
+            HIP_TRY(c, apd::launch_super_cull(g, sd, b.sc, b.eig, out, rg, b.super_lists, b.super_ids, b.super_count,
                                               c->stream));
             out.super_list = b.super_lists;
+            out.super_ids = b.super_ids;
             out.super_count = b.super_count;
         }
     }
@@ -1252,7 +1306,8 @@ apd_status ws_infer_impl(apd_ctx *c, apd_ws_model *m, const float *F, int64_t S,
 namespace {
 constexpr size_t kStaticScratch = (size_t)96 << 20;  // bytes per device
 constexpr int kStaticListCap = 256;                  // seeds counted per tile (the limit)
-constexpr int kStaticSuperCap = 512;                 // candidates kept per super-tile
+constexpr int kStaticSuperCap = 512;                 // and per super-tile
+constexpr size_t kStaticRecords = 1024;              // records per super-tile worth keeping there
 constexpr int kMaxDevices = 64;
 }  // namespace
 
@@ -1413,11 +1468,11 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
     b.mom = k.take<uint64_t>((size_t)n * 10);
     b.eig = k.take<double>((size_t)n * 2);
     b.ord = k.take<int>((size_t)n);
-    b.queue = k.take<unsigned>((size_t)J);
     if (geo.power != 2) {
         b.cap_parts = apd::fp64_blocks(geo);
         b.cost_part = k.take<double>((size_t)b.cap_parts);
     }
+    b.queue = k.take<unsigned>((size_t)J);
     if (cull && prec != APD_FP64) {
         // the call's documented limit counts a list of kStaticListCap seeds,
         // its length and bound and a queue segment for every tile (of 4 pixels
@@ -1437,19 +1492,24 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
                     "this problem needs %zu bytes of scratch; the static array holds %zu (n = %lld, J = %lld)",
                     k.off, kStaticScratch, (long long)n, (long long)J);
     if (cull) {
-        // the super-tiles' counts and records take the room that the limit
-        // counts for the queue (a pass with lists has none) and the lists, as
-        // many records per super-tile as fit
-        const int64_t nsuper = list_geometry(p, geo, list_rows(geo, prec)).nsuper;
+        // the super-tiles' counts and lists take the rest of the array (a pass
+        // with lists has no queue): records where there is room for the
+        // longest usual list (3D, three cell diameters: 544 seeds on average, 750
+        // at most; after rounding to whole tiles up to four: 1164 and 1850),
+        // else the seeds' numbers
+        const ListGeometry L = list_geometry(p, geo, list_rows(geo, prec));
         Carve in{reinterpret_cast<unsigned char *>(b.queue)};
         b.queue = nullptr;
-        b.cap_super = nsuper;
-        b.super_count = in.take<int>((size_t)nsuper);
-        b.super_lists = in.take<float4>(0);
-        const unsigned char *end = b.cost_part ? reinterpret_cast<unsigned char *>(b.cost_part) : base + k.off;
-        const size_t room = (size_t)(end - reinterpret_cast<unsigned char *>(b.super_lists));
-        b.super_cap = (int)std::min<size_t>({(size_t)kStaticSuperCap, (size_t)n,
-                                             room / ((size_t)nsuper * apd::rec_vec(p->dim) * sizeof(float4))});
+        b.cap_super = L.nsuper;
+        b.super_count = in.take<int>((size_t)L.nsuper);
+        float4 *lists = in.take<float4>(0);
+        const size_t room = (size_t)(base + kStaticScratch - reinterpret_cast<unsigned char *>(lists)) / (size_t)L.nsuper;
+        const size_t most = std::min<size_t>((size_t)apd::kSuperCap, (size_t)n);
+        const size_t recs = std::min(most, room / (apd::rec_vec(p->dim) * sizeof(float4)));
+        const bool records = recs >= std::min(most, kStaticRecords);
+        if (records) b.super_lists = lists;
+        else b.super_ids = reinterpret_cast<int *>(lists);
+        b.super_cap = (int)(records ? recs : std::min(most, room / sizeof(int)));
     }
     // the block partials' ticket must start at zero (each launch leaves it
     // so; the array starts zeroed, but an aborted call may not have)

@@ -230,7 +230,7 @@ __global__ __launch_bounds__(kThreads) void kb_super(const BInst *inst, const BS
         out.nst[d] = I.nst[d];
     }
     super_tile_list<D, kThreads>(I.g, sd, S.wmax, Cert{S.lam, S.kap, S.sab, S.lsl}, I.eig, out, Regions{}, local,
-                                 I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D),
+                                 I.super_lists + (size_t)local * kBatchSuperCap * rec_vec(D), nullptr,
                                  I.super_count + local, kBatchSuperCap, sm);
 }
 

@@ -1778,8 +1778,9 @@ struct SuperSmem {
 };
 
 // The candidate list of super-tile st (a box of sf[0] x sf[1] x sf[2] tiles of
-// out.tp pixels per lane) into list (room for cap), their number into *count
-// (above cap: every seed): the survivors of its box (box_survivors, from its
+// out.tp pixels per lane) into list (room for cap) or, where ids is given, the
+// seeds' numbers alone into ids, how many there are into *count (above cap: every
+// seed): the survivors of its box (box_survivors, from its
 // region's list where the pass has regions), then, unless the pass returns the
 // relative gaps (whose tiles need lists that bound the cost of every seed left
 // out) or its costs are of another power, of these by the owner's difference.
@@ -1787,8 +1788,8 @@ struct SuperSmem {
 // tiles.  All T threads of the block call it.
 template <int D, int T>
 __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wmax, Cert ct, const double *eig,
-                                       const PassOut &out, const Regions &rg, int st, float4 *list, int *count,
-                                       int cap, SuperSmem<D, T> &sm) {
+                                       const PassOut &out, const Regions &rg, int st, float4 *list, int *ids,
+                                       int *count, int cap, SuperSmem<D, T> &sm) {
     int c[3];
     c[2] = st % out.nst[2];
     c[1] = (st / out.nst[2]) % out.nst[1];
@@ -1826,14 +1827,18 @@ __device__ inline void super_tile_list(const Geo &g, const Seeds &sd, double wma
     }
     int n;
     if (out.rel_gap || g.power != 2) {
-        for (int q = threadIdx.x; q < min(m, cap); q += T)
-            store_rec<D>(list, cap, q, seed_rec<D>(sd, wmax, ctr, sm.list[q]), sm.list[q]);
+        for (int q = threadIdx.x; q < min(m, cap); q += T) {
+            if (ids) ids[q] = sm.list[q];
+            else store_rec<D>(list, cap, q, seed_rec<D>(sd, wmax, ctr, sm.list[q]), sm.list[q]);
+        }
         n = m;
     } else {
         n = owner_filter<D, T>(
             m, [&](int q) { return seed_rec<D>(sd, wmax, ctr, sm.list[q]); }, h, hh, ct.lam,
             ct.lsl, sm.cnt, sm.own, [&](int q, const SeedRec<D> &r, int pos) {
-                if (pos < cap) store_rec<D>(list, cap, pos, r, sm.list[q]);
+                if (pos >= cap) return;
+                if (ids) ids[pos] = sm.list[q];
+                else store_rec<D>(list, cap, pos, r, sm.list[q]);
             });
     }
     if (threadIdx.x == 0) *count = n;
@@ -1869,13 +1874,15 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
         cull_box<D>(g, k0, ext, blo, bhi);
     };
     const float4 *src = nullptr;
+    const int *ids = nullptr;
     int nsrc = g.n, cap = out.super_cap;
     const int sc[3] = {b0 / out.sf[0], b1 / out.sf[1], b2 / out.sf[2]};
-    if (out.super_list) {
+    if (out.super_count) {
         const int st = (sc[0] * out.nst[1] + sc[1]) * out.nst[2] + sc[2];
         const int c = out.super_count[st];
         if (c <= cap) {
-            src = out.super_list + (size_t)st * (size_t)cap * rec_vec(D);
+            if (out.super_ids) ids = out.super_ids + (size_t)st * (size_t)cap;
+            else src = out.super_list + (size_t)st * (size_t)cap * rec_vec(D);
             nsrc = c;
         }
     }
@@ -1883,7 +1890,8 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
         double blo[3], bhi[3];
         tile_box(blo, bhi);
         return build_candidates<D>(sd, eig, wmax, blo, bhi,
-                                   [&](int q) { return src ? __float_as_int(src[q].w) : q; }, nsrc, dst, kCullCap,
+                                   [&](int q) { return src ? __float_as_int(src[q].w) : ids ? ids[q] : q; }, nsrc, dst,
+                                   kCullCap,
                                    sm.cnt, sm.red, U, g.power);
     } else {
         float h[D], hh = 0.0f, shift[3] = {0.0f, 0.0f, 0.0f};
@@ -1913,9 +1921,9 @@ __device__ inline int tile_candidates(const Geo &g, const Seeds &sd, double wmax
         tile_box(blo, bhi);
         hh = box_centre<D>(blo, bhi, ctr, h);
         return owner_filter<D, kThreads>(
-            nsrc, [&](int q) { return seed_rec<D>(sd, wmax, ctr, q); }, h, hh, ct.lam, slack, sm.cnt, sm.own,
-            [&](int q, const SeedRec<D> &, int pos) {
-                if (pos < kCullCap) dst[pos] = q;
+            nsrc, [&](int q) { return seed_rec<D>(sd, wmax, ctr, ids ? ids[q] : q); }, h, hh, ct.lam, slack, sm.cnt,
+            sm.own, [&](int q, const SeedRec<D> &, int pos) {
+                if (pos < kCullCap) dst[pos] = ids ? ids[q] : q;
             });
     }
 }

@@ -141,6 +141,7 @@ struct PassOut {
     // their candidate seeds, from which the tiles pick theirs
     // (packed records, store_rec)
     const float4 *super_list = nullptr;   // [super-tiles][rec_vec][super_cap]
+    const int *super_ids = nullptr;    // or the seeds' numbers only, [super-tiles][super_cap]
     const int *super_count = nullptr;  // above super_cap: every seed
     int super_cap = 2048;
     int sf[3] = {1, 1, 1};
@@ -208,10 +209,11 @@ int bf16_pixels_per_lane(const Geo &g);
 // seeds, matrices and volumes left (a fit's later evaluations).
 hipError_t launch_prep(const Geo &g, const Seeds &sd, Scalars *sc, uint64_t *mom, double *eig,
                        BlockParts *bp, hipStream_t st, const double *w_src = nullptr, bool w_only = false);
-// Candidate lists of the super-tiles described by out (sf, nst), written to
-// list / count.
+// Candidate lists of the super-tiles described by out (sf, nst): their numbers
+// to count, the seeds' records to list or, with ids, their numbers there.
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, const Regions &rg, float4 *list, int *count, hipStream_t st);
+                             const PassOut &out, const Regions &rg, float4 *list, int *ids, int *count,
+                             hipStream_t st);
 hipError_t launch_assign_cull(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig,
                               const PassOut &out, hipStream_t st);
 // The FP64 pass over every seed (eig null) or over the tiles' candidate lists

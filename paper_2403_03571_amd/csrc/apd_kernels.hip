@@ -421,11 +421,12 @@ __global__ __launch_bounds__(kThreads) void k_assign_bf16(Geo g, Seeds sd, Scala
 // One block of T threads per super-tile (dev::super_tile_list).
 template <int D, int T>
 __global__ __launch_bounds__(T) void k_super_cull(Geo g, Seeds sd, const Scalars *sc, const double *eig, PassOut out,
-                                                  Regions rg, float4 *list, int *count) {
+                                                  Regions rg, float4 *list, int *ids, int *count) {
     __shared__ SuperSmem<D, T> sm;
     const int st = blockIdx.x;
+    const size_t at = (size_t)st * (size_t)out.super_cap;
     super_tile_list<D, T>(g, sd, sc->wmax, Cert{sc->lam, sc->kap, sc->sab, sc->lsl}, eig, out, rg, st,
-                          list + (size_t)st * (size_t)out.super_cap * rec_vec(D), count + st, out.super_cap, sm);
+                          list + at * rec_vec(D), ids ? ids + at : nullptr, count + st, out.super_cap, sm);
 }
 
 // One block per region (dev::region_list).
@@ -733,24 +734,25 @@ hipError_t launch_assign_fp32(const Geo &g, const Seeds &sd, Scalars *sc, const 
 
 template <int D>
 static void launch_super(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig, const PassOut &out,
-                         const Regions &rg, float4 *list, int *count, hipStream_t st) {
+                         const Regions &rg, float4 *list, int *ids, int *count, hipStream_t st) {
     const int nb = out.nst[0] * out.nst[1] * out.nst[2];
     if (rg.rec) {
         k_region_cull<D><<<rg.nh[0] * rg.nh[1] * rg.nh[2], kRegionThreads, 0, st>>>(g, sd, sc, eig, out, rg);
-        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, ids, count);
     } else if (g.n > kSuperWideSeeds) {
         // a block reads every seed: many seeds need many loads in flight
-        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+        k_super_cull<D, 512><<<nb, 512, 0, st>>>(g, sd, sc, eig, out, rg, list, ids, count);
     } else {
-        k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, rg, list, count);
+        k_super_cull<D, 256><<<nb, 256, 0, st>>>(g, sd, sc, eig, out, rg, list, ids, count);
     }
 }
 
 hipError_t launch_super_cull(const Geo &g, const Seeds &sd, const Scalars *sc, const double *eig,
-                             const PassOut &out, const Regions &rg, float4 *list, int *count, hipStream_t st) {
+                             const PassOut &out, const Regions &rg, float4 *list, int *ids, int *count,
+                             hipStream_t st) {
     (void)hipGetLastError();
-    if (g.dim == 2) launch_super<2>(g, sd, sc, eig, out, rg, list, count, st);
-    else launch_super<3>(g, sd, sc, eig, out, rg, list, count, st);
+    if (g.dim == 2) launch_super<2>(g, sd, sc, eig, out, rg, list, ids, count, st);
+    else launch_super<3>(g, sd, sc, eig, out, rg, list, ids, count, st);
     return hipGetLastError();
 }
 

@@ -143,3 +143,85 @@ def test_first_moments_of_a_very_long_axis(ctx):
         assert abs(int(k[0]) - cut) <= 1 and k.sum() == M
         want = np.array([0.5 * k[0], k[0] + 0.5 * k[1]]) / M
         np.testing.assert_allclose(out["centroids"].cpu().numpy()[:, 0], want, rtol=1e-12, atol=0)
+
+
+def _spread(dim, grid, n, seed):
+    """Many seeds, made quickly."""
+    rng = np.random.default_rng(seed)
+    R = np.linalg.qr(rng.normal(size=(n, dim, dim)))[0]
+    ev = np.exp(0.3 * rng.standard_normal((n, dim)))
+    A = (R * ev[:, None, :]) @ np.swapaxes(R, -1, -2)
+    return _instance(grid, rng.random((n, dim)), 0.5 * (A + np.swapaxes(A, -1, -2)))
+
+
+@pytest.mark.parametrize("dim,grid,n", [
+    (3, (128, 120, 126), 90000),   # 21 voxels per cell: two tiles per super-tile
+    (3, (100, 128, 97), 31000),    # 40: four
+    (3, (8, 8, 40960), 40000),     # tiles along one axis only
+    (2, (1000, 1100), 30000),      # 36 pixels per cell: a list per tile
+    (2, (1000, 1100), 4000),       # too few pairs: every seed
+    (3, (96, 100, 90), 14000)])    # 62 per cell, numbers in the fixed scratch
+def test_lists_of_dense_seeds(ctx, dim, grid, n):
+    """Super-tiles of a few tiles or of one, lists of records or of numbers, in the
+    context's room and in the fixed scratch: labels, gaps and counts against the
+    pass over every seed."""
+    import torch
+    prob = _prob(_spread(dim, grid, n, n))
+    w = torch.as_tensor(np.random.default_rng(n).uniform(-0.1, 0.1, n) * n ** (-2.0 / dim), device="cuda:0")
+    ref = _every_seed(ctx, prob, w)
+    want = torch.bincount(ref.reshape(-1).cpu().long(), minlength=n)
+    for prec in ("fp32", "fp64"):
+        assert torch.equal(ctx.apd_assign(prob, w, prec=prec), ref)
+        for noalloc in (False, True):
+            out = ctx.apd_dual_objective_grad(prob, w, prec=prec, counts=True, noalloc=noalloc)
+            assert torch.equal(out["counts"].cpu(), want)
+    lab, gap = ctx.apd_assign(prob, w, rel_gap=True)
+    assert torch.equal(lab, ref) and bool(((gap >= 0) & (gap <= 1)).all())
+
+
+def test_dense_seeds_and_fixed_scratch_keep_their_lists(ctx):
+    """Seeds just too dense for super-tiles of three cell diameters, and lists too
+    long for records in the fixed scratch, are not left to scans of every seed by
+    every tile (four and eight times the time)."""
+    import torch
+
+    def took(side, n, **kw):
+        prob = _prob(_spread(3, (side,) * 3, n, 1))
+        w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+        return _seconds(lambda: ctx.apd_dual_objective_grad(prob, w, **kw))
+
+    assert took(128, 34952) < 3.0 * took(128, 26214)
+    assert took(230, 30000, noalloc=True) < 4.0 * took(230, 30000)
+
+
+@pytest.mark.parametrize("side,n,room", [(200, 200000, 700), (356, 150000, 250)])
+def test_lists_in_little_memory(side, n, room):
+    """Lists that are not used take no room, and where the records don't fit the
+    lists hold numbers; an evaluation and the captured evaluations of a fit."""
+    import torch
+    import paper_2403_03571_amd as apd
+    prob = _prob(_spread(3, (side,) * 3, n, 2))
+    w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+
+    def work():
+        c = apd.Context(0)
+        try:
+            out = c.apd_dual_objective_grad(prob, w, counts=True)
+            fit, rep = c.apd_fit_weights(prob, eps=1e-6, max_evals=3, raise_on_fail=False)
+            return out["counts"], out["g"], fit
+        finally:
+            c.close()
+
+    want = work()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    held = []
+    for step in (1 << 30, 1 << 26, 1 << 22):
+        while torch.cuda.mem_get_info()[0] > (room << 20) + step:
+            held.append(torch.empty(step, dtype=torch.uint8, device="cuda:0"))
+    try:
+        got = work()
+    finally:
+        held.clear()
+        torch.cuda.empty_cache()
+    assert torch.equal(got[0], want[0]) and got[1] == want[1] and torch.equal(got[2], want[2])
