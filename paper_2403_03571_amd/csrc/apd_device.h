@@ -765,7 +765,7 @@ __device__ inline void moments_flush(const MomSmem<P, W> &sm, const int *anc, co
     const int c = max(0, q - 1 - D);
     const int d = D == 2 ? (c == 2) : (c < 3 ? 0 : c < 5 ? 1 : 2);
     const int e = D == 2 ? (c >= 1) : (c < 3 ? c : c < 5 ? c - 2 : 2);
-    auto G = [&](int k) { return 2 * (int64_t)(k == 0 ? anc[0] : k == 1 ? anc[1] : anc[2]); };
+    auto G = [&](int k) { return (int64_t)(2u * (unsigned)(k == 0 ? anc[0] : k == 1 ? anc[1] : anc[2])); };
     for (int k = threadIdx.x >> 4; k < n; k += kThreads / 16) {
         const int *a = sm.acc[k];
         const int m = a[0];
