@@ -254,8 +254,8 @@ constexpr int64_t kTileListPairs = (int64_t)1 << 22;
 // average, one of four 1609 and at times more than the 2048 of kSuperCap.
 constexpr double kDenseCells = 52.0;
 
-int list_rows(const apd::Geo &g, apd_precision prec) {
-    return prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true);
+int list_rows(const apd::Geo &g, apd_precision prec, bool gap) {
+    return prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true, gap);
 }
 
 ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
@@ -402,7 +402,7 @@ apd_status enqueue_pass(apd_ctx *c, const apd_problem *p, const double *x, const
     int tp = 0;  // pixels per lane of the lists' tiles
     apd::Regions rg;
     if (cull) {
-        const ListGeometry L = list_geometry(p, g, list_rows(g, prec));
+        const ListGeometry L = list_geometry(p, g, list_rows(g, prec, rel_gap != nullptr));
         out.tp = tp = L.tp;
         out.adaptive = c->adaptive;
         out.credited = &b.sc->credited;
@@ -1497,7 +1497,7 @@ apd_status apd_dual_objective_grad_noalloc(apd_ctx *c, const apd_problem *p, con
         // longest usual list (3D, three cell diameters: 544 seeds on average, 750
         // at most; after rounding to whole tiles up to four: 1164 and 1850),
         // else the seeds' numbers
-        const ListGeometry L = list_geometry(p, geo, list_rows(geo, prec));
+        const ListGeometry L = list_geometry(p, geo, list_rows(geo, prec, false));
         Carve in{reinterpret_cast<unsigned char *>(b.queue)};
         b.queue = nullptr;
         b.cap_super = L.nsuper;

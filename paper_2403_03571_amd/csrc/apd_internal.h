@@ -198,8 +198,9 @@ struct FinalOut {
 };
 
 // Pixels per lane of the vector kernel on this grid, with or without
-// candidate lists (its tiles are kWaves * that many pixels long along axis 0).
-int vec_pixels_per_lane(const Geo &g, bool cull);
+// candidate lists, for a pass that returns the relative gaps or not (its tiles are
+// kWaves * that many pixels long along axis 0).
+int vec_pixels_per_lane(const Geo &g, bool cull, bool gap = false);
 // Pixel rows per lane of the bf16 kernel over every seed on this grid (its tiles are kWaves
 // * that many pixels long along axis 0, with the vector kernel's other axes).
 int bf16_pixels_per_lane(const Geo &g);

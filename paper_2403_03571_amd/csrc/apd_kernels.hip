@@ -650,17 +650,21 @@ hipError_t launch_vec(const Geo &g, const Seeds &sd, Scalars *sc, const PassOut 
 template <int D, bool GAP, bool W = false>
 hipError_t launch_list(const Geo &g, const Seeds &sd, Scalars *sc, const double *eig, const PassOut &out,
                        hipStream_t st) {
-    switch (vec_pixels_per_lane(g, true)) {
-    case 8: k_assign_list<D, 8, GAP, W><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
-    case 4: k_assign_list<D, 4, GAP, W><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out); break;
-    default: k_assign_list<D, 2, GAP, W><<<tile_grid<D, 2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    if (out.tp == 8) {
+        k_assign_list<D, 8, GAP, W><<<tile_grid<D, 8>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    } else if (out.tp == 4) {
+        k_assign_list<D, 4, GAP, W><<<tile_grid<D, 4>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+    } else {
+        if constexpr (D == 3)  // the rule takes 2 rows in 3D only
+            k_assign_list<D, 2, GAP, W><<<tile_grid<D, 2>(g), kThreads, 0, st>>>(g, sd, sc, eig, out);
+        else return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 }  // namespace
 
-int vec_pixels_per_lane(const Geo &g, bool cull) {
+int vec_pixels_per_lane(const Geo &g, bool cull, bool gap) {
     if (g.vec_p == 4 || g.vec_p == 8) return g.vec_p;
     int64_t J = 1;
     for (int d = 0; d < g.dim; ++d) J *= g.grid[d];
@@ -678,7 +682,17 @@ int vec_pixels_per_lane(const Geo &g, bool cull) {
     // 128^3 78.2 / 74.3, 256^3 393 / 357; at 1700 48^3 35.3 / 36.1, 80^3 48.6 /
     // 48.7, 96^3 55.7 / 52.3.  (2D: 256^2 34.3 / 34.4, 512^2 41.4 / 42.5, 1024^2
     // 46.4 / 43.0: 4 rows.)
-    if (cull && g.dim == 3 && (J < (int64_t)1 << 19 || J < (int64_t)450 * g.n)) return 2;
+    if (cull && g.dim == 3) {
+        const dim3 t = tile_grid<3, 4>(g);
+        const int64_t tiles = (int64_t)t.x * t.y * t.z;
+        if (J < (int64_t)1 << 19 && tiles < 1024) return 2;
+        // not where the tiles stick out of a thin grid, whose wave boxes hold the
+        // same pixels either way (600000 x 1 x 1, N = 2000: 2.6 / 1.4 ms), nor for the
+        // relative gaps, whose lists come from separate bounds, which smaller
+        // boxes shorten less than they multiply the tiles (256^3, N = 55924: 922 /
+        // 681 us; 128^3, 6990: 102 / 97)
+        if (J < (int64_t)450 * g.n && tiles * 1024 <= 2 * J && !gap) return 2;
+    }
     // In 2D not from 8000 pixels per cell: the smaller tiles lie inside one cell
     // often enough to be credited whole, which the boundary-aware refinement is
     // for (4096^2 with 1000 cells: 5177 of 16384 tiles against 853 of 8192; the

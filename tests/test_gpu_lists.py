@@ -225,3 +225,21 @@ def test_lists_in_little_memory(side, n, room):
         held.clear()
         torch.cuda.empty_cache()
     assert torch.equal(got[0], want[0]) and got[1] == want[1] and torch.equal(got[2], want[2])
+
+
+@pytest.mark.parametrize("grid,n,rows,gap_rows", [
+    ((100, 101, 102), 2700, 2, 4), ((79, 80, 82), 2000, 2, 2), ((100, 101, 102), 2200, 4, 4),
+    ((600000, 1, 1), 2000, 4, 4), ((20000, 3, 2), 900, 4, 4), ((9, 7, 3), 40, 2, 2)])
+def test_rows_of_passes_with_gaps_and_of_thin_grids(ctx, grid, n, rows, gap_rows):
+    """Two rows per lane on dense 3D grids, but not for the relative gaps and not
+    where the tiles stick out of the grid; labels and gaps against every seed."""
+    import torch
+    prob = _prob(_spread(3, grid, n, n))
+    w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    ref = _every_seed(ctx, prob, w)
+    assert torch.equal(ctx.apd_assign(prob, w), ref)
+    assert ctx.apd_last_pass_stats()["pixels_per_lane"] == rows
+    lab, gap = ctx.apd_assign(prob, w, rel_gap=True)
+    assert ctx.apd_last_pass_stats()["pixels_per_lane"] == gap_rows
+    exact = ctx.apd_assign(prob, w, prec="fp64", rel_gap=True)[1]
+    assert torch.equal(lab, ref) and bool((gap <= exact * (1 + 1e-6) + 1e-12).all())
