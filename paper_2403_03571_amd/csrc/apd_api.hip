@@ -303,9 +303,9 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
 // The context's room for the super-tiles' and regions' lists of a pass.  Where a
 // super-tile is one tile its list is read once and holds the seeds' numbers alone
 // (8 KiB per tile; the records, 96, save the gathers of the tiles that share
-// them), and so it does where the records don't fit in the device's memory.  That
-// is settled by an eager pass: a captured one, which must not allocate, takes what
-// the eager pass before it took.
+// them), and so it does where the records would take more than half of the device's
+// free memory.  That is settled by an eager pass: a captured one, which must not
+// allocate, takes what the eager pass before it took.
 bool grow_super(apd_ctx *c, size_t bytes) {
     if (bytes <= c->super_bytes) return true;
     (void)hipFree(c->super_lists);
@@ -326,7 +326,13 @@ apd_status ensure_super(apd_ctx *c, const ListGeometry &L, int dim, int64_t n, b
     const size_t region = (size_t)L.nregion * 2 * apd::kRegionCap * sizeof(float4);
     const size_t seeds = (size_t)L.nsuper * b.super_cap;
     bool records = !L.single() && !(captured && c->super_ids_only);
-    if (records) records = grow_super(c, region + seeds * apd::rec_vec(dim) * sizeof(float4));
+    if (records) {
+        const size_t bytes = region + seeds * apd::rec_vec(dim) * sizeof(float4);
+        size_t free_bytes = 0, total = 0;
+        records = bytes <= c->super_bytes ||
+                  (hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= (free_bytes + c->super_bytes) / 2 &&
+                   grow_super(c, bytes));
+    }
     if (!captured) c->super_ids_only = !records;
     bool ok = records || grow_super(c, region + seeds * sizeof(int));
     const int64_t counts = L.nsuper + L.nregion;

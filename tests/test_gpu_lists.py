@@ -194,21 +194,45 @@ def test_dense_seeds_and_fixed_scratch_keep_their_lists(ctx):
     assert took(230, 30000, noalloc=True) < 4.0 * took(230, 30000)
 
 
-@pytest.mark.parametrize("side,n,room", [(200, 200000, 700), (356, 150000, 250)])
-def test_lists_in_little_memory(side, n, room):
-    """Lists that are not used take no room, and where the records don't fit the
-    lists hold numbers; an evaluation and the captured evaluations of a fit."""
+def test_room_of_lists_that_are_not_used(ctx):
+    """Dense seeds in a context of their own (the runtime's own room taken before):
+    4225 super-tiles' records and at most as many regions' half as large, 415 and
+    288 MB, and some 60 for the seeds, not 1.5 GB for each of 15625 tiles."""
     import torch
     import paper_2403_03571_amd as apd
-    prob = _prob(_spread(3, (side,) * 3, n, 2))
+    n = 200000
+    prob = _prob(_spread(3, (200, 200, 200), n, 2))
+    w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    small = _prob(_spread(3, (100, 100, 100), 25000, 2))
+    ctx.apd_dual_objective_grad(small, w[:25000])
+    c = apd.Context(0)
+    try:
+        free = torch.cuda.mem_get_info()[0]
+        c.apd_dual_objective_grad(prob, w)
+        assert free - torch.cuda.mem_get_info()[0] < 1 << 30
+    finally:
+        c.close()
+
+
+def test_numbers_instead_of_records_in_little_memory(ctx):
+    """Records of 8.4 GiB with 14 GiB free: the lists hold the seeds' numbers, in an
+    evaluation and in a fit's captured ones, and the results stay the same."""
+    import torch
+    import paper_2403_03571_amd as apd
+    side, per = 22912, 280
+    n = side * side // per
+    rng = np.random.default_rng(9)
+    a, t = rng.uniform(1.0, 3.0, n), rng.uniform(0.0, np.pi, n)
+    prob = _prob(_instance((side, side), rng.random((n, 2)), S.aniso2d(a, t)))
     w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
 
     def work():
         c = apd.Context(0)
         try:
+            free = torch.cuda.mem_get_info()[0]
             out = c.apd_dual_objective_grad(prob, w, counts=True)
-            fit, rep = c.apd_fit_weights(prob, eps=1e-6, max_evals=3, raise_on_fail=False)
-            return out["counts"], out["g"], fit
+            fit, _ = c.apd_fit_weights(prob, eps=1e-6, max_evals=3)
+            return out["counts"], out["g"], fit, free - torch.cuda.mem_get_info()[0]
         finally:
             c.close()
 
@@ -216,14 +240,14 @@ def test_lists_in_little_memory(side, n, room):
     torch.cuda.synchronize()
     torch.cuda.empty_cache()
     held = []
-    for step in (1 << 30, 1 << 26, 1 << 22):
-        while torch.cuda.mem_get_info()[0] > (room << 20) + step:
-            held.append(torch.empty(step, dtype=torch.uint8, device="cuda:0"))
+    while torch.cuda.mem_get_info()[0] > 15 << 30:
+        held.append(torch.empty(1 << 30, dtype=torch.uint8, device="cuda:0"))
     try:
         got = work()
     finally:
         held.clear()
         torch.cuda.empty_cache()
+    assert want[3] > 8 << 30 and got[3] < 3 << 30
     assert torch.equal(got[0], want[0]) and got[1] == want[1] and torch.equal(got[2], want[2])
 
 
