@@ -253,6 +253,12 @@ constexpr int64_t kTileListPairs = (int64_t)1 << 22;
 // A box of 3.7 cell diameters (3D) leaves 1350 seeds to its eigenvalue bounds on
 // average, one of four 1609 and at times more than the 2048 of kSuperCap.
 constexpr double kDenseCells = 52.0;
+// Longest side of a region in cell diameters, 2D and 3D: the bounds of a 3D box of 5
+// (5.5) diameters leave 2930 (3700) seeds on average, those of a 2D box of 16 about
+// 2800, and kRegionCap is 4096.  Without the limit / with it: 400^3 with 213333
+// seeds and relative gaps 10.0 / 5.1 ms (8.7 without regions), 256^3 with 55924 854 / 681
+// us (827); 4000^2 with 160000 7.1 / 1.0 ms (22), 8000^2 with 213333 11.7 / 1.4 (14.6).
+constexpr double kRegionDiam[2] = {16.0, 5.5};
 
 int list_rows(const apd::Geo &g, apd_precision prec, bool gap) {
     return prec == APD_FP64 ? apd::kP : apd::vec_pixels_per_lane(g, true, gap);
@@ -287,15 +293,19 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
     L.super = p->n > apd::kThreads && (!L.single() || L.tiles * p->n >= kTileListPairs);
     // s super-tiles each read n seeds; h regions read n and leave each
     // super-tile about c n / h (c = 8 for the margin around the region's box):
-    // least at h = sqrt(c s)
+    // least at h = sqrt(c s).  But a region whose bounds leave more seeds than its
+    // list has room for sends its super-tiles back to every seed, for nothing, so
+    // none is longer than kRegionDiam cell diameters along an axis
     if (L.super && g.power == 2 && L.nsuper * p->n >= apd::kRegionPairs && L.nsuper > 64) {
         const int f = std::max(2, (int)lround(pow((double)L.nsuper / 8.0, 0.5 / p->dim)));
-        L.nregion = 1;
+        int64_t count = 1;
         for (int d = 0; d < 3; ++d) {
-            L.hf[d] = d < p->dim ? f : 1;
+            const int most = (int)(kRegionDiam[p->dim == 3] * diam / ((double)L.sf[d] * ext[d]));
+            L.hf[d] = d < p->dim ? std::max(1, std::min(f, most)) : 1;
             L.nh[d] = (L.nst[d] + L.hf[d] - 1) / L.hf[d];
-            L.nregion *= L.nh[d];
+            count *= L.nh[d];
         }
+        if (count < L.nsuper) L.nregion = count;
     }
     return L;
 }

@@ -267,3 +267,16 @@ def test_rows_of_passes_with_gaps_and_of_thin_grids(ctx, grid, n, rows, gap_rows
     assert ctx.apd_last_pass_stats()["pixels_per_lane"] == gap_rows
     exact = ctx.apd_assign(prob, w, prec="fp64", rel_gap=True)[1]
     assert torch.equal(lab, ref) and bool((gap <= exact * (1 + 1e-6) + 1e-12).all())
+
+
+def test_regions_have_room_for_their_seeds(ctx):
+    """Regions no longer than their lists have room for: four times the pixels at
+    the same density take about four times as long, not sixteen."""
+    import torch
+    took = []
+    for side in (2000, 4000):
+        n = side * side // 100
+        prob = _prob(S.custom(2, n, (side, side), seed=1, sigma=0.0))
+        w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+        took.append(_seconds(lambda: ctx.apd_dual_objective_grad(prob, w)))
+    assert took[1] < 10.0 * took[0], took
