@@ -417,8 +417,11 @@ apd_status apd_set_pixels_per_lane(apd_ctx *ctx, int32_t p);
  * tier (APD_FP32: vector with candidate lists at 4 and at 8 pixels per
  * lane, vector over every seed at 4 and at 8, matrix cores, hybrid) over
  * `reps` passes of prob at weights w (device) with HIP events, sets ctx to
- * the fastest and reports the mean pass times (ms) in the order above.  All
- * candidates return identical results. */
+ * the fastest and reports the mean pass times (ms) in the order above.  Where
+ * apd_set_pixels_per_lane(0) takes 2 pixels per lane for prob, the lists are
+ * also timed with 2; the first time is then the smaller of 4 and 2, and
+ * pixels_per_lane is 0 if 2 was the fastest.  All candidates return identical
+ * results. */
 typedef struct {
     int32_t variant;          /* apd_set_variant value of the fastest */
     int32_t culling;          /* apd_set_culling value of the fastest */

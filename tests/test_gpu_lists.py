@@ -280,3 +280,24 @@ def test_regions_have_room_for_their_seeds(ctx):
         w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
         took.append(_seconds(lambda: ctx.apd_dual_objective_grad(prob, w)))
     assert took[1] < 10.0 * took[0], took
+
+
+def test_autotune_knows_the_default(ctx):
+    """Where the default's two rows per lane, which cannot be set, are the fastest
+    (36 us, 44 with four), the tuned context keeps the rule that takes them."""
+    import torch
+    n = 213
+    prob = _prob(_spread(3, (40, 40, 40), n, 3))
+    w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+    labels = ctx.apd_assign(prob, w)
+    assert ctx.apd_last_pass_stats()["pixels_per_lane"] == 2
+    try:
+        choice = ctx.apd_autotune(prob, w, reps=20)
+        assert len(choice["pass_ms"]) == 6 and min(choice["pass_ms"]) > 0.0
+        assert (choice["variant"], choice["culling"], choice["pixels_per_lane"]) == (1, 1, 0)
+        assert torch.equal(ctx.apd_assign(prob, w), labels)
+        assert ctx.apd_last_pass_stats()["pixels_per_lane"] == 2
+    finally:
+        ctx.apd_set_variant(2)
+        ctx.apd_set_culling(True)
+        ctx.apd_set_pixels_per_lane(0)
