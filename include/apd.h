@@ -439,8 +439,9 @@ apd_status apd_autotune(apd_ctx *ctx, const apd_problem *prob, const double *w,
  * graph replays with HIP events, sets ctx to the fastest and reports the
  * times (ms).  Candidates, in the order of fit_ms: FP32 vector with
  * candidate lists at 4 and at 8 pixels per lane, FP32 vector over every
- * seed (8), FP32 matrix cores, bf16 matrix cores with candidate lists, bf16
- * matrix cores over every seed.  Every candidate yields the same certified
+ * seed (8), FP32 matrix cores, the bf16 tier's candidate lists (which run the
+ * FP32 lists' kernel at 8: its time again), bf16 matrix cores over every seed.
+ * Every candidate yields the same certified
  * labels, hence the same weights, so from then on apd_fit_weights_batched
  * runs the chosen kernel for either tier asked for (apd_set_batch_kernel
  * with kernel -1 returns to the rule by tier).  The trial weights live in

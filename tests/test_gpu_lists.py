@@ -301,3 +301,14 @@ def test_autotune_knows_the_default(ctx):
         ctx.apd_set_variant(2)
         ctx.apd_set_culling(True)
         ctx.apd_set_pixels_per_lane(0)
+
+
+def test_batched_autotune_times_a_kernel_once(ctx):
+    """The two tiers' lists run one kernel: one time for both, and the FP32 name if
+    it is the fastest."""
+    probs = [_prob(S.custom(2, 40 + b, (128, 96), seed=b, sigma=0.0)) for b in range(6)]
+    try:
+        r = ctx.apd_autotune_batched(probs, evals=4)
+        assert r["fit_ms"][4] == r["fit_ms"][1] > 0.0 and r["kernel"] != "bf16-lists"
+    finally:
+        ctx.apd_set_batch_kernel(None)
