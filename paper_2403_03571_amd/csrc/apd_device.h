@@ -1648,9 +1648,10 @@ __device__ inline int box_survivors(const Geo &g, const Seeds &sd, double wmax, 
             far2 = fmaf(fd, fd, far2);
         }
         const float wp = (float)(sd.w[i] - wmax);
-        const double2 ev = reinterpret_cast<const double2 *>(eig)[i];
-        const float u = (float)ev.y * far2, slack = fmaf(0x1p-18f, u + fabsf(wp), ct.lsl);
-        lb = fmaf((float)ev.x, dist2, -wp) - slack;
+        // (one load of 16 bytes, at 8-byte addresses in the batched solver)
+        const float lmin = (float)eig[2 * (size_t)i], lmax = (float)eig[2 * (size_t)i + 1];
+        const float u = lmax * far2, slack = fmaf(0x1p-18f, u + fabsf(wp), ct.lsl);
+        lb = fmaf(lmin, dist2, -wp) - slack;
         ub = (u - wp) + slack;
     };
     // from a region's record: x about its centre, w - w_max, the eigenvalue
