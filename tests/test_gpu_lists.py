@@ -312,3 +312,23 @@ def test_batched_autotune_times_a_kernel_once(ctx):
         assert r["fit_ms"][4] == r["fit_ms"][1] > 0.0 and r["kernel"] != "bf16-lists"
     finally:
         ctx.apd_set_batch_kernel(None)
+
+
+@pytest.mark.parametrize("dim,grid", [(2, (400, 390)), (3, (60, 61, 59))])
+@pytest.mark.parametrize("n", [1024, 1025, 10240, 10241])
+def test_edges_of_the_blocks_over_seeds(ctx, dim, grid, n):
+    """One or several blocks in the first and last kernel of an evaluation, and the
+    most seeds whose super-tile bounds a thread of 512 keeps in registers: labels and
+    counts against every seed, the scalars of all tiers the same to the last bit."""
+    import torch
+    prob = _prob(_spread(dim, grid, n, n))
+    w = torch.as_tensor(np.random.default_rng(n).uniform(-0.1, 0.1, n) * n ** (-2.0 / dim), device="cuda:0")
+    ref = _every_seed(ctx, prob, w)
+    want = torch.bincount(ref.reshape(-1).cpu().long(), minlength=n)
+    outs = []
+    for prec in ("fp32", "bf16", "fp64"):
+        assert torch.equal(ctx.apd_assign(prob, w, prec=prec), ref)
+        outs += [ctx.apd_dual_objective_grad(prob, w, prec=prec, counts=True, noalloc=na) for na in (False, True)]
+    for out in outs:
+        assert torch.equal(out["counts"].cpu(), want) and torch.equal(out["grad"], outs[0]["grad"])
+        assert out["g"] == outs[0]["g"] and out["maxrel"] == outs[0]["maxrel"]

@@ -295,3 +295,81 @@ def test_lists_of_a_wave(box, kappa, reach, offset, soft):
     case = Case(rng, *BOXES[box], m=20000, kappa=kappa, reach=reach, offset=offset, soft=soft)
     for wa, wb in waves_of(case, BOXES[box][4]):
         assert worst(case.from_staged(wa, wb)) <= 1.0
+
+
+# ------------------------------------------------ the bounds of the super-tiles
+
+@pytest.mark.parametrize("box", range(len(BOXES)))
+@pytest.mark.parametrize("kappa,reach,offset", [(9.0, (0.05, 400.0), 0.0), (9.0, (0.5, 4000.0), 1e3), (1e6, (0.05, 400.0), 0.0)])
+@pytest.mark.parametrize("region", [False, True])
+def test_bounds_of_a_super_tile(box, kappa, reach, offset, region):
+    """The FP32 bounds of a seed's cost over a super-tile, from the caller's arrays
+    or from a region's record (offsets shifted in FP32), lie outside the exact
+    lambda_min dist^2 - w' and lambda_max maxdist^2 - w' by at least what the double
+    costs can be off."""
+    rng = np.random.default_rng(400 + box)
+    dim, grid, lo, hi, p, sf, tile = BOXES[box]
+    case = Case(rng, dim, grid, lo, hi, p, sf, tile, m=30000, kappa=kappa, reach=reach, offset=offset)
+    # the region: four super-tiles per axis around this one
+    ext = [case.ext[d] * sf[d] for d in range(dim)]
+    ra = [case.sa[d] // (4 * ext[d]) * 4 * ext[d] for d in range(dim)]
+    rb = [min(ra[d] + 4 * ext[d], grid[d]) - 1 for d in range(dim)]
+    ev = np.linalg.eigvalsh(case.A)
+    span = 1e-6 * (np.abs(ev[..., -1]) + np.abs(ev[..., 0]))
+    lmin, lmax = ev[..., 0] - span, ev[..., -1] + span
+    for q in (0, 1):
+        ctr = [case.centre(d, case.sa, case.sb) for d in range(dim)]
+        dist2, far2 = np.zeros(case.m, f4), np.zeros(case.m, f4)
+        edist, efar = np.zeros(case.m, ld), np.zeros(case.m, ld)
+        for d in range(dim):
+            b0, b1 = (lo[d] + (k[d] + 0.5) * case.s[d] for k in (case.sa, case.sb))
+            h = f4(0.5 * (b1 - b0)) * f4(1 + 2.0 ** -20)
+            if region:
+                rc = case.centre(d, ra, rb)
+                shift = f4(rc - ctr[d])
+                e = np.abs((case.x[:, q, d] - rc).astype(f4) + shift)
+                h = fma(f4(2.0 ** -22), np.abs(shift), h) * f4(1 + 2.0 ** -20)
+            else:
+                e = np.abs((case.x[:, q, d] - ctr[d]).astype(f4))
+            dd, fd = np.maximum(f4(0), e - h), e + h
+            dist2, far2 = fma(dd, dd, dist2), fma(fd, fd, far2)
+            x0 = case.x[:, q, d].astype(ld)
+            xd = np.maximum(np.maximum(ld(b0) - x0, x0 - ld(b1)), 0)
+            edist, efar = edist + xd ** 2, efar + np.maximum(x0 - ld(b0), ld(b1) - x0) ** 2
+        wp = (case.w[:, q] - case.wmax).astype(f4)
+        u = lmax[:, q].astype(f4) * far2
+        slack = fma(f4(2.0 ** -18), u + np.abs(wp), case.lsl)
+        lb, ub = fma(lmin[:, q].astype(f4), dist2, -wp) - slack, (u - wp) + slack
+        we = case.w[:, q].astype(ld) - case.wmax.astype(ld)
+        off = ld(2) ** -49 * (case.lg[:, q] * efar + np.abs(case.w[:, q]) + case.lg[:, q] * case.Y2)
+        assert np.all(lb <= ev[:, q, 0] * edist - we - off)
+        assert np.all(ub >= ev[:, q, -1] * efar - we + off)
+
+
+# ---------------------------------------------------------- the settle rules
+
+def test_short_settle_rule_implies_the_full_one():
+    """A pixel settled by the rule without square roots at the tile's corner radius
+    is settled by the per-pixel certificate, for any radius inside the tile."""
+    rng = np.random.default_rng(500)
+    m = 400000
+    r2t = np.exp(rng.uniform(-12, 6, m)).astype(f4)
+    r2 = (r2t * rng.random(m).astype(f4)).astype(f4)
+    fb = (np.exp(rng.uniform(-14, 8, m)) * rng.choice([1, 1, 1, -1e-3], m)).astype(f4)
+    sab = (np.exp(rng.uniform(-30, -10, m))).astype(f4)
+    skb = (f4(2.0 ** -44) * np.exp(rng.uniform(1, 30, m)).astype(f4)).astype(f4)
+    for kbits in (f4(0), f4(2.0 ** -18)):
+        k1 = (f4(1.5 * 2.0 ** -18) + skb + kbits) * f4(1 + 2.0 ** -7)
+        c = f4(1.5 * 2.0 ** -18) + skb
+        k2 = ((f4(1.5 * 2.0 ** -17) + skb + f4(2.0 ** -9) * c) * r2t + sab) * f4(1 + 2.0 ** -7)
+        need = fma(np.abs(fb), k1, k2)
+        # the runner-up just above and well above what the short rule asks for
+        for far in (f4(1 + 2.0 ** -20), f4(1.5), f4(40)):
+            fs = fb + need * far
+            short = (fs - fb) > need
+            bb = np.maximum(fb, f4(0))
+            B1 = bb + f4(2.0 ** -10) * (bb + r2)
+            e1 = f4(2.0 ** -20) * (B1 + f4(4) * np.sqrt(r2) * np.sqrt(B1) + f4(4) * r2)
+            thr = f4(2) * e1 + kbits * np.maximum(np.abs(fb), np.abs(fs)) + sab + skb * (B1 + r2)
+            assert short.sum() > m // 4
+            assert np.all((fs - fb)[short] > thr[short])
