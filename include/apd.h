@@ -406,9 +406,10 @@ apd_status apd_set_adaptive(apd_ctx *ctx, int32_t on);
  * that many rows x 32 columns; in 3D a tile is 16 x 16 x 8 voxels at 8 and
  * 16 x 8 x 8 at 4).  0 (the default) picks, with candidate lists, 8 on 3D
  * grids of at least 2^21 voxels with 1000 voxels per seed and 2D ones of 2^22
- * pixels with 1000 up to 8000 per seed, 2 (8 x 8 x 8 voxels) on 3D grids under 2^19 voxels or 450 voxels
- * per seed, else 4; over every seed 8 on grids of at least 2^21 pixels, else
- * 4.  The single-instance
+ * pixels with 1000 up to 8000 per seed, 2 (8 x 8 x 8 voxels) on 3D grids
+ * under 2^19 voxels (and 1024 tiles of 16 x 8 x 8) or, without rel_gap and
+ * unless half of such tiles' room lies outside the grid, under 450 voxels per
+ * seed, else 4; over every seed 8 on grids of at least 2^21 pixels, else 4.  The single-instance
  * APD_BF16 kernel over every seed takes half of a set value as its rows per
  * lane (default 4 in 2D, 2 in 3D).  The labels do not depend on it. */
 apd_status apd_set_pixels_per_lane(apd_ctx *ctx, int32_t p);

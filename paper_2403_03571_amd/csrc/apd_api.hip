@@ -1023,10 +1023,9 @@ apd_status fit_batched_impl(apd_ctx *c, const apd_problem *probs, int32_t B,
         nm += (size_t)p.n * K;
         qcap += num_pixels(&p);
         // tile extents of the kernel: fp32 matrix cores 16 x 32 (2D) /
-        // 16 x 4 x 8 (3D); vector 64 x 32 / 32 x 8 x 8 (8 pixels per lane:
-        // the batched tiles build their candidate lists from every seed of
-        // the instance, so fewer, larger tiles pay less for them --
-        // measured); bf16 32 x 32 / 8 x 8 x 8
+        // 16 x 4 x 8 (3D); vector 64 x 32 / 16 x 16 x 8 (8 pixels per lane:
+        // fewer, larger tiles; the solve of 512 2D maps took 580 ms with 4 when
+        // it took 515 with 8); bf16 32 x 32 / 8 x 8 x 8
         const bool vec = bvariant != 0;
         const int e0 = vec ? apd::tile_ext(dim, btp, 0) : apd::kWaves * apd::kP;
         const int e1 = vec ? apd::tile_ext(dim, btp, 1) : (dim == 2 ? 32 : 4);
