@@ -314,8 +314,11 @@ ListGeometry list_geometry(const apd_problem *p, const apd::Geo &g, int rows) {
 // super-tile is one tile its list is read once and holds the seeds' numbers alone
 // (8 KiB per tile; the records, 96, save the gathers of the tiles that share
 // them), and so it does where the records would take more than half of the device's
-// free memory.  That is settled by an eager pass: a captured one, which must not
-// allocate, takes what the eager pass before it took.
+// free memory (asked, 5 us, only for more than kRoomUnasked bytes: 256^3 voxels and
+// 10^4 seeds keep below it).  That is settled by an eager pass: a captured one,
+// which must not allocate, takes what the eager pass before it took.
+constexpr size_t kRoomUnasked = (size_t)64 << 20;
+
 bool grow_super(apd_ctx *c, size_t bytes) {
     if (bytes <= c->super_bytes) return true;
     (void)hipFree(c->super_lists);
@@ -340,7 +343,8 @@ apd_status ensure_super(apd_ctx *c, const ListGeometry &L, int dim, int64_t n, b
         const size_t bytes = region + seeds * apd::rec_vec(dim) * sizeof(float4);
         size_t free_bytes = 0, total = 0;
         records = bytes <= c->super_bytes ||
-                  (hipMemGetInfo(&free_bytes, &total) == hipSuccess && bytes <= (free_bytes + c->super_bytes) / 2 &&
+                  ((bytes <= kRoomUnasked || (hipMemGetInfo(&free_bytes, &total) == hipSuccess &&
+                                              bytes <= (free_bytes + c->super_bytes) / 2)) &&
                    grow_super(c, bytes));
     }
     if (!captured) c->super_ids_only = !records;
