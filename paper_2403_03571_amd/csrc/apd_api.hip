@@ -580,6 +580,9 @@ apd_status check_volumes(apd_ctx *c, const apd_problem *p) {
 apd_status evaluate(apd_ctx *c, const apd_problem *p, const double *x, const double *w,
                     apd_precision prec, bool host_grad, double *g, double *maxrel,
                     const apd::FinalOut *extra, bool validate) {
+    // sized before gbuf is taken: growing it frees the old one
+    apd_status st = ensure_scratch(c, p->n);
+    if (st != APD_OK) return st;
     apd::FinalOut fo{c->gbuf, nullptr, nullptr};
     if (extra) {
         if (extra->grad) fo.grad = extra->grad;
@@ -596,7 +599,7 @@ apd_status evaluate(apd_ctx *c, const apd_problem *p, const double *x, const dou
         fo.host_sc = c->h_sc;
         want = next_published(c);
     }
-    apd_status st = enqueue_pass(c, p, x, w, nullptr, true, true, fo, prec);
+    st = enqueue_pass(c, p, x, w, nullptr, true, true, fo, prec);
     c->need_qtotal = false;
     if (st != APD_OK) {
         if (publish) --c->published;  // its finalize was never enqueued

@@ -303,6 +303,27 @@ def test_autotune_knows_the_default(ctx):
         ctx.apd_set_pixels_per_lane(0)
 
 
+def test_autotune_after_the_seeds_grew():
+    """The autotuner's passes write their gradient into the context's own buffer, which
+    more seeds than it holds (1024 at first) replace: the new one is written, and nothing
+    beside it."""
+    import torch
+
+    import paper_2403_03571_amd as apd
+    ctx = apd.Context(0)
+    small = _prob(_spread(3, (40, 40, 40), 213, 3))
+    ctx.apd_autotune(small, torch.zeros(213, dtype=torch.float64, device="cuda:0"), reps=1)
+    for n in (1025, 3971, 5000):
+        prob = _prob(_spread(3, (64, 64, 64), n, 3))
+        w = torch.zeros(n, dtype=torch.float64, device="cuda:0")
+        beside = [torch.full((1 << 14,), 7, dtype=torch.uint8, device="cuda:0") for _ in range(8)]
+        choice = ctx.apd_autotune(prob, w, reps=1)
+        assert len(choice["pass_ms"]) == 6 and min(choice["pass_ms"]) > 0.0
+        assert all(bool((b == 7).all()) for b in beside)
+        a, b = ctx.apd_dual_objective_grad(prob, w), apd.Context(0).apd_dual_objective_grad(prob, w)
+        assert a["g"] == b["g"] and torch.equal(a["grad"], b["grad"])
+
+
 def test_batched_autotune_times_a_kernel_once(ctx):
     """The two tiers' lists run one kernel: one time for both, and the FP32 name if
     it is the fastest."""
