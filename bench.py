@@ -58,11 +58,11 @@ KERNEL_SOURCES = ("paper_2403_03571_amd/csrc/apd_device.h", "paper_2403_03571_am
                   "paper_2403_03571_amd/csrc/apd_kernels.hip")
 MEASURED_TRAFFIC = {
     ("k_assign_hyb<3>", "c3"): {
-        "fetch_kib": 5692.0, "write_kib": 20526.7, "fetch_factor": 1048576 / 524302.5, "write_factor": 1.0,
-        "sources_sha256": "d6e1432f3ee2cf41122062e0506e6c059bd5ca704adf47dfbddb357b20ae9a4e"},
+        "fetch_kib": 5692.5, "write_kib": 20525.0, "fetch_factor": 1048576 / 524305.0, "write_factor": 1.0,
+        "sources_sha256": "bc9377e3253e91da52b0759897b7e0d2061fc67c90aa5d9c2af4734d1927a542"},
     ("k_assign_vec<2, 4>", "c2"): {
-        "fetch_kib": 366.0, "write_kib": 715.9, "fetch_factor": 1048576 / 524302.5, "write_factor": 1.0,
-        "sources_sha256": "d6e1432f3ee2cf41122062e0506e6c059bd5ca704adf47dfbddb357b20ae9a4e"},
+        "fetch_kib": 362.0, "write_kib": 716.3, "fetch_factor": 1048576 / 524305.0, "write_factor": 1.0,
+        "sources_sha256": "bc9377e3253e91da52b0759897b7e0d2061fc67c90aa5d9c2af4734d1927a542"},
 }
 
 
@@ -114,7 +114,9 @@ def kernel_name(args, inst, cull=False) -> str:
         return f"k_assign_fp64<{d}, {'true' if cull else 'false'}>"
     if cull:
         if p not in (4, 8):
-            if d == 3 and (inst.J < 1 << 19 or inst.J < 450 * inst.n):
+            g = inst.grid
+            tiles = -(-g[0] // 16) * -(-g[1] // 8) * -(-g[2] // 8) if d == 3 else 0
+            if d == 3 and ((inst.J < 1 << 19 and tiles < 1024) or (inst.J < 450 * inst.n and tiles * 1024 <= 2 * inst.J)):
                 p = 2
             else:
                 large = inst.J >= 1 << (22 if d == 2 else 21) and inst.J >= 1000 * inst.n

@@ -2295,8 +2295,8 @@ struct ListSmem {
 // come from separate bounds of each seed's cost, which give one.
 //
 // Bound by the issue of vector instructions: a wave of 512 voxels takes about
-// 1310 of them on 256^3 with N = 10^4 (9 candidates, 45 each; the lists about
-// 400), at 80 % of the issue rate.  So what every wave repeats is kept short
+// 1330 of them on 256^3 with N = 10^4 (9 candidates, 45 each; the lists about
+// 420), one per 5.7 clocks and SIMD.  So what every wave repeats is kept short
 // (the settled / outside state of its pixels as bits of one register, a
 // certificate of 3 instructions per pixel, the minima of two candidates at a
 // time) and what is rare (several chunks, an unsettled pixel) shares its code.

@@ -695,7 +695,7 @@ int vec_pixels_per_lane(const Geo &g, bool cull, bool gap) {
     }
     // In 2D not from 8000 pixels per cell: the smaller tiles lie inside one cell
     // often enough to be credited whole, which the boundary-aware refinement is
-    // for (4096^2 with 1000 cells: 5177 of 16384 tiles against 853 of 8192; the
+    // for (4096^2 with 1000 cells: 5021 of 16384 tiles against 853 of 8192; the
     // pass itself would take 82 instead of 119 us with 8 rows).
     const bool large = J >= (int64_t)1 << (g.dim == 2 ? 22 : 21) && J >= (int64_t)1000 * g.n;
     if (cull) return large && (g.dim == 3 || J < (int64_t)8000 * g.n) ? 8 : 4;
